@@ -5,13 +5,17 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "tabx.h"
 
 #pragma clang fp contract(off)
 
 namespace tabx {
 
-constexpr int kMaxPasses = 10;     // store passes that stream one set of staged rows
+constexpr int kTileFloats = 1280;  // a tile of rows is about 4 KB, at least one row
+constexpr int kMaxPasses = 10;     // most store passes of one flush of the packed form
+constexpr int kPassBatch = 5;      // ... fetched from LDS together
 
 struct PolicyArgs {
     TabxPolicy       pol;
@@ -34,20 +38,27 @@ struct KArgs {
     uint8_t  *action_mask;
     int       obs_dim;             // D
     int       envs_per_block;      // G
-    int       row_pitch;           // floats between staged rows: D rounded up to 4
-    int       copy_passes;         // ceil(G * R * row_pitch / 4 / lanes), <= kMaxPasses
-    int       rows_per_flush;      // R: consecutive rows of an env staged before they are stored
+    int       rows_per_pass;       // S: consecutive rows the lanes of a wavefront work on at a time
+    int       rows_per_tile;       // T: consecutive rows a wavefront assembles and stores together
+    int       tiles;               // tiles of a full env group: ceil(G * N / T)
+    int       passes_per_tile;     // T / S
+    int       stage_floats;        // a wavefront's staging area in dynamic LDS (they come first)
+    int       zone_chunks;         // ZC: 16-byte chunks of the zone part of a row
+    unsigned  magic_n, magic_zc, magic_s, magic_tc;   // x / N, / ZC, / S, / (4 + ZC) as multiplications (see quotient)
     int       num_groups;          // workgroups that have envs to process
-    int       zdesc_offset;        // copy of the zone descriptors in dynamic LDS, floats (from the wavefront's
-                                   //    area; from the start if the workgroup keeps one copy, see the kernel)
-    int       zdesc_staged;        // ... which exists for elliptical zones and for deciding units
+    int       zone_offset;         // the envs' zone descriptors (ZoneLds) in dynamic LDS, floats
+    int       zones_in_lds;        // ... which sit there for elliptical zones, for deciding units and
+                                   //     for the zone part of the rows
     int       script_offset;       // scripted units deciding in the observe stage: their LDS, floats
     int       groups_per_xcd;      // ceil(num_groups / 8)
-    int       twin;                // 2 or 4: that many wavefronts of a workgroup own the same env
-                                   //    group and share its observers (chunk = wavefront index)
-    int       dyn_stride;          // floats of dynamic LDS per wavefront (when several share an env group)
-    int       obs_chunks;          // workgroups that share the observers of one env group (>= 1)
-    int       obs_per_chunk;       // observers per such workgroup (a multiple of rows_per_flush)
+    int       twin;                // 2 or 4: that many wavefronts of a workgroup share the tiles of
+                                   //    its env group; the first of them steps the envs
+    int       obs_chunks;          // workgroups that share the tiles of one env group (>= 1)
+    int       tiles_per_chunk;     // tiles per such workgroup
+    int       packed;              // 1: rows with the units in registers (tabx_observe_packed.h)
+    int       copy_passes;         // ... store passes of one flush, <= kMaxPasses
+    int       rows_per_flush;      // ... R: consecutive rows of an env staged before they are stored
+    int       obs_per_chunk;       // ... observers per workgroup that shares an env group
     float     inv_cell;            // 1 / cell_size, used only when that is exact (power of two)
     int       cell_pow2;
     PolicyArgs pa;
@@ -137,7 +148,7 @@ struct Unit {
 // workgroup lane of the env's unit 0, e = env index, k = e * N + u.
 struct Place {
     int grp;           // which run of G envs this workgroup owns
-    int chunk;         // which share of the observers of these envs it writes (observe stage)
+    int chunk;         // which share of the rows of these envs it writes (stand-alone observe)
     int l, g, u, base, e;
     bool has;
     size_t k;
@@ -145,8 +156,25 @@ struct Place {
     size_t ks;         // row * N + u
 };
 
-template <int WAVES>
-struct Shared {
+// What the observe stage needs of every unit, left in LDS by the wavefront that holds it.
+template <int L>
+struct Records {
+    float4 own[4][L];             // the four chunks of the unit's block in its own row:
+                                  //   health, health / maximum, x, y
+                                  //   heading, attack range, damage, cooldown left
+                                  //   cooldown ratio, body radius, mass, sight angle
+                                  //   alive, current speed, zone type, team
+    float4 view[L];               // cos(heading), sin(heading), sight range^2, cos(cone / 2)
+    float2 mark[L];               // hurtbox half-width, flags (an int): alive | team<<1 | heals<<2 |
+                                  //   enabled<<3 | assassin<<4 | decides<<5 | hidden in its bush<<6 |
+                                  //   bush key<<8 | zone code<<20
+};
+
+struct NoRecords {};
+
+// TILES: the observe stage reads records (tabx_observe.h).
+template <int WAVES, bool TILES>
+struct __attribute__((aligned(64))) Shared {
     static constexpr int L = 64 * WAVES;
     union {
         struct {                  // step stage
@@ -162,24 +190,17 @@ struct Shared {
         struct {                  // policy stage: what a deciding unit needs of the others
             float4 pose[L];       // x, y, cos(theta), sin(theta)
             float4 body[L];       // radius, max health, health, -
+            int    seer[L];       // alive | team<<1 | concealable<<2 | bush key<<8
         } po;
-        struct {                  // observe stage: what an observer's row needs
+        std::conditional_t<TILES, Records<L>, NoRecords> rec;   // observe stage, rows in tiles
+        struct {                  // observe stage, units in registers: what an observer's row needs
             float4 pose[L];       // x, y, cos(theta), sin(theta)
             float4 reach[L];      // attack range, hurtbox half-width, sight range^2, cos(cone / 2)
+            int    seer[L];       // alive | team<<1 | heals<<2 | enabled<<3 | bush key<<8
         } ob;
     };
-    int      seer[L];             // observer flags: alive | team<<1 | heals<<2 | enabled<<3 | bush key<<8
-                                  // (policy stage: alive | team<<1 | concealable<<2 | bush key<<8)
-    uint64_t rowbits[WAVES == 1 ? 1 : L][WAVES];   // two-wave workgroups: ballots of "observer i sees lane"
     uint64_t ballots[WAVES][4];
-};
-
-// Several wavefronts of one workgroup may share an env group (fused tick): the first one runs
-// the step stage and alone touches the state; the others take the stepped units over through
-// LDS and each writes the rows of its share of the observers.  What they all see sits here
-// (one per workgroup, whether or not its wavefronts share a group).
-struct TwinShared {
-    int rows[64];      // level bank: the row an env slot has just switched to, or -1
+    int      level_rows[64];      // level bank: the row an env slot has just switched to, or -1
 };
 
 // Orders LDS traffic between the lanes of a workgroup without waiting for global
@@ -259,6 +280,16 @@ __device__ __forceinline__ LateArgs late_args()
     return (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// x / n for the small values that occur inside a workgroup (x < 1024, n <= 64: exact, since
+// x * (magic * n - 65536) < 1024 * 64), magic = ceil(65536 / n) from the host.
+__device__ __forceinline__ int quotient(int x, unsigned magic)
+{
+    return (int)(__umul24((unsigned)x, magic) >> 16);
+}
+
+// Product of small non-negative values: one full-rate instruction.
+__device__ __forceinline__ int mul24(int x, int y) { return (int)__umul24((unsigned)x, (unsigned)y); }
+
 // Element k of a per-unit array (at most 2^30 elements: its byte offset fits 32 bits, so the
 // access is "uniform base + 32-bit lane offset" and needs no 64-bit address arithmetic per lane).
 template <class T>
@@ -266,6 +297,72 @@ __device__ __forceinline__ const T &at32(const T *base, size_t k)
 {
     return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
                                         (uint32_t)(k * sizeof(T)));
+}
+
+// Row of the scenario arrays that configures env `env`.
+__device__ __forceinline__ int row_of(const KArgs &a, int env)
+{
+    if (a.p.num_levels <= 0) return env;
+    const int lv = a.st.level[env];
+    return lv < 0 ? 0 : (lv >= a.p.num_levels ? a.p.num_levels - 1 : lv);
+}
+
+// How many envs the group holds (the last one may be partial, surplus workgroups have none).
+__device__ __forceinline__ int envs_of_group(const KArgs &a, int grp)
+{
+    const int left = grp < a.num_groups ? a.p.num_envs - grp * a.envs_per_block : 0;
+    return left < a.envs_per_block ? left : a.envs_per_block;
+}
+
+// The zone descriptors of the workgroup's envs in LDS, ZC 16-byte chunks per env, laid out as the
+// zone part of the rows (so they can be read as 6 floats per slot, and an inactive slot is zero).  A slot is (type, centre x, centre y, three more), so three chunks
+// hold two slots and a chunk has the centre of one slot at most: chunk 0 of three has x and y of the
+// first slot in its floats 1 and 2, chunk 1 the second slot's x in float 3, chunk 2 its y in float 0.
+// `rel` is -1 if that slot is active (its centre is relative to the observer), else 0.
+struct ZoneLds {
+    float4 *val;      // [G][ZC]
+    int    *rel;      // [G][ZC]
+};
+
+__device__ __forceinline__ ZoneLds zone_lds(const KArgs &a, float *dyn)
+{
+    float4 *v = reinterpret_cast<float4 *>(dyn + a.zone_offset);
+    return {v, reinterpret_cast<int *>(v + a.envs_per_block * a.zone_chunks)};
+}
+
+// x / 3 for x < 100
+__device__ __forceinline__ int third(int x) { return mul24(x, 171) >> 9; }
+
+// Chunk zc of env slot g, whose zones are row `row` of the descriptors.
+__device__ __forceinline__ void put_zone_chunk(const KArgs &a, const ZoneLds &Z, int g, int zc, int row)
+{
+    const int zlen = 6 * a.p.max_zones;
+    const float *d = a.sc.zone_desc + (size_t)row * zlen;
+    float v[4];
+    int rel = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int zz = 4 * zc + k;
+        const int type_at = 3 * (third(zz) & ~1);            // first float of its slot
+        const bool active = zz < zlen && d[zz < zlen ? type_at : 0] != 0.0f;
+        v[k] = active ? d[zz < zlen ? zz : 0] : 0.0f;
+        const int comp = zz - type_at;
+        if (active && (comp == 1 || comp == 2)) rel = -1;
+    }
+    Z.val[g * a.zone_chunks + zc] = make_float4(v[0], v[1], v[2], v[3]);
+    Z.rel[g * a.zone_chunks + zc] = rel;
+}
+
+// All zone chunks of the workgroup's envs, by the LANES lanes that call it (`l`: index among them).
+template <int LANES>
+__device__ __forceinline__ void put_zones(const KArgs &a, const ZoneLds &Z, int grp, int l)
+{
+    const int envs_here = envs_of_group(a, grp);
+    const int ZC = a.zone_chunks;
+    for (int q = l; q < envs_here * ZC; q += LANES) {
+        const int g = quotient(q, a.magic_zc);
+        put_zone_chunk(a, Z, g, q - g * ZC, row_of(a, grp * a.envs_per_block + g));
+    }
 }
 
 __device__ __forceinline__ void load_spec(const KArgs &a, size_t k, Unit &U)
@@ -338,7 +435,7 @@ __device__ __forceinline__ Place locate(const KArgs &a)
 {
     Place P;
     const int N = a.p.num_units;
-    P.l = a.twin ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
+    P.l = (int)threadIdx.x;           // (only the wavefronts that step or publish hold units)
     if (WAVES == 1) {
         P.g = P.l / N;
         P.u = P.l - P.g * N;
@@ -351,7 +448,7 @@ __device__ __forceinline__ Place locate(const KArgs &a)
     // of their SoA segments, meet in the same L2.
     const int slot = (int)(blockIdx.x >> 3);
     const int in_xcd = a.obs_chunks > 1 ? slot / a.obs_chunks : slot;
-    P.chunk = a.twin ? (int)(threadIdx.x >> 6) : slot - in_xcd * a.obs_chunks;
+    P.chunk = slot - in_xcd * a.obs_chunks;
     P.grp = in_xcd < a.groups_per_xcd ? (int)(blockIdx.x & 7) * a.groups_per_xcd + in_xcd : a.num_groups;
     P.e = P.grp * a.envs_per_block + P.g;
     P.has = P.grp < a.num_groups && P.g < a.envs_per_block && P.u < N && P.e < a.p.num_envs;
@@ -367,8 +464,8 @@ __device__ __forceinline__ Place locate(const KArgs &a)
 }
 
 // How many lanes of the caller's env satisfy each of four predicates.
-template <int WAVES>
-__device__ __forceinline__ void env_counts(Shared<WAVES> &sh, const Place &P, int N,
+template <int WAVES, class Sh>
+__device__ __forceinline__ void env_counts(Sh &sh, const Place &P, int N,
                                            const bool (&pred)[4], int (&cnt)[4])
 {
     if (WAVES == 1) {
@@ -396,8 +493,8 @@ __device__ __forceinline__ void env_counts(Shared<WAVES> &sh, const Place &P, in
 // Mean health ratio of both teams over their enabled units (the bracketed means of
 // Eq. 1): the terms published in sh.share are added in ascending unit index; a term
 // of +0.0f (unit of the other team, or disabled) leaves a finite sum unchanged.
-template <int WAVES>
-__device__ __forceinline__ void team_means(const Shared<WAVES> &sh, const Place &P, int N,
+template <class Sh>
+__device__ __forceinline__ void team_means(const Sh &sh, const Place &P, int N,
                                            int c0, int c1, float &m0, float &m1)
 {
     float s0 = 0.0f, s1 = 0.0f;

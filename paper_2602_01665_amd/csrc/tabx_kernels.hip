@@ -37,6 +37,7 @@
 #include "tabx_policy.h"
 #include "tabx_step.h"
 #include "tabx_observe.h"
+#include "tabx_observe_packed.h"
 
 namespace tabx {
 
@@ -44,13 +45,13 @@ template <int WAVES, bool DO_POLICY, bool DO_STEP, bool DO_OBS, bool SCRIPT = fa
           int TWIN = 0>
 __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kernel(const KArgs a)
 {
-    __shared__ Shared<WAVES> sh_all[TWIN ? TWIN : 1];
-    __shared__ TwinShared twin;
-    extern __shared__ __attribute__((aligned(16))) float dyn_all[];
-    const int half = TWIN ? (int)(threadIdx.x >> 6) : 0;
-    Shared<WAVES> &sh = sh_all[half];
-    float *dyn_lds = dyn_all + half * a.dyn_stride;
-    int *rows = twin.rows;                      // TWIN: 0, or how many wavefronts share an env group
+    // the single-wavefront forms of a plain tick or observe keep the units in registers
+    constexpr bool PACKED = DO_OBS && WAVES == 1 && TWIN == 0 && !SCRIPT && !DO_POLICY;
+    __shared__ Shared<WAVES, DO_OBS && !PACKED> sh;
+    extern __shared__ __attribute__((aligned(16))) float dyn[];
+    // all wavefronts of the workgroup write rows; with TWIN only the first of them steps the envs
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool lead = !TWIN || wave == 0;
     TABX_STAMP(0);
 #ifdef TABX_TRACE
     if ((threadIdx.x & 63) == 0) {
@@ -62,125 +63,100 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
     }
 #endif
     Place P = locate<WAVES>(a);
-    Unit U = {};
-    int code_u = 0;
-    // TWIN: the first wavefront of the workgroup runs the step stage; the others, which only
-    // write their share of the observers' rows afterwards, take its result over through LDS
-    const bool lead = !TWIN || half == 0;
-    if (P.has) {
-        load_spec(a, P.ks, U);
-        if (lead) load_state(a, P.k, U);
-    }
-    ZoneRegs Zr = {};
-    if (DO_OBS) Zr = load_zone_regs<WAVES>(a, P);
-    // elliptical zones, deciding units: the descriptors of the workgroup's envs sit in LDS for
-    // the zone lookups and the bush search
-    const int zlen = 6 * a.p.max_zones;
-    // (wavefronts that only write rows never look at them: then the workgroup keeps one copy,
-    // behind the wavefronts' areas, and only the first wavefront fills it)
-    constexpr bool ZSHARED = TWIN != 0 && !SCRIPT;
-    float *zdesc = (ZSHARED ? dyn_all : dyn_lds) + a.zdesc_offset;
-    if (a.zdesc_staged && (lead || !ZSHARED)) {
-        const int G = a.envs_per_block;
-        for (int q = P.l; q < G * zlen; q += 64 * WAVES) {
-            const int g = q / zlen;
-            const int env = P.grp * G + g;
-            const bool live = P.grp < a.num_groups && env < a.p.num_envs;
-            zdesc[q] = live ? a.sc.zone_desc[(size_t)row_of(a, env) * zlen + (q - g * zlen)] : 0.0f;
-        }
-        lds_barrier<WAVES>();
-    }
-    float *zd = zdesc + (P.has ? P.g : 0) * zlen;
+    const ZoneLds Z = zone_lds(a, dyn);
+    ScriptLds<WAVES> *script = reinterpret_cast<ScriptLds<WAVES> *>(dyn + a.script_offset);
+    const float *zd = reinterpret_cast<const float *>(Z.val + (P.has ? P.g : 0) * a.zone_chunks);
     Carry C = {1.0f, 0.0f, 0.0f, 0, false, 0, 0, 0.0f, 0.0f};
-    float zeff_unused = 0.0f;
-    int forced = -1;
-    if (SCRIPT) {
-        // the action this unit decided on at the end of the previous call
-        // (a wavefront that does not step has no alive flags yet: it loads the memories of
-        // all the units the policy may move)
-        const bool decides = P.has && U.enabled && (U.alive || !lead) &&
-                             (!a.pa.controlled || at32(a.pa.controlled, P.k));
-        if (decides) {
-            if (lead) {
-                forced = at32(a.pa.next_action, P.k);
-                a.pa.actions_out[P.k] = (uint8_t)forced;
-            }
-            C.mem_valid = at32(a.pa.mem.mem_valid, P.k);
-            C.mem_x = at32(a.pa.mem.mem_x, P.k);
-            C.mem_y = at32(a.pa.mem.mem_y, P.k);
-        }
+    float speed = 0.0f;
+    // a wavefront that waits for the step fetches the zones meanwhile, unless the step looks at them
+    // itself or may move an env to another level, whose zones it then writes
+    const bool zones_elsewhere = TWIN && a.p.num_levels == 0 && a.p.zone_shapes == 0;
+    if (DO_OBS && TWIN && wave == 1 && zones_elsewhere) {
+        put_zones<64>(a, Z, P.grp, (int)(threadIdx.x & 63));
+        lds_barrier<1>();
+        if (P.chunk == 0) global_state_zones<64>(a, Z, P.grp, (int)(threadIdx.x & 63));
     }
-    if (DO_POLICY) {
-        float cu = 1.0f, su = 0.0f;
+    if (lead) {
+        Unit U = {};
+        int code_u = 0;
         if (P.has) {
+            load_spec(a, P.ks, U);
+            load_state(a, P.k, U);
+        }
+        // scripted units: the action decided on at the end of the previous call and the memory, asked for
+        // with the state (whether the unit is the policy's to move or not: one round trip for all)
+        int told = 0, waiting = 0;
+        if (SCRIPT && P.has) {
+            const LateArgs late = late_args();
+            const uint8_t *const controlled = late->pa.controlled;
+            told = controlled ? at32(controlled, P.k) : 1;
+            waiting = at32(late->pa.next_action, P.k);
+            C.mem_valid = at32(late->pa.mem.mem_valid, P.k);
+            C.mem_x = at32(late->pa.mem.mem_x, P.k);
+            C.mem_y = at32(late->pa.mem.mem_y, P.k);
+        }
+        ZoneRegs Zr = {};
+        if (PACKED) Zr = load_zone_regs(a, P);
+        if (a.zones_in_lds && !zones_elsewhere) {
+            put_zones<64 * WAVES>(a, Z, P.grp, P.l);
+            lds_barrier<WAVES>();
+        }
+        float zeff_unused = 0.0f;
+        int forced = -1;
+        if (SCRIPT && told && U.enabled && U.alive) {
+            forced = waiting;
+            late_args()->pa.actions_out[P.k] = (uint8_t)forced;
+        }
+        if (DO_POLICY) {
+            float cu = 1.0f, su = 0.0f;
+            if (P.has) {
+                code_u = zone_at(a, zd, P.row, U.x, U.y, zeff_unused);
+                heading_sincos(U.theta, su, cu);
+            }
+            forced = policy_env<WAVES>(a, sh, P, U, code_u, cu, su, zd);
+        }
+        TABX_STAMP(6);
+        if (DO_STEP) {
+            const bool restarted = step_env<WAVES>(a, sh, Z, zd, P, U, code_u, C, forced);
+            if (PACKED && a.p.num_levels > 0 && restarted) {
+                // zone slots of the envs that changed level
+                const int row = Zr.lane ? sh.level_rows[Zr.zg] : -1;
+                if (row >= 0) Zr = load_zone_regs(a, P, row);
+            }
+        } else if (DO_OBS && P.has) {
             code_u = zone_at(a, zd, P.row, U.x, U.y, zeff_unused);
-            heading_sincos(U.theta, su, cu);
+            heading_sincos(U.theta, C.su, C.cu);
+            C.ratio = U.hp / U.hmax;       // (disabled units: masked in the rows)
         }
-        forced = policy_env<WAVES>(a, sh, P, U, code_u, cu, su, zd);
-    }
-    bool restarted = false;
-    TABX_STAMP(6);
-    if (DO_STEP && lead) {
-        restarted = step_env<WAVES, TWIN != 0>(a, sh, zd, rows, P, U, code_u, C, forced);
-        if (TWIN) {
-            // hand the stepped units to the other wavefronts: three 16-byte records per lane in
-            // each one's row staging area, which it does not use before it has read them
-            const float4 r0 = make_float4(U.x, U.y, U.theta, U.hp);
-            const float4 r1 = make_float4(U.cd, U.reveal, U.cur_speed, __int_as_float(C.tick));
-            const float4 r2 = make_float4(C.cu, C.su, __int_as_float(code_u),
-                                          __int_as_float(U.alive | (C.restarted ? 2 : 0)));
-            for (int w = 1; w < TWIN; ++w) {
-                float4 *box = reinterpret_cast<float4 *>(dyn_all + w * a.dyn_stride);
-                box[P.l] = r0;
-                box[64 + P.l] = r1;
-                box[128 + P.l] = r2;
+        TABX_STAMP(1);
+        if constexpr (PACKED) {
+            if (P.grp < a.num_groups) observe_packed(a, sh, dyn, P, U, code_u, C, Zr);
+        } else if constexpr (DO_OBS) {
+            lds_barrier<WAVES>();          // the step stage is done with the LDS union
+            publish_units<WAVES, SCRIPT>(a, sh, P, U, code_u, C.ratio, C.cu, C.su, told, script);
+            if (!zones_elsewhere && P.chunk == 0) {
+                lds_barrier<WAVES>();
+                global_state_zones<64 * WAVES>(a, Z, P.grp, P.l);
             }
-            lds_barrier<2>();
+            speed = U.speed;
         }
-    } else if (DO_STEP) {
-        lds_barrier<2>();
-        const float4 *box = reinterpret_cast<const float4 *>(dyn_lds);
-        const float4 r0 = box[P.l], r1 = box[64 + P.l], r2 = box[128 + P.l];
-        U.x = r0.x; U.y = r0.y; U.theta = r0.z; U.hp = r0.w;
-        U.cd = r1.x; U.reveal = r1.y; U.cur_speed = r1.z; C.tick = __float_as_int(r1.w);
-        C.cu = r2.x; C.su = r2.y; code_u = __float_as_int(r2.z);
-        const int flags = __float_as_int(r2.w);
-        U.alive = flags & 1;
-        C.restarted = (flags & 2) != 0;
-        restarted = __ballot(C.restarted) != 0ull;
-        lds_barrier<1>();          // the records are read: the staging area may take rows now
-        if (SCRIPT && P.has && C.restarted) {
-            // a new episode remembers nothing: the wavefront that decides for a unit clears its flag
-            const int first = P.chunk * a.obs_per_chunk;
-            if (P.u >= first && P.u < first + a.obs_per_chunk) a.pa.mem.mem_valid[P.k] = 0;
-        }
-        if (a.p.num_levels > 0 && restarted) {
-            // envs that moved to another level: their specifications and elliptical zones
-            const int row = (P.has && C.restarted) ? rows[P.g] : -1;
-            if (row >= 0) {
-                P.row = row;
-                P.ks = (size_t)row * a.p.num_units + P.u;
-                load_spec(a, P.ks, U);
-                if (a.zdesc_staged && !ZSHARED)
-                    for (int q = P.u; q < zlen; q += a.p.num_units)
-                        zd[q] = a.sc.zone_desc[(size_t)row * zlen + q];
-            }
-            if (a.zdesc_staged && !ZSHARED) lds_barrier<1>();
-        }
-        // the unit's health ratio, as the step stage leaves it (same operands, same rounding)
-        C.ratio = (P.has && U.enabled) ? U.hp / U.hmax : 0.0f;
-    } else if (P.has && !DO_POLICY) {
-        code_u = zone_at(a, zd, P.row, U.x, U.y, zeff_unused);
     }
-    if (DO_STEP && DO_OBS && a.p.num_levels > 0 && restarted) {
-        // zone slots of the envs that changed level
-        const int row = Zr.lane ? rows[Zr.zg] : -1;
-        if (row >= 0) Zr = load_zone_regs<WAVES>(a, P, row);
+    if constexpr (DO_OBS && !PACKED) {
+        if (TWIN) lds_barrier<2>(); else lds_barrier<WAVES>();
+        TABX_STAMP(2);
+        float *stg = dyn + (WAVES == 1 ? wave * a.stage_floats : 0);
+        if (P.grp < a.num_groups) {
+            const int first = P.chunk * a.tiles_per_chunk;
+            const int end = first + a.tiles_per_chunk < a.tiles ? first + a.tiles_per_chunk : a.tiles;
+            write_rows<WAVES, SCRIPT>(a, sh.rec, Z, stg, P.grp, WAVES == 1 ? first + wave : first,
+                                      TWIN ? TWIN : 1, end, script);
+        }
+        TABX_STAMP(4);
+        if (SCRIPT) {
+            if (TWIN) lds_barrier<2>(); else lds_barrier<WAVES>();      // all bids are in
+            if (lead) decide_units<WAVES>(a, sh.rec, script, P, speed, C, zd);
+        }
     }
-    TABX_STAMP(1);
-    if (SCRIPT && !DO_STEP && P.has) C.tick = a.st.t[P.e];
-    ScriptLds<WAVES> *script = reinterpret_cast<ScriptLds<WAVES> *>(dyn_lds + a.script_offset);
-    if (DO_OBS) observe_env<WAVES, DO_STEP, SCRIPT>(a, sh, dyn_lds, P, U, code_u, C, Zr, script, zd);
     if (DO_STEP) asm volatile("" ::"v"(C.warm));    // keeps the cache-warming load of step_env
     TABX_STAMP(5);
 }
@@ -188,13 +164,12 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void tabx_reset_kernel(const KArgs a)
 {
-    __shared__ Shared<WAVES> sh;
-    __shared__ int level_rows[64];      // level bank: the row an env slot has just switched to
+    __shared__ Shared<WAVES, false> sh;
     Place P = locate<WAVES>(a);
     const int N = a.p.num_units;
     const bool go = P.has && !(a.env_mask && a.env_mask[P.e] == 0);
     if (a.p.num_levels > 0) {
-        const int row = advance_level<WAVES>(a, sh, P, go, level_rows);
+        const int row = advance_level<WAVES>(a, sh, P, go);
         if (row >= 0) {
             P.row = row;
             P.ks = (size_t)row * N + P.u;
@@ -218,7 +193,7 @@ __global__ __launch_bounds__(64 * WAVES) void tabx_reset_kernel(const KArgs a)
                                    (en && U.team != 0) ? ratio : 0.0f);
     const bool pred[4] = {en && U.team == 0, en && U.team != 0, false, false};
     int cnt[4];
-    env_counts(sh, P, N, pred, cnt);
+    env_counts<WAVES>(sh, P, N, pred, cnt);
     lds_barrier<WAVES>();
     float m0, m1;
     team_means(sh, P, N, cnt[0], cnt[1], m0, m1);
@@ -363,40 +338,30 @@ static int check_state(const TabxParams *p, const TabxState *s)
 }
 
 // Dynamic LDS of a launch and where its parts lie (fills the offsets in `a`).
-struct LdsPlan { size_t dyn_bytes, step_bytes; };
-template <int WAVES>
-static LdsPlan plan_lds(Mode mode, KArgs &a)
+static size_t plan_lds(Mode mode, KArgs &a, int waves)
 {
-    // dynamic LDS: the staged rows (G rows for a single wavefront, two alternating one-row
-    // buffers for a two-wave workgroup)
-    const size_t rows_staged = WAVES == 1 ? (size_t)a.envs_per_block * a.rows_per_flush : 2;
-    // (the two alternating buffers of a two-wave workgroup are whole 64-byte groups apart)
-    const size_t pitch = WAVES == 1 ? (size_t)a.row_pitch : (size_t)((a.row_pitch + 15) / 16 * 16);
-    // ... rounded up to whole store passes, which read their 16 bytes per lane unconditionally
-    size_t dyn_floats = rows_staged * pitch;
-    const size_t pass_floats = (size_t)a.copy_passes * 64 * WAVES * 4 + (WAVES == 2 ? pitch : 0);
-    if (dyn_floats < pass_floats) dyn_floats = pass_floats;
-    // (wavefronts that take over another one's step receive three 16-byte records per lane here)
-    if (a.twin && dyn_floats < 3 * 64 * 4) dyn_floats = 3 * 64 * 4;
-    // ... in whole 64-byte groups (staged_chunk permutes the chunks of a group among themselves)
-    dyn_floats = (dyn_floats + 15) / 16 * 16;
-    // ... followed, for elliptical zones, by the zone descriptors of the workgroup's envs
-    const size_t zdesc_floats = a.zdesc_staged ? (size_t)a.envs_per_block * 6 * a.p.max_zones : 0;
-    // ... and by the bidding area of scripted units that decide in the observe stage
-    const size_t zdesc_even = (zdesc_floats + 1) & ~(size_t)1;
-    const size_t script_floats = mode == MODE_SCRIPTED_STEP_OBSERVE ? sizeof(ScriptLds<WAVES>) / 4 : 0;
-    // (wavefronts sharing an env group: one such area each; the zone descriptors only once, behind
-    // the areas, unless the wavefronts decide for scripted units and each look zones up: a
-    // workgroup of two wavefronts on c3 takes 23.8 KB, and six of them must fit a CU's 160 KB)
-    const int sharers = a.twin ? a.twin : 1;
-    const bool zshared = a.twin && mode != MODE_SCRIPTED_STEP_OBSERVE;   // the kernels' ZSHARED
-    a.dyn_stride = (int)((dyn_floats + (zshared ? 0 : zdesc_even) + script_floats + 3) & ~(size_t)3);
-    const size_t dyn_bytes = ((size_t)a.dyn_stride * sharers + (zshared ? zdesc_even : 0)) * sizeof(float);
-    const size_t step_bytes = zdesc_floats * sizeof(float);
-    a.zdesc_offset = (mode == MODE_STEP || mode == MODE_POLICY) ? 0
-                     : zshared ? a.dyn_stride * sharers : (int)dyn_floats;
-    a.script_offset = zshared ? (int)dyn_floats : a.zdesc_offset + (int)zdesc_even;
-    return {dyn_bytes, step_bytes};
+    const bool observing = mode == MODE_OBSERVE || mode == MODE_STEP_OBSERVE ||
+                           mode == MODE_POLICY_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE;
+    if (mode == MODE_RESET) return 0;
+    size_t floats = 0;
+    if (observing) {
+        // one staging area per wavefront, in whole store passes (64 lanes of 16 bytes)
+        const size_t tile = a.packed ? (size_t)a.envs_per_block * a.rows_per_flush * a.obs_dim
+                                     : (size_t)a.rows_per_tile * a.obs_dim + (a.obs_dim % 4 ? 2 : 0);
+        a.stage_floats = (int)((tile + 255) / 256 * 256);
+        floats = (size_t)a.stage_floats * waves * (a.twin ? a.twin : 1);
+    }
+    // the zone descriptors of the workgroup's envs: 16-byte chunks with a mask each
+    a.zones_in_lds = a.zone_chunks > 0 && (a.p.zone_shapes == 1 || mode == MODE_POLICY ||
+                                           (observing && !a.packed));
+    a.zone_offset = (int)floats;
+    if (a.zones_in_lds) floats += ((size_t)a.envs_per_block * a.zone_chunks * 5 + 3) / 4 * 4;
+    // the bidding area of scripted units that decide in the observe stage
+    floats = (floats + 3) / 4 * 4;
+    a.script_offset = (int)floats;
+    if (mode == MODE_SCRIPTED_STEP_OBSERVE)
+        floats += (waves == 1 ? sizeof(ScriptLds<1>) : sizeof(ScriptLds<2>)) / sizeof(float);
+    return floats * sizeof(float);
 }
 
 // Enqueues one kernel and returns the status of THIS launch (the runtime's sticky "last error"
@@ -414,65 +379,56 @@ static hipError_t launch_mode(Mode mode, KArgs a, hipStream_t stream)
 {
     const dim3 grid((unsigned)(8 * a.groups_per_xcd * a.obs_chunks));
     const dim3 block(64 * WAVES * (a.twin ? a.twin : 1));
-    const LdsPlan lds = plan_lds<WAVES>(mode, a);
-    const size_t dyn_bytes = lds.dyn_bytes, step_bytes = lds.step_bytes;
+    const size_t lds = plan_lds(mode, a, WAVES);
     switch (mode) {
     case MODE_RESET:
-        return enqueue(tabx_reset_kernel<WAVES>, grid, block, 0, stream, a);
+        return enqueue(tabx_reset_kernel<WAVES>, grid, block, lds, stream, a);
     case MODE_STEP:
-        return enqueue(tabx_tick_kernel<WAVES, false, true, false>, grid, block, step_bytes, stream, a);
+        return enqueue(tabx_tick_kernel<WAVES, false, true, false>, grid, block, lds, stream, a);
     case MODE_OBSERVE:
-        return enqueue(tabx_tick_kernel<WAVES, false, false, true>, grid, block, dyn_bytes, stream, a);
+        if (WAVES == 1 && a.twin)
+            return enqueue(tabx_tick_kernel<1, false, false, true, false, 2>, grid, block, lds, stream, a);
+        return enqueue(tabx_tick_kernel<WAVES, false, false, true>, grid, block, lds, stream, a);
     case MODE_STEP_OBSERVE:
         if (WAVES == 1 && a.twin > 2)
-            return enqueue(tabx_tick_kernel<1, false, true, true, false, 4>, grid, block, dyn_bytes,
-                           stream, a);
+            return enqueue(tabx_tick_kernel<1, false, true, true, false, 4>, grid, block, lds, stream, a);
         if (WAVES == 1 && a.twin)
-            return enqueue(tabx_tick_kernel<1, false, true, true, false, 2>, grid, block, dyn_bytes,
-                           stream, a);
-        return enqueue(tabx_tick_kernel<WAVES, false, true, true>, grid, block, dyn_bytes, stream, a);
+            return enqueue(tabx_tick_kernel<1, false, true, true, false, 2>, grid, block, lds, stream, a);
+        return enqueue(tabx_tick_kernel<WAVES, false, true, true>, grid, block, lds, stream, a);
     case MODE_POLICY:
-        return enqueue(tabx_tick_kernel<WAVES, true, false, false>, grid, block, step_bytes, stream, a);
+        return enqueue(tabx_tick_kernel<WAVES, true, false, false>, grid, block, lds, stream, a);
     case MODE_POLICY_STEP_OBSERVE:
-        return enqueue(tabx_tick_kernel<WAVES, true, true, true>, grid, block, dyn_bytes, stream, a);
+        return enqueue(tabx_tick_kernel<WAVES, true, true, true>, grid, block, lds, stream, a);
     case MODE_SCRIPTED_STEP_OBSERVE:
-        if (WAVES == 1 && a.twin)
-            return enqueue(tabx_tick_kernel<1, false, true, true, true, 2>, grid, block, dyn_bytes,
-                           stream, a);
-        return enqueue(tabx_tick_kernel<WAVES, false, true, true, true>, grid, block, dyn_bytes,
-                       stream, a);
+        if (WAVES == 1)
+            return enqueue(tabx_tick_kernel<1, false, true, true, true, 2>, grid, block, lds, stream, a);
+        return enqueue(tabx_tick_kernel<2, false, true, true, true>, grid, block, lds, stream, a);
     }
     return hipErrorInvalidValue;
 }
 
-// How a call is laid out on the machine: envs per workgroup, rows per flush, wavefronts per env
-// group, store passes (all written into `a`; needs a.obs_dim and a.p).  Returns the wavefronts
-// an env takes (1 or 2).
+// How a call is laid out on the machine: envs per workgroup, rows per tile, wavefronts per env
+// group (all written into `a`; needs a.obs_dim and a.p).  Returns the wavefronts an env takes
+// (1 or 2).
 static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
 {
-    // N <= 64: one wavefront per workgroup with G whole envs packed into it; G is floor(64 / N)
-    // unless the staged rows of G envs would need more than kMaxPasses store passes or more
-    // zone chunks than lanes.  64 < N <= 128: two wavefronts per env.
+    // N <= 64: one wavefront steps G = floor(64 / N) whole envs.  64 < N <= 128: two wavefronts
+    // per env.
     const int N = p->num_units;
     const int waves = N <= 64 ? 1 : 2;
-    a.row_pitch = (a.obs_dim + 3) & ~3;
-    const int cpr = a.row_pitch / 4;
-    const int zc = (6 * p->max_zones + 3) / 4;
-    int G = 1;
-    if (waves == 1) {
-        G = 64 / N;
-        const int by_passes = kMaxPasses * 64 / cpr;
-        if (G > by_passes) G = by_passes;
-        if (zc > 0 && G > 64 / zc) G = 64 / zc;
-        if (G < 1) G = 1;
-    }
+    const int G = waves == 1 ? 64 / N : 1;
     a.envs_per_block = G;
-    // two rows per flush: longer contiguous runs per env, and whole 128-byte lines where a
-    // single row ends on half a line
-    int R = 1;
-    if (waves == 1 && a.obs_dim % 4 == 0 && N % 2 == 0 && (2 * G * cpr + 63) / 64 <= kMaxPasses)
-        R = 2;
-    a.rows_per_flush = R;
+    a.zone_chunks = (6 * p->max_zones + 3) / 4;
+    a.magic_n = (65536u + N - 1) / N;
+    a.magic_zc = a.zone_chunks ? (65536u + a.zone_chunks - 1) / a.zone_chunks : 0;
+    // rows per tile: one observer per row that the 64 lanes hold all units of, about 4 KB
+    int S = G;
+    if (S > kTileFloats / a.obs_dim) S = kTileFloats / a.obs_dim;
+    if (S < 1) S = 1;
+    a.rows_per_pass = S;
+    a.magic_tc = (65536u + 4 + a.zone_chunks - 1) / (4 + a.zone_chunks);
+    a.magic_s = (65536u + S - 1) / S;
+    a.tiles = (G * N + S - 1) / S;
     a.num_groups = (p->num_envs + G - 1) / G;
     a.groups_per_xcd = (a.num_groups + 7) / 8;
     {
@@ -481,69 +437,52 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         a.cell_pow2 = (mant == 0.5f && ex > -100 && ex < 100) ? 1 : 0;
         a.inv_cell = 1.0f / p->cell_size;
     }
-    // Long-lived wavefronts make a long tail at the end of the launch, and a wavefront's chain
-    // of flushes is the latency floor of a small batch.  Where that matters the observers of an
-    // env group are split between several wavefronts:
-    //  - a stand-alone observe uses several workgroups per group (each loads the group's units
-    //    and writes its share of the rows): up to -14 % on the packed-env kernels (below), +5 %
-    //    with two-wave envs, which therefore do not split;
-    //  - a launch that also steps cannot (the second workgroup would need the state after the
-    //    first one's step), but the wavefronts of ONE workgroup can: the first one runs the step
-    //    stage and hands the stepped units to the others through LDS (see the kernel); all of
-    //    them load the specifications meanwhile and then write their share of the rows.
-    //    Measured: c3 107 -> 99.5 us, c2 15.8 -> 14.0 us, but c4 (10 observers, five flushes per
-    //    wavefront, a full machine) 87 -> 102 us; with a longer step stage the wavefronts that
-    //    wait for it cost more than the shorter chains save:
-    //    body collisions 111.9 -> 114.0 us, the scripted c3 tick 117.0 -> 129.0 us; hence the
-    //    conditions below.  Three or four wavefronts per group: 120 us and more on c3, but a
-    //    gain from 32 units per env on (below).
+    // Long-lived wavefronts make a long tail at the end of the launch, and a wavefront's chain of
+    // rows is the latency floor of a small batch, so the rows of an env group are split:
+    //  - a stand-alone observe uses several workgroups per group (each loads the group's units and
+    //    writes its share of the rows);
+    //  - a launch that also steps cannot (the second workgroup would need the state after the first
+    //    one's step), but the wavefronts of ONE workgroup can: the first one steps the envs and
+    //    leaves the units in LDS, then all of them write rows.
     a.obs_chunks = 1;
-    a.obs_per_chunk = N;
     a.twin = 0;
-    if (waves == 1 && N >= 4) {
-        const int per = ((N + 1) / 2 + R - 1) / R * R;
-        const int num_groups = (p->num_envs + G - 1) / G;
+    a.packed = 0;
+    int K = 1;                                   // passes per tile
+    if (waves == 1) {
+        // the form with the units in registers: whole 16-byte chunks per row, a zone chunk per lane
+        // at most, R rows of G envs in kMaxPasses store passes; two rows per flush where they fit
+        const int cpr = a.obs_dim / 4;
+        const int R = N % 2 == 0 && 2 * G * cpr <= 64 * kMaxPasses ? 2 : 1;
+        const bool packs = a.obs_dim % 4 == 0 && G * a.zone_chunks <= 64 && R * G * cpr <= 64 * kMaxPasses;
         // under one residency round (eight single-wavefront workgroups per CU)
-        const bool small_batch = num_groups <= 8 * kComputeUnits;
-        // eight or more flushes, and a short step stage
-        const bool long_chain = N >= 16 * R / 2 && !(p->collision_alpha > 0.0f);
-        if (per < N && mode == MODE_OBSERVE) {
-            // about four flushes per workgroup, one workgroup more for short chains (c3: ten
-            // flushes over 3 workgroups 91.7 us, over 2: 95.3, 5: 100.3, one: 106.4; c4: five
-            // flushes over 3: 73.6 us, 2: 76.8, one: 84.4; 16v16: sixteen over 4: 85 us, 2: 92.7,
-            // 8: 89.4; 32v32: thirty-two over 8: 80.7 us, 4: 88, 2: 92.8); at most two with zone
-            // descriptors to stage per workgroup (elliptical zones: 95.2 us with 2, 96.9 with 3)
-            const int flushes = (N + R - 1) / R;
-            int share = (flushes + 3) / 4 + (flushes < 8 ? 1 : 0);
+        const bool small_batch = a.num_groups <= 8 * kComputeUnits;
+        const bool long_chain = N >= 16 && !(p->collision_alpha > 0.0f);
+        if (mode == MODE_OBSERVE) {
+            const int flushes = (N + 1) / 2;
+            int share = N < 4 ? 1 : (flushes + 3) / 4 + (flushes < 8 ? 1 : 0);
             if (share > 8) share = 8;
             if (share > 2 && p->zone_shapes == 1) share = 2;
+            a.packed = packs;
+            a.twin = packs ? 0 : 2;
             a.obs_per_chunk = ((N + share - 1) / share + R - 1) / R * R;
-            a.obs_chunks = (N + a.obs_per_chunk - 1) / a.obs_per_chunk;
-        } else if (per < N && ((mode == MODE_STEP_OBSERVE && (small_batch || long_chain)) ||
-                               (mode == MODE_SCRIPTED_STEP_OBSERVE && small_batch))) {
-            a.obs_per_chunk = per;
+            a.obs_chunks = packs ? (N + a.obs_per_chunk - 1) / a.obs_per_chunk : share;
+        } else if (mode == MODE_STEP_OBSERVE) {
+            a.twin = packs && !small_batch && !long_chain ? 0 : 2;
+            a.packed = a.twin == 0;
+            a.obs_per_chunk = N;
+            const bool tiny_batch = a.num_groups <= 3 * kComputeUnits && N > 4;
+            if ((N >= 32 || tiny_batch) && p->zone_shapes == 0) a.twin = 4;
+        } else if (mode == MODE_SCRIPTED_STEP_OBSERVE) {
             a.twin = 2;
-            // 16 or more flushes: four wavefronts (N = 32: 99.6 -> 96.8 us, N = 64: 97.4 ->
-            // 91.7 us at 0.45 GB of rows per tick; fewer than four flushes each costs more than
-            // it saves: N = 16 with four, 92 -> 124 us)
-            // (as long as four staging areas fit the 64 KB of LDS a workgroup may take)
-            const size_t staged = (size_t)G * R * a.row_pitch * sizeof(float) + 64;
-            const size_t lds4 = 4 * (staged + sizeof(Shared<1>)) + sizeof(TwinShared);
-            // ... or a batch of at most three env groups per CU, whose launch is one wavefront's
-            // chain from the first load to the last store (3v3 x 16 envs 9.8 -> 8.8 us, 5v5 x
-            // 4096 13.0 -> 12.2 us, 10v10 x 1024 18.8 -> 15.4 us; from five groups per CU on it
-            // costs: 5v5 x 8192 18.5 -> 21.9 us, 10v10 x 4096 33.4 -> 35.8 us)
-            const bool tiny_batch = num_groups <= 3 * kComputeUnits && N > 2 * R;
-            if (mode == MODE_STEP_OBSERVE && (N >= 16 * R || tiny_batch) && p->zone_shapes == 0 &&
-                lds4 <= kLdsPerWorkgroupBytes - 4 * 1024) {
-                a.twin = 4;
-                a.obs_per_chunk = ((N + 3) / 4 + R - 1) / R * R;
-            }
         }
+        a.rows_per_flush = R;
+        a.copy_passes = (R * G * cpr + 63) / 64;
+        if (mode == MODE_STEP_OBSERVE && a.twin && !small_batch && a.tiles >= 8 * a.twin && 2 * S * a.obs_dim <= 2 * kTileFloats) K = 2;
     }
-    // (two-wave envs: each wavefront streams one half of a row, both halves whole 64-byte groups)
-    const int half = ((cpr / 2) + 3) & ~3, rest = ((cpr + 3) & ~3) - half;
-    a.copy_passes = waves == 1 ? (G * R * cpr + 63) / 64 : ((half > rest ? half : rest) + 63) / 64;
+    a.passes_per_tile = K;
+    a.rows_per_tile = K * S;
+    a.tiles = (G * N + a.rows_per_tile - 1) / a.rows_per_tile;
+    a.tiles_per_chunk = (a.tiles + a.obs_chunks - 1) / a.obs_chunks;
     return waves;
 }
 
@@ -595,7 +534,6 @@ static int run(Mode mode, const TabxParams *p, const TabxScenario *sc, const Tab
     a.action_mask = action_mask;
     a.obs_dim = 16 * p->num_units + 6 * p->max_zones;
     a.pa = {};
-    a.zdesc_staged = (p->zone_shapes == 1 || (deciding && p->max_zones > 0)) ? 1 : 0;
     if (deciding) {
         a.pa.pol = *policy;
         a.pa.mem = *memory;
@@ -606,7 +544,6 @@ static int run(Mode mode, const TabxParams *p, const TabxScenario *sc, const Tab
 
     hipStream_t s = (hipStream_t)stream;
     const int waves = plan_shape(mode, p, a);
-    if (a.copy_passes > kMaxPasses) return TABX_ERR_SHAPE;
     const hipError_t err = waves == 1 ? launch_mode<1>(mode, a, s) : launch_mode<2>(mode, a, s);
     return err == hipSuccess ? TABX_OK : TABX_ERR_LAUNCH;
 }
@@ -787,22 +724,17 @@ int tabx_launch_info(const TabxParams *p, int call, TabxLaunchInfo *info)
     static const Mode modes[] = {MODE_RESET, MODE_STEP, MODE_OBSERVE, MODE_STEP_OBSERVE, MODE_POLICY,
                                  MODE_POLICY_STEP_OBSERVE, MODE_SCRIPTED_STEP_OBSERVE};
     const Mode mode = modes[call];
-    const bool deciding = mode == MODE_POLICY || mode == MODE_POLICY_STEP_OBSERVE ||
-                          mode == MODE_SCRIPTED_STEP_OBSERVE;
     KArgs a = {};
     a.p = *p;
     a.obs_dim = 16 * p->num_units + 6 * p->max_zones;
-    a.zdesc_staged = (p->zone_shapes == 1 || (deciding && p->max_zones > 0)) ? 1 : 0;
     const int waves = plan_shape(mode, p, a);
-    if (a.copy_passes > kMaxPasses) return TABX_ERR_SHAPE;
-    const LdsPlan lds = waves == 1 ? plan_lds<1>(mode, a) : plan_lds<2>(mode, a);
-    const bool staged = mode != MODE_RESET && mode != MODE_STEP && mode != MODE_POLICY;
+    const size_t lds = plan_lds(mode, a, waves);
     info->workgroups = 8 * a.groups_per_xcd * a.obs_chunks;
     info->threads_per_workgroup = 64 * waves * (a.twin ? a.twin : 1);
     info->envs_per_workgroup = a.envs_per_block;
     info->wavefronts_per_env_group = waves * (a.twin ? a.twin : 1);
-    info->rows_per_flush = a.rows_per_flush;
-    info->dynamic_lds_bytes = mode == MODE_RESET ? 0 : (int32_t)(staged ? lds.dyn_bytes : lds.step_bytes);
+    info->rows_per_flush = a.packed ? a.rows_per_flush : a.rows_per_tile;
+    info->dynamic_lds_bytes = (int32_t)lds;
     info->assumed_compute_units = kComputeUnits;
     info->assumed_lds_per_cu_bytes = kLdsPerCuBytes;
     info->assumed_lds_per_workgroup_bytes = kLdsPerWorkgroupBytes;

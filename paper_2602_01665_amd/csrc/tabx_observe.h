@@ -10,73 +10,14 @@ namespace tabx {
 // Observation rows of every unit of the workgroup's envs, visibility masks, action masks.
 //
 // A row is N blocks of 16 floats (the observer's own block first, then the other units in
-// ascending index) followed by the zone slots.  The rows of pass i (observer i of every env
-// packed in the workgroup) are assembled in LDS as exact images of the HBM rows, pitch
-// row_pitch = D rounded up to 4 floats, and then go out in 16-byte chunks, chunk t of the
-// staged rows handled by lane t % lanes of store pass t / lanes.
-// Zone slots of the observation rows: lane (env slot zg, 16-byte chunk zc of the zone part)
-// keeps its four zone floats in registers for the whole launch: the value (zero if the slot
-// is inactive) and which observer coordinate to subtract (centre x / y of an active slot).
-struct ZoneRegs {
-    bool  lane;
-    int   zg, zc;
-    float val[4];
-    int   sx[4], sy[4];
-};
-
-// Issued at the top of the kernel so that the descriptor loads are long done when the
-// observe stage needs them.
-// Row of the scenario arrays that configures env `env`.
-__device__ __forceinline__ int row_of(const KArgs &a, int env)
-{
-    if (a.p.num_levels <= 0) return env;
-    const int lv = a.st.level[env];
-    return lv < 0 ? 0 : (lv >= a.p.num_levels ? a.p.num_levels - 1 : lv);
-}
-
-template <int WAVES>
-__device__ __forceinline__ ZoneRegs load_zone_regs(const KArgs &a, const Place &P, int row_override = -1)
-{
-    ZoneRegs Z = {};
-    const int G = a.envs_per_block;
-    const int zlen = 6 * a.p.max_zones;
-    const int ZC = (zlen + 3) >> 2;
-    const int envs_left = P.grp < a.num_groups ? a.p.num_envs - P.grp * G : 0;
-    Z.zg = ZC > 0 ? P.l / ZC : 0;
-    Z.zc = P.l - Z.zg * ZC;
-    Z.lane = ZC > 0 && Z.zg < (envs_left < G ? envs_left : G);
-    if (Z.lane) {
-        const int row = row_override >= 0 ? row_override : row_of(a, P.grp * G + Z.zg);
-        const float *d = a.sc.zone_desc + (size_t)row * zlen;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int zz = 4 * Z.zc + k;
-            if (zz < zlen) {
-                const int comp = zz % 6;
-                const bool active = d[zz - comp] != 0.0f;
-                Z.val[k] = active ? d[zz] : 0.0f;
-                Z.sx[k] = (active && comp == 1) ? -1 : 0;
-                Z.sy[k] = (active && comp == 2) ? -1 : 0;
-            }
-        }
-    }
-    return Z;
-}
-
-// Where 16-byte chunk c of a set of staged row images lives in LDS (c counts from the start of
-// the set): the four chunks of every aligned 64-byte group are permuted by the group's index
-// (XOR with bits 3..4 of c).  Measured on gfx950 (SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE of
-// one-pattern kernels): a 16-byte write of 64 lanes takes 8 cycles when every 8 consecutive lanes
-// hit 8 different 16-byte slots modulo 128 bytes; the unit blocks that neighbouring lanes write
-// are 64 bytes apart, which unpermuted puts every other lane on the same slot (32 cycles; 16
-// with one spare chunk per 16; 8 with this permutation).  A 16-byte read takes 4 cycles only
-// if lane t reads chunk base + t, 8 as soon as a spare chunk interrupts the run and 12 if the
-// lanes of a group read it in permuted order.  So the store passes read the physical chunks in
-// lane order and undo the permutation on the way out: lane t's chunk goes to the place of
-// logical chunk staged_chunk(t) in HBM, which is in the same 64-byte group, so every store
-// instruction still writes whole lines.  The map is its own inverse, and staged_chunk(c + 32 k)
-// = staged_chunk(c) + 32 k.
-__device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); }
+// ascending index) followed by the zone slots.  The envs of a workgroup are consecutive, so all
+// their rows, in the order (env, observer), are ONE contiguous run of HBM.  It is produced in
+// tiles of S = floor(64 / N) consecutive rows: lane l holds unit l % N of the env that row
+// l / N of the tile belongs to and tests itself against that row's observer.  What a lane needs
+// of its unit and of the observer comes from records that the wavefront which stepped the envs
+// has left in LDS, so any wavefront of the workgroup can take any tile and no unit state stays
+// in registers from tile to tile.  The rows of a tile (about 4 KB) are assembled in LDS, in the
+// wavefront's own staging area, as an exact image of the run and go out in 16-byte chunks.
 
 // LDS of the scripted units that decide their next action inside the observe stage: per
 // deciding unit the smallest bids for "target" and "nearest enemy" and the "something to
@@ -87,408 +28,414 @@ struct ScriptLds {
     unsigned long long tkey[L];   // role key << 40 | bits(distance^2) << 8 | index << 1 | in hurtbox
     unsigned long long nkey[L];   // bits(distance^2) << 32 | index
     int                canhit[L];
-    float2             extra[L];  // body radius, max health
+    int                order[L];  // injured | units of the env with a smaller maximum health << 1
+    float              hmax[L];
 };
 
-// SCRIPT: the units the heuristic policy moves decide their next action here, from the very
-// pair tests the observation rows are made of (App. A "Role-Appropriate Heuristic Policy
-// Mechanism": a unit acts on what it sees and can reach).  While observer i's pass runs,
-// every unit it sees bids with LDS atomic minima for "i's target" (key: the role's order,
-// then distance, then index, with "in i's hurtbox" riding in the lowest bit) and for "i's
-// nearest enemy"; afterwards each deciding unit reads its winners and runs the rule cascade.
-template <int WAVES, bool CARRIED, bool SCRIPT>
-__device__ __forceinline__ void observe_env(const KArgs &a, Shared<WAVES> &sh, float *stg,
-                                            const Place &P, const Unit &U, int code_u,
-                                            const Carry &C, const ZoneRegs &Zr,
-                                            ScriptLds<WAVES> *script, const float *zd)
+// Leaves the lane's unit in LDS as the observe stage needs it (state in U, heading cosine / sine
+// cu, su, zone code code_u; `told`: the policy moves it); also the action mask and the units' part of the global state.
+template <int WAVES, bool SCRIPT>
+__device__ __forceinline__ void publish_units(const KArgs &a, Shared<WAVES, true> &sh, const Place &P,
+                                              const Unit U, int code_u, float ratio, float cu,
+                                              float su, int told, ScriptLds<WAVES> *script)
 {
-    constexpr int LANES = 64 * WAVES;
-    const int N = a.p.num_units;
-    const int G = a.envs_per_block;
-    const int D = a.obs_dim;
-    const int Dp = a.row_pitch;
-    const int CPR = Dp >> 2;                     // 16-byte chunks per staged row
-    const int zlen = 6 * a.p.max_zones;
     const bool has = P.has;
-    const bool want_vis = late_args()->vis_mask != nullptr;
-    const bool want_gs = late_args()->st.global_state != nullptr;
-    const int lane = P.l & 63;
-    const int wv = P.l >> 6;
-    const int envs_left = P.grp < a.num_groups ? a.p.num_envs - P.grp * G : 0;
-    const int envs_here = envs_left < G ? envs_left : G;
-
-    float4 *stage = reinterpret_cast<float4 *>(stg);
-    const bool blocks_aligned = (Dp & 15) == 0;  // every block is then one aligned 64-byte group
-
-    lds_barrier<WAVES>();                        // the step stage is done with the LDS union
-
-    // ---- publish this unit as an observer
-    float cu = 1.0f, su = 0.0f;
     const int alive = has ? U.alive : 0;
     const bool enabled = has && U.enabled;
     const bool in_bush = (code_u & 3) == TABX_ZONE_BUSH;
-    const int my_code = code_u & 0xff;
-    const bool hidden = in_bush && !(U.reveal > 0.0f);
-    const float ratio = CARRIED ? C.ratio : U.hp / U.hmax;   // disabled units: masked below
+    const int code = code_u & 0xff;
     const float cd_ratio = U.cooldown != 0.0f ? U.cd / U.cooldown : 0.0f;
-    const float r2_me = U.radius * U.radius;
-    {
-        if (CARRIED) {
-            cu = C.cu;
-            su = C.su;
-        } else if (has) {
-            heading_sincos(U.theta, su, cu);
-        }
-        const int key = in_bush ? my_code : 0x100;         // 0x100 matches no cell code
-        sh.ob.pose[P.l] = make_float4(U.x, U.y, cu, su);
-        sh.ob.reach[P.l] = make_float4(U.range, U.hurt_hw, U.sight_range * U.sight_range, U.cos_half);
-        int role = 0;
-        if (SCRIPT) {
-            const bool decides = enabled && alive && (!a.pa.controlled || at32(a.pa.controlled, P.k));
-            role = (U.speed >= a.pa.pol.assassin_speed ? 0x10 : 0) | (decides ? 0x20 : 0);
-            script->tkey[P.l] = ~0ull;
-            script->nkey[P.l] = ~0ull;
-            script->canhit[P.l] = 0;
-            script->extra[P.l] = make_float2(U.radius, has ? U.hmax : 0.0f);
-        }
-        sh.seer[P.l] = alive | (U.team << 1) | (U.dmg < 0.0f ? 4 : 0) | (enabled ? 8 : 0) | role |
-                       (key << 8);
-        uint8_t *const action_mask = late_args()->action_mask;
-        if (has && action_mask && P.chunk == 0)
-            action_mask[P.k] = (alive && U.cd <= 0.0f) ? 1 : 0;
-    }
-    // what differs between a unit's block in its own row and in another unit's row
-    const int own_mask = enabled ? -1 : 0;
-    const float own_alive = alive ? 1.0f : 0.0f;
-    const float own_zone = (float)(code_u & 3);
-    const float own_team = (float)U.team;
-
-    // ---- zone chunks: lane (env slot zg, chunk zc) holds its four zone floats in registers
-    const int zg = Zr.zg, zc = Zr.zc;
-    const bool zone_lane = Zr.lane;
-    const float (&zval)[4] = Zr.val;
-    const int (&zsx)[4] = Zr.sx;
-    const int (&zsy)[4] = Zr.sy;
-    const int zone_seer0 = (WAVES == 1) ? zg * N : 0;     // lane of observer 0 of the zone lane's env
-    const bool cone_free = a.p.hurtbox_cone == 0;          // the hurtbox is the plain rectangle
-    const int R = a.rows_per_flush;
-    const int zone_dst0 = ((WAVES == 1) ? zg * R * Dp : 0) + 16 * N + 4 * zc;
-
-    // ---- store passes: chunk t = p * LANES + l of the staged rows -> (row slot, chunk in row)
-    unsigned dst_off[kMaxPasses];
-    int valid[kMaxPasses];
-    // two-wave workgroups (one env, one row per flush): each wavefront streams one contiguous half
-    // of the row, 64 chunks per pass
-    // (both halves are whole 64-byte groups, so that the permutation stays within a half)
-    const int half_row = ((CPR >> 1) + 3) & ~3;
-    const int row_chunks = (CPR + 3) & ~3;         // pitch of the two alternating row buffers
-    // the PHYSICAL chunk the lane reads in pass 0; it holds logical chunk staged_chunk(first_chunk)
-    const int first_chunk = WAVES == 2 ? wv * half_row + lane : P.l;
-    if (WAVES == 2) {
-        const bool whole = (D & 3) == 0;
-        const int end = wv == 0 ? half_row : row_chunks;
-        int phys = first_chunk;
-        int q = staged_chunk(first_chunk);
-#pragma unroll
-        for (int p = 0; p < kMaxPasses; ++p) {
-            const int left = D - 4 * q;
-            const int vm = (whole || left >= 4) ? 15 : ((1 << (left > 0 ? left : 0)) - 1);
-            valid[p] = (phys < end && q < CPR && envs_here > 0) ? vm : 0;
-            dst_off[p] = (unsigned)(4 * q);
-            q += 64;
-            phys += 64;
-        }
-    } else {
-        const int RC = R * CPR;                    // chunks per env slot and flush
-        const bool whole = (D & 3) == 0;           // no row ends inside a chunk (always so if R > 1)
-        int tg = 0;                                // env slot of chunk t
-        int q = staged_chunk(P.l);                 // chunk within the env's R staged rows
-        while (q >= RC) {                          // (RC >= 64 for all but tiny rows)
-            q -= RC;
-            tg += 1;
-        }
-#pragma unroll
-        for (int p = 0; p < kMaxPasses; ++p) {
-            // which of the chunk's four floats belong to the row
-            const int left = D - 4 * q;
-            const int vm = (whole || left >= 4) ? 15 : ((1 << (left > 0 ? left : 0)) - 1);
-            // (a pass beyond copy_passes holds only chunks of env slots >= G >= envs_here)
-            valid[p] = tg < envs_here ? vm : 0;
-            dst_off[p] = (unsigned)(tg * N * D + 4 * q);
-            q += LANES;                            // chunk t + LANES of the next pass
-            if (RC >= LANES) {                     // at most one env slot further
-                const bool next_slot = q >= RC;
-                q = next_slot ? q - RC : q;
-                tg = next_slot ? tg + 1 : tg;
-            } else {
-                while (q >= RC) {
-                    q -= RC;
-                    tg += 1;
-                }
-            }
-        }
-    }
-
-    lds_barrier<WAVES>();
-
-    // scripted deciders: what this unit contributes to a bid, whoever the observer is
-    bool injured_me = false;
-    unsigned rank_me = 0;          // how many units of the env have a smaller maximum health
-    unsigned order_heal = 0, key_tail = 0;
+    int flags = alive | (U.team << 1) | (U.dmg < 0.0f ? 4 : 0) | (enabled ? 8 : 0) |
+                (in_bush && !(U.reveal > 0.0f) ? 64 : 0) |
+                ((in_bush ? code : 0x100) << 8) |          // 0x100 matches no cell code
+                (code << 20);
     if (SCRIPT) {
-        injured_me = U.hp < U.hmax;
-        order_heal = injured_me ? 0u : 1u;
-        key_tail = (unsigned)P.u << 1;
-        for (int jj = 0; jj < N; ++jj) rank_me += script->extra[P.base + jj].y < U.hmax ? 1u : 0u;
+        const bool decides = enabled && alive && told;
+        flags |= (U.speed >= late_args()->pa.pol.assassin_speed ? 16 : 0) | (decides ? 32 : 0);
+        script->tkey[P.l] = ~0ull;
+        script->nkey[P.l] = ~0ull;
+        script->canhit[P.l] = 0;
+        script->hmax[P.l] = has ? U.hmax : 0.0f;
     }
-
-    // ---- one pass per observer index i: every lane's unit seen from observer i of its env
-    float *out = a.obs + (size_t)P.grp * G * N * D;
-    uint64_t my_row = 0;
-    const int blk_row0 = (WAVES == 1) ? P.g * R * Dp : 0;
-    // the observers this workgroup writes the rows of: all of them, or its share when the rows
-    // of an env group are spread over several short-lived workgroups
-    const int i_begin = P.chunk * a.obs_per_chunk;
-    const int i_end = (i_begin + a.obs_per_chunk < N) ? i_begin + a.obs_per_chunk : N;
-    TABX_STAMP(2);
-    for (int i0 = i_begin; i0 < i_end; i0 += R) {
-    for (int rr = 0; rr < R; ++rr) {
-        const int i = i0 + rr;
-        const int oi = P.base + i;
-        const float4 A = sh.ob.pose[oi];
-        const float4 B = sh.ob.reach[oi];
-        const int fi = sh.seer[oi];
-        // two-wave workgroups alternate between two row buffers; a single wavefront stages R rows
-        const int base = (WAVES == 1) ? 0 : (i & 1) * row_chunks;
-        const int buf = (WAVES == 1) ? rr * Dp : 0;
-        // offset of this unit from the observer; `dot` is its component along the heading
-        const float dx = U.x - A.x;
-        const float dy = U.y - A.y;
-        float dot;
-        const float g2 = hurtbox_gap2(dx, dy, A.z, A.w, B.x, B.y, -B.y, dot);
-        const float d2 = (dx * dx) + (dy * dy);
-        const bool in_range = d2 <= B.z;
-        const bool in_cone = (d2 == 0.0f) || (dot >= B.w * __builtin_sqrtf(d2));
-        const bool same_team = ((fi >> 1) & 1) == U.team;
-        const bool same_bush = (fi >> 8) == my_code;
-        const bool concealed = hidden && !same_team && !same_bush;
-        const bool self = i == P.u;
-        const bool pair = alive && (fi & 1) && !self;
-        const bool seen = pair && in_range && in_cone && !concealed;
-        const bool hit = pair && ((((fi >> 2) & 1) != 0) == same_team) && (g2 <= r2_me) &&
-                         (in_cone || cone_free);
-        if (SCRIPT) {
-            // observer i decides its next action: this unit bids if i sees it (nothing to do
-            // in a pass whose observers decide nothing or see nobody)
-            const bool vis = seen && (fi & 0x20);
-            if (__ballot(vis) != 0ull) {
-                const bool i_heals = (fi & 4) != 0;
-                const unsigned d2b = (unsigned)__float_as_int(d2);
-                if (vis && hit && (!i_heals || injured_me)) atomicOr(&script->canhit[oi], 1);
-                if (vis && !same_team)
-                    atomicMin(&script->nkey[oi], ((unsigned long long)d2b << 32) | (unsigned)P.u);
-                if (vis && (i_heals == same_team)) {
-                    // Healer: injured allies first; Assassin: lowest maximum health first
-                    const unsigned order = i_heals ? order_heal : ((fi & 0x10) ? rank_me : 0u);
-                    const unsigned hi = (order << 8) | (d2b >> 24);
-                    const unsigned lo = (d2b << 8) | key_tail | (hit ? 1u : 0u);
-                    atomicMin(&script->tkey[oi], ((unsigned long long)hi << 32) | lo);
-                }
-            }
-        }
-        if (want_vis) {
-            // the ballot over the lanes is observer i's row; its own lane keeps it
-            const uint64_t b = __ballot(seen);
-            if (WAVES == 1) my_row = self ? b : my_row;
-            else if (lane == 0) sh.rowbits[i][wv] = b;
-        }
-        if (has) {
-            // block position in the row: own block first, then the others in index order
-            const int blk = self ? 0 : (P.u < i ? P.u + 1 : P.u);
-            const int m = self ? own_mask : (seen ? -1 : 0);
-            const float c2 = self ? U.x : dx;
-            const float c3 = self ? U.y : dy;
-            const float c12 = self ? own_alive : 1.0f;
-            const float c13 = self ? U.cur_speed : (same_team ? 1.0f : 0.0f);
-            const float c14 = self ? own_zone : (hit ? 1.0f : 0.0f);
-            const float c15 = self ? own_team : U.cur_speed;
-            const float4 q0 = make_float4(__int_as_float(__float_as_int(U.hp) & m),
-                                          __int_as_float(__float_as_int(ratio) & m),
-                                          __int_as_float(__float_as_int(c2) & m),
-                                          __int_as_float(__float_as_int(c3) & m));
-            const float4 q1 = make_float4(__int_as_float(__float_as_int(U.theta) & m),
-                                          __int_as_float(__float_as_int(U.range) & m),
-                                          __int_as_float(__float_as_int(U.dmg) & m),
-                                          __int_as_float(__float_as_int(U.cd) & m));
-            const float4 q2 = make_float4(__int_as_float(__float_as_int(cd_ratio) & m),
-                                          __int_as_float(__float_as_int(U.radius) & m),
-                                          __int_as_float(__float_as_int(U.mass) & m),
-                                          __int_as_float(__float_as_int(U.sight_angle) & m));
-            const float4 q3 = make_float4(__int_as_float(__float_as_int(c12) & m),
-                                          __int_as_float(__float_as_int(c13) & m),
-                                          __int_as_float(__float_as_int(c14) & m),
-                                          __int_as_float(__float_as_int(c15) & m));
-            if (self && want_gs) {
-                // the own block with its absolute position is the unit's block of the global state
-                f4u *gs = reinterpret_cast<f4u *>(late_args()->st.global_state + (size_t)P.e * D + 16 * P.u);
-                gs[0] = f4u{q0.x, q0.y, q0.z, q0.w};
-                gs[1] = f4u{q1.x, q1.y, q1.z, q1.w};
-                gs[2] = f4u{q2.x, q2.y, q2.z, q2.w};
-                gs[3] = f4u{q3.x, q3.y, q3.z, q3.w};
-            }
-            const int cb = (buf + blk_row0 + 16 * blk) >> 2;       // first 16-byte chunk of the block
-            // (written as 128-bit vector values: as four-member structs the last chunk has been
-            // seen to go out as four separate dwords, each a many-way bank conflict)
-            typedef float v4 __attribute__((ext_vector_type(4)));
-            v4 *vstage = reinterpret_cast<v4 *>(stg);
-            const v4 w0 = {q0.x, q0.y, q0.z, q0.w}, w1 = {q1.x, q1.y, q1.z, q1.w};
-            const v4 w2 = {q2.x, q2.y, q2.z, q2.w}, w3 = {q3.x, q3.y, q3.z, q3.w};
-            if (blocks_aligned) {
-                // (cb is a multiple of 4: the block's chunks are permuted among themselves)
-                v4 *d = vstage + base + cb;
-                const int sw = (cb >> 3) & 3;
-                d[sw] = w0;
-                d[1 ^ sw] = w1;
-                d[2 ^ sw] = w2;
-                d[3 ^ sw] = w3;
-            } else {
-                vstage[base + staged_chunk(cb)] = w0;
-                vstage[base + staged_chunk(cb + 1)] = w1;
-                vstage[base + staged_chunk(cb + 2)] = w2;
-                vstage[base + staged_chunk(cb + 3)] = w3;
-            }
-        }
-        if (zone_lane) {
-            const float4 Z = sh.ob.pose[zone_seer0 + i];
-            const int en = (sh.seer[zone_seer0 + i] & 8) ? -1 : 0;
-            const int xb = __float_as_int(Z.x), yb = __float_as_int(Z.y);
-            float zo[4];
+    const float4 own[4] = {make_float4(U.hp, ratio, U.x, U.y),
+                           make_float4(U.theta, U.range, U.dmg, U.cd),
+                           make_float4(cd_ratio, U.radius, U.mass, U.sight_angle),
+                           make_float4(alive ? 1.0f : 0.0f, U.cur_speed, (float)(code_u & 3),
+                                       (float)U.team)};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sh.rec.own[k][P.l] = own[k];
+    sh.rec.view[P.l] = make_float4(cu, su, U.sight_range * U.sight_range, U.cos_half);
+    sh.rec.mark[P.l] = make_float2(U.hurt_hw, __int_as_float(flags));
+    if (has && P.chunk == 0) {
+        uint8_t *const action_mask = late_args()->action_mask;
+        if (action_mask) action_mask[P.k] = (alive && U.cd <= 0.0f) ? 1 : 0;
+        float *const global_state = late_args()->st.global_state;
+        if (global_state) {
+            // the own block with its absolute position is the unit's block of the global state
+            f4u *gs = reinterpret_cast<f4u *>(global_state + (size_t)P.e * a.obs_dim + 16 * P.u);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const float shift = __int_as_float((xb & zsx[k]) | (yb & zsy[k]));
-                zo[k] = __int_as_float(__float_as_int(zval[k] - shift) & en);
-            }
-            stage[base + staged_chunk((buf + zone_dst0) >> 2)] = make_float4(zo[0], zo[1], zo[2], zo[3]);
-            if (want_gs && i == 0) {
-                // ... and the zone slots with absolute centres are its tail
-                float *gz = late_args()->st.global_state + (size_t)(P.grp * G + zg) * D + 16 * N + 4 * zc;
-                const int left = zlen - 4 * zc;
-                if (left >= 4) {
-                    *reinterpret_cast<f4u *>(gz) = f4u{zval[0], zval[1], zval[2], zval[3]};
-                } else {
-                    // (constant indices: a runtime index would move the zone registers to
-                    // scratch memory for the whole kernel)
-#pragma unroll
-                    for (int k = 0; k < 3; ++k)
-                        if (k < left) gz[k] = zval[k];
-                }
+                const f4u q = {own[k].x, own[k].y, own[k].z, own[k].w}, none = {};
+                gs[k] = enabled ? q : none;
             }
         }
     }
+    if (SCRIPT) {
+        lds_barrier<WAVES>();
+        int rank = 0;
+        for (int jj = 0; jj < a.p.num_units; ++jj)
+            rank += script->hmax[P.base + jj] < U.hmax ? 1 : 0;
+        script->order[P.l] = (rank << 1) | (U.hp < U.hmax ? 1 : 0);
+    }
+}
+
+// The zone slots with absolute centres are the tail of the global state (from the chunks in LDS).
+template <int LANES>
+__device__ __forceinline__ void global_state_zones(const KArgs &a, const ZoneLds &Z, int grp, int l)
+{
+    float *const out = late_args()->st.global_state;
+    if (!out) return;
+    const int zlen = 6 * a.p.max_zones, ZC = a.zone_chunks;
+    const int envs_here = envs_of_group(a, grp);
+    for (int q = l; q < envs_here * ZC; q += LANES) {
+        const int g = quotient(q, a.magic_zc);
+        const int zc = q - g * ZC;
+        const float4 v = Z.val[q];
+        float *d = out + (size_t)(grp * a.envs_per_block + g) * a.obs_dim + 16 * a.p.num_units + 4 * zc;
+        const int left = zlen - 4 * zc;
+        if (left >= 4) {
+            *reinterpret_cast<f4u *>(d) = f4u{v.x, v.y, v.z, v.w};
+        } else {                                   // (zlen is even: half a chunk)
+            d[0] = v.x;
+            d[1] = v.y;
+        }
+    }
+}
+
+// Where 16-byte chunk c of a staged tile lives in LDS: the four chunks of every aligned 64-byte
+// group are permuted by the group's index (XOR with bits 3..4 of c).  Measured on gfx950
+// (SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE of one-pattern kernels): a 16-byte write of 64 lanes
+// takes 8 cycles when every 8 consecutive lanes hit 8 different 16-byte slots modulo 128 bytes;
+// the unit blocks that neighbouring lanes write are 64 bytes apart, which unpermuted puts every
+// other lane on the same slot (32 cycles; 16 with one spare chunk per 16; 8 with this
+// permutation).  A 16-byte read takes 4 cycles only if lane t reads chunk base + t, 8 as soon as
+// a spare chunk interrupts the run and 12 if the lanes of a group read it in permuted order.  So
+// the store passes read the physical chunks in lane order and undo the permutation on the way
+// out: lane t's chunk goes to the place of logical chunk staged_chunk(t) in HBM, which is in the
+// same 64-byte group, so every store instruction still writes whole lines.  The map is its own
+// inverse, and staged_chunk(c + 32 k) = staged_chunk(c) + 32 k.
+__device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); }
+
+// Writes the rows of the tiles tile, tile + tile_step, ... < tile_end of env group `grp`
+// (wavefront-uniform values).  `stg` is the calling wavefront's staging area.
+//
+// WAVES == 1: a tile is the business of one wavefront.  The records of the next pass are fetched
+// before the tile goes out, so that their latency passes behind the stores.
+// WAVES == 2 (one env, a tile is one row): both wavefronts work on every row; wavefront h keeps the
+// records of units 64 h ... 64 h + 63 in registers and stores one half of the row, and two staging
+// areas alternate so that one barrier per row is enough.
+//
+// SCRIPT: the units the heuristic policy moves decide their next action from the very pair
+// tests the observation rows are made of (App. A "Role-Appropriate Heuristic Policy Mechanism":
+// a unit acts on what it sees and can reach).  Every unit that a deciding observer sees bids
+// with LDS atomic minima for "its target" (key: the role's order, then distance, then index,
+// with "in its hurtbox" riding in the lowest bit) and for "its nearest enemy"; afterwards the
+// deciding units read their winners (decide_units).
+template <int WAVES, bool SCRIPT>
+__device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WAVES> &rec,
+                                           const ZoneLds &Z, float *stg, int grp, int tile,
+                                           int tile_step, int tile_end, ScriptLds<WAVES> *script)
+{
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    typedef float v2 __attribute__((ext_vector_type(2)));
+    typedef float v4h __attribute__((ext_vector_type(4), aligned(8)));
+    const int N = a.p.num_units;
+    const int D = a.obs_dim;
+    const int T = a.rows_per_tile, S = a.rows_per_pass;
+    const int ZC = a.zone_chunks;
+    const int lane = (int)(threadIdx.x & 63);
+    const int wave = WAVES == 2 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    const int l = lane + 64 * wave;              // among the lanes that share a tile
+    const int rows = envs_of_group(a, grp) * N;
+    const size_t row0 = (size_t)grp * a.envs_per_block * N;       // the group's first row
+    uint64_t *const vis_mask = late_args()->vis_mask;
+    const bool whole = (D & 3) == 0;             // rows are whole 16-byte chunks
+    const bool grouped = (D & 15) == 0;          // ... and whole 64-byte groups
+    // the lane's place in a pass: row slot s, unit u
+    const int s = WAVES == 1 ? quotient(lane, a.magic_n) : 0;
+    const int u = WAVES == 1 ? lane - s * N : l;
+    const bool holds = s < S && u < N;
+    // the rest of a row, copied chunk by chunk: the own block (four chunks) and the zone slots
+    const int TC = 4 + ZC;
+    const int ts0 = WAVES == 1 ? quotient(lane, a.magic_tc) : 0;
+    int vis_lo = 0, vis_hi = 0;
+    uint64_t passes_done = 0;
+    // the logical chunk in the lane's place of a store pass, counted from where the wavefront's part
+    // of the tile starts (WAVES == 2: the second half of the row)
+    const int half_row = WAVES == 2 ? ((D >> 3) + 3) & ~3 : 0;
+    const int from = wave ? half_row : 0;
+    const int lane_chunk = whole ? staged_chunk(from + lane) - from : lane;
+
+    // what a pass works on: the lane's row f (observer i of the env whose units start at record gN)
+    // and what it reads of the observer and of its unit
+    int f = 0, i = 0, gN = 0, fi = 0, fu = 0;
+    v2 opos = {};
+    float4 V = {}, Ub = {}, Ug = {}, Uk = {};
+    float orange = 0.0f, ohw = 0.0f, speed = 0.0f;
+    auto fetch = [&](int f0, int r0, int rows_here, bool units) {
+        f = f0 + (r0 + s < rows_here ? r0 + s : 0);
+        gN = WAVES == 1 ? mul24(quotient(f, a.magic_n), N) : 0;
+        i = f - gN;
+        opos = *reinterpret_cast<const v2 *>(&rec.own[0][f].z);
+        V = rec.view[f];
+        orange = rec.own[1][f].y;
+        const float2 M = rec.mark[f];
+        ohw = M.x;
+        fi = __float_as_int(M.y);
+        if (units) {
+            const int uk = gN + (WAVES == 1 && u >= N ? 0 : u);
+            Ub = rec.own[0][uk];
+            Ug = rec.own[1][uk];
+            Uk = rec.own[2][uk];
+            speed = rec.own[3][uk].y;
+            fu = __float_as_int(rec.mark[uk].y);
+        }
+    };
+    auto rows_of = [&](int t) { const int left = rows - t * T; return left < T ? left : T; };
+    if (tile < tile_end && tile * T < rows) fetch(tile * T, 0, rows_of(tile), true);
+
+    for (; tile < tile_end && tile * T < rows; tile += tile_step) {
+        const int f0 = tile * T;                 // the tile's first row within the group
+        const int rows_here = rows_of(tile);
+        // where the tile starts relative to a 16-byte boundary (rows of 2 mod 4 floats)
+        const int pad = whole ? 0 : 2 * (int)((row0 + f0) & 1);
+        float *const buf = stg + (WAVES == 2 ? (tile & 1) * a.stage_floats : 0);
+        v4 *const vstage = reinterpret_cast<v4 *>(buf);
+        int pass = tile * a.passes_per_tile;
+        for (int r0 = 0; r0 < rows_here; r0 += S, ++pass) {
+            const int sr = r0 + s;               // the lane's row of the tile
+            const bool has = holds && sr < rows_here;
+            // offset of this unit from the observer; `dot` is its component along the heading
+            const float dx = Ub.z - opos.x;
+            const float dy = Ub.w - opos.y;
+            float dot;
+            const float g2 = hurtbox_gap2(dx, dy, V.x, V.y, orange, ohw, -ohw, dot);
+            const float d2 = (dx * dx) + (dy * dy);
+            const bool same_team = ((fi ^ fu) & 2) == 0;
+            const bool same_bush = ((fi >> 8) & 0x1ff) == (fu >> 20);
+            const bool concealed = (fu & 64) && !same_team && !same_bush;
+            const bool self = i == u;
+            const bool pair = has && (fi & fu & 1) && !self && d2 <= V.z && !concealed;
+            const bool seen = pair && (d2 == 0.0f || dot >= V.w * __builtin_sqrtf(d2));
+            // (only ever asked of a unit that is seen, so a cone-bounded hurtbox adds no test)
+            const bool hit = (((fi & 4) != 0) == same_team) && (g2 <= Uk.y * Uk.y);
+            if (SCRIPT) {
+                // the observer decides its next action: this unit bids if it is seen (nothing to
+                // do in a pass whose observers decide nothing or see nobody)
+                const bool vis = seen && (fi & 32);
+                if (__ballot(vis) != 0ull) {
+                    const int uk = gN + (WAVES == 1 && u >= N ? 0 : u);
+                    const bool i_heals = (fi & 4) != 0;
+                    const unsigned d2b = (unsigned)__float_as_int(d2);
+                    const int ord = script->order[uk];
+                    const bool injured = (ord & 1) != 0;
+                    if (vis && hit && (!i_heals || injured)) atomicOr(&script->canhit[f], 1);
+                    if (vis && !same_team)
+                        atomicMin(&script->nkey[f], ((unsigned long long)d2b << 32) | (unsigned)u);
+                    if (vis && (i_heals == same_team)) {
+                        // Healer: injured allies first; Assassin: lowest maximum health first
+                        const unsigned order = i_heals ? (injured ? 0u : 1u)
+                                                       : ((fi & 16) ? (unsigned)(ord >> 1) : 0u);
+                        const unsigned hi = (order << 8) | (d2b >> 24);
+                        const unsigned lo = (d2b << 8) | ((unsigned)u << 1) | (hit ? 1u : 0u);
+                        atomicMin(&script->tkey[f], ((unsigned long long)hi << 32) | lo);
+                    }
+                }
+            }
+            if (vis_mask) {
+                // the ballot over the lanes holds the rows of the pass's observers: lane p keeps
+                // the ballot of pass p of the group (WAVES == 2: of row p of 64, rows of a pass = 1)
+                const uint64_t b = __ballot(seen);
+                if (WAVES == 1) {
+                    vis_lo = lane == pass ? (int)(uint32_t)b : vis_lo;
+                    vis_hi = lane == pass ? (int)(uint32_t)(b >> 32) : vis_hi;
+                    passes_done |= 1ull << pass;
+                } else {
+                    vis_lo = lane == (pass & 63) ? (int)(uint32_t)b : vis_lo;
+                    vis_hi = lane == (pass & 63) ? (int)(uint32_t)(b >> 32) : vis_hi;
+                    if ((pass & 63) == 63 || pass + 1 == N) {
+                        const int row = (pass & ~63) + lane;
+                        const int words = (N + 63) >> 6;
+                        if (row <= pass)
+                            vis_mask[(row0 + row) * words + wave] =
+                                ((uint64_t)(uint32_t)vis_hi << 32) | (uint32_t)vis_lo;
+                    }
+                }
+            }
+            if (has && !self) {
+                // block position in the row: behind the own block, in index order
+                const int at = pad + mul24(sr, D) + 16 * (u < i ? u + 1 : u);
+                const int m = seen ? -1 : 0;
+                auto masked = [m](float v) { return __int_as_float(__float_as_int(v) & m); };
+                // (written as 128-bit vector values: as four-member structs the last chunk has been
+                // seen to go out as four separate dwords, each a many-way bank conflict)
+                const v4 w0 = {masked(Ub.x), masked(Ub.y), masked(dx), masked(dy)};
+                const v4 w1 = {masked(Ug.x), masked(Ug.y), masked(Ug.z), masked(Ug.w)};
+                const v4 w2 = {masked(Uk.x), masked(Uk.y), masked(Uk.z), masked(Uk.w)};
+                const v4 w3 = {masked(1.0f), seen && same_team ? 1.0f : 0.0f,
+                               seen && hit ? 1.0f : 0.0f, masked(speed)};
+                if (grouped) {
+                    // (the block is one 64-byte group: its chunks are permuted among themselves)
+                    char *const d = reinterpret_cast<char *>(buf);
+                    const int at0 = 4 * at | ((at >> 1) & 48);
+                    *reinterpret_cast<v4 *>(d + at0) = w0;
+                    *reinterpret_cast<v4 *>(d + (at0 ^ 16)) = w1;
+                    *reinterpret_cast<v4 *>(d + (at0 ^ 32)) = w2;
+                    *reinterpret_cast<v4 *>(d + (at0 ^ 48)) = w3;
+                } else if (whole) {
+                    const int cb = at >> 2;
+                    vstage[staged_chunk(cb)] = w0;
+                    vstage[staged_chunk(cb + 1)] = w1;
+                    vstage[staged_chunk(cb + 2)] = w2;
+                    vstage[staged_chunk(cb + 3)] = w3;
+                } else {
+                    // (8-byte aligned: two 8-byte halves per instruction)
+                    v4h *d = reinterpret_cast<v4h *>(buf + at);
+                    d[0] = w0;
+                    d[1] = w1;
+                    d[2] = w2;
+                    d[3] = w3;
+                }
+            }
+            if (r0 + S < rows_here) fetch(f0, r0 + S, rows_here, true);
+        }
+        for (int q = l, ts = ts0; q < rows_here * TC;
+             q += 64 * WAVES, ts = WAVES == 1 ? quotient(q, a.magic_tc) : 0) {
+            const int c = q - mul24(ts, TC);
+            const int tf = f0 + ts;
+            const int zc = c - 4;
+            const bool zone = zc >= 0;
+            const int zi = WAVES == 1 ? mul24(quotient(tf, a.magic_n), ZC) + zc : zc;
+            const float4 v = zone ? Z.val[zi] : rec.own[0][c * (64 * WAVES) + tf];
+            const int rel = zone ? Z.rel[zi] : 0;
+            const v2 pos = *reinterpret_cast<const v2 *>(&rec.own[0][tf].z);
+            const int en = (__float_as_int(rec.mark[tf].y) << 28) >> 31;         // enabled: bit 3
+            const int kind = zc - 3 * third(zc);
+            const float x = __int_as_float(__float_as_int(pos.x) & rel);
+            const float y = __int_as_float(__float_as_int(pos.y) & rel);
+            const float tv[4] = {v.x - (kind == 2 ? y : 0.0f), v.y - (kind == 0 ? x : 0.0f),
+                                 v.z - (kind == 0 ? y : 0.0f), v.w - (kind == 1 ? x : 0.0f)};
+            float to[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) to[k] = __int_as_float(__float_as_int(tv[k]) & en);
+            const int at = pad + mul24(ts, D) + 4 * c + (zone ? 16 * N - 16 : 0);
+            if (whole) {
+                const v4 w = {to[0], to[1], to[2], to[3]};
+                vstage[staged_chunk(at >> 2)] = w;
+            } else {
+                // (a row ends on half a chunk: its second half belongs to the next row)
+                v2 *d = reinterpret_cast<v2 *>(buf + at);
+                d[0] = v2{to[0], to[1]};
+                if (!zone || 4 * zc + 2 < 6 * a.p.max_zones) d[1] = v2{to[2], to[3]};
+            }
+        }
+        {
+            const int next = tile + tile_step;
+            if (next < tile_end && next * T < rows) fetch(next * T, 0, rows_of(next), WAVES == 1);
+        }
         lds_barrier<WAVES>();
 
-        // stream the finished rows: LDS chunk -> one 16-byte store, row order, 1 KB per instruction
-        float *row = out + i0 * D;
-        // the lane reads physical chunk first_chunk + 64 p in pass p: whole runs, in lane order
-        const float4 *src = stage + ((WAVES == 1) ? 0 : (i0 & 1) * row_chunks) + first_chunk;
-        constexpr int PASS_STRIDE = 64;
-        if (D == Dp) {
-            // every chunk is whole: fetch all passes from LDS first, then issue the stores
-            float4 v[kMaxPasses];
+        // stream the finished rows: LDS chunk -> one 16-byte store, 1 KB per instruction
+        // (WAVES == 2: a wavefront stores one half, both halves whole 64-byte groups)
+        float *const out = a.obs + (row0 + f0) * D - pad;            // 16-byte aligned
+        const int floats = pad + rows_here * D;
+        const int chunks = floats >> 2;          // (whole chunks, the first one perhaps half ours)
+        const int to = WAVES == 2 && !wave ? half_row : chunks;
+        const int first = wave ? 0 : pad >> 1;   // 0, or 1: chunk 0 starts in the previous row
+        const float4 *src = reinterpret_cast<const float4 *>(buf) + from + lane;
+        char *dst = reinterpret_cast<char *>(out) + 16 * from;
+        for (int left = to - from, skip = first; left > 0; left -= 64 * kPassBatch, skip = 0) {
+            float4 v[kPassBatch];
 #pragma unroll
-            for (int p = 0; p < kMaxPasses; ++p)
-                if (p < a.copy_passes)
-                    v[p] = src[p * PASS_STRIDE];
+            for (int p = 0; p < kPassBatch; ++p)
+                if (64 * p < left) v[p] = src[64 * p];
 #pragma unroll
-            for (int p = 0; p < kMaxPasses; ++p) {
-                // (the mask is made opaque here: as a loop invariant its tests would be hoisted
-                // out of the observer loop as forty lane masks, most of them spilled)
-                int vm = valid[p];
-                asm volatile("" : "+v"(vm));
-                if (p < a.copy_passes && vm != 0) {
-                    // single-wave workgroups stream with the non-temporal hint: the rows are
-                    // never read back by the kernel, and the hint measurably raises the store
-                    // rate there (it lowers it for the two-wave, 8 KB-row case)
+            for (int p = 0; p < kPassBatch; ++p) {
+                const int c = lane_chunk + 64 * p;
+                if (c < left && (p > 0 || c >= skip)) {
                     f4u o = {v[p].x, v[p].y, v[p].z, v[p].w};
-                    f4u *dp = reinterpret_cast<f4u *>(row + dst_off[p]);
+                    f4u *dp = reinterpret_cast<f4u *>(dst + 1024 * p + (uint32_t)(16 * lane_chunk));
+                    // single-wave envs stream with the non-temporal hint: the rows are never
+                    // read back by the kernel, and the hint measurably raises the store rate there
+                    // (it lowers it for the two-wave, 8 KB-row case)
                     if (WAVES == 1) __builtin_nontemporal_store(o, dp);
                     else *dp = o;
                 }
             }
-        } else {
-            // rows that are not a multiple of 16 bytes end in a partial chunk
-#pragma unroll
-            for (int p = 0; p < kMaxPasses; ++p) {
-                int vm = valid[p];
-                asm volatile("" : "+v"(vm));
-                if (p < a.copy_passes && vm != 0) {
-                    const float4 v = src[p * PASS_STRIDE];
-                    float *dp = row + dst_off[p];
-                    if (vm == 15) {
-                        f4u o = {v.x, v.y, v.z, v.w};
-                        *reinterpret_cast<f4u *>(dp) = o;
-                    } else {
-                        if (vm & 1) dp[0] = v.x;
-                        if (vm & 2) dp[1] = v.y;
-                        if (vm & 4) dp[2] = v.z;
-                        if (vm & 8) dp[3] = v.w;
-                    }
-                }
+            src += 64 * kPassBatch;
+            dst += 1024 * kPassBatch;
+        }
+        if (!whole && !wave) {
+            // the half chunks at the two ends: lane 0 the first, lane 1 the last
+            const bool head = lane == 0 && pad != 0, tail = lane == 1 && (floats & 2) != 0;
+            if (head || tail) {
+                const int at = head ? 2 : floats - 2;
+                *reinterpret_cast<v2 *>(out + at) = *reinterpret_cast<const v2 *>(buf + at);
             }
         }
-        if (WAVES == 1) lds_barrier<WAVES>();    // two waves alternate between two staging buffers
+        if (WAVES == 1) lds_barrier<1>();        // (two wavefronts alternate between two areas)
         // Two-wave envs (one workgroup per env for the whole launch): the wavefront lets its row
         // stores land before it goes on.  Without this the XCDs drain at different rates and the
-        // launch lasts as long as the slowest (ends of the eight between 163 and 216 us on 64v64);
-        // with at most one row per wavefront in flight they stay together (191 ... 209 us) and the
-        // launch is 3 % shorter.  Waiting before the next row's stores instead, or allowing two
-        // or four stores to stay in flight, gains less; the packed-env kernels gain nothing.
+        // launch lasts as long as the slowest.
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (i0 == i_begin) TABX_STAMP(3);
     }
-    TABX_STAMP(4);
+    if (WAVES == 1 && vis_mask) {
+        // lane l writes row l of the group, if it was this wavefront's: row l % S of pass l / S
+        const int p = quotient(lane, a.magic_s);
+        const uint32_t lo = (uint32_t)__shfl(vis_lo, p), hi = (uint32_t)__shfl(vis_hi, p);
+        const uint64_t range = N >= 64 ? ~0ull : ((1ull << N) - 1ull);
+        if (lane < rows && ((passes_done >> p) & 1))
+            vis_mask[row0 + lane] = ((((uint64_t)hi << 32) | lo) >> mul24(lane - mul24(p, S), N)) & range;
+    }
+}
 
-    if (want_vis) {
-        uint64_t *const vis_mask = late_args()->vis_mask;
-        lds_barrier<WAVES>();
-        if (has && P.u >= i_begin && P.u < i_end) {
-            if (WAVES == 1) {
-                const uint64_t range = N >= 64 ? ~0ull : ((1ull << N) - 1ull);
-                vis_mask[P.k] = (my_row >> P.base) & range;
-            } else {
-                const int words = (N + 63) >> 6;
-                for (int w = 0; w < words; ++w) vis_mask[P.k * words + w] = sh.rowbits[P.u][w];
-            }
-        }
-    }
-
-    if (SCRIPT) {
-        lds_barrier<WAVES>();      // all bids are in
-        // (wavefronts sharing an env group: the one that ran the unit's pass as observer holds its bids)
-        const bool decides = (sh.seer[P.l] & 0x20) != 0 && P.u >= i_begin && P.u < i_end;
-        if (decides) {
-            const unsigned long long tk = script->tkey[P.l];
-            const unsigned long long nk = script->nkey[P.l];
-            Sighting S;
-            S.tgt = tk == ~0ull ? -1 : (int)((tk >> 1) & 0x7f);
-            S.tgt_d2 = __int_as_float((int)(unsigned)(tk >> 8));
-            S.tgt_in_box = (tk & 1ull) != 0ull;
-            const int tl = P.base + (S.tgt >= 0 ? S.tgt : 0);
-            S.T = sh.ob.pose[tl];
-            S.tr = script->extra[tl].x;
-            S.any_enemy = nk != ~0ull;
-            S.near_d2 = __int_as_float((int)(unsigned)(nk >> 32));
-            const float4 E = sh.ob.pose[P.base + (S.any_enemy ? (int)(nk & 0x7f) : 0)];
-            S.near_dx = E.x - U.x;
-            S.near_dy = E.y - U.y;
-            S.can_hit = script->canhit[P.l] != 0;
-            const int remembered = C.restarted ? 0 : C.mem_valid;
-            const float mx = C.mem_x;
-            const float my = C.mem_y;
-            policy_cascade(a, P, U, cu, su, in_bush, S, (uint32_t)C.tick, remembered, mx, my, zd,
-                           a.pa.next_action);
-        }
-    }
+// Scripted units: everybody has bid (all rows of the group are written); the lane's unit reads
+// its winners and runs the rule cascade.
+template <int WAVES>
+__device__ __forceinline__ void decide_units(const KArgs &a, const Records<64 * WAVES> &rec,
+                                             const ScriptLds<WAVES> *script, const Place &P,
+                                             float speed, const Carry &C, const float *zd)
+{
+    const float4 B = rec.own[0][P.l], G = rec.own[1][P.l], V = rec.view[P.l];
+    const int fu = __float_as_int(rec.mark[P.l].y);
+    if (!(fu & 32)) return;
+    Unit U = {};
+    U.x = B.z;
+    U.y = B.w;
+    U.range = G.y;
+    U.dmg = G.z;
+    U.cd = G.w;
+    U.speed = speed;
+    const unsigned long long tk = script->tkey[P.l];
+    const unsigned long long nk = script->nkey[P.l];
+    Sighting S;
+    S.tgt = tk == ~0ull ? -1 : (int)((tk >> 1) & 0x7f);
+    S.tgt_d2 = __int_as_float((int)(unsigned)(tk >> 8));
+    S.tgt_in_box = (tk & 1ull) != 0ull;
+    const int tl = P.base + (S.tgt >= 0 ? S.tgt : 0);
+    const float4 Tb = rec.own[0][tl], Tv = rec.view[tl];
+    S.T = make_float4(Tb.z, Tb.w, Tv.x, Tv.y);
+    S.tr = rec.own[2][tl].y;
+    S.any_enemy = nk != ~0ull;
+    S.near_d2 = __int_as_float((int)(unsigned)(nk >> 32));
+    const float4 E = rec.own[0][P.base + (S.any_enemy ? (int)(nk & 0x7f) : 0)];
+    S.near_dx = E.z - U.x;
+    S.near_dy = E.w - U.y;
+    S.can_hit = script->canhit[P.l] != 0;
+    const int remembered = C.restarted ? 0 : C.mem_valid;
+    const bool in_bush = ((fu >> 20) & 3) == TABX_ZONE_BUSH;
+    policy_cascade(a, P, U, V.x, V.y, in_bush, S, (uint32_t)C.tick, remembered, C.mem_x, C.mem_y,
+                   zd, late_args()->pa.next_action);
 }
 
 } // namespace tabx

@@ -132,8 +132,8 @@ __device__ __forceinline__ int policy_cascade(const KArgs &a, const Place &P, co
 // Decides for the lane's unit from the state in U (heading cosine / sine cu, su, zone code
 // code_u under it); returns the action, or -1 if the unit is not the policy's to move.  Writes
 // the action and the remembered target position.  All lanes of the workgroup call it.
-template <int WAVES>
-__device__ __forceinline__ int policy_env(const KArgs &a, Shared<WAVES> &sh, const Place &P,
+template <int WAVES, class Sh>
+__device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P,
                                           const Unit &U, int code_u, float cu, float su,
                                           const float *zd)
 {
@@ -144,7 +144,7 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Shared<WAVES> &sh, con
     const bool concealable = in_bush && !(U.reveal > 0.0f);
     sh.po.pose[P.l] = make_float4(U.x, U.y, cu, su);
     sh.po.body[P.l] = make_float4(U.radius, U.hmax, U.hp, 0.0f);
-    sh.seer[P.l] = (P.has ? U.alive : 0) | (U.team << 1) | (concealable ? 4 : 0) | (my_key << 8);
+    sh.po.seer[P.l] = (P.has ? U.alive : 0) | (U.team << 1) | (concealable ? 4 : 0) | (my_key << 8);
     // per-env tick counter and the unit's memory, requested before the scan
     const bool decide = P.has && U.enabled && U.alive && (!pa.controlled || at32(pa.controlled, P.k));
     const uint32_t tick = decide ? (uint32_t)a.st.t[P.e] : 0u;
@@ -166,7 +166,7 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Shared<WAVES> &sh, con
     bool any_enemy = false, can_hit = false, tgt_in_box = false;
     float tgt_d2 = 0.0f, tgt_key = 0.0f, near_d2 = 0.0f, near_dx = 0.0f, near_dy = 0.0f;
     for (int j = 0; j < N; ++j) {
-        const int fj = sh.seer[P.base + j];
+        const int fj = sh.po.seer[P.base + j];
         const float4 A = sh.po.pose[P.base + j];
         const float4 B = sh.po.body[P.base + j];
         const float dx = A.x - U.x;

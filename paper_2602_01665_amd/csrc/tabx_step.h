@@ -11,13 +11,13 @@ namespace tabx {
 // Level bank: an episode of the lane's env is about to start (`take`, uniform over the env's
 // lanes).  Unit 0 takes the queued level (folded into [0, num_levels)), refills the queue with
 // a uniform draw, the hash of (level_seed, env, draws so far), and tells the env's other lanes
-// through LDS (`rows`: one slot per env of the workgroup).  Returns the env's new row, or -1
+// through LDS (one slot per env of the workgroup).  Returns the env's new row, or -1
 // if it keeps its level.  All lanes call it.
-template <int WAVES>
-__device__ __forceinline__ int advance_level(const KArgs &a, Shared<WAVES> &sh, const Place &P,
-                                             bool take, int *rows)
+template <int WAVES, class Sh>
+__device__ __forceinline__ int advance_level(const KArgs &a, Sh &sh, const Place &P,
+                                             bool take)
 {
-    if (P.has && P.u == 0 && P.chunk == 0) {
+    if (P.has && P.u == 0) {
         int row = -1;
         if (take) {
             const LateArgs late = late_args();
@@ -30,19 +30,19 @@ __device__ __forceinline__ int advance_level(const KArgs &a, Shared<WAVES> &sh, 
             next_level[P.e] = (int)(policy_hash(a.p.level_seed, (uint32_t)(P.e + a.p.env_id_offset), 0u, n, 3u) % L);
             level_draws[P.e] = (int)(n + 1u);
         }
-        rows[P.g] = row;
+        sh.level_rows[P.g] = row;
     }
     lds_barrier<WAVES>();
-    return P.has ? rows[P.g] : -1;
+    return P.has ? sh.level_rows[P.g] : -1;
 }
 
 // `forced` >= 0 replaces the unit's entry of the action array (the policy stage chose it).
-// `zd`: the env's zone descriptors in LDS (elliptical zones), rewritten when the env changes
-// level.  Returns whether any env of the workgroup restarted.
-// SHARED: further wavefronts of the workgroup take the stepped units over and decide for some of them.
-template <int WAVES, bool SHARED = false>
-__device__ __forceinline__ bool step_env(const KArgs &a, Shared<WAVES> &sh, float *zd,
-                                         int *rows, Place &P, Unit &U, int &code_u, Carry &C,
+// `Z`: the zone descriptors of the group's envs in LDS, rewritten for envs that change level; `zd`
+// those of the lane's env.  Returns whether any env of the workgroup restarted.
+template <int WAVES, class Sh>
+__device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
+                                         const ZoneLds &Z, const float *zd,
+                                         Place &P, Unit &U, int &code_u, Carry &C,
                                          int forced)
 {
     float zeff = 0.0f;             // effect magnitude of the zone under the unit (elliptical zones)
@@ -63,7 +63,6 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Shared<WAVES> &sh, floa
     const int kills_run = (want_kills && has) ? at32(kill_run_p, (size_t)P.e) : 0;
     const float ret_run = (ret_run_p && has) ? at32(ret_run_p, (size_t)P.e) : 0.0f;
     float bdmg = 0.0f;
-    const bool writer = P.chunk == 0;      // (always: only a group's first wavefront steps)
     // persistent velocities: the acceleration the last action stage set is part of the state
     const bool dynamic = late->p.dynamics == 1;
     float acx = 0.0f, acy = 0.0f;
@@ -163,7 +162,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Shared<WAVES> &sh, floa
     // their XCD's share of the array (lane l of the j-th wavefront: line 64 j + l); the later
     // generations find them in the cache.  Measured with a fresh action batch per tick:
     // c3 108.6 -> 102.5 us, c4 95.4 -> 89.7 us (101 / 88 us with actions that are cached anyway).
-    if (writer) {
+    {
         const size_t span = (size_t)a.groups_per_xcd * a.envs_per_block * N;   // units per XCD
         const size_t first = (size_t)(blockIdx.x & 7) * span;
         const size_t off = ((size_t)(blockIdx.x >> 3) * 64 + (size_t)(threadIdx.x & 63)) * 128;
@@ -326,12 +325,12 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Shared<WAVES> &sh, floa
     const bool pred[4] = {en && U.team == 0, en && U.team != 0,
                           has && U.alive && U.team == 0, has && U.alive && U.team != 0};
     int cnt[4];
-    env_counts(sh, P, N, pred, cnt);
+    env_counts<WAVES>(sh, P, N, pred, cnt);
     // episode metrics need the alive counts at entry as well (first loss of a unit)
     int before[4] = {0, 0, 0, 0};
     if (want_kills) {
         const bool pred0[4] = {alive0 && U.team == 0, alive0 && U.team != 0, false, false};
-        env_counts(sh, P, N, pred0, before);
+        env_counts<WAVES>(sh, P, N, pred0, before);
     }
     lds_barrier<WAVES>();
 
@@ -358,7 +357,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Shared<WAVES> &sh, floa
         r0 = r0 + (ally_win ? 1.0f : -1.0f);
         r1 = r1 + (ally_win ? -1.0f : 1.0f);
     }
-    if (has && writer) a.rewards[P.k] = U.enabled ? (U.team ? r1 : r0) : 0.0f;
+    if (has) a.rewards[P.k] = U.enabled ? (U.team ? r1 : r0) : 0.0f;
 
     // auto-reset of finished envs; the potential of the fresh state seeds phi_prev
     float phi_next = phi;
@@ -367,25 +366,28 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Shared<WAVES> &sh, floa
         bool en_next = en;
         if (a.p.num_levels > 0) {
             // the finished envs move to their queued level: new specifications, new zones
-            const int row = advance_level<WAVES>(a, sh, P, done, rows);
+            const int row = advance_level<WAVES>(a, sh, P, done);
             if (row >= 0) {
                 P.row = row;
                 P.ks = (size_t)row * N + P.u;
                 load_spec(a, P.ks, U);
                 en_next = U.enabled != 0;
-                if (a.zdesc_staged) {
-                    const int zlen = 6 * a.p.max_zones;
-                    for (int q = P.u; q < zlen; q += N) zd[q] = a.sc.zone_desc[(size_t)row * zlen + q];
-                }
             }
-            if (a.zdesc_staged) lds_barrier<WAVES>();
+            if (a.zones_in_lds) {
+                // (level_rows holds an entry for every env of the group, and only for those)
+                const int chunks = envs_of_group(a, P.grp) * a.zone_chunks;
+                for (int q = P.l; q < chunks; q += 64 * WAVES) {
+                    const int g = quotient(q, a.magic_zc);
+                    const int moved = sh.level_rows[g];
+                    if (moved >= 0) put_zone_chunk(a, Z, g, q - g * a.zone_chunks, moved);
+                }
+                lds_barrier<WAVES>();
+            }
         }
         if (done) {
-            // a new episode remembers nothing.  Where several wavefronts share the env group, the
-            // wavefront that later decides for the unit clears its flag itself (it may set it again
-            // at once, and two wavefronts' stores to one byte have no order between them)
+            // a new episode remembers nothing
             uint8_t *const mem_valid = late->pa.mem.mem_valid;
-            if (mem_valid && writer && (!SHARED || P.u < a.obs_per_chunk)) mem_valid[P.k] = 0;
+            if (mem_valid) mem_valid[P.k] = 0;
             code_u = spawn_unit(a, zd, P.row, P.ks, U, zeff);
             acx = 0.0f;
             acy = 0.0f;
@@ -397,7 +399,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Shared<WAVES> &sh, floa
             // teams and placeholders may differ in the new level
             const bool pred1[4] = {en_next && U.team == 0, en_next && U.team != 0, false, false};
             int fresh[4];
-            env_counts(sh, P, N, pred1, fresh);
+            env_counts<WAVES>(sh, P, N, pred1, fresh);
             c0 = fresh[0];
             c1 = fresh[1];
         }
@@ -408,7 +410,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Shared<WAVES> &sh, floa
         team_means(sh, P, N, c0, c1, f0, f1);
         if (done) phi_next = f0 - f1;
     }
-    if (has && P.u == 0 && writer) {
+    if (has && P.u == 0) {
         a.st.t[P.e] = done ? 0 : t_new;
         a.st.phi_prev[P.e] = phi_next;
         a.dones[P.e] = done ? 1 : 0;
@@ -432,8 +434,8 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Shared<WAVES> &sh, floa
             if (late->st.ep_first_kill && want_kills) late->st.ep_first_kill[P.e] = (int8_t)kills;
         }
     }
-    if (has && writer) store_state(a, P.k, U);
-    if (dynamic && has && writer) {
+    if (has) store_state(a, P.k, U);
+    if (dynamic && has) {
         late->st.ax[P.k] = acx;
         late->st.ay[P.k] = acy;
     }
