@@ -83,6 +83,8 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
             load_spec(a, P.ks, U);
             load_state(a, P.k, U);
         }
+        StepIn in = {};
+        if (DO_STEP) in = load_step(a, P);
         // scripted units: the action decided on at the end of the previous call and the memory, asked for
         // with the state (whether the unit is the policy's to move or not: one round trip for all)
         int told = 0, waiting = 0;
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
         }
         TABX_STAMP(6);
         if (DO_STEP) {
-            const bool restarted = step_env<WAVES>(a, sh, Z, zd, P, U, code_u, C, forced);
+            const bool restarted = step_env<WAVES>(a, sh, Z, zd, P, U, code_u, C, in, forced);
             if (PACKED && a.p.num_levels > 0 && restarted) {
                 // zone slots of the envs that changed level
                 const int row = Zr.lane ? sh.level_rows[Zr.zg] : -1;
