@@ -172,10 +172,12 @@ struct Records {
 
 struct NoRecords {};
 
-// TILES: the observe stage reads records (tabx_observe.h).
-template <int WAVES, bool TILES>
+// TILES: the observe stage reads records (tabx_observe.h).  PAIR: the two wavefronts that step an env
+// are not the whole workgroup (group_barrier).
+template <int WAVES, bool TILES, bool PAIR_ = false>
 struct __attribute__((aligned(64))) Shared {
     static constexpr int L = 64 * WAVES;
+    static constexpr bool PAIR = PAIR_;
     union {
         struct {                  // step stage
             union {
@@ -201,6 +203,7 @@ struct __attribute__((aligned(64))) Shared {
     };
     uint64_t ballots[WAVES][4];
     int      level_rows[64];      // level bank: the row an env slot has just switched to, or -1
+    unsigned arrivals;            // PAIR: arrivals of the two wavefronts at their barriers so far
 };
 
 // Orders LDS traffic between the lanes of a workgroup without waiting for global
@@ -217,6 +220,28 @@ __device__ __forceinline__ void lds_barrier()
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    }
+}
+
+// The barrier of the wavefronts that hold the units of an env (the stages up to the rows).  Where they
+// are two of more wavefronts of the workgroup, the others wait at the workgroup's own barrier
+// meanwhile, so the two count each other's arrivals in LDS: the n-th barrier is passed once 2 n
+// arrivals are in.  Both execute the same sequence of barriers (every condition around one is uniform
+// over the env), and both are resident, so the wait ends.
+template <int WAVES, class Sh>
+__device__ __forceinline__ void group_barrier(Sh &sh)
+{
+    if constexpr (Sh::PAIR) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        unsigned before = 0;
+        if ((threadIdx.x & 63) == 0)
+            before = __hip_atomic_fetch_add(&sh.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const unsigned goal = ((unsigned)__builtin_amdgcn_readfirstlane((int)before) | 1u) + 1u;
+        while (__hip_atomic_load(&sh.arrivals, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < goal)
+            __builtin_amdgcn_s_sleep(1);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    } else {
+        lds_barrier<WAVES>();
     }
 }
 
@@ -479,14 +504,14 @@ __device__ __forceinline__ void env_counts(Sh &sh, const Place &P, int N,
             const uint64_t b = __ballot(pred[q]);
             if ((P.l & 63) == 0) sh.ballots[wv][q] = b;
         }
-        lds_barrier<WAVES>();
+        group_barrier<WAVES>(sh);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             cnt[q] = 0;
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) cnt[q] += __popcll(sh.ballots[w][q]);
         }
-        lds_barrier<WAVES>();
+        group_barrier<WAVES>(sh);
     }
 }
 

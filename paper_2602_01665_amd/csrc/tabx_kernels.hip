@@ -45,13 +45,19 @@ template <int WAVES, bool DO_POLICY, bool DO_STEP, bool DO_OBS, bool SCRIPT = fa
           int TWIN = 0>
 __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kernel(const KArgs a)
 {
-    // the single-wavefront forms of a plain tick or observe keep the units in registers
-    constexpr bool PACKED = DO_OBS && WAVES == 1 && TWIN == 0 && !SCRIPT && !DO_POLICY;
-    __shared__ Shared<WAVES, DO_OBS && !PACKED> sh;
+    // without further wavefronts to share the rows with, the units stay in registers
+    constexpr bool PACKED = DO_OBS && TWIN == 0;
+    // TWIN: the workgroup has TWIN times the wavefronts that hold an env's units
+    constexpr bool PAIR = WAVES == 2 && TWIN != 0;
+    __shared__ Shared<WAVES, DO_OBS && !PACKED, PAIR> sh;
     extern __shared__ __attribute__((aligned(16))) float dyn[];
     // all wavefronts of the workgroup write rows; with TWIN only the first of them steps the envs
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const bool lead = !TWIN || wave == 0;
+    const bool lead = !TWIN || wave < WAVES;
+    if (PAIR) {
+        if (threadIdx.x == 0) sh.arrivals = 0;
+        lds_barrier<2>();
+    }
     TABX_STAMP(0);
 #ifdef TABX_TRACE
     if ((threadIdx.x & 63) == 0) {
@@ -71,7 +77,7 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
     // a wavefront that waits for the step fetches the zones meanwhile, unless the step looks at them
     // itself or may move an env to another level, whose zones it then writes
     const bool zones_elsewhere = TWIN && a.p.num_levels == 0 && a.p.zone_shapes == 0;
-    if (DO_OBS && TWIN && wave == 1 && zones_elsewhere) {
+    if (DO_OBS && TWIN && wave == WAVES && zones_elsewhere) {
         put_zones<64>(a, Z, P.grp, (int)(threadIdx.x & 63));
         lds_barrier<1>();
         if (P.chunk == 0) global_state_zones<64>(a, Z, P.grp, (int)(threadIdx.x & 63));
@@ -101,7 +107,7 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
         if (PACKED) Zr = load_zone_regs(a, P);
         if (a.zones_in_lds && !zones_elsewhere) {
             put_zones<64 * WAVES>(a, Z, P.grp, P.l);
-            lds_barrier<WAVES>();
+            group_barrier<WAVES>(sh);
         }
         float zeff_unused = 0.0f;
         int forced = -1;
@@ -132,30 +138,29 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
         }
         TABX_STAMP(1);
         if constexpr (PACKED) {
-            if (P.grp < a.num_groups) observe_packed(a, sh, dyn, P, U, code_u, C, Zr);
+            observe_packed<WAVES, SCRIPT>(a, sh, dyn, P, U, code_u, C, Zr, told, script, zd);
         } else if constexpr (DO_OBS) {
-            lds_barrier<WAVES>();          // the step stage is done with the LDS union
+            group_barrier<WAVES>(sh);          // the step stage is done with the LDS union
             publish_units<WAVES, SCRIPT>(a, sh, P, U, code_u, C.ratio, C.cu, C.su, told, script);
             if (!zones_elsewhere && P.chunk == 0) {
-                lds_barrier<WAVES>();
+                group_barrier<WAVES>(sh);
                 global_state_zones<64 * WAVES>(a, Z, P.grp, P.l);
             }
             speed = U.speed;
         }
     }
     if constexpr (DO_OBS && !PACKED) {
-        if (TWIN) lds_barrier<2>(); else lds_barrier<WAVES>();
+        lds_barrier<2>();                  // the whole workgroup
         TABX_STAMP(2);
-        float *stg = dyn + (WAVES == 1 ? wave * a.stage_floats : 0);
+        float *stg = dyn + wave * a.stage_floats;
         if (P.grp < a.num_groups) {
             const int first = P.chunk * a.tiles_per_chunk;
             const int end = first + a.tiles_per_chunk < a.tiles ? first + a.tiles_per_chunk : a.tiles;
-            write_rows<WAVES, SCRIPT>(a, sh.rec, Z, stg, P.grp, WAVES == 1 ? first + wave : first,
-                                      TWIN ? TWIN : 1, end, script);
+            write_rows<WAVES, SCRIPT>(a, sh.rec, Z, stg, P.grp, first + wave, WAVES * TWIN, end, script);
         }
         TABX_STAMP(4);
         if (SCRIPT) {
-            if (TWIN) lds_barrier<2>(); else lds_barrier<WAVES>();      // all bids are in
+            lds_barrier<2>();              // all bids are in
             if (lead) decide_units<WAVES>(a, sh.rec, script, P, speed, C, zd);
         }
     }
@@ -347,15 +352,23 @@ static size_t plan_lds(Mode mode, KArgs &a, int waves)
     if (mode == MODE_RESET) return 0;
     size_t floats = 0;
     if (observing) {
-        // one staging area per wavefront, in whole store passes (64 lanes of 16 bytes)
-        const size_t tile = a.packed ? (size_t)a.envs_per_block * a.rows_per_flush * a.obs_dim
-                                     : (size_t)a.rows_per_tile * a.obs_dim + (a.obs_dim % 4 ? 2 : 0);
-        a.stage_floats = (int)((tile + 255) / 256 * 256);
-        floats = (size_t)a.stage_floats * waves * (a.twin ? a.twin : 1);
+        if (a.packed && waves == 2) {
+            // two alternating areas of one row; the second half's store passes read whole passes
+            const int cpr = a.obs_dim / 4, row_chunks = (cpr + 3) & ~3, half = ((cpr >> 1) + 3) & ~3;
+            floats = 4 * ((size_t)row_chunks + half + 64 * a.copy_passes);
+        } else {
+            // one staging area per wavefront, in whole store passes (64 lanes of 16 bytes)
+            const size_t tile = a.packed ? (size_t)a.envs_per_block * a.rows_per_flush * a.obs_dim
+                                         : (size_t)a.rows_per_tile * a.obs_dim + (a.obs_dim % 4 ? 2 : 0);
+            a.stage_floats = (int)((tile + 255) / 256 * 256);
+            floats = (size_t)a.stage_floats * waves * (a.twin ? a.twin : 1);
+        }
     }
     // the zone descriptors of the workgroup's envs: 16-byte chunks with a mask each
-    a.zones_in_lds = a.zone_chunks > 0 && (a.p.zone_shapes == 1 || mode == MODE_POLICY ||
-                                           (observing && !a.packed));
+    // (elliptical zones; the bush search of deciding units; the copied part of the rows of a tile)
+    a.zones_in_lds = a.zone_chunks > 0 &&
+                     (a.p.zone_shapes == 1 || mode == MODE_POLICY || mode == MODE_POLICY_STEP_OBSERVE ||
+                      mode == MODE_SCRIPTED_STEP_OBSERVE || (observing && !a.packed));
     a.zone_offset = (int)floats;
     if (a.zones_in_lds) floats += ((size_t)a.envs_per_block * a.zone_chunks * 5 + 3) / 4 * 4;
     // the bidding area of scripted units that decide in the observe stage
@@ -390,20 +403,34 @@ static hipError_t launch_mode(Mode mode, KArgs a, hipStream_t stream)
     case MODE_OBSERVE:
         if (WAVES == 1 && a.twin)
             return enqueue(tabx_tick_kernel<1, false, false, true, false, 2>, grid, block, lds, stream, a);
+        if (WAVES == 2 && a.twin > 2)
+            return enqueue(tabx_tick_kernel<2, false, false, true, false, 3>, grid, block, lds, stream, a);
+        if (WAVES == 2 && a.twin)
+            return enqueue(tabx_tick_kernel<2, false, false, true, false, 2>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<WAVES, false, false, true>, grid, block, lds, stream, a);
     case MODE_STEP_OBSERVE:
         if (WAVES == 1 && a.twin > 2)
             return enqueue(tabx_tick_kernel<1, false, true, true, false, 4>, grid, block, lds, stream, a);
         if (WAVES == 1 && a.twin)
             return enqueue(tabx_tick_kernel<1, false, true, true, false, 2>, grid, block, lds, stream, a);
+        if (WAVES == 2 && a.twin > 2)
+            return enqueue(tabx_tick_kernel<2, false, true, true, false, 3>, grid, block, lds, stream, a);
+        if (WAVES == 2 && a.twin)
+            return enqueue(tabx_tick_kernel<2, false, true, true, false, 2>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<WAVES, false, true, true>, grid, block, lds, stream, a);
     case MODE_POLICY:
         return enqueue(tabx_tick_kernel<WAVES, true, false, false>, grid, block, lds, stream, a);
     case MODE_POLICY_STEP_OBSERVE:
+        if (a.twin)
+            return enqueue(tabx_tick_kernel<WAVES, true, true, true, false, 2>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<WAVES, true, true, true>, grid, block, lds, stream, a);
     case MODE_SCRIPTED_STEP_OBSERVE:
         if (WAVES == 1)
             return enqueue(tabx_tick_kernel<1, false, true, true, true, 2>, grid, block, lds, stream, a);
+        if (a.twin > 2)
+            return enqueue(tabx_tick_kernel<2, false, true, true, true, 3>, grid, block, lds, stream, a);
+        if (a.twin)
+            return enqueue(tabx_tick_kernel<2, false, true, true, true, 2>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<2, false, true, true, true>, grid, block, lds, stream, a);
     }
     return hipErrorInvalidValue;
@@ -447,40 +474,64 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     //    one's step), but the wavefronts of ONE workgroup can: the first one steps the envs and
     //    leaves the units in LDS, then all of them write rows.
     a.obs_chunks = 1;
+    a.obs_per_chunk = N;
     a.twin = 0;
     a.packed = 0;
     int K = 1;                                   // passes per tile
+    // The form with the units in registers (tabx_observe_packed.h) needs whole 16-byte chunks per row,
+    // a zone chunk per lane at most and R rows of G envs in kMaxPasses store passes.
+    const int cpr = a.obs_dim / 4;
+    const int R = waves == 1 && N % 2 == 0 && 2 * G * cpr <= 64 * kMaxPasses ? 2 : 1;
+    const bool packs = a.obs_dim % 4 == 0 && G * a.zone_chunks <= 64 * waves &&
+                       (waves == 2 || R * G * cpr <= 64 * kMaxPasses);
+    const bool rows = mode == MODE_OBSERVE || mode == MODE_STEP_OBSERVE ||
+                      mode == MODE_POLICY_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE;
+    a.rows_per_flush = R;
     if (waves == 1) {
-        // the form with the units in registers: whole 16-byte chunks per row, a zone chunk per lane
-        // at most, R rows of G envs in kMaxPasses store passes; two rows per flush where they fit
-        const int cpr = a.obs_dim / 4;
-        const int R = N % 2 == 0 && 2 * G * cpr <= 64 * kMaxPasses ? 2 : 1;
-        const bool packs = a.obs_dim % 4 == 0 && G * a.zone_chunks <= 64 && R * G * cpr <= 64 * kMaxPasses;
+        a.copy_passes = (R * G * cpr + 63) / 64;
         // under one residency round (eight single-wavefront workgroups per CU)
         const bool small_batch = a.num_groups <= 8 * kComputeUnits;
+        // eight or more flushes of two rows and a short step stage (10v10 x 16384: 120 us with one
+        // wavefront per group, 101.5 with two; 5v5 x 65536 84 and 82; with body collisions 63.5 and 64)
         const bool long_chain = N >= 16 && !(p->collision_alpha > 0.0f);
+        // a batch of at most three env groups per CU is one chain from the first load to the last store
+        const bool tiny_batch = a.num_groups <= 3 * kComputeUnits && N > 4;
         if (mode == MODE_OBSERVE) {
+            // about four flushes of two rows per workgroup (10v10: 3 workgroups per group 94.7 us, 2 96.8,
+            // 4 99), at most two where each fetches elliptical zones
             const int flushes = (N + 1) / 2;
             int share = N < 4 ? 1 : (flushes + 3) / 4 + (flushes < 8 ? 1 : 0);
             if (share > 8) share = 8;
             if (share > 2 && p->zone_shapes == 1) share = 2;
-            a.packed = packs;
             a.twin = packs ? 0 : 2;
             a.obs_per_chunk = ((N + share - 1) / share + R - 1) / R * R;
             a.obs_chunks = packs ? (N + a.obs_per_chunk - 1) / a.obs_per_chunk : share;
         } else if (mode == MODE_STEP_OBSERVE) {
             a.twin = packs && !small_batch && !long_chain ? 0 : 2;
-            a.packed = a.twin == 0;
-            a.obs_per_chunk = N;
-            const bool tiny_batch = a.num_groups <= 3 * kComputeUnits && N > 4;
+            // (16v16 x 6144: 90 us with two wavefronts, 88 with four; 5v5 x 4096 14 and 12.5)
             if ((N >= 32 || tiny_batch) && p->zone_shapes == 0) a.twin = 4;
-        } else if (mode == MODE_SCRIPTED_STEP_OBSERVE) {
-            a.twin = 2;
+        } else if (rows) {
+            // scripted: 10v10 x 16384 139 us with one wavefront per group, 121 with two; the policy as a
+            // scan stage keeps them all waiting, so it has one unless the rows ask for tiles
+            a.twin = mode == MODE_POLICY_STEP_OBSERVE && packs ? 0 : 2;
         }
-        a.rows_per_flush = R;
-        a.copy_passes = (R * G * cpr + 63) / 64;
-        if (mode == MODE_STEP_OBSERVE && a.twin && !small_batch && a.tiles >= 8 * a.twin && 2 * S * a.obs_dim <= 2 * kTileFloats) K = 2;
+        // On a full machine a plain tick stores two passes' rows at a time: 10v10 x 16384 107 -> 101.5 us,
+        // 16v16 x 6144 93.8 -> 88; with a generation or less, shorter chains count (9v8 x 5003 39 and 48).
+        if (mode == MODE_STEP_OBSERVE && a.twin && !small_batch && a.tiles >= 8 * a.twin &&
+            2 * S * a.obs_dim <= 2 * kTileFloats)
+            K = 2;
+    } else if (rows) {
+        const int half = ((cpr >> 1) + 3) & ~3, rest = ((cpr + 3) & ~3) - half;
+        a.copy_passes = ((half > rest ? half : rest) + 63) / 64;
+        // At most two envs per CU: the chain of N rows is what such a launch waits for, so four more
+        // wavefronts (two, if their staging areas would not fit) write rows as well (64v64 x 64
+        // 139 -> 72 us, x 512 151 -> 117; x 768 153 -> 169 us, where HBM takes what two write).
+        const size_t area = (size_t)(a.obs_dim + 2 + 255) / 256 * 1024;
+        const size_t rest_bytes = sizeof(Shared<2, true, true>) + sizeof(ScriptLds<2>) + 1024;
+        const int more = 6 * area + rest_bytes <= kLdsPerWorkgroupBytes ? 3 : 2;
+        if (p->num_envs <= 2 * kComputeUnits || !packs) a.twin = mode == MODE_POLICY_STEP_OBSERVE ? 2 : more;
     }
+    a.packed = rows && a.twin == 0;
     a.passes_per_tile = K;
     a.rows_per_tile = K * S;
     a.tiles = (G * N + a.rows_per_tile - 1) / a.rows_per_tile;

@@ -34,8 +34,8 @@ struct ScriptLds {
 
 // Leaves the lane's unit in LDS as the observe stage needs it (state in U, heading cosine / sine
 // cu, su, zone code code_u; `told`: the policy moves it); also the action mask and the units' part of the global state.
-template <int WAVES, bool SCRIPT>
-__device__ __forceinline__ void publish_units(const KArgs &a, Shared<WAVES, true> &sh, const Place &P,
+template <int WAVES, bool SCRIPT, class Sh>
+__device__ __forceinline__ void publish_units(const KArgs &a, Sh &sh, const Place &P,
                                               const Unit U, int code_u, float ratio, float cu,
                                               float su, int told, ScriptLds<WAVES> *script)
 {
@@ -81,7 +81,7 @@ __device__ __forceinline__ void publish_units(const KArgs &a, Shared<WAVES, true
         }
     }
     if (SCRIPT) {
-        lds_barrier<WAVES>();
+        group_barrier<WAVES>(sh);
         int rank = 0;
         for (int jj = 0; jj < a.p.num_units; ++jj)
             rank += script->hmax[P.base + jj] < U.hmax ? 1 : 0;
@@ -129,11 +129,9 @@ __device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); 
 // Writes the rows of the tiles tile, tile + tile_step, ... < tile_end of env group `grp`
 // (wavefront-uniform values).  `stg` is the calling wavefront's staging area.
 //
-// WAVES == 1: a tile is the business of one wavefront.  The records of the next pass are fetched
+// A tile is the business of one wavefront.  WAVES == 1: the records of the next pass are fetched
 // before the tile goes out, so that their latency passes behind the stores.
-// WAVES == 2 (one env, a tile is one row): both wavefronts work on every row; wavefront h keeps the
-// records of units 64 h ... 64 h + 63 in registers and stores one half of the row, and two staging
-// areas alternate so that one barrier per row is enough.
+// WAVES == 2 (one env, a tile is one row): the wavefront goes over the units in two halves.
 //
 // SCRIPT: the units the heuristic policy moves decide their next action from the very pair
 // tests the observation rows are made of (App. A "Role-Appropriate Heuristic Policy Mechanism":
@@ -154,8 +152,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     const int T = a.rows_per_tile, S = a.rows_per_pass;
     const int ZC = a.zone_chunks;
     const int lane = (int)(threadIdx.x & 63);
-    const int wave = WAVES == 2 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
-    const int l = lane + 64 * wave;              // among the lanes that share a tile
+    constexpr int HALVES = WAVES;
     const int rows = envs_of_group(a, grp) * N;
     const size_t row0 = (size_t)grp * a.envs_per_block * N;       // the group's first row
     uint64_t *const vis_mask = late_args()->vis_mask;
@@ -163,18 +160,14 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     const bool grouped = (D & 15) == 0;          // ... and whole 64-byte groups
     // the lane's place in a pass: row slot s, unit u
     const int s = WAVES == 1 ? quotient(lane, a.magic_n) : 0;
-    const int u = WAVES == 1 ? lane - s * N : l;
-    const bool holds = s < S && u < N;
+    int u = WAVES == 1 ? lane - s * N : lane;
+    const bool holds = s < S && (HALVES == 2 || u < N);
     // the rest of a row, copied chunk by chunk: the own block (four chunks) and the zone slots
     const int TC = 4 + ZC;
     const int ts0 = WAVES == 1 ? quotient(lane, a.magic_tc) : 0;
     int vis_lo = 0, vis_hi = 0;
     uint64_t passes_done = 0;
-    // the logical chunk in the lane's place of a store pass, counted from where the wavefront's part
-    // of the tile starts (WAVES == 2: the second half of the row)
-    const int half_row = WAVES == 2 ? ((D >> 3) + 3) & ~3 : 0;
-    const int from = wave ? half_row : 0;
-    const int lane_chunk = whole ? staged_chunk(from + lane) - from : lane;
+    const int lane_chunk = whole ? staged_chunk(lane) : lane;
 
     // what a pass works on: the lane's row f (observer i of the env whose units start at record gN)
     // and what it reads of the observer and of its unit
@@ -182,7 +175,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     v2 opos = {};
     float4 V = {}, Ub = {}, Ug = {}, Uk = {};
     float orange = 0.0f, ohw = 0.0f, speed = 0.0f;
-    auto fetch = [&](int f0, int r0, int rows_here, bool units) {
+    auto fetch = [&](int f0, int r0, int rows_here) {
         f = f0 + (r0 + s < rows_here ? r0 + s : 0);
         gN = WAVES == 1 ? mul24(quotient(f, a.magic_n), N) : 0;
         i = f - gN;
@@ -192,29 +185,69 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         const float2 M = rec.mark[f];
         ohw = M.x;
         fi = __float_as_int(M.y);
-        if (units) {
-            const int uk = gN + (WAVES == 1 && u >= N ? 0 : u);
-            Ub = rec.own[0][uk];
-            Ug = rec.own[1][uk];
-            Uk = rec.own[2][uk];
-            speed = rec.own[3][uk].y;
-            fu = __float_as_int(rec.mark[uk].y);
-        }
+        const int uk = gN + (u < N ? u : 0);
+        Ub = rec.own[0][uk];
+        Ug = rec.own[1][uk];
+        Uk = rec.own[2][uk];
+        speed = rec.own[3][uk].y;
+        fu = __float_as_int(rec.mark[uk].y);
+    };
+    // the copied part of the rows of a tile, into its staging area
+    auto copy_tail = [&](int f0, int rows_here, int pad, float *buf) {
+                for (int q = lane, ts = ts0; q < rows_here * TC;
+                     q += 64, ts = WAVES == 1 ? quotient(q, a.magic_tc) : 0) {
+                    const int c = q - mul24(ts, TC);
+                    const int tf = f0 + ts;
+                    const int zc = c - 4;
+                    const bool zone = zc >= 0;
+                    const int zi = WAVES == 1 ? mul24(quotient(tf, a.magic_n), ZC) + zc : zc;
+                    const float4 v = zone ? Z.val[zi] : rec.own[0][c * (64 * WAVES) + tf];
+                    const int rel = zone ? Z.rel[zi] : 0;
+                    const v2 pos = *reinterpret_cast<const v2 *>(&rec.own[0][tf].z);
+                    const int en = (__float_as_int(rec.mark[tf].y) << 28) >> 31;         // enabled: bit 3
+                    const int kind = zc - 3 * third(zc);
+                    const float x = __int_as_float(__float_as_int(pos.x) & rel);
+                    const float y = __int_as_float(__float_as_int(pos.y) & rel);
+                    const float tv[4] = {v.x - (kind == 2 ? y : 0.0f), v.y - (kind == 0 ? x : 0.0f),
+                                         v.z - (kind == 0 ? y : 0.0f), v.w - (kind == 1 ? x : 0.0f)};
+                    float to[4];
+        #pragma unroll
+                    for (int k = 0; k < 4; ++k) to[k] = __int_as_float(__float_as_int(tv[k]) & en);
+                    const int at = pad + mul24(ts, D) + 4 * c + (zone ? 16 * N - 16 : 0);
+                    if (whole) {
+                        const v4 w = {to[0], to[1], to[2], to[3]};
+                        reinterpret_cast<v4 *>(buf)[staged_chunk(at >> 2)] = w;
+                    } else {
+                        // (a row ends on half a chunk: its second half belongs to the next row)
+                        v2 *d = reinterpret_cast<v2 *>(buf + at);
+                        d[0] = v2{to[0], to[1]};
+                        if (!zone || 4 * zc + 2 < 6 * a.p.max_zones) d[1] = v2{to[2], to[3]};
+                    }
+                }
     };
     auto rows_of = [&](int t) { const int left = rows - t * T; return left < T ? left : T; };
-    if (tile < tile_end && tile * T < rows) fetch(tile * T, 0, rows_of(tile), true);
+    auto pad_of = [&](int t) { return whole ? 0 : 2 * (int)((row0 + t * T) & 1); };
+    if (tile < tile_end && tile * T < rows) {
+        fetch(tile * T, 0, rows_of(tile));
+    }
 
     for (; tile < tile_end && tile * T < rows; tile += tile_step) {
         const int f0 = tile * T;                 // the tile's first row within the group
         const int rows_here = rows_of(tile);
         // where the tile starts relative to a 16-byte boundary (rows of 2 mod 4 floats)
-        const int pad = whole ? 0 : 2 * (int)((row0 + f0) & 1);
-        float *const buf = stg + (WAVES == 2 ? (tile & 1) * a.stage_floats : 0);
+        const int pad = pad_of(tile);
+        float *const buf = stg;
         v4 *const vstage = reinterpret_cast<v4 *>(buf);
         int pass = tile * a.passes_per_tile;
         for (int r0 = 0; r0 < rows_here; r0 += S, ++pass) {
+#pragma unroll 1
+        for (int h = 0; h < HALVES; ++h) {
+            if (HALVES == 2 && h) {
+                u = lane + 64;
+                fetch(f0, r0, rows_here);
+            }
             const int sr = r0 + s;               // the lane's row of the tile
-            const bool has = holds && sr < rows_here;
+            const bool has = holds && sr < rows_here && (HALVES == 1 || u < N);
             // offset of this unit from the observer; `dot` is its component along the heading
             const float dx = Ub.z - opos.x;
             const float dy = Ub.w - opos.y;
@@ -234,7 +267,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
                 // do in a pass whose observers decide nothing or see nobody)
                 const bool vis = seen && (fi & 32);
                 if (__ballot(vis) != 0ull) {
-                    const int uk = gN + (WAVES == 1 && u >= N ? 0 : u);
+                    const int uk = gN + (u < N ? u : 0);
                     const bool i_heals = (fi & 4) != 0;
                     const unsigned d2b = (unsigned)__float_as_int(d2);
                     const int ord = script->order[uk];
@@ -254,22 +287,14 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
             }
             if (vis_mask) {
                 // the ballot over the lanes holds the rows of the pass's observers: lane p keeps
-                // the ballot of pass p of the group (WAVES == 2: of row p of 64, rows of a pass = 1)
+                // the ballot of pass p of the group (WAVES == 2: one word of the one row)
                 const uint64_t b = __ballot(seen);
-                if (WAVES == 1) {
+                if (HALVES == 2) {
+                    if (lane == 0) vis_mask[2 * (row0 + f) + h] = b;
+                } else {
                     vis_lo = lane == pass ? (int)(uint32_t)b : vis_lo;
                     vis_hi = lane == pass ? (int)(uint32_t)(b >> 32) : vis_hi;
                     passes_done |= 1ull << pass;
-                } else {
-                    vis_lo = lane == (pass & 63) ? (int)(uint32_t)b : vis_lo;
-                    vis_hi = lane == (pass & 63) ? (int)(uint32_t)(b >> 32) : vis_hi;
-                    if ((pass & 63) == 63 || pass + 1 == N) {
-                        const int row = (pass & ~63) + lane;
-                        const int words = (N + 63) >> 6;
-                        if (row <= pass)
-                            vis_mask[(row0 + row) * words + wave] =
-                                ((uint64_t)(uint32_t)vis_hi << 32) | (uint32_t)vis_lo;
-                    }
                 }
             }
             if (has && !self) {
@@ -307,54 +332,25 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
                     d[3] = w3;
                 }
             }
-            if (r0 + S < rows_here) fetch(f0, r0 + S, rows_here, true);
+            if (HALVES == 1 && r0 + S < rows_here) fetch(f0, r0 + S, rows_here);
         }
-        for (int q = l, ts = ts0; q < rows_here * TC;
-             q += 64 * WAVES, ts = WAVES == 1 ? quotient(q, a.magic_tc) : 0) {
-            const int c = q - mul24(ts, TC);
-            const int tf = f0 + ts;
-            const int zc = c - 4;
-            const bool zone = zc >= 0;
-            const int zi = WAVES == 1 ? mul24(quotient(tf, a.magic_n), ZC) + zc : zc;
-            const float4 v = zone ? Z.val[zi] : rec.own[0][c * (64 * WAVES) + tf];
-            const int rel = zone ? Z.rel[zi] : 0;
-            const v2 pos = *reinterpret_cast<const v2 *>(&rec.own[0][tf].z);
-            const int en = (__float_as_int(rec.mark[tf].y) << 28) >> 31;         // enabled: bit 3
-            const int kind = zc - 3 * third(zc);
-            const float x = __int_as_float(__float_as_int(pos.x) & rel);
-            const float y = __int_as_float(__float_as_int(pos.y) & rel);
-            const float tv[4] = {v.x - (kind == 2 ? y : 0.0f), v.y - (kind == 0 ? x : 0.0f),
-                                 v.z - (kind == 0 ? y : 0.0f), v.w - (kind == 1 ? x : 0.0f)};
-            float to[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) to[k] = __int_as_float(__float_as_int(tv[k]) & en);
-            const int at = pad + mul24(ts, D) + 4 * c + (zone ? 16 * N - 16 : 0);
-            if (whole) {
-                const v4 w = {to[0], to[1], to[2], to[3]};
-                vstage[staged_chunk(at >> 2)] = w;
-            } else {
-                // (a row ends on half a chunk: its second half belongs to the next row)
-                v2 *d = reinterpret_cast<v2 *>(buf + at);
-                d[0] = v2{to[0], to[1]};
-                if (!zone || 4 * zc + 2 < 6 * a.p.max_zones) d[1] = v2{to[2], to[3]};
-            }
         }
+        if (HALVES == 2) u = lane;
+        copy_tail(f0, rows_here, pad, buf);
         {
             const int next = tile + tile_step;
-            if (next < tile_end && next * T < rows) fetch(next * T, 0, rows_of(next), WAVES == 1);
+            if (next < tile_end && next * T < rows) fetch(next * T, 0, rows_of(next));
         }
-        lds_barrier<WAVES>();
+        lds_barrier<1>();
 
         // stream the finished rows: LDS chunk -> one 16-byte store, 1 KB per instruction
-        // (WAVES == 2: a wavefront stores one half, both halves whole 64-byte groups)
         float *const out = a.obs + (row0 + f0) * D - pad;            // 16-byte aligned
         const int floats = pad + rows_here * D;
         const int chunks = floats >> 2;          // (whole chunks, the first one perhaps half ours)
-        const int to = WAVES == 2 && !wave ? half_row : chunks;
-        const int first = wave ? 0 : pad >> 1;   // 0, or 1: chunk 0 starts in the previous row
-        const float4 *src = reinterpret_cast<const float4 *>(buf) + from + lane;
-        char *dst = reinterpret_cast<char *>(out) + 16 * from;
-        for (int left = to - from, skip = first; left > 0; left -= 64 * kPassBatch, skip = 0) {
+        const int first = pad >> 1;   // 0, or 1: chunk 0 starts in the previous row
+        const float4 *src = reinterpret_cast<const float4 *>(buf) + lane;
+        char *dst = reinterpret_cast<char *>(out);
+        for (int left = chunks, skip = first; left > 0; left -= 64 * kPassBatch, skip = 0) {
             float4 v[kPassBatch];
 #pragma unroll
             for (int p = 0; p < kPassBatch; ++p)
@@ -375,7 +371,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
             src += 64 * kPassBatch;
             dst += 1024 * kPassBatch;
         }
-        if (!whole && !wave) {
+        if (!whole) {
             // the half chunks at the two ends: lane 0 the first, lane 1 the last
             const bool head = lane == 0 && pad != 0, tail = lane == 1 && (floats & 2) != 0;
             if (head || tail) {
@@ -383,10 +379,9 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
                 *reinterpret_cast<v2 *>(out + at) = *reinterpret_cast<const v2 *>(buf + at);
             }
         }
-        if (WAVES == 1) lds_barrier<1>();        // (two wavefronts alternate between two areas)
-        // Two-wave envs (one workgroup per env for the whole launch): the wavefront lets its row
-        // stores land before it goes on.  Without this the XCDs drain at different rates and the
-        // launch lasts as long as the slowest.
+        lds_barrier<1>();
+        // (8 KB rows: the wavefront lets its row land before it goes on, which keeps the XCDs together,
+        // as in tabx_observe_packed.h: 64v64 x 512 125 us without, 117 with)
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     if (WAVES == 1 && vis_mask) {
@@ -397,6 +392,32 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         if (lane < rows && ((passes_done >> p) & 1))
             vis_mask[row0 + lane] = ((((uint64_t)hi << 32) | lo) >> mul24(lane - mul24(p, S), N)) & range;
     }
+}
+
+// A scripted unit with the winning bids `tk`, `nk`: what it has made out of the units it sees, and the
+// rule cascade.  pose_of(j): x, y, cos, sin of unit j of its env; radius_of(j): its body radius.
+template <class PoseOf, class RadiusOf>
+__device__ __forceinline__ void decide_unit(const KArgs &a, const Place &P, const Unit &U, float cu,
+                                            float su, bool in_bush, unsigned long long tk,
+                                            unsigned long long nk, bool can_hit, PoseOf pose_of,
+                                            RadiusOf radius_of, const Carry &C, const float *zd)
+{
+    Sighting S;
+    S.tgt = tk == ~0ull ? -1 : (int)((tk >> 1) & 0x7f);
+    S.tgt_d2 = __int_as_float((int)(unsigned)(tk >> 8));
+    S.tgt_in_box = (tk & 1ull) != 0ull;
+    const int tl = S.tgt >= 0 ? S.tgt : 0;
+    S.T = pose_of(tl);
+    S.tr = radius_of(tl);
+    S.any_enemy = nk != ~0ull;
+    S.near_d2 = __int_as_float((int)(unsigned)(nk >> 32));
+    const float4 E = pose_of(S.any_enemy ? (int)(nk & 0x7f) : 0);
+    S.near_dx = E.x - U.x;
+    S.near_dy = E.y - U.y;
+    S.can_hit = can_hit;
+    const int remembered = C.restarted ? 0 : C.mem_valid;
+    policy_cascade(a, P, U, cu, su, in_bush, S, (uint32_t)C.tick, remembered, C.mem_x, C.mem_y, zd,
+                   late_args()->pa.next_action);
 }
 
 // Scripted units: everybody has bid (all rows of the group are written); the lane's unit reads
@@ -416,26 +437,12 @@ __device__ __forceinline__ void decide_units(const KArgs &a, const Records<64 * 
     U.dmg = G.z;
     U.cd = G.w;
     U.speed = speed;
-    const unsigned long long tk = script->tkey[P.l];
-    const unsigned long long nk = script->nkey[P.l];
-    Sighting S;
-    S.tgt = tk == ~0ull ? -1 : (int)((tk >> 1) & 0x7f);
-    S.tgt_d2 = __int_as_float((int)(unsigned)(tk >> 8));
-    S.tgt_in_box = (tk & 1ull) != 0ull;
-    const int tl = P.base + (S.tgt >= 0 ? S.tgt : 0);
-    const float4 Tb = rec.own[0][tl], Tv = rec.view[tl];
-    S.T = make_float4(Tb.z, Tb.w, Tv.x, Tv.y);
-    S.tr = rec.own[2][tl].y;
-    S.any_enemy = nk != ~0ull;
-    S.near_d2 = __int_as_float((int)(unsigned)(nk >> 32));
-    const float4 E = rec.own[0][P.base + (S.any_enemy ? (int)(nk & 0x7f) : 0)];
-    S.near_dx = E.z - U.x;
-    S.near_dy = E.w - U.y;
-    S.can_hit = script->canhit[P.l] != 0;
-    const int remembered = C.restarted ? 0 : C.mem_valid;
-    const bool in_bush = ((fu >> 20) & 3) == TABX_ZONE_BUSH;
-    policy_cascade(a, P, U, V.x, V.y, in_bush, S, (uint32_t)C.tick, remembered, C.mem_x, C.mem_y,
-                   zd, late_args()->pa.next_action);
+    auto pose_of = [&](int j) {
+        const float4 b = rec.own[0][P.base + j], v = rec.view[P.base + j];
+        return make_float4(b.z, b.w, v.x, v.y);
+    };
+    decide_unit(a, P, U, V.x, V.y, ((fu >> 20) & 3) == TABX_ZONE_BUSH, script->tkey[P.l], script->nkey[P.l],
+                script->canhit[P.l] != 0, pose_of, [&](int j) { return rec.own[2][P.base + j].y; }, C, zd);
 }
 
 } // namespace tabx

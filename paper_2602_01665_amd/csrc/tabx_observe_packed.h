@@ -1,4 +1,5 @@
-// Observe stage of the TABX tick with the units in registers: one wavefront per env group.
+// Observe stage of the TABX tick with the units in registers: the wavefronts that hold the units of an
+// env group also write all of its rows.
 #pragma once
 #include "tabx_device.h"
 #include "tabx_observe.h"
@@ -7,14 +8,14 @@
 
 namespace tabx {
 
-// The form of the observe stage for a wavefront that does all the rows of its group (or, stand-alone,
-// every third of them) and already holds the units: lane l keeps unit l % N of env slot l / N for the
-// whole launch, and pass i writes the rows of observer i of all G envs.  Compared with the tiles of
-// tabx_observe.h nothing but the observer is read from LDS per pass, at the price of G short runs per
-// flush and of an address register per store pass.  Measured (10v10 x 16384 stand-alone observe, 5v5 x
-// 65536 fused tick, same box): 94.7 and 84.9 us here, 97.0 and 87.6 us with tiles; where several
-// wavefronts share a group the tiles win (they need no copy of the units per wavefront).  Rows of
-// whole 16-byte chunks only.
+// Lane l keeps unit l % N of env slot l / N for the whole launch, and pass i writes the rows of observer
+// i of all G envs (64 < N: two wavefronts hold the one env and make every row together).  Compared with
+// the tiles of tabx_observe.h nothing but the observer is read from LDS per pass, at the price of G
+// short runs per flush and of an address register per store pass; where further wavefronts share a
+// group the tiles win (no copy of the units per wavefront).  Measured, same box, here / with tiles:
+// 10v10 x 16384 stand-alone observe 94.7 / 97.0 us, 5v5 x 65536 fused tick 84.9 / 87.6 us, 64v64 x 768
+// fused tick 153 / 169 us (but 64v64 x 512 151 / 117 us with six wavefronts).  Rows of whole 16-byte
+// chunks only.
 //
 // Zone slots of the rows: lane (env slot zg, 16-byte chunk zc of the zone part) keeps its four zone
 // floats in registers for the whole launch: the value (zero if the slot is inactive) and which
@@ -54,10 +55,13 @@ __device__ __forceinline__ ZoneRegs load_zone_regs(const KArgs &a, const Place &
     return Z;
 }
 
-// `stg`: the staging area, G * R rows; `C`: what the step stage left (heading, health ratio).
-__device__ __forceinline__ void observe_packed(const KArgs &a, Shared<1, false> &sh, float *stg,
-                                               const Place &P, const Unit &U, int code_u,
-                                               const Carry &C, const ZoneRegs &Zr)
+// `stg`: the staging area, G * R rows (WAVES == 2: two alternating areas of one row); `C`: what the step
+// stage left (heading, health ratio); `told`: the policy moves the unit (SCRIPT, see tabx_observe.h).
+template <int WAVES, bool SCRIPT, class Sh>
+__device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *stg, const Place &P,
+                                               const Unit &U, int code_u, const Carry &C,
+                                               const ZoneRegs &Zr, int told,
+                                               ScriptLds<WAVES> *script, const float *zd)
 {
     typedef float v4 __attribute__((ext_vector_type(4)));
     const int N = a.p.num_units;
@@ -69,10 +73,12 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Shared<1, false> 
     const bool want_vis = late_args()->vis_mask != nullptr;
     const bool want_gs = late_args()->st.global_state != nullptr;
     const int envs_here = envs_of_group(a, P.grp);
+    const int lane = P.l & 63;
+    const int wv = P.l >> 6;
     v4 *const stage = reinterpret_cast<v4 *>(stg);
     const bool blocks_aligned = (D & 15) == 0;   // every block is then one aligned 64-byte group
 
-    lds_barrier<1>();                            // the step stage is done with the LDS union
+    lds_barrier<WAVES>();                        // the step stage is done with the LDS union
 
     // ---- publish this unit as an observer
     const float cu = C.cu, su = C.su, ratio = C.ratio;
@@ -83,11 +89,21 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Shared<1, false> 
     const bool hidden = in_bush && !(U.reveal > 0.0f);
     const float cd_ratio = U.cooldown != 0.0f ? U.cd / U.cooldown : 0.0f;
     const float r2_me = U.radius * U.radius;
+    const bool decides = SCRIPT && enabled && alive && told;
     {
         const int key = in_bush ? my_code : 0x100;         // 0x100 matches no cell code
         sh.ob.pose[P.l] = make_float4(U.x, U.y, cu, su);
         sh.ob.reach[P.l] = make_float4(U.range, U.hurt_hw, U.sight_range * U.sight_range, U.cos_half);
-        sh.ob.seer[P.l] = alive | (U.team << 1) | (U.dmg < 0.0f ? 4 : 0) | (enabled ? 8 : 0) | (key << 8);
+        int role = 0;
+        if (SCRIPT) {
+            role = (U.speed >= late_args()->pa.pol.assassin_speed ? 16 : 0) | (decides ? 32 : 0);
+            script->tkey[P.l] = ~0ull;
+            script->nkey[P.l] = ~0ull;
+            script->canhit[P.l] = 0;
+            script->hmax[P.l] = has ? U.hmax : 0.0f;
+            script->order[P.l] = __float_as_int(U.radius);
+        }
+        sh.ob.seer[P.l] = alive | (U.team << 1) | (U.dmg < 0.0f ? 4 : 0) | (enabled ? 8 : 0) | role | (key << 8);
         uint8_t *const action_mask = late_args()->action_mask;
         if (has && action_mask && P.chunk == 0)
             action_mask[P.k] = (alive && U.cd <= 0.0f) ? 1 : 0;
@@ -99,15 +115,31 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Shared<1, false> 
     const float own_team = (float)U.team;
 
     const int zg = Zr.zg, zc = Zr.zc;
-    const int zone_seer0 = zg * N;               // lane of observer 0 of the zone lane's env
+    const int zone_seer0 = WAVES == 1 ? zg * N : 0;        // lane of observer 0 of the zone lane's env
     const bool cone_free = a.p.hurtbox_cone == 0;          // the hurtbox is the plain rectangle
     const int R = a.rows_per_flush;
-    const int zone_dst0 = zg * R * D + 16 * N + 4 * zc;
+    const int zone_dst0 = (WAVES == 1 ? zg * R * D : 0) + 16 * N + 4 * zc;
 
     // ---- store passes: chunk t = 64 p + l of the staged rows -> (env slot, chunk in its R rows)
     unsigned dst_off[kMaxPasses];
     bool valid[kMaxPasses];
-    {
+    // (WAVES == 2: each wavefront streams one contiguous half of the row, both whole 64-byte groups)
+    const int half_row = ((CPR >> 1) + 3) & ~3;
+    const int row_chunks = (CPR + 3) & ~3;       // pitch of the two alternating row areas
+    // the PHYSICAL chunk the lane reads in pass 0; it holds logical chunk staged_chunk(first_chunk)
+    const int first_chunk = WAVES == 2 ? wv * half_row + lane : P.l;
+    if (WAVES == 2) {
+        const int end = wv == 0 ? half_row : row_chunks;
+        int phys = first_chunk;
+        int q = staged_chunk(first_chunk);
+#pragma unroll
+        for (int p = 0; p < kMaxPasses; ++p) {
+            valid[p] = phys < end && q < CPR && envs_here > 0;
+            dst_off[p] = (unsigned)(4 * q);
+            q += 64;
+            phys += 64;
+        }
+    } else {
         const int RC = R * CPR;                  // chunks per env slot and flush
         int tg = 0;                              // env slot of chunk t
         int q = staged_chunk(P.l);               // chunk within the env's R staged rows
@@ -134,17 +166,26 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Shared<1, false> 
         }
     }
 
-    lds_barrier<1>();
+    lds_barrier<WAVES>();
+
+    // scripted deciders: what this unit contributes to a bid, whoever the observer is
+    bool injured_me = false;
+    unsigned rank_me = 0;          // how many units of the env have a smaller maximum health
+    if (SCRIPT) {
+        injured_me = U.hp < U.hmax;
+        for (int jj = 0; jj < N; ++jj) rank_me += script->hmax[P.base + jj] < U.hmax ? 1u : 0u;
+    }
 
     // ---- one pass per observer index i: every lane's unit seen from observer i of its env
     float *out = a.obs + (size_t)P.grp * G * N * D;
     uint64_t my_row = 0;
-    const int blk_row0 = P.g * R * D;
+    const int blk_row0 = WAVES == 1 ? P.g * R * D : 0;
     // the observers this workgroup writes the rows of: all of them, or its share when the rows
     // of an env group are spread over several short-lived workgroups
     const int i_begin = P.chunk * a.obs_per_chunk;
     const int i_end = (i_begin + a.obs_per_chunk < N) ? i_begin + a.obs_per_chunk : N;
     for (int i0 = i_begin; i0 < i_end; i0 += R) {
+        v4 *const area = stage + (WAVES == 1 ? 0 : (i0 & 1) * row_chunks);
         for (int rr = 0; rr < R; ++rr) {
             const int i = i0 + rr;
             const int oi = P.base + i;
@@ -168,10 +209,35 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Shared<1, false> 
             const bool seen = pair && in_range && in_cone && !concealed;
             const bool hit = pair && ((((fi >> 2) & 1) != 0) == same_team) && (g2 <= r2_me) &&
                              (in_cone || cone_free);
+            if (SCRIPT) {
+                // observer i decides its next action: this unit bids if i sees it (nothing to do
+                // in a pass whose observers decide nothing or see nobody)
+                const bool vis = seen && (fi & 32);
+                if (__ballot(vis) != 0ull) {
+                    const bool i_heals = (fi & 4) != 0;
+                    const unsigned d2b = (unsigned)__float_as_int(d2);
+                    if (vis && hit && (!i_heals || injured_me)) atomicOr(&script->canhit[oi], 1);
+                    if (vis && !same_team)
+                        atomicMin(&script->nkey[oi], ((unsigned long long)d2b << 32) | (unsigned)P.u);
+                    if (vis && (i_heals == same_team)) {
+                        // Healer: injured allies first; Assassin: lowest maximum health first
+                        const unsigned order = i_heals ? (injured_me ? 0u : 1u) : ((fi & 16) ? rank_me : 0u);
+                        const unsigned hi = (order << 8) | (d2b >> 24);
+                        const unsigned lo = (d2b << 8) | ((unsigned)P.u << 1) | (hit ? 1u : 0u);
+                        atomicMin(&script->tkey[oi], ((unsigned long long)hi << 32) | lo);
+                    }
+                }
+            }
             if (want_vis) {
-                // the ballot over the lanes is observer i's row; its own lane keeps it
+                // the ballot over the lanes is observer i's row: its own lane keeps it (WAVES == 2:
+                // one word per wavefront, lane i % 64 keeps it and 64 rows go out together)
                 const uint64_t b = __ballot(seen);
-                my_row = self ? b : my_row;
+                my_row = (WAVES == 1 ? self : lane == (i & 63)) ? b : my_row;
+                if (WAVES == 2 && ((i & 63) == 63 || i + 1 == N)) {
+                    const int row = (i & ~63) + lane;
+                    if (row <= i && envs_here > 0)         // (N > 64: two words)
+                        late_args()->vis_mask[2 * ((size_t)P.grp * N + row) + wv] = my_row;
+                }
             }
             if (has) {
                 // block position in the row: own block first, then the others in index order
@@ -198,17 +264,17 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Shared<1, false> 
                 const int cb = (buf + blk_row0 + 16 * blk) >> 2;       // first 16-byte chunk of the block
                 if (blocks_aligned) {
                     // (cb is a multiple of 4: the block's chunks are permuted among themselves)
-                    v4 *d = stage + cb;
+                    v4 *d = area + cb;
                     const int sw = (cb >> 3) & 3;
                     d[sw] = w0;
                     d[1 ^ sw] = w1;
                     d[2 ^ sw] = w2;
                     d[3 ^ sw] = w3;
                 } else {
-                    stage[staged_chunk(cb)] = w0;
-                    stage[staged_chunk(cb + 1)] = w1;
-                    stage[staged_chunk(cb + 2)] = w2;
-                    stage[staged_chunk(cb + 3)] = w3;
+                    area[staged_chunk(cb)] = w0;
+                    area[staged_chunk(cb + 1)] = w1;
+                    area[staged_chunk(cb + 2)] = w2;
+                    area[staged_chunk(cb + 3)] = w3;
                 }
             }
             if (Zr.lane) {
@@ -221,7 +287,7 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Shared<1, false> 
                     const float shift = __int_as_float((xb & Zr.sx[k]) | (yb & Zr.sy[k]));
                     zo[k] = __int_as_float(__float_as_int(Zr.val[k] - shift) & en);
                 }
-                stage[staged_chunk((buf + zone_dst0) >> 2)] = v4{zo[0], zo[1], zo[2], zo[3]};
+                area[staged_chunk((buf + zone_dst0) >> 2)] = v4{zo[0], zo[1], zo[2], zo[3]};
                 if (want_gs && i == 0) {
                     // ... and the zone slots with absolute centres are its tail
                     float *gz = late_args()->st.global_state + (size_t)(P.grp * G + zg) * D + 16 * N + 4 * zc;
@@ -230,34 +296,49 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Shared<1, false> 
                 }
             }
         }
-        lds_barrier<1>();
+        lds_barrier<WAVES>();
 
         // stream the finished rows: LDS chunk -> one 16-byte store, row order, 1 KB per instruction
         float *row = out + i0 * D;
-        // the lane reads physical chunk l + 64 p in pass p: whole runs, in lane order; all passes are
-        // fetched from LDS first, then the stores are issued
-        const float4 *src = reinterpret_cast<const float4 *>(stg) + P.l;
-        float4 v[kMaxPasses];
+        // the lane reads physical chunk first_chunk + 64 p in pass p: whole runs, in lane order; all
+        // passes are fetched from LDS first, then the stores are issued
+        const v4 *src = area + first_chunk;
+        v4 v[kMaxPasses];
 #pragma unroll
         for (int p = 0; p < kMaxPasses; ++p)
             if (p < a.copy_passes) v[p] = src[p * 64];
 #pragma unroll
         for (int p = 0; p < kMaxPasses; ++p) {
             if (p < a.copy_passes && valid[p]) {
-                // (non-temporal: the rows are never read back by the kernel, and the hint measurably
-                // raises the store rate)
-                f4u o = {v[p].x, v[p].y, v[p].z, v[p].w};
-                __builtin_nontemporal_store(o, reinterpret_cast<f4u *>(row + dst_off[p]));
+                // (single-wavefront rows go out non-temporal: they are never read back by the kernel, and
+                // the hint measurably raises the store rate there; it lowers it for 8 KB rows)
+                f4u o = v[p];
+                f4u *dp = reinterpret_cast<f4u *>(row + dst_off[p]);
+                if (WAVES == 1) __builtin_nontemporal_store(o, dp);
+                else *dp = o;
             }
         }
-        lds_barrier<1>();
+        if (WAVES == 1) lds_barrier<1>();        // (two wavefronts alternate between two areas)
+        // Two-wavefront envs (a full machine of workgroups that live as long as the launch): the wavefront
+        // lets its row stores land before it goes on.  Without this the XCDs drain at different
+        // rates and the launch lasts as long as the slowest (64v64 x 1024: 217 us against 208).
+        if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
 
-    if (want_vis) {
+    if (want_vis && WAVES == 1) {
         uint64_t *const vis_mask = late_args()->vis_mask;
         if (has && P.u >= i_begin && P.u < i_end) {
             const uint64_t range = N >= 64 ? ~0ull : ((1ull << N) - 1ull);
             vis_mask[P.k] = (my_row >> P.base) & range;
+        }
+    }
+
+    if (SCRIPT) {
+        lds_barrier<WAVES>();                    // all bids are in
+        if (decides) {
+            auto T = [&](int l) { return sh.ob.pose[P.base + l]; };
+            decide_unit(a, P, U, cu, su, in_bush, script->tkey[P.l], script->nkey[P.l], script->canhit[P.l] != 0,
+                        T, [&](int l) { return __int_as_float(script->order[P.base + l]); }, C, zd);
         }
     }
 }

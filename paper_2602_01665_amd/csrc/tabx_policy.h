@@ -151,7 +151,7 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P
     const int remembered = decide ? pa.mem.mem_valid[P.k] : 0;
     const float mx = decide ? pa.mem.mem_x[P.k] : 0.0f;
     const float my = decide ? pa.mem.mem_y[P.k] : 0.0f;
-    lds_barrier<WAVES>();
+    group_barrier<WAVES>(sh);
 
     const bool healer = U.dmg < 0.0f;
     const bool assassin = U.speed >= pa.pol.assassin_speed;
@@ -215,7 +215,7 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P
         act = policy_cascade(a, P, U, cu, su, in_bush, S, tick, remembered, mx, my, zd,
                              pa.actions_out);
     }
-    lds_barrier<WAVES>();          // the records may be overwritten by the next stage
+    group_barrier<WAVES>(sh);          // the records may be overwritten by the next stage
     return act;
 }
 

@@ -32,7 +32,7 @@ __device__ __forceinline__ int advance_level(const KArgs &a, Sh &sh, const Place
         }
         sh.level_rows[P.g] = row;
     }
-    lds_barrier<WAVES>();
+    group_barrier<WAVES>(sh);
     return P.has ? sh.level_rows[P.g] : -1;
 }
 
@@ -123,7 +123,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
         // (with persistent velocities the partners' velocities travel in the next array, which
         // the combat stage rewrites only after the barrier that ends this stage)
         if (dynamic) sh.st.aim1[P.l] = make_float4(U.vx, U.vy, 0.0f, 0.0f);
-        lds_barrier<WAVES>();
+        group_barrier<WAVES>(sh);
         float ax = 0.0f, ay = 0.0f;
         float dvx = 0.0f, dvy = 0.0f;
         const float inv_i = 1.0f / U.mass;             // 0 for a kinematic body, which takes no impulse
@@ -207,7 +207,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
                 U.vy = U.vy + dvy;
             }
         }
-        lds_barrier<WAVES>();          // the partner records are rewritten for the combat stage
+        group_barrier<WAVES>(sh);          // the partner records are rewritten for the combat stage
     }
 
     // the position is final for this tick: fetch the terrain cell under it now, the zone
@@ -291,7 +291,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
             sh.ballots[P.l >> 6][0] = b;
         }
     }
-    lds_barrier<WAVES>();
+    group_barrier<WAVES>(sh);
     if (WAVES == 2) {
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) strikers[w] = sh.ballots[w][0];
@@ -331,7 +331,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
             }
         }
     }
-    lds_barrier<WAVES>();
+    group_barrier<WAVES>(sh);
 
     // stage 2c: a strike has landed if anybody bid; unless everybody in the hurtbox is struck,
     // the victims now look up which striker designated them
@@ -390,7 +390,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
         const bool pred0[4] = {alive0 && U.team == 0, alive0 && U.team != 0, false, false};
         env_counts<WAVES>(sh, P, N, pred0, before);
     }
-    lds_barrier<WAVES>();
+    group_barrier<WAVES>(sh);
 
     // reward (Eq. 1), termination, terminal bonus
     float m0, m1;
@@ -407,7 +407,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
     } else {
         const uint64_t b = __ballot(done);
         if ((P.l & 63) == 0) sh.ballots[P.l >> 6][0] = b;
-        lds_barrier<WAVES>();
+        group_barrier<WAVES>(sh);
         any_done = (sh.ballots[0][0] | sh.ballots[WAVES - 1][0]) != 0ull;
     }
     if (done) {
@@ -419,7 +419,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
 
     // auto-reset of finished envs; the potential of the fresh state seeds phi_prev
     float phi_next = phi;
-    lds_barrier<WAVES>();          // everyone has read the ratio terms of the finished tick
+    group_barrier<WAVES>(sh);          // everyone has read the ratio terms of the finished tick
     if (any_done) {
         bool en_next = en;
         if (a.p.num_levels > 0) {
@@ -439,7 +439,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
                     const int moved = sh.level_rows[g];
                     if (moved >= 0) put_zone_chunk(a, Z, g, q - g * a.zone_chunks, moved);
                 }
-                lds_barrier<WAVES>();
+                group_barrier<WAVES>(sh);
             }
         }
         if (done) {
@@ -463,7 +463,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
         }
         sh.st.share[P.l] = make_float2((en_next && U.team == 0) ? ratio : 0.0f,
                                     (en_next && U.team != 0) ? ratio : 0.0f);
-        lds_barrier<WAVES>();
+        group_barrier<WAVES>(sh);
         float f0, f1;
         team_means(sh, P, N, c0, c1, f0, f1);
         if (done) phi_next = f0 - f1;
