@@ -170,11 +170,24 @@ struct Records {
                                   //   bush key<<8 | zone code<<20
 };
 
+// Policy stage: what a deciding unit needs of itself and of the others.
+template <int L>
+struct Scan {
+    float4 pose[L];               // x, y, cos(theta), sin(theta)
+    float4 body[L];               // radius, max health, health, -
+    int    seer[L];               // alive | team<<1 | concealable<<2 | bush key<<8
+    float4 reach[L];              // attack range, hurtbox half-width, sight range^2, cos(cone / 2)
+    int    role[L];               // team | heals<<1 | assassin<<2 | bush key<<8
+    int    who[L];                // the n-th deciding unit: lane | lane of its env's unit 0 <<8 | unit<<16
+};
+
 struct NoRecords {};
 
-// TILES: the observe stage reads records (tabx_observe.h).  PAIR: the two wavefronts that step an env
+// TILES: the observe stage reads records (tabx_observe.h).  POLICY: the policy stage runs (a single-
+// wavefront workgroup without it keeps the 1.3 KB, which decide how many fit a CU: 10v10 x 8192 with
+// body collisions 63.5 us with 11, 72.9 with 10).  PAIR: the two wavefronts that step an env
 // are not the whole workgroup (group_barrier).
-template <int WAVES, bool TILES, bool PAIR_ = false>
+template <int WAVES, bool TILES, bool POLICY, bool PAIR_ = false>
 struct __attribute__((aligned(64))) Shared {
     static constexpr int L = 64 * WAVES;
     static constexpr bool PAIR = PAIR_;
@@ -189,11 +202,7 @@ struct __attribute__((aligned(64))) Shared {
                                   //     half-width, damage, cos(cone / 2)
             unsigned long long best[L];   // ... the closest body in it: (distance^2 bits, index)
         } st;
-        struct {                  // policy stage: what a deciding unit needs of the others
-            float4 pose[L];       // x, y, cos(theta), sin(theta)
-            float4 body[L];       // radius, max health, health, -
-            int    seer[L];       // alive | team<<1 | concealable<<2 | bush key<<8
-        } po;
+        std::conditional_t<POLICY, Scan<L>, NoRecords> po;      // policy stage
         std::conditional_t<TILES, Records<L>, NoRecords> rec;   // observe stage, rows in tiles
         struct {                  // observe stage, units in registers: what an observer's row needs
             float4 pose[L];       // x, y, cos(theta), sin(theta)

@@ -9,17 +9,16 @@
 //
 // The observation tensor is almost all of the HBM traffic, and HBM only takes it
 // at full rate when every cache line is completed by consecutive stores.  The
-// observe stage therefore loops over the observers i of an env; in pass i every
-// lane tests "does observer i see / reach my unit" and writes its unit's 16-float
-// block, taken from its own registers, into an LDS image of observer i's row;
-// the finished rows (one per packed env) are then streamed to HBM front to back,
-// 16 bytes per lane and 1 KB per store instruction.  Own blocks and zone slots
-// join the same stream.
+// observe stage therefore assembles rows in LDS, as exact images, and streams them to
+// HBM front to back, 16 bytes per lane and 1 KB per store instruction: either in tiles
+// of consecutive rows that any wavefront of the workgroup makes from unit records in
+// LDS (tabx_observe.h), or, where no further wavefront shares the work, observer by
+// observer with the units in registers (tabx_observe_packed.h).
 //
-// Files: tabx_device.h (launch arguments, registers, LDS exchange area, helpers),
-// tabx_policy.h (heuristic policy: scan stage and rule cascade), tabx_step.h
-// (step stage), tabx_observe.h (observe stage, where scripted units also decide),
-// this file (kernels, argument checks, launches, the C entry points).
+// Files: tabx_device.h (launch arguments, registers, LDS exchange area, zones, helpers),
+// tabx_policy.h (heuristic policy: scan stage and rule cascade), tabx_step.h (step
+// stage), tabx_observe.h and tabx_observe_packed.h (observe stage, where scripted units
+// also decide), this file (kernels, argument checks, launches, the C entry points).
 //
 // The rules follow the paper's App. A ("Interaction Dynamics", "Reward",
 // "Observation and Global State", "Zones").  All arithmetic is float32 with one
@@ -49,7 +48,7 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
     constexpr bool PACKED = DO_OBS && TWIN == 0;
     // TWIN: the workgroup has TWIN times the wavefronts that hold an env's units
     constexpr bool PAIR = WAVES == 2 && TWIN != 0;
-    __shared__ Shared<WAVES, DO_OBS && !PACKED, PAIR> sh;
+    __shared__ Shared<WAVES, DO_OBS && !PACKED, DO_POLICY, PAIR> sh;
     extern __shared__ __attribute__((aligned(16))) float dyn[];
     // all wavefronts of the workgroup write rows; with TWIN only the first of them steps the envs
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -115,7 +114,7 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
             forced = waiting;
             late_args()->pa.actions_out[P.k] = (uint8_t)forced;
         }
-        if (DO_POLICY) {
+        if constexpr (DO_POLICY) {
             float cu = 1.0f, su = 0.0f;
             if (P.has) {
                 code_u = zone_at(a, zd, P.row, U.x, U.y, zeff_unused);
@@ -171,7 +170,7 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void tabx_reset_kernel(const KArgs a)
 {
-    __shared__ Shared<WAVES, false> sh;
+    __shared__ Shared<WAVES, false, false> sh;
     Place P = locate<WAVES>(a);
     const int N = a.p.num_units;
     const bool go = P.has && !(a.env_mask && a.env_mask[P.e] == 0);
@@ -527,7 +526,7 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         // wavefronts (two, if their staging areas would not fit) write rows as well (64v64 x 64
         // 139 -> 72 us, x 512 151 -> 117; x 768 153 -> 169 us, where HBM takes what two write).
         const size_t area = (size_t)(a.obs_dim + 2 + 255) / 256 * 1024;
-        const size_t rest_bytes = sizeof(Shared<2, true, true>) + sizeof(ScriptLds<2>) + 1024;
+        const size_t rest_bytes = sizeof(Shared<2, true, true, true>) + sizeof(ScriptLds<2>) + 1024;
         const int more = 6 * area + rest_bytes <= kLdsPerWorkgroupBytes ? 3 : 2;
         if (p->num_envs <= 2 * kComputeUnits || !packs) a.twin = mode == MODE_POLICY_STEP_OBSERVE ? 2 : more;
     }

@@ -137,59 +137,82 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P
                                           const Unit &U, int code_u, float cu, float su,
                                           const float *zd)
 {
-    const PolicyArgs &pa = a.pa;
+    const LateArgs late = late_args();
     const int N = a.p.num_units;
     const bool in_bush = (code_u & 3) == TABX_ZONE_BUSH;
     const int my_key = in_bush ? (code_u & 0xff) : 0x100;          // 0x100 matches no cell code
     const bool concealable = in_bush && !(U.reveal > 0.0f);
     sh.po.pose[P.l] = make_float4(U.x, U.y, cu, su);
     sh.po.body[P.l] = make_float4(U.radius, U.hmax, U.hp, 0.0f);
+    sh.po.reach[P.l] = make_float4(U.range, U.hurt_hw, U.sight_range * U.sight_range, U.cos_half);
+    sh.po.role[P.l] = U.team | (U.dmg < 0.0f ? 2 : 0) | (U.speed >= late->pa.pol.assassin_speed ? 4 : 0) | (my_key << 8);
     sh.po.seer[P.l] = (P.has ? U.alive : 0) | (U.team << 1) | (concealable ? 4 : 0) | (my_key << 8);
     // per-env tick counter and the unit's memory, requested before the scan
-    const bool decide = P.has && U.enabled && U.alive && (!pa.controlled || at32(pa.controlled, P.k));
+    const bool decide = P.has && U.enabled && U.alive && (!late->pa.controlled || at32(late->pa.controlled, P.k));
     const uint32_t tick = decide ? (uint32_t)a.st.t[P.e] : 0u;
-    const int remembered = decide ? pa.mem.mem_valid[P.k] : 0;
-    const float mx = decide ? pa.mem.mem_x[P.k] : 0.0f;
-    const float my = decide ? pa.mem.mem_y[P.k] : 0.0f;
+    const int remembered = decide ? late->pa.mem.mem_valid[P.k] : 0;
+    const float mx = decide ? late->pa.mem.mem_x[P.k] : 0.0f;
+    const float my = decide ? late->pa.mem.mem_y[P.k] : 0.0f;
     group_barrier<WAVES>(sh);
 
-    const bool healer = U.dmg < 0.0f;
-    const bool assassin = U.speed >= pa.pol.assassin_speed;
-    const float sight2 = U.sight_range * U.sight_range;
-    const float neg_hw = -U.hurt_hw;
+    // Which lane scans for whom.  Usually half of the units decide (the adversaries), so as many lanes
+    // as there are to spare, `parts` in all, share the partners of each deciding unit, every one
+    // taking each parts-th of them (10v10 x 16384, adversaries: 25.4 -> 21 us, the scan being bound by
+    // VALU issue).  Two wavefronts (N > 64): every lane scans for its own unit.
+    int parts = 1, part = 0, rank = 0;
+    int me = P.l, base = P.base, self = P.u;
+    bool scans = decide;
+    if (WAVES == 1) {
+        const uint64_t deciding = __ballot(decide);
+        const int count = __popcll(deciding);
+        parts = count > 0 ? 64 / count : 1;
+        parts = parts > 8 ? 8 : parts;
+        rank = __popcll(deciding & ((1ull << P.l) - 1ull));
+        if (decide) sh.po.who[rank] = P.l | (P.base << 8) | (P.u << 16);
+        group_barrier<WAVES>(sh);
+        const int mine = quotient(P.l, (65536u + parts - 1) / parts);
+        part = P.l - mul24(mine, parts);
+        scans = mine < count;
+        const int w = sh.po.who[scans ? mine : 0];
+        me = scans ? w & 0xff : P.l;
+        base = scans ? (w >> 8) & 0xff : P.base;
+        self = scans ? w >> 16 : P.u;
+    }
+    const float4 O = sh.po.pose[me];
+    const float4 Q = sh.po.reach[me];
+    const int role = sh.po.role[me];
+    const int team = role & 1;
+    const bool healer = (role & 2) != 0;
+    const bool assassin = (role & 4) != 0;
 
     // One scan, no divergent branches: the target by role (Healer: injured allies first, then
-    // nearest; Assassin: lowest maximum health, then nearest; others: nearest enemy; a strict
-    // "better" keeps the lower index on ties), the nearest visible enemy, and whether
-    // anything worth a strike is in the hurtbox.
-    int tgt = -1;
-    bool any_enemy = false, can_hit = false, tgt_in_box = false;
-    float tgt_d2 = 0.0f, tgt_key = 0.0f, near_d2 = 0.0f, near_dx = 0.0f, near_dy = 0.0f;
-    for (int j = 0; j < N; ++j) {
-        const int fj = sh.po.seer[P.base + j];
-        const float4 A = sh.po.pose[P.base + j];
-        const float4 B = sh.po.body[P.base + j];
-        const float dx = A.x - U.x;
-        const float dy = A.y - U.y;
+    // nearest; Assassin: lowest maximum health, then nearest; others: nearest enemy; the lower index
+    // on ties), the nearest visible enemy, and whether anything worth a strike is in the hurtbox.
+    int tgt = -1, near = -1;
+    bool can_hit = false, tgt_in_box = false;
+    float tgt_d2 = 0.0f, tgt_key = 0.0f, near_d2 = 0.0f;
+    for (int j = part; j < N; j += parts) {
+        const int fj = sh.po.seer[base + j];
+        const float4 A = sh.po.pose[base + j];
+        const float4 B = sh.po.body[base + j];
+        const float dx = A.x - O.x;
+        const float dy = A.y - O.y;
         float dot;
-        const float g2 = hurtbox_gap2(dx, dy, cu, su, U.range, U.hurt_hw, neg_hw, dot);
+        const float g2 = hurtbox_gap2(dx, dy, O.z, O.w, Q.x, Q.y, -Q.y, dot);
         const float d2 = (dx * dx) + (dy * dy);
-        const bool in_range = d2 <= sight2;
-        const bool in_cone = (d2 == 0.0f) || (dot >= U.cos_half * __builtin_sqrtf(d2));
-        const bool same_team = ((fj >> 1) & 1) == U.team;
-        const bool same_bush = (fj >> 8) == my_key;
+        const bool in_range = d2 <= Q.z;
+        const bool in_cone = (d2 == 0.0f) || (dot >= Q.w * __builtin_sqrtf(d2));
+        const bool same_team = ((fj >> 1) & 1) == team;
+        const bool same_bush = (fj >> 8) == (role >> 8);
         const bool concealed = (fj & 4) && !same_team && !same_bush;
-        const bool seen = (j != P.u) && (fj & 1) && in_range && in_cone && !concealed;
+        const bool seen = (j != self) && (fj & 1) && in_range && in_cone && !concealed;
         // (a seen unit is inside the cone, so a cone-bounded hurtbox needs no further test)
         const bool attackable = seen && (healer == same_team) && (g2 <= B.x * B.x);
         const bool injured = B.z < B.y;
         can_hit = can_hit || (attackable && (!healer || injured));
-        const bool enemy = seen && !same_team;
-        const bool nearer = enemy && (!any_enemy || d2 < near_d2);
-        any_enemy = any_enemy || enemy;
+        const bool nearer = seen && !same_team && (near < 0 || d2 < near_d2);
+        near = nearer ? j : near;
         near_d2 = nearer ? d2 : near_d2;
-        near_dx = nearer ? dx : near_dx;
-        near_dy = nearer ? dy : near_dy;
         const bool candidate = seen && (healer == same_team);
         const float key = healer ? (injured ? 0.0f : 1.0f) : (assassin ? B.y : 0.0f);
         const bool better = candidate && (tgt < 0 || key < tgt_key || (key == tgt_key && d2 < tgt_d2));
@@ -197,6 +220,36 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P
         tgt_d2 = better ? d2 : tgt_d2;
         tgt_key = better ? key : tgt_key;
         tgt_in_box = better ? attackable : tgt_in_box;
+    }
+    if (WAVES == 1) {
+        // the parts of a unit sit in consecutive lanes: the first one merges the others' winners (the
+        // order of the scan: key, distance, index), then the unit's own lane fetches the result
+        const int tgt_p = tgt, near_p = near, flags_p = (can_hit ? 1 : 0) | (tgt_in_box ? 2 : 0);
+        const float tgt_d2_p = tgt_d2, tgt_key_p = tgt_key, near_d2_p = near_d2;
+        for (int p = 1; p < parts; ++p) {
+            const int from = P.l + p;
+            const int t = __shfl(tgt_p, from), n = __shfl(near_p, from), f = __shfl(flags_p, from);
+            const float td = __shfl(tgt_d2_p, from), tk = __shfl(tgt_key_p, from);
+            const float nd = __shfl(near_d2_p, from);
+            const bool better = t >= 0 && (tgt < 0 || tk < tgt_key ||
+                                           (tk == tgt_key && (td < tgt_d2 || (td == tgt_d2 && t < tgt))));
+            tgt = better ? t : tgt;
+            tgt_d2 = better ? td : tgt_d2;
+            tgt_key = better ? tk : tgt_key;
+            tgt_in_box = better ? (f & 2) != 0 : tgt_in_box;
+            const bool nearer = n >= 0 && (near < 0 || nd < near_d2 || (nd == near_d2 && n < near));
+            near = nearer ? n : near;
+            near_d2 = nearer ? nd : near_d2;
+            can_hit = can_hit || (f & 1) != 0;
+        }
+        const int at = mul24(rank, parts);
+        tgt = __shfl(tgt, at);
+        tgt_d2 = __shfl(tgt_d2, at);
+        near = __shfl(near, at);
+        near_d2 = __shfl(near_d2, at);
+        const int flags = __shfl((can_hit ? 1 : 0) | (tgt_in_box ? 2 : 0), at);
+        can_hit = (flags & 1) != 0;
+        tgt_in_box = (flags & 2) != 0;
     }
 
     int act = -1;
@@ -207,13 +260,14 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P
         S.tgt_in_box = tgt_in_box;
         S.T = sh.po.pose[P.base + (tgt >= 0 ? tgt : 0)];
         S.tr = sh.po.body[P.base + (tgt >= 0 ? tgt : 0)].x;
-        S.any_enemy = any_enemy;
+        S.any_enemy = near >= 0;
         S.near_d2 = near_d2;
-        S.near_dx = near_dx;
-        S.near_dy = near_dy;
+        const float4 E = sh.po.pose[P.base + (near >= 0 ? near : 0)];
+        S.near_dx = E.x - U.x;
+        S.near_dy = E.y - U.y;
         S.can_hit = can_hit;
         act = policy_cascade(a, P, U, cu, su, in_bush, S, tick, remembered, mx, my, zd,
-                             pa.actions_out);
+                             late->pa.actions_out);
     }
     group_barrier<WAVES>(sh);          // the records may be overwritten by the next stage
     return act;

@@ -1,0 +1,71 @@
+"""How the observation rows are made depends on the row length (whole 16-byte chunks or not), the
+zone slots, the units per env and the batch size; every form at sizes where it can go wrong: tiles
+that end inside an env, rows that start in the middle of a chunk, inactive zone slots between active
+ones, partial last groups, few envs of many units (further wavefronts write rows) and many of them.
+Every env and field against the checker, with the parity tests' own comparison."""
+import numpy as np
+import pytest
+
+from paper_2602_01665_amd import inputs as I
+from tests.test_gpu_parity import _rollout
+from tests.test_gpu_policy import _policy_rollout, _scripted_rollout
+
+pytestmark = pytest.mark.gpu
+
+
+def _scene(team, zones, E):
+    w = I.Workload(f"rows_{2 * team}u_{zones}z", E, team, 40.0, 20, "iid", 0.6, "iid", max_zones=zones,
+                   steps=9, seed=700 + 17 * team + zones)
+    sc = I.make_scenario(w, E)
+    if zones:
+        rng = np.random.default_rng(zones)
+        d = rng.uniform(1.0, 30.0, size=(E, zones, 6)).astype(np.float32)
+        d[..., 0] = rng.integers(0, 4, size=(E, zones))       # a type of 0 leaves the slot out
+        sc["zone_desc"] = d
+    return w, sc
+
+
+TICKS = [
+    # team size, zone slots, envs, ticks
+    (1, 16, 70, 12), (1, 5, 33, 12), (2, 1, 9, 12), (5, 3, 61, 12), (8, 7, 9, 12), (16, 11, 5, 9),
+    (32, 1, 3, 9),                                            # one row per tile
+    (8, 1, 8300, 3), (10, 3, 6200, 3), (16, 8, 4200, 3),      # a full machine, two passes per tile or not
+    (33, 0, 5, 9), (50, 5, 5, 9), (64, 16, 3, 9), (64, 15, 2, 9),        # few envs of many units
+    (33, 8, 520, 4), (33, 7, 520, 4), (64, 1, 515, 3),        # many of them
+]
+
+
+@pytest.mark.parametrize("fused", [True, False], ids=["fused", "separate"])
+@pytest.mark.parametrize("team,zones,E,ticks", TICKS)
+def test_rows(team, zones, E, ticks, fused):
+    w, sc = _scene(team, zones, E)
+    print(f"[gpu] rows N={2 * team} Z={zones} E={E} fused={fused}", flush=True)
+    _rollout(w, E, ticks, fused, scenario=sc, max_steps=5)
+
+
+DECIDING = [(8, 3, 9, 8), (10, 8, 2100, 3), (33, 0, 520, 3), (33, 3, 520, 3), (50, 4, 5, 6), (64, 16, 3, 6)]
+
+
+@pytest.mark.parametrize("form", ["scripted", "scan"])
+@pytest.mark.parametrize("team,zones,E,ticks", DECIDING)
+def test_rows_with_deciding_units(team, zones, E, ticks, form):
+    w, sc = _scene(team, zones, E)
+    print(f"[gpu] deciding N={2 * team} Z={zones} E={E} {form}", flush=True)
+    if form == "scripted":
+        _scripted_rollout(w, E, ticks, "medium", "adversaries", scenario=sc, max_steps=4)
+    else:
+        _policy_rollout(w, E, ticks, "medium", "adversaries", scenario=sc, fused=True, max_steps=4)
+
+
+@pytest.mark.parametrize("slop", [-0.8, 0.0, 0.4])
+@pytest.mark.parametrize("team,E", [(5, 40), (32, 5), (40, 4)])
+@pytest.mark.parametrize("dynamics", [False, True], ids=["kinematic", "persistent"])
+def test_contacts_near_the_reach(team, E, slop, dynamics):
+    """Crowded arenas: many pairs at about the distance where the pair test of body collisions stops
+    (a negative slop pushes bodies that do not touch yet)."""
+    w = I.Workload(f"crowd_{team}", E, team, 14.0, 0, "none", 1.0, "iid", steps=9, seed=31 + team)
+    over = dict(collision_alpha=0.8, collision_slop=slop, max_steps=6)
+    if dynamics:
+        over.update(dynamics=1, move_gain=2.0, restitution=0.5)
+    print(f"[gpu] contacts N={2 * team} slop={slop} {over}", flush=True)
+    _rollout(w, E, 8, True, **over)
