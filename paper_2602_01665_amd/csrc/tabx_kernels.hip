@@ -155,7 +155,10 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
         if (P.grp < a.num_groups) {
             const int first = P.chunk * a.tiles_per_chunk;
             const int end = first + a.tiles_per_chunk < a.tiles ? first + a.tiles_per_chunk : a.tiles;
-            write_rows<WAVES, SCRIPT>(a, sh.rec, Z, stg, P.grp, first + wave, WAVES * TWIN, end, script);
+            if (a.zone_chunks == 0)
+                write_rows<WAVES, SCRIPT, true>(a, sh.rec, Z, stg, P.grp, first + wave, WAVES * TWIN, end, script);
+            else
+                write_rows<WAVES, SCRIPT, false>(a, sh.rec, Z, stg, P.grp, first + wave, WAVES * TWIN, end, script);
         }
         TABX_STAMP(4);
         if (SCRIPT) {
@@ -408,6 +411,8 @@ static hipError_t launch_mode(Mode mode, KArgs a, hipStream_t stream)
             return enqueue(tabx_tick_kernel<2, false, false, true, false, 2>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<WAVES, false, false, true>, grid, block, lds, stream, a);
     case MODE_STEP_OBSERVE:
+        if (WAVES == 1 && a.twin > 4)
+            return enqueue(tabx_tick_kernel<1, false, true, true, false, 8>, grid, block, lds, stream, a);
         if (WAVES == 1 && a.twin > 2)
             return enqueue(tabx_tick_kernel<1, false, true, true, false, 4>, grid, block, lds, stream, a);
         if (WAVES == 1 && a.twin)
@@ -424,6 +429,10 @@ static hipError_t launch_mode(Mode mode, KArgs a, hipStream_t stream)
             return enqueue(tabx_tick_kernel<WAVES, true, true, true, false, 2>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<WAVES, true, true, true>, grid, block, lds, stream, a);
     case MODE_SCRIPTED_STEP_OBSERVE:
+        if (WAVES == 1 && a.twin > 4)
+            return enqueue(tabx_tick_kernel<1, false, true, true, true, 8>, grid, block, lds, stream, a);
+        if (WAVES == 1 && a.twin > 2)
+            return enqueue(tabx_tick_kernel<1, false, true, true, true, 4>, grid, block, lds, stream, a);
         if (WAVES == 1)
             return enqueue(tabx_tick_kernel<1, false, true, true, true, 2>, grid, block, lds, stream, a);
         if (a.twin > 2)
@@ -495,6 +504,9 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         const bool long_chain = N >= 16 && !(p->collision_alpha > 0.0f);
         // a batch of at most three env groups per CU is one chain from the first load to the last store
         const bool tiny_batch = a.num_groups <= 3 * kComputeUnits && N > 4;
+        // ... and one group per CU with a tile per row (32v32 x 200: 24.4 us with four wavefronts, 18 with
+        // eight; scripted 42 and 20; 20v20 x 600, more than two groups per CU: 20.6 and 24.1)
+        const bool lone_groups = a.num_groups <= kComputeUnits;
         if (mode == MODE_OBSERVE) {
             // about four flushes of two rows per workgroup (10v10: 3 workgroups per group 94.7 us, 2 96.8,
             // 4 99), at most two where each fetches elliptical zones
@@ -509,10 +521,12 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
             a.twin = packs && !small_batch && !long_chain ? 0 : 2;
             // (16v16 x 6144: 90 us with two wavefronts, 88 with four; 5v5 x 4096 14 and 12.5)
             if ((N >= 32 || tiny_batch) && p->zone_shapes == 0) a.twin = 4;
+            if (lone_groups && N > 32) a.twin = 8;
         } else if (rows) {
             // scripted: 10v10 x 16384 139 us with one wavefront per group, 121 with two; the policy as a
             // scan stage keeps them all waiting, so it has one unless the rows ask for tiles
             a.twin = mode == MODE_POLICY_STEP_OBSERVE && packs ? 0 : 2;
+            if (mode == MODE_SCRIPTED_STEP_OBSERVE && tiny_batch) a.twin = lone_groups && N > 32 ? 8 : 4;
         }
         // On a full machine a plain tick stores two passes' rows at a time: 10v10 x 16384 107 -> 101.5 us,
         // 16v16 x 6144 93.8 -> 88; with a generation or less, shorter chains count (9v8 x 5003 39 and 48).

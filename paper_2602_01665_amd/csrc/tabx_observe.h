@@ -132,6 +132,7 @@ __device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); 
 // A tile is the business of one wavefront.  WAVES == 1: the records of the next pass are fetched
 // before the tile goes out, so that their latency passes behind the stores.
 // WAVES == 2 (one env, a tile is one row): the wavefront goes over the units in two halves.
+// FOLD: there are no zone slots.
 //
 // SCRIPT: the units the heuristic policy moves decide their next action from the very pair
 // tests the observation rows are made of (App. A "Role-Appropriate Heuristic Policy Mechanism":
@@ -139,7 +140,7 @@ __device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); 
 // with LDS atomic minima for "its target" (key: the role's order, then distance, then index,
 // with "in its hurtbox" riding in the lowest bit) and for "its nearest enemy"; afterwards the
 // deciding units read their winners (decide_units).
-template <int WAVES, bool SCRIPT>
+template <int WAVES, bool SCRIPT, bool FOLD>
 __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WAVES> &rec,
                                            const ZoneLds &Z, float *stg, int grp, int tile,
                                            int tile_step, int tile_end, ScriptLds<WAVES> *script)
@@ -162,8 +163,10 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     const int s = WAVES == 1 ? quotient(lane, a.magic_n) : 0;
     int u = WAVES == 1 ? lane - s * N : lane;
     const bool holds = s < S && (HALVES == 2 || u < N);
-    // the rest of a row, copied chunk by chunk: the own block (four chunks) and the zone slots
-    const int TC = 4 + ZC;
+    // the rest of a row, copied chunk by chunk: the own block (four chunks) and the zone slots; without
+    // zone slots the observer's own lane puts its block where the others put theirs, which saves the
+    // extra trip through LDS
+    const int TC = FOLD ? 0 : 4 + ZC;
     const int ts0 = WAVES == 1 ? quotient(lane, a.magic_tc) : 0;
     int vis_lo = 0, vis_hi = 0;
     uint64_t passes_done = 0;
@@ -173,8 +176,8 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     // and what it reads of the observer and of its unit
     int f = 0, i = 0, gN = 0, fi = 0, fu = 0;
     v2 opos = {};
-    float4 V = {}, Ub = {}, Ug = {}, Uk = {};
-    float orange = 0.0f, ohw = 0.0f, speed = 0.0f;
+    float4 V = {}, Ub = {}, Ug = {}, Uk = {}, Us = {};
+    float orange = 0.0f, ohw = 0.0f;
     auto fetch = [&](int f0, int r0, int rows_here) {
         f = f0 + (r0 + s < rows_here ? r0 + s : 0);
         gN = WAVES == 1 ? mul24(quotient(f, a.magic_n), N) : 0;
@@ -189,7 +192,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         Ub = rec.own[0][uk];
         Ug = rec.own[1][uk];
         Uk = rec.own[2][uk];
-        speed = rec.own[3][uk].y;
+        Us = rec.own[3][uk];
         fu = __float_as_int(rec.mark[uk].y);
     };
     // the copied part of the rows of a tile, into its staging area
@@ -297,18 +300,23 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
                     passes_done |= 1ull << pass;
                 }
             }
-            if (has && !self) {
+            if (has && (FOLD || !self)) {
                 // block position in the row: behind the own block, in index order
-                const int at = pad + mul24(sr, D) + 16 * (u < i ? u + 1 : u);
-                const int m = seen ? -1 : 0;
+                const int at = pad + mul24(sr, D) + 16 * (FOLD && self ? 0 : u < i ? u + 1 : u);
+                const int m = seen || (FOLD && self && (fi & 8)) ? -1 : 0;
                 auto masked = [m](float v) { return __int_as_float(__float_as_int(v) & m); };
                 // (written as 128-bit vector values: as four-member structs the last chunk has been
                 // seen to go out as four separate dwords, each a many-way bank conflict)
-                const v4 w0 = {masked(Ub.x), masked(Ub.y), masked(dx), masked(dy)};
+                v4 w0 = {masked(Ub.x), masked(Ub.y), masked(dx), masked(dy)};
                 const v4 w1 = {masked(Ug.x), masked(Ug.y), masked(Ug.z), masked(Ug.w)};
                 const v4 w2 = {masked(Uk.x), masked(Uk.y), masked(Uk.z), masked(Uk.w)};
-                const v4 w3 = {masked(1.0f), seen && same_team ? 1.0f : 0.0f,
-                               seen && hit ? 1.0f : 0.0f, masked(speed)};
+                v4 w3 = {masked(1.0f), seen && same_team ? 1.0f : 0.0f, seen && hit ? 1.0f : 0.0f,
+                         masked(Us.y)};
+                if (FOLD && self) {
+                    w0.z = masked(Ub.z);
+                    w0.w = masked(Ub.w);
+                    w3 = v4{masked(Us.x), masked(Us.y), masked(Us.z), masked(Us.w)};
+                }
                 if (grouped) {
                     // (the block is one 64-byte group: its chunks are permuted among themselves)
                     char *const d = reinterpret_cast<char *>(buf);

@@ -43,7 +43,7 @@ def test_rows(team, zones, E, ticks, fused):
     _rollout(w, E, ticks, fused, scenario=sc, max_steps=5)
 
 
-DECIDING = [(8, 3, 9, 8), (10, 8, 2100, 3), (33, 0, 520, 3), (33, 3, 520, 3), (50, 4, 5, 6), (64, 16, 3, 6)]
+DECIDING = [(8, 3, 9, 8), (25, 0, 7, 6), (10, 8, 50, 6), (31, 5, 300, 3), (10, 8, 2100, 3), (33, 0, 520, 3), (33, 3, 520, 3), (50, 4, 5, 6), (64, 16, 3, 6)]
 
 
 @pytest.mark.parametrize("form", ["scripted", "scan"])
