@@ -73,9 +73,10 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
     const float *zd = reinterpret_cast<const float *>(Z.val + (P.has ? P.g : 0) * a.zone_chunks);
     Carry C = {1.0f, 0.0f, 0.0f, 0, false, 0, 0, 0.0f, 0.0f};
     float speed = 0.0f;
-    // a wavefront that waits for the step fetches the zones meanwhile, unless the step looks at them
-    // itself or may move an env to another level, whose zones it then writes
-    const bool zones_elsewhere = TWIN && a.p.num_levels == 0 && a.p.zone_shapes == 0;
+    // a wavefront that waits for the step fetches the zones meanwhile, unless the wavefronts that step
+    // read them first (a policy's bush search, elliptical zones: nothing but the workgroup's barrier
+    // before the rows orders the two) or may move an env to another level, whose zones they then write
+    const bool zones_elsewhere = TWIN && !DO_POLICY && a.p.num_levels == 0 && a.p.zone_shapes == 0;
     if (DO_OBS && TWIN && wave == WAVES && zones_elsewhere) {
         put_zones<64>(a, Z, P.grp, (int)(threadIdx.x & 63));
         lds_barrier<1>();
