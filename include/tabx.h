@@ -161,7 +161,7 @@ typedef struct TabxScenario {
  * these arrays. */
 typedef struct TabxState {
     float *x, *y, *vx, *vy, *theta, *hp, *cd, *reveal, *cur_speed;
-    uint8_t *alive;
+    uint8_t *alive;      /* written as 0 or 1; any other non-zero byte is read as 1   */
     int32_t *t;          /* [E] ticks since the episode began                 */
     float   *phi_prev;   /* [E] health-ratio potential after the previous tick */
     /* Episode metrics (the paper's appendix "Additional Performance Metrics": episode

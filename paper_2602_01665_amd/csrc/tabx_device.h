@@ -427,7 +427,7 @@ __device__ __forceinline__ void load_state(const KArgs &a, size_t k, Unit &U)
     U.cd = at32(a.st.cd, k);
     U.reveal = at32(a.st.reveal, k);
     U.cur_speed = at32(a.st.cur_speed, k);
-    U.alive = at32(a.st.alive, k);
+    U.alive = ((int)at32(a.st.alive, k) + 255) >> 8;  // 0 or 1: any non-zero byte means alive
 }
 
 __device__ __forceinline__ void store_state(const KArgs &a, size_t k, const Unit &U)
