@@ -367,20 +367,27 @@ __device__ __forceinline__ ZoneLds zone_lds(const KArgs &a, float *dyn)
 // x / 3 for x < 100
 __device__ __forceinline__ int third(int x) { return mul24(x, 171) >> 9; }
 
-// Chunk zc of env slot g, whose zones are row `row` of the descriptors.
+// Chunk zc of env slot g, whose zones are row `row` of the descriptors.  Its four floats and the types of
+// the two slots they can belong to are fetched together: asking for the floats of active slots only is a
+// second round trip, which a small batch waits for (step of 30v33 x 252, four ellipses: 9.9 -> 9.1 us).
 __device__ __forceinline__ void put_zone_chunk(const KArgs &a, const ZoneLds &Z, int g, int zc, int row)
 {
     const int zlen = 6 * a.p.max_zones;
     const float *d = a.sc.zone_desc + (size_t)row * zlen;
+    const int first_slot = 3 * (third(4 * zc) & ~1);         // first float of the slot of float 4 zc
+    const int last_slot = first_slot + (4 * zc + 3 >= first_slot + 6 ? 6 : 0);
+    const float kind[2] = {d[first_slot], d[last_slot < zlen ? last_slot : 0]};
     float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = d[4 * zc + k < zlen ? 4 * zc + k : 0];
     int rel = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const int zz = 4 * zc + k;
-        const int type_at = 3 * (third(zz) & ~1);            // first float of its slot
-        const bool active = zz < zlen && d[zz < zlen ? type_at : 0] != 0.0f;
-        v[k] = active ? d[zz < zlen ? zz : 0] : 0.0f;
-        const int comp = zz - type_at;
+        const bool second = zz >= first_slot + 6;
+        const bool active = zz < zlen && (second ? kind[1] : kind[0]) != 0.0f;
+        const int comp = zz - (second ? last_slot : first_slot);
+        v[k] = active ? v[k] : 0.0f;
         if (active && (comp == 1 || comp == 2)) rel = -1;
     }
     Z.val[g * a.zone_chunks + zc] = make_float4(v[0], v[1], v[2], v[3]);
