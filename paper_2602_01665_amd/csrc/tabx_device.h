@@ -421,7 +421,7 @@ __device__ __forceinline__ void load_spec(const KArgs &a, size_t k, Unit &U)
     U.cos_half = at32(a.sc.sight_cos_half, k);
     U.sight_range = at32(a.sc.sight_range, k);
     U.hurt_hw = at32(a.sc.hurt_halfwidth, k);
-    U.team = ((int)at32(a.sc.team, k) + 255) >> 8;    // 0 or 1: any non-zero byte means the adversaries
+    U.team = at32(a.sc.team, k);
     U.enabled = at32(a.sc.enabled, k);
 }
 
@@ -436,7 +436,17 @@ __device__ __forceinline__ void load_state(const KArgs &a, size_t k, Unit &U)
     U.cd = at32(a.st.cd, k);
     U.reveal = at32(a.st.reveal, k);
     U.cur_speed = at32(a.st.cur_speed, k);
-    U.alive = ((int)at32(a.st.alive, k) + 255) >> 8;  // 0 or 1: any non-zero byte means alive
+    U.alive = at32(a.st.alive, k);
+}
+
+// The bytes as 0 or 1: any non-zero one means the adversaries, or alive.  Apart from the loads, since
+// folding a byte waits for it: what is asked for after that is a round trip later.  (The empty
+// instruction keeps the compiler from moving the folding, and with it the wait, up to the loads.)
+__device__ __forceinline__ void fold_bytes(Unit &U)
+{
+    asm volatile("" : "+v"(U.team), "+v"(U.alive));
+    U.team = (U.team + 255) >> 8;
+    U.alive = (U.alive + 255) >> 8;
 }
 
 __device__ __forceinline__ void store_state(const KArgs &a, size_t k, const Unit &U)

@@ -105,6 +105,7 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
         }
         ZoneRegs Zr = {};
         if (PACKED) Zr = load_zone_regs(a, P);
+        fold_bytes(U);
         if (a.zones_in_lds && !zones_elsewhere) {
             put_zones<64 * WAVES>(a, Z, P.grp, P.l);
             group_barrier<WAVES>(sh);
@@ -189,6 +190,7 @@ __global__ __launch_bounds__(64 * WAVES) void tabx_reset_kernel(const KArgs a)
     float ratio = 0.0f;
     if (go) {
         load_spec(a, P.ks, U);
+        fold_bytes(U);
         float zeff = 0.0f;
         spawn_unit(a, a.sc.zone_desc + (size_t)P.row * 6 * a.p.max_zones, P.row, P.ks, U, zeff);
         ratio = U.enabled ? U.hp / U.hmax : 0.0f;
@@ -231,6 +233,7 @@ __global__ __launch_bounds__(256) void tabx_global_state_kernel(const KArgs a, f
         Unit U = {};
         load_spec(a, (size_t)row * N + u, U);
         load_state(a, tid, U);
+        fold_bytes(U);
         float4 q[4];
         if (U.enabled) {
             float zeff = 0.0f;

@@ -429,6 +429,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
                 P.row = row;
                 P.ks = (size_t)row * N + P.u;
                 load_spec(a, P.ks, U);
+                fold_bytes(U);
                 en_next = U.enabled != 0;
             }
             if (a.zones_in_lds) {
