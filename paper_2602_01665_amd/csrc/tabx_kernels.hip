@@ -274,6 +274,7 @@ constexpr int kComputeUnits = 256;
 constexpr int kLdsPerCuBytes = 160 * 1024;          // a CU's LDS, shared by its resident workgroups
 constexpr int kLdsPerWorkgroupBytes = 64 * 1024;    // the most one workgroup may take
 constexpr int kWavefrontLanes = 64;
+constexpr size_t kLastLevelCacheBytes = (size_t)256 << 20;   // the cache in front of HBM, all XCDs
 
 enum Mode { MODE_RESET, MODE_STEP, MODE_OBSERVE, MODE_STEP_OBSERVE, MODE_POLICY,
             MODE_POLICY_STEP_OBSERVE, MODE_SCRIPTED_STEP_OBSERVE };
@@ -350,6 +351,16 @@ static int check_state(const TabxParams *p, const TabxState *s)
     return TABX_OK;
 }
 
+// A wavefront's staging area for `floats` floats: whole store passes (64 lanes of 16 bytes).
+static size_t whole_passes(size_t floats) { return (floats + 255) / 256 * 256; }
+
+// The staging area of a tile of `rows` rows of `dim` floats; rows of 2 mod 4 floats may start in the middle
+// of a chunk.
+static size_t tile_floats(int rows, int dim) { return whole_passes((size_t)rows * dim + (dim % 4 ? 2 : 0)); }
+
+// The zone descriptors of a workgroup's envs: 16-byte chunks with a mask each.
+static size_t zone_floats(const KArgs &a) { return ((size_t)a.envs_per_block * a.zone_chunks * 5 + 3) / 4 * 4; }
+
 // Dynamic LDS of a launch and where its parts lie (fills the offsets in `a`).
 static size_t plan_lds(Mode mode, KArgs &a, int waves)
 {
@@ -360,23 +371,21 @@ static size_t plan_lds(Mode mode, KArgs &a, int waves)
     if (observing) {
         if (a.packed && waves == 2) {
             // two alternating areas of one row; the second half's store passes read whole passes
-            const int cpr = a.obs_dim / 4, row_chunks = (cpr + 3) & ~3, half = ((cpr >> 1) + 3) & ~3;
+            const int row_chunks = ((a.obs_dim + 3) / 4 + 3) & ~3, half = ((a.obs_dim / 4 >> 1) + 3) & ~3;
             floats = 4 * ((size_t)row_chunks + half + 64 * a.copy_passes);
         } else {
-            // one staging area per wavefront, in whole store passes (64 lanes of 16 bytes)
-            const size_t tile = a.packed ? (size_t)a.envs_per_block * a.rows_per_flush * a.obs_dim
-                                         : (size_t)a.rows_per_tile * a.obs_dim + (a.obs_dim % 4 ? 2 : 0);
-            a.stage_floats = (int)((tile + 255) / 256 * 256);
+            // one staging area per wavefront
+            a.stage_floats = (int)(a.packed ? whole_passes((size_t)a.envs_per_block * a.rows_per_flush * a.obs_dim)
+                                            : tile_floats(a.rows_per_tile, a.obs_dim));
             floats = (size_t)a.stage_floats * waves * (a.twin ? a.twin : 1);
         }
     }
-    // the zone descriptors of the workgroup's envs: 16-byte chunks with a mask each
-    // (elliptical zones; the bush search of deciding units; the copied part of the rows of a tile)
+    // zones: elliptical ones; the bush search of deciding units; the copied part of the rows of a tile
     a.zones_in_lds = a.zone_chunks > 0 &&
                      (a.p.zone_shapes == 1 || mode == MODE_POLICY || mode == MODE_POLICY_STEP_OBSERVE ||
                       mode == MODE_SCRIPTED_STEP_OBSERVE || (observing && !a.packed));
     a.zone_offset = (int)floats;
-    if (a.zones_in_lds) floats += ((size_t)a.envs_per_block * a.zone_chunks * 5 + 3) / 4 * 4;
+    if (a.zones_in_lds) floats += zone_floats(a);
     // the bidding area of scripted units that decide in the observe stage
     floats = (floats + 3) / 4 * 4;
     a.script_offset = (int)floats;
@@ -538,15 +547,27 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
             2 * S * a.obs_dim <= 2 * kTileFloats)
             K = 2;
     } else if (rows) {
-        const int half = ((cpr >> 1) + 3) & ~3, rest = ((cpr + 3) & ~3) - half;
-        a.copy_passes = ((half > rest ? half : rest) + 63) / 64;
-        // At most two envs per CU: the chain of N rows is what such a launch waits for, so four more
-        // wavefronts (two, if their staging areas would not fit) write rows as well (64v64 x 64
-        // 139 -> 72 us, x 512 151 -> 117; x 768 153 -> 169 us, where HBM takes what two write).
-        const size_t area = (size_t)(a.obs_dim + 2 + 255) / 256 * 1024;
-        const size_t rest_bytes = sizeof(Shared<2, true, true, true>) + sizeof(ScriptLds<2>) + 1024;
-        const int more = 6 * area + rest_bytes <= kLdsPerWorkgroupBytes ? 3 : 2;
-        if (p->num_envs <= 2 * kComputeUnits || !packs) a.twin = mode == MODE_POLICY_STEP_OBSERVE ? 2 : more;
+        const int row_chunks = ((a.obs_dim + 3) / 4 + 3) & ~3, half = ((cpr >> 1) + 3) & ~3;
+        a.copy_passes = ((half > row_chunks - half ? half : row_chunks - half) + 63) / 64;
+        // What a workgroup with `w` wavefronts that make tiles takes of a CU's LDS.
+        const auto tile_lds = [&](int w) {
+            return sizeof(Shared<2, true, true, true>) + sizeof(float) * (w * tile_floats(1, a.obs_dim) + zone_floats(a)) +
+                   (mode == MODE_SCRIPTED_STEP_OBSERVE ? sizeof(ScriptLds<2>) : 0);
+        };
+        const int E = p->num_envs;
+        const size_t row_bytes = sizeof(float) * (size_t)E * N * a.obs_dim;
+        if (E <= 2 * kComputeUnits) {
+            // At most two envs per CU: the chain of N rows is what such a launch waits for, so more
+            // wavefronts write rows as well.  Four more with one env per CU, or while the last-level cache
+            // takes all rows; beyond that HBM takes what two more write (64v64, two / four / six in all:
+            // x 64 140 / 68 / 53 us, x 256 142 / 70 / 62, x 300 147 / 76 / 87, x 512 150 / 115 / 124;
+            // 33v33 x 512 82 / 42 / 37; 50v50 x 300 118 / 61 / 55, x 400 - / 62 / 68).
+            const bool six = (E <= kComputeUnits || row_bytes <= kLastLevelCacheBytes / 4 * 3) &&
+                             tile_lds(6) <= kLdsPerWorkgroupBytes;
+            a.twin = six && mode != MODE_POLICY_STEP_OBSERVE ? 3 : 2;
+        } else if (!packs) {
+            a.twin = mode != MODE_POLICY_STEP_OBSERVE && tile_lds(6) <= kLdsPerWorkgroupBytes ? 3 : 2;
+        }
     }
     a.packed = rows && a.twin == 0;
     a.passes_per_tile = K;

@@ -14,7 +14,7 @@ namespace tabx {
 // short runs per flush and of an address register per store pass; where further wavefronts share a
 // group the tiles win (no copy of the units per wavefront).  Measured, same box, here / with tiles:
 // 10v10 x 16384 stand-alone observe 94.7 / 97.0 us, 5v5 x 65536 fused tick 84.9 / 87.6 us, 64v64 x 768
-// fused tick 153 / 169 us (but 64v64 x 512 151 / 117 us with six wavefronts).  Rows of whole 16-byte
+// fused tick 153 / 169 us (but 64v64 x 512 150 / 115 us with four wavefronts).  Rows of whole 16-byte
 // chunks only.
 //
 // Zone slots of the rows: lane (env slot zg, 16-byte chunk zc of the zone part) keeps its four zone

@@ -32,6 +32,7 @@ TICKS = [
     (8, 1, 8300, 3), (10, 3, 6200, 3), (16, 8, 4200, 3),      # a full machine, two passes per tile or not
     (33, 0, 5, 9), (50, 5, 5, 9), (64, 16, 3, 9), (64, 15, 2, 9),        # few envs of many units
     (33, 8, 520, 4), (33, 7, 520, 4), (64, 1, 515, 3),        # many of them
+    (64, 0, 20, 6), (60, 0, 270, 3), (33, 2, 1030, 2),        # six and four wavefronts, two
 ]
 
 
@@ -43,7 +44,8 @@ def test_rows(team, zones, E, ticks, fused):
     _rollout(w, E, ticks, fused, scenario=sc, max_steps=5)
 
 
-DECIDING = [(8, 3, 9, 8), (25, 0, 7, 6), (10, 8, 50, 6), (31, 5, 300, 3), (10, 8, 2100, 3), (33, 0, 520, 3), (33, 3, 520, 3), (50, 4, 5, 6), (64, 16, 3, 6)]
+DECIDING = [(8, 3, 9, 8), (25, 0, 7, 6), (10, 8, 50, 6), (31, 5, 300, 3), (10, 8, 2100, 3), (33, 0, 520, 3), (33, 3, 520, 3), (50, 4, 5, 6), (64, 16, 3, 6),
+            (64, 0, 20, 4), (10, 8, 2400, 2)]
 
 
 @pytest.mark.parametrize("form", ["scripted", "scan"])

@@ -1,0 +1,71 @@
+"""Which form of a launch a batch gets (host only): the GPU tests of the forms mean what they say only as
+long as their shapes select them, and a rule of a dispatch lies where both sides were measured."""
+import pytest
+
+from paper_2602_01665_amd import binding as B
+from paper_2602_01665_amd import inputs as I
+from tests import test_gpu_row_forms as rows
+
+
+def _info(N, Z, E, call, **over):
+    return B.tabx_launch_info(B.make_params(I.custom_params(N, 40.0, 0, Z, num_envs=E, **over)), call)
+
+
+def _waves(N, Z, E, call, **over):
+    info = _info(N, Z, E, call, **over)
+    assert info["threads_per_workgroup"] == 64 * info["wavefronts_per_env_group"]
+    return info["wavefronts_per_env_group"]
+
+
+# units, zone slots, envs: wavefronts per env group of observe, the tick, the scripted and the policy tick
+TWO = [
+    (128, 0, 64, 6, 6, 6, 4), (128, 0, 256, 6, 6, 6, 4), (128, 0, 257, 4, 4, 4, 4),
+    (128, 0, 512, 4, 4, 4, 4), (128, 0, 513, 2, 2, 2, 2), (127, 0, 64, 6, 6, 6, 4),
+    (66, 0, 512, 6, 6, 6, 4), (66, 0, 513, 2, 2, 2, 2), (66, 7, 512, 6, 6, 6, 4),
+    (100, 0, 300, 6, 6, 6, 4), (100, 0, 400, 4, 4, 4, 4),
+    (128, 16, 3, 4, 4, 4, 4),                  # (six staging areas would not fit a workgroup's LDS)
+]
+
+
+@pytest.mark.parametrize("N,Z,E,observe,tick,scripted,policy", TWO)
+def test_envs_of_two_wavefronts(N, Z, E, observe, tick, scripted, policy):
+    got = [_waves(N, Z, E, c) for c in ("observe", "step_observe", "scripted_step_observe", "policy_step_observe")]
+    assert got == [observe, tick, scripted, policy]
+
+
+# the same of envs of at most 64 units
+ONE = [
+    (64, 0, 200, 1, 8, 8, 1), (32, 1, 3, 2, 4, 4, 2), (33, 0, 200, 1, 8, 8, 1), (33, 0, 300, 1, 4, 4, 1),
+    (20, 8, 700, 1, 4, 4, 1), (20, 8, 16384, 1, 2, 2, 1), (10, 0, 65536, 1, 1, 2, 1),
+    (16, 3, 9, 2, 4, 4, 2), (20, 7, 200, 2, 4, 4, 2), (2, 16, 70, 2, 2, 2, 2),
+]
+
+
+@pytest.mark.parametrize("N,Z,E,observe,tick,scripted,policy", ONE)
+def test_envs_of_one_wavefront(N, Z, E, observe, tick, scripted, policy):
+    got = [_waves(N, Z, E, c) for c in ("observe", "step_observe", "scripted_step_observe", "policy_step_observe")]
+    assert got == [observe, tick, scripted, policy]
+
+
+def test_every_form_has_a_gpu_test():
+    """The shapes of the GPU tests of the rows between them select every number of wavefronts (a single one
+    for a plain tick is in test_gpu_parity's own list)."""
+    ticks = {(2 * t > 64, _waves(2 * t, z, E, "step_observe")) for t, z, E, _ in rows.TICKS}
+    assert ticks >= {(False, 2), (False, 4), (False, 8), (True, 2), (True, 4), (True, 6)}
+    alone = {(2 * t > 64, _waves(2 * t, z, E, "observe")) for t, z, E, _ in rows.TICKS}
+    assert alone >= {(False, 1), (False, 2), (True, 2), (True, 4), (True, 6)}
+    for call, want in (("scripted_step_observe", {(False, 2), (False, 4), (False, 8), (True, 2), (True, 4), (True, 6)}),
+                       ("policy_step_observe", {(False, 1), (False, 2), (True, 2), (True, 4)})):
+        assert {(2 * t > 64, _waves(2 * t, z, E, call)) for t, z, E, _ in rows.DECIDING} >= want
+
+
+@pytest.mark.parametrize("call", ["observe", "step_observe", "scripted_step_observe", "policy_step_observe"])
+def test_every_shape_fits_a_workgroup(call):
+    """Dynamic LDS plus the most a kernel has besides (12 KB) within what a workgroup may take."""
+    for N in range(1, 129):
+        for Z in (0, 1, 2, 7, 8, 15, 16):
+            for E in (1, 300, 700, 3000, 20000):
+                for shapes in (0, 1) if Z else (0,):
+                    info = _info(N, Z, E, call, zone_shapes=shapes)
+                    static = 11648 if N > 64 else 5952
+                    assert info["dynamic_lds_bytes"] + static <= info["assumed_lds_per_workgroup_bytes"], (N, Z, E, info)
