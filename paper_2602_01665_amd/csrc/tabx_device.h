@@ -56,6 +56,7 @@ struct KArgs {
     int       obs_chunks;          // workgroups that share the tiles of one env group (>= 1)
     int       tiles_per_chunk;     // tiles per such workgroup
     int       packed;              // 1: rows with the units in registers (tabx_observe_packed.h)
+    int       even;                // ... 64 < N: by the kernel that keeps three wavefronts per SIMD
     int       copy_passes;         // ... store passes of one flush, <= kMaxPasses
     int       rows_per_flush;      // ... R: consecutive rows of an env staged before they are stored
     int       obs_per_chunk;       // ... observers per workgroup that shares an env group
@@ -80,6 +81,7 @@ __device__ unsigned long long g_trace[1 << 21];
 #endif
 
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte store, 4-byte aligned
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));   // 8-byte store, 4-byte aligned
 
 constexpr float kTwoPi = 6.28318530717958647692f;
 // Sine and cosine of a heading in [0, 2*pi]: quadrant index n = trunc(theta *

@@ -41,8 +41,9 @@
 namespace tabx {
 
 template <int WAVES, bool DO_POLICY, bool DO_STEP, bool DO_OBS, bool SCRIPT = false,
-          int TWIN = 0>
-__global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kernel(const KArgs a)
+          int TWIN = 0, bool EVEN = false>
+__global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1))
+__attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(const KArgs a)
 {
     // without further wavefronts to share the rows with, the units stay in registers
     constexpr bool PACKED = DO_OBS && TWIN == 0;
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1)) void tabx_tick_kern
         }
         TABX_STAMP(1);
         if constexpr (PACKED) {
-            observe_packed<WAVES, SCRIPT>(a, sh, dyn, P, U, code_u, C, Zr, told, script, zd);
+            observe_packed<WAVES, SCRIPT, SCRIPT || DO_POLICY, EVEN>(a, sh, dyn, P, U, code_u, C, Zr, told, script, zd);
         } else if constexpr (DO_OBS) {
             group_barrier<WAVES>(sh);          // the step stage is done with the LDS union
             publish_units<WAVES, SCRIPT>(a, sh, P, U, code_u, C.ratio, C.cu, C.su, told, script);
@@ -274,7 +275,10 @@ constexpr int kComputeUnits = 256;
 constexpr int kLdsPerCuBytes = 160 * 1024;          // a CU's LDS, shared by its resident workgroups
 constexpr int kLdsPerWorkgroupBytes = 64 * 1024;    // the most one workgroup may take
 constexpr int kWavefrontLanes = 64;
+constexpr size_t kLdsGranuleBytes = 1280;           // LDS is given out in these
 constexpr size_t kLastLevelCacheBytes = (size_t)256 << 20;   // the cache in front of HBM, all XCDs
+
+static size_t lds_granules(size_t bytes) { return (bytes + kLdsGranuleBytes - 1) / kLdsGranuleBytes * kLdsGranuleBytes; }
 
 enum Mode { MODE_RESET, MODE_STEP, MODE_OBSERVE, MODE_STEP_OBSERVE, MODE_POLICY,
             MODE_POLICY_STEP_OBSERVE, MODE_SCRIPTED_STEP_OBSERVE };
@@ -422,6 +426,8 @@ static hipError_t launch_mode(Mode mode, KArgs a, hipStream_t stream)
             return enqueue(tabx_tick_kernel<2, false, false, true, false, 3>, grid, block, lds, stream, a);
         if (WAVES == 2 && a.twin)
             return enqueue(tabx_tick_kernel<2, false, false, true, false, 2>, grid, block, lds, stream, a);
+        if (WAVES == 2 && a.even)
+            return enqueue(tabx_tick_kernel<2, false, false, true, false, 0, true>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<WAVES, false, false, true>, grid, block, lds, stream, a);
     case MODE_STEP_OBSERVE:
         if (WAVES == 1 && a.twin > 4)
@@ -434,6 +440,8 @@ static hipError_t launch_mode(Mode mode, KArgs a, hipStream_t stream)
             return enqueue(tabx_tick_kernel<2, false, true, true, false, 3>, grid, block, lds, stream, a);
         if (WAVES == 2 && a.twin)
             return enqueue(tabx_tick_kernel<2, false, true, true, false, 2>, grid, block, lds, stream, a);
+        if (WAVES == 2 && a.even)
+            return enqueue(tabx_tick_kernel<2, false, true, true, false, 0, true>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<WAVES, false, true, true>, grid, block, lds, stream, a);
     case MODE_POLICY:
         return enqueue(tabx_tick_kernel<WAVES, true, false, false>, grid, block, lds, stream, a);
@@ -498,13 +506,14 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     a.obs_per_chunk = N;
     a.twin = 0;
     a.packed = 0;
+    a.even = 0;
     int K = 1;                                   // passes per tile
-    // The form with the units in registers (tabx_observe_packed.h) needs whole 16-byte chunks per row,
-    // a zone chunk per lane at most and R rows of G envs in kMaxPasses store passes.
+    // The form with the units in registers (tabx_observe_packed.h) needs, for envs of one wavefront, whole
+    // 16-byte chunks per row, a zone chunk per lane at most and R rows of G envs in kMaxPasses store passes.
     const int cpr = a.obs_dim / 4;
     const int R = waves == 1 && N % 2 == 0 && 2 * G * cpr <= 64 * kMaxPasses ? 2 : 1;
-    const bool packs = a.obs_dim % 4 == 0 && G * a.zone_chunks <= 64 * waves &&
-                       (waves == 2 || R * G * cpr <= 64 * kMaxPasses);
+    const bool packs = waves == 2 || (a.obs_dim % 4 == 0 && G * a.zone_chunks <= 64 &&
+                                      R * G * cpr <= 64 * kMaxPasses);
     const bool rows = mode == MODE_OBSERVE || mode == MODE_STEP_OBSERVE ||
                       mode == MODE_POLICY_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE;
     a.rows_per_flush = R;
@@ -565,8 +574,27 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
             const bool six = (E <= kComputeUnits || row_bytes <= kLastLevelCacheBytes / 4 * 3) &&
                              tile_lds(6) <= kLdsPerWorkgroupBytes;
             a.twin = six && mode != MODE_POLICY_STEP_OBSERVE ? 3 : 2;
-        } else if (!packs) {
-            a.twin = mode != MODE_POLICY_STEP_OBSERVE && tile_lds(6) <= kLdsPerWorkgroupBytes ? 3 : 2;
+        } else if (a.obs_dim % 4 != 0) {
+            // Rows that end on half a chunk go out in whole ones from tiles only: worth it for one
+            // generation of workgroups that is not yet bound by HBM (33v33, 7 zone slots: x 600 64 us, 83
+            // with the units in registers, x 1000 77 and 87, x 1280 109 and 96; 50v50 x 768 121 and 124,
+            // x 1000 161 and 139; 63v64 x 768 191 and 165).
+            const int held = kLdsPerCuBytes / (int)lds_granules(tile_lds(4));
+            if (E <= held * kComputeUnits && row_bytes <= 2 * kLastLevelCacheBytes) a.twin = 2;
+        }
+        // Units in registers, from six envs per CU on: the kernel that keeps three wavefronts per SIMD, if
+        // it needs no more rounds over the machine than the one that lets the CU hold eight envs, which
+        // leaves some SIMDs with four wavefronts and some with two.  (33v33, three / four: x 1200 91 / 86
+        // us, x 1500 93 / 98, x 2048 162 / 127, x 2500 176 / 189, x 3000 185 / 202, x 4000 258 / 240.)
+        // It also has the code for rows that end on half a chunk, which costs the other 2 us.
+        if ((mode == MODE_STEP_OBSERVE || mode == MODE_OBSERVE) && !a.twin) {
+            const size_t lds = sizeof(Shared<2, false, false>) + 16 * (size_t)(row_chunks + half + 64 * a.copy_passes);
+            const int held = kLdsPerCuBytes / (int)lds_granules(lds);
+            const auto rounds = [&](int envs) {
+                const int at_once = (envs < held ? envs : held) * kComputeUnits;
+                return (E + at_once - 1) / at_once;
+            };
+            a.even = a.obs_dim % 4 != 0 || (E > 5 * kComputeUnits && rounds(6) == rounds(8));
         }
     }
     a.packed = rows && a.twin == 0;

@@ -14,8 +14,8 @@ namespace tabx {
 // short runs per flush and of an address register per store pass; where further wavefronts share a
 // group the tiles win (no copy of the units per wavefront).  Measured, same box, here / with tiles:
 // 10v10 x 16384 stand-alone observe 94.7 / 97.0 us, 5v5 x 65536 fused tick 84.9 / 87.6 us, 64v64 x 768
-// fused tick 153 / 169 us (but 64v64 x 512 150 / 115 us with four wavefronts).  Rows of whole 16-byte
-// chunks only.
+// fused tick 153 / 169 us (but 64v64 x 512 150 / 115 us with four wavefronts).  Envs of one wavefront: rows
+// of whole 16-byte chunks only.
 //
 // Zone slots of the rows: lane (env slot zg, 16-byte chunk zc of the zone part) keeps its four zone
 // floats in registers for the whole launch: the value (zero if the slot is inactive) and which
@@ -55,9 +55,10 @@ __device__ __forceinline__ ZoneRegs load_zone_regs(const KArgs &a, const Place &
     return Z;
 }
 
+// DECIDING: a launch with a policy.  EVEN: see plan_shape (tabx_kernels.hip), at most three wavefronts per SIMD.
 // `stg`: the staging area, G * R rows (WAVES == 2: two alternating areas of one row); `C`: what the step
 // stage left (heading, health ratio); `told`: the policy moves the unit (SCRIPT, see tabx_observe.h).
-template <int WAVES, bool SCRIPT, class Sh>
+template <int WAVES, bool SCRIPT, bool DECIDING, bool EVEN, class Sh>
 __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *stg, const Place &P,
                                                const Unit &U, int code_u, const Carry &C,
                                                const ZoneRegs &Zr, int told,
@@ -66,8 +67,10 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
     typedef float v4 __attribute__((ext_vector_type(4)));
     const int N = a.p.num_units;
     const int G = a.envs_per_block;
-    const int D = a.obs_dim;                     // a multiple of 4
-    const int CPR = D >> 2;                      // 16-byte chunks per row
+    const int D = a.obs_dim;                     // (WAVES == 1: a multiple of 4)
+    const int CPR = D >> 2;                      // whole 16-byte chunks per row
+    // whether a row may end on half a chunk besides (the plain launches have it in the EVEN kernels only)
+    constexpr bool HALF_CHUNK = WAVES == 2 && (EVEN || DECIDING);
     const int zlen = 6 * a.p.max_zones;
     const bool has = P.has;
     const bool want_vis = late_args()->vis_mask != nullptr;
@@ -125,7 +128,7 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
     bool valid[kMaxPasses];
     // (WAVES == 2: each wavefront streams one contiguous half of the row, both whole 64-byte groups)
     const int half_row = ((CPR >> 1) + 3) & ~3;
-    const int row_chunks = (CPR + 3) & ~3;       // pitch of the two alternating row areas
+    const int row_chunks = ((HALF_CHUNK ? (D + 3) >> 2 : CPR) + 3) & ~3;   // pitch of the two alternating row areas
     // the PHYSICAL chunk the lane reads in pass 0; it holds logical chunk staged_chunk(first_chunk)
     const int first_chunk = WAVES == 2 ? wv * half_row + lane : P.l;
     if (WAVES == 2) {
@@ -291,8 +294,12 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
                 if (want_gs && i == 0) {
                     // ... and the zone slots with absolute centres are its tail
                     float *gz = late_args()->st.global_state + (size_t)(P.grp * G + zg) * D + 16 * N + 4 * zc;
-                    if (zlen - 4 * zc >= 4)      // (always: the row is whole chunks)
+                    if (!HALF_CHUNK || zlen - 4 * zc >= 4) {
                         *reinterpret_cast<f4u *>(gz) = f4u{Zr.val[0], Zr.val[1], Zr.val[2], Zr.val[3]};
+                    } else {
+                        gz[0] = Zr.val[0];
+                        gz[1] = Zr.val[1];
+                    }
                 }
             }
         }
@@ -309,7 +316,11 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
             if (p < a.copy_passes) v[p] = src[p * 64];
 #pragma unroll
         for (int p = 0; p < kMaxPasses; ++p) {
-            if (p < a.copy_passes && valid[p]) {
+            int store = valid[p] ? 1 : 0;
+            // (made opaque, the masks stay in vector registers and the stores of a row are tested one by
+            // one: 33v33 x 1500 98 -> 93 us; with fewer envs per CU it costs, x 1000 77 -> 83)
+            if (EVEN) asm volatile("" : "+v"(store));
+            if (p < a.copy_passes && store) {
                 // (single-wavefront rows go out non-temporal: they are never read back by the kernel, and
                 // the hint measurably raises the store rate there; it lowers it for 8 KB rows)
                 f4u o = v[p];
@@ -317,6 +328,10 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
                 if (WAVES == 1) __builtin_nontemporal_store(o, dp);
                 else *dp = o;
             }
+        }
+        if (HALF_CHUNK && (D & 3) != 0 && P.l == 64 && envs_here > 0) {
+            const v4 t = area[staged_chunk(D >> 2)];
+            *reinterpret_cast<f2u *>(row + (D & ~3)) = f2u{t.x, t.y};
         }
         if (WAVES == 1) lds_barrier<1>();        // (two wavefronts alternate between two areas)
         // Two-wavefront envs (a full machine of workgroups that live as long as the launch): the wavefront

@@ -33,6 +33,7 @@ TICKS = [
     (33, 0, 5, 9), (50, 5, 5, 9), (64, 16, 3, 9), (64, 15, 2, 9),        # few envs of many units
     (33, 8, 520, 4), (33, 7, 520, 4), (64, 1, 515, 3),        # many of them
     (64, 0, 20, 6), (60, 0, 270, 3), (33, 2, 1030, 2),        # six and four wavefronts, two
+    (33, 0, 1290, 2), (33, 7, 1030, 2), (40, 1, 1290, 2),     # three wavefronts per SIMD at most; half a chunk
 ]
 
 
@@ -45,7 +46,7 @@ def test_rows(team, zones, E, ticks, fused):
 
 
 DECIDING = [(8, 3, 9, 8), (25, 0, 7, 6), (10, 8, 50, 6), (31, 5, 300, 3), (10, 8, 2100, 3), (33, 0, 520, 3), (33, 3, 520, 3), (50, 4, 5, 6), (64, 16, 3, 6),
-            (64, 0, 20, 4), (10, 8, 2400, 2)]
+            (33, 3, 1030, 2), (64, 0, 20, 4), (10, 8, 2400, 2)]
 
 
 @pytest.mark.parametrize("form", ["scripted", "scan"])

@@ -22,7 +22,8 @@ TWO = [
     (128, 0, 64, 6, 6, 6, 4), (128, 0, 256, 6, 6, 6, 4), (128, 0, 257, 4, 4, 4, 4),
     (128, 0, 512, 4, 4, 4, 4), (128, 0, 513, 2, 2, 2, 2), (127, 0, 64, 6, 6, 6, 4),
     (66, 0, 512, 6, 6, 6, 4), (66, 0, 513, 2, 2, 2, 2), (66, 7, 512, 6, 6, 6, 4),
-    (100, 0, 300, 6, 6, 6, 4), (100, 0, 400, 4, 4, 4, 4),
+    (66, 7, 513, 4, 4, 4, 4), (66, 7, 1024, 4, 4, 4, 4), (66, 7, 1025, 2, 2, 2, 2),
+    (100, 0, 300, 6, 6, 6, 4), (100, 0, 400, 4, 4, 4, 4), (127, 1, 600, 2, 2, 2, 2),
     (128, 16, 3, 4, 4, 4, 4),                  # (six staging areas would not fit a workgroup's LDS)
 ]
 
