@@ -86,9 +86,11 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
     if (lead) {
         Unit U = {};
         int code_u = 0;
+        PolicyIn pin = {};
         if (P.has) {
             load_spec(a, P.ks, U);
             load_state(a, P.k, U);
+            if (DO_POLICY) load_policy(a, P, pin);
         }
         StepIn in = {};
         if (DO_STEP) in = load_step(a, P);
@@ -106,11 +108,11 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
         }
         ZoneRegs Zr = {};
         if (PACKED) Zr = load_zone_regs(a, P);
-        fold_bytes(U);
         if (a.zones_in_lds && !zones_elsewhere) {
             put_zones<64 * WAVES>(a, Z, P.grp, P.l);
             group_barrier<WAVES>(sh);
         }
+        fold_bytes(U);
         float zeff_unused = 0.0f;
         int forced = -1;
         if (SCRIPT && told && U.enabled && U.alive) {
@@ -123,7 +125,7 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
                 code_u = zone_at(a, zd, P.row, U.x, U.y, zeff_unused);
                 heading_sincos(U.theta, su, cu);
             }
-            forced = policy_env<WAVES>(a, sh, P, U, code_u, cu, su, zd);
+            forced = policy_env<WAVES>(a, sh, P, U, pin, code_u, cu, su, zd);
         }
         TABX_STAMP(6);
         if (DO_STEP) {

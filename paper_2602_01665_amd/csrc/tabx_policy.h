@@ -129,58 +129,85 @@ __device__ __forceinline__ int policy_cascade(const KArgs &a, const Place &P, co
     return act;
 }
 
+// What the policy stage reads besides the unit's state and specification; issued with them at the top of
+// the kernel, for every unit: whether it decides is known only a round trip later (6v9 x 227, GPU time of
+// the heuristic call 8.3 -> 7.8 us).
+struct PolicyIn {
+    int   told;                    // the policy moves it, if it lives
+    int   tick;                    // the env's tick counter
+    int   remembered;              // the unit's memory
+    float mx, my;
+};
+
+__device__ __forceinline__ void load_policy(const KArgs &a, const Place &P, PolicyIn &in)
+{
+    // (no branch: the loads of one block leave together)
+    const uint8_t *const controlled = a.pa.controlled;
+    const int byte = at32(controlled ? controlled : a.st.alive, P.k);
+    in.told = controlled ? byte : 1;
+    in.tick = at32(a.st.t, (size_t)P.e);
+    in.remembered = at32(a.pa.mem.mem_valid, P.k);
+    in.mx = at32(a.pa.mem.mem_x, P.k);
+    in.my = at32(a.pa.mem.mem_y, P.k);
+}
+
 // Decides for the lane's unit from the state in U (heading cosine / sine cu, su, zone code
 // code_u under it); returns the action, or -1 if the unit is not the policy's to move.  Writes
 // the action and the remembered target position.  All lanes of the workgroup call it.
 template <int WAVES, class Sh>
 __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P,
-                                          const Unit &U, int code_u, float cu, float su,
-                                          const float *zd)
+                                          const Unit &U, const PolicyIn &in, int code_u, float cu,
+                                          float su, const float *zd)
 {
-    const LateArgs late = late_args();
     const int N = a.p.num_units;
     const bool in_bush = (code_u & 3) == TABX_ZONE_BUSH;
     const int my_key = in_bush ? (code_u & 0xff) : 0x100;          // 0x100 matches no cell code
     const bool concealable = in_bush && !(U.reveal > 0.0f);
     sh.po.pose[P.l] = make_float4(U.x, U.y, cu, su);
     sh.po.body[P.l] = make_float4(U.radius, U.hmax, U.hp, 0.0f);
-    sh.po.reach[P.l] = make_float4(U.range, U.hurt_hw, U.sight_range * U.sight_range, U.cos_half);
-    sh.po.role[P.l] = U.team | (U.dmg < 0.0f ? 2 : 0) | (U.speed >= late->pa.pol.assassin_speed ? 4 : 0) | (my_key << 8);
     sh.po.seer[P.l] = (P.has ? U.alive : 0) | (U.team << 1) | (concealable ? 4 : 0) | (my_key << 8);
-    // per-env tick counter and the unit's memory, requested before the scan
-    const bool decide = P.has && U.enabled && U.alive && (!late->pa.controlled || at32(late->pa.controlled, P.k));
-    const uint32_t tick = decide ? (uint32_t)a.st.t[P.e] : 0u;
-    const int remembered = decide ? late->pa.mem.mem_valid[P.k] : 0;
-    const float mx = decide ? late->pa.mem.mem_x[P.k] : 0.0f;
-    const float my = decide ? late->pa.mem.mem_y[P.k] : 0.0f;
-    group_barrier<WAVES>(sh);
+    const bool decide = U.enabled && U.alive && in.told;
 
     // Which lane scans for whom.  Usually half of the units decide (the adversaries), so as many lanes
     // as there are to spare, `parts` in all, share the partners of each deciding unit, every one
     // taking each parts-th of them (10v10 x 16384, adversaries: 25.4 -> 21 us, the scan being bound by
-    // VALU issue).  Two wavefronts (N > 64): every lane scans for its own unit.
+    // VALU issue).  Merging a part (six shuffles) costs about two thirds of testing a partner, so parts^2
+    // stays within 2 N: two parts for 2v2, where eight took longer than no sharing.  Two wavefronts
+    // (N > 64): every lane scans for its own unit.
     int parts = 1, part = 0, rank = 0;
     int me = P.l, base = P.base, self = P.u;
-    bool scans = decide;
+    float4 O = make_float4(U.x, U.y, cu, su);
+    float4 Q = make_float4(U.range, U.hurt_hw, U.sight_range * U.sight_range, U.cos_half);
+    int role = U.team | (U.dmg < 0.0f ? 2 : 0) | (U.speed >= a.pa.pol.assassin_speed ? 4 : 0) | (my_key << 8);
+    int count = 0;
     if (WAVES == 1) {
         const uint64_t deciding = __ballot(decide);
-        const int count = __popcll(deciding);
-        parts = count > 0 ? 64 / count : 1;
-        parts = parts > 8 ? 8 : parts;
+        count = __popcll(deciding);
         rank = __popcll(deciding & ((1ull << P.l) - 1ull));
-        if (decide) sh.po.who[rank] = P.l | (P.base << 8) | (P.u << 16);
-        group_barrier<WAVES>(sh);
+        if (count > 0) {
+            parts = 64 / count < 8 ? 64 / count : 8;
+            while (parts * parts > 2 * N) --parts;
+        }
+        if (parts > 1) {
+            sh.po.reach[P.l] = Q;
+            sh.po.role[P.l] = role;
+            if (decide) sh.po.who[rank] = P.l | (P.base << 8) | (P.u << 16);
+        }
+    }
+    group_barrier<WAVES>(sh);
+    if (WAVES == 1 && parts > 1) {
         const int mine = quotient(P.l, (65536u + parts - 1) / parts);
         part = P.l - mul24(mine, parts);
-        scans = mine < count;
-        const int w = sh.po.who[scans ? mine : 0];
-        me = scans ? w & 0xff : P.l;
-        base = scans ? (w >> 8) & 0xff : P.base;
-        self = scans ? w >> 16 : P.u;
+        if (mine < count) {
+            const int w = sh.po.who[mine];
+            me = w & 0xff;
+            base = (w >> 8) & 0xff;
+            self = w >> 16;
+        }
+        O = sh.po.pose[me];
+        Q = sh.po.reach[me];
+        role = sh.po.role[me];
     }
-    const float4 O = sh.po.pose[me];
-    const float4 Q = sh.po.reach[me];
-    const int role = sh.po.role[me];
     const int team = role & 1;
     const bool healer = (role & 2) != 0;
     const bool assassin = (role & 4) != 0;
@@ -221,7 +248,7 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P
         tgt_key = better ? key : tgt_key;
         tgt_in_box = better ? attackable : tgt_in_box;
     }
-    if (WAVES == 1) {
+    if (WAVES == 1 && parts > 1) {
         // the parts of a unit sit in consecutive lanes: the first one merges the others' winners (the
         // order of the scan: key, distance, index), then the unit's own lane fetches the result
         const int tgt_p = tgt, near_p = near, flags_p = (can_hit ? 1 : 0) | (tgt_in_box ? 2 : 0);
@@ -266,8 +293,8 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P
         S.near_dx = E.x - U.x;
         S.near_dy = E.y - U.y;
         S.can_hit = can_hit;
-        act = policy_cascade(a, P, U, cu, su, in_bush, S, tick, remembered, mx, my, zd,
-                             late->pa.actions_out);
+        act = policy_cascade(a, P, U, cu, su, in_bush, S, (uint32_t)in.tick, in.remembered, in.mx, in.my, zd,
+                             a.pa.actions_out);
     }
     group_barrier<WAVES>(sh);          // the records may be overwritten by the next stage
     return act;
