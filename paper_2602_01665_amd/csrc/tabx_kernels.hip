@@ -476,9 +476,19 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     // per env.
     const int N = p->num_units;
     const int waves = N <= 64 ? 1 : 2;
-    const int G = waves == 1 ? 64 / N : 1;
-    a.envs_per_block = G;
+    int G = waves == 1 ? 64 / N : 1;
     a.zone_chunks = (6 * p->max_zones + 3) / 4;
+    if (a.zone_chunks > 0 && G > 64 / a.zone_chunks) {
+        // More zone chunks than lanes (few units per env, many zone slots).  Full wavefronts count where the
+        // machine is full (2v2 with 16 slots x 16384 33 us with two envs per wavefront, 17 with sixteen); a
+        // small batch is one chain, which grows with the envs of a wavefront (x 64 8.9 and 13 us, x 4096
+        // 10.9 and 14.4; 4v5 with 12 slots, three and seven: x 2048 12.5 and 13.7, x 4096 17.4 and 14.8).
+        const int few = a.zone_chunks > 64 ? 1 : 64 / a.zone_chunks;
+        const int most = (p->num_envs + 8 * kComputeUnits - 1) / (8 * kComputeUnits);   // eight groups per CU
+        if ((p->num_envs + few - 1) / few <= 3 * kComputeUnits) G = few;
+        else if ((p->num_envs + G - 1) / G <= kComputeUnits) G = few > most ? few : most;
+    }
+    a.envs_per_block = G;
     a.magic_n = (65536u + N - 1) / N;
     a.magic_zc = a.zone_chunks ? (65536u + a.zone_chunks - 1) / a.zone_chunks : 0;
     // rows per tile: one observer per row that the 64 lanes hold all units of, about 4 KB

@@ -38,7 +38,7 @@ def test_envs_of_two_wavefronts(N, Z, E, observe, tick, scripted, policy):
 ONE = [
     (64, 0, 200, 1, 8, 8, 1), (32, 1, 3, 2, 4, 4, 2), (33, 0, 200, 1, 8, 8, 1), (33, 0, 300, 1, 4, 4, 1),
     (20, 8, 700, 1, 4, 4, 1), (20, 8, 16384, 1, 2, 2, 1), (10, 0, 65536, 1, 1, 2, 1),
-    (16, 3, 9, 2, 4, 4, 2), (20, 7, 200, 2, 4, 4, 2), (2, 16, 70, 2, 2, 2, 2),
+    (16, 3, 9, 2, 4, 4, 2), (20, 7, 200, 2, 4, 4, 2), (2, 16, 8200, 2, 2, 2, 2),
 ]
 
 
@@ -46,6 +46,18 @@ ONE = [
 def test_envs_of_one_wavefront(N, Z, E, observe, tick, scripted, policy):
     got = [_waves(N, Z, E, c) for c in ("observe", "step_observe", "scripted_step_observe", "policy_step_observe")]
     assert got == [observe, tick, scripted, policy]
+
+
+@pytest.mark.parametrize("N,Z,E,envs", [
+    (4, 16, 64, 2), (4, 16, 4096, 2), (4, 16, 4097, 16), (8, 16, 2048, 2), (8, 16, 2049, 8), (9, 12, 2304, 3),
+    (9, 12, 2305, 7), (10, 8, 4096, 6), (2, 16, 8192, 4), (2, 16, 20000, 32), (1, 16, 16384, 8),
+    (1, 16, 16385, 64), (20, 8, 64, 3), (64, 16, 64, 1)])
+def test_envs_of_a_wavefront(N, Z, E, envs):
+    """As many as the lanes hold, unless the zone chunks are more than the lanes and the batch is small."""
+    for call in ("reset", "step", "observe", "step_observe", "heuristic_actions", "scripted_step_observe"):
+        info = _info(N, Z, E, call)
+        assert info["envs_per_workgroup"] == envs, (call, info)
+        assert info["workgroups"] * envs >= E
 
 
 def test_every_form_has_a_gpu_test():
