@@ -160,10 +160,15 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
         if (P.grp < a.num_groups) {
             const int first = P.chunk * a.tiles_per_chunk;
             const int end = first + a.tiles_per_chunk < a.tiles ? first + a.tiles_per_chunk : a.tiles;
+            // Each wavefront writes one contiguous run of the group's tiles.  Taken in turn, tile by tile,
+            // batches whose rows are a power of two bytes long lost a tenth of the store rate (16v16 without
+            // zones x 12000 155 us in turn, 137 like this; 32v32 x 6000 319 and 295; others are level).
+            const int share = (end - first + WAVES * TWIN - 1) / (WAVES * TWIN);
+            const int begin = first + wave * share, stop = begin + share < end ? begin + share : end;
             if (a.zone_chunks == 0)
-                write_rows<WAVES, SCRIPT, true>(a, sh.rec, Z, stg, P.grp, first + wave, WAVES * TWIN, end, script);
+                write_rows<WAVES, SCRIPT, true>(a, sh.rec, Z, stg, P.grp, begin, stop, script);
             else
-                write_rows<WAVES, SCRIPT, false>(a, sh.rec, Z, stg, P.grp, first + wave, WAVES * TWIN, end, script);
+                write_rows<WAVES, SCRIPT, false>(a, sh.rec, Z, stg, P.grp, begin, stop, script);
         }
         TABX_STAMP(4);
         if (SCRIPT) {
