@@ -543,8 +543,9 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         const bool long_chain = N >= 16 && !(p->collision_alpha > 0.0f);
         // a batch of at most three env groups per CU is one chain from the first load to the last store
         const bool tiny_batch = a.num_groups <= 3 * kComputeUnits && N > 4;
-        // ... and one group per CU with a tile per row (32v32 x 200: 24.4 us with four wavefronts, 18 with
-        // eight; scripted 42 and 20; 20v20 x 600, more than two groups per CU: 20.6 and 24.1)
+        // ... and one group per CU with many tiles (32v32 x 200: 24.4 us with four wavefronts, 18 with
+        // eight; scripted 42 and 20; 15v15 x 120 15.4 and 12.5, 12v12 x 500 13.4 and 11.4; 20v20 x 600, more
+        // than two groups per CU: 20.6 and 24.1)
         const bool lone_groups = a.num_groups <= kComputeUnits;
         if (mode == MODE_OBSERVE) {
             // about four flushes of two rows per workgroup (10v10: 3 workgroups per group 94.7 us, 2 96.8,
@@ -560,7 +561,7 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
             a.twin = packs && !small_batch && !long_chain ? 0 : 2;
             // (16v16 x 6144: 90 us with two wavefronts, 88 with four; 5v5 x 4096 14 and 12.5)
             if ((N >= 32 || tiny_batch) && p->zone_shapes == 0) a.twin = 4;
-            if (lone_groups && N > 32) a.twin = 8;
+            if (lone_groups && (N > 32 || (N > 20 && p->zone_shapes == 0))) a.twin = 8;
         } else if (rows) {
             // scripted: 10v10 x 16384 139 us with one wavefront per group, 121 with two; the policy as a
             // scan stage keeps them all waiting, so it has one unless the rows ask for tiles
@@ -571,6 +572,11 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         // 16v16 x 6144 93.8 -> 88; with a generation or less, shorter chains count (9v8 x 5003 39 and 48).
         if (mode == MODE_STEP_OBSERVE && a.twin && !small_batch && a.tiles >= 8 * a.twin &&
             2 * S * a.obs_dim <= 2 * kTileFloats)
+            K = 2;
+        // Likewise where four wavefronts have six or more tiles each and there are at most two groups per CU
+        // (20v20 x 400 18.8 -> 17.4 us, 15v15 x 800 17.1 -> 16.7; with fewer tiles, or three groups, one pass
+        // per tile is better: 10v10 x 1200 14.9 and 15.4, 12v12 x 1400 16.9 and 17.4).
+        if (mode == MODE_STEP_OBSERVE && a.twin == 4 && a.num_groups <= 2 * kComputeUnits && a.tiles >= 6 * a.twin)
             K = 2;
     } else if (rows) {
         const int row_chunks = ((a.obs_dim + 3) / 4 + 3) & ~3, half = ((cpr >> 1) + 3) & ~3;

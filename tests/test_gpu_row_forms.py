@@ -34,7 +34,7 @@ TICKS = [
     (33, 8, 520, 4), (33, 7, 520, 4), (64, 1, 515, 3),        # many of them
     (64, 0, 20, 6), (60, 0, 270, 3), (33, 2, 1030, 2),        # six and four wavefronts, two
     (33, 0, 1290, 2), (33, 7, 1030, 2), (40, 1, 1290, 2),     # three wavefronts per SIMD at most; half a chunk
-    (2, 16, 70, 8), (2, 16, 4200, 3), (1, 16, 8203, 3),       # more zone chunks than lanes: few envs per wavefront or not
+    (12, 0, 70, 6), (20, 2, 300, 4), (2, 16, 70, 8), (2, 16, 4200, 3), (1, 16, 8203, 3),       # more zone chunks than lanes: few envs per wavefront or not
 ]
 
 
