@@ -455,6 +455,8 @@ static hipError_t launch_mode(Mode mode, KArgs a, hipStream_t stream)
     case MODE_POLICY_STEP_OBSERVE:
         if (a.twin)
             return enqueue(tabx_tick_kernel<WAVES, true, true, true, false, 2>, grid, block, lds, stream, a);
+        if (WAVES == 2 && a.even)
+            return enqueue(tabx_tick_kernel<2, true, true, true, false, 0, true>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<WAVES, true, true, true>, grid, block, lds, stream, a);
     case MODE_SCRIPTED_STEP_OBSERVE:
         if (WAVES == 1 && a.twin > 4)
@@ -610,8 +612,10 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         // leaves some SIMDs with four wavefronts and some with two.  (33v33, three / four: x 1200 91 / 86
         // us, x 1500 93 / 98, x 2048 162 / 127, x 2500 176 / 189, x 3000 185 / 202, x 4000 258 / 240.)
         // It also has the code for rows that end on half a chunk, which costs the other 2 us.
-        if ((mode == MODE_STEP_OBSERVE || mode == MODE_OBSERVE) && !a.twin) {
-            const size_t lds = sizeof(Shared<2, false, false>) + 16 * (size_t)(row_chunks + half + 64 * a.copy_passes);
+        // The same of the tick with the policy as a scan stage (x 1500 8 % between the two); the scripted tick's
+        // kernel never has room for four.
+        if (mode != MODE_SCRIPTED_STEP_OBSERVE && !a.twin) {
+            const size_t lds = (mode == MODE_POLICY_STEP_OBSERVE ? sizeof(Shared<2, false, true>) : sizeof(Shared<2, false, false>)) + 16 * (size_t)(row_chunks + half + 64 * a.copy_passes);
             const int held = kLdsPerCuBytes / (int)lds_granules(lds);
             const auto rounds = [&](int envs) {
                 const int at_once = (envs < held ? envs : held) * kComputeUnits;
