@@ -350,7 +350,8 @@ typedef struct TabxLaunchInfo {
     int32_t threads_per_workgroup;
     int32_t envs_per_workgroup;      /* envs packed into a workgroup                          */
     int32_t wavefronts_per_env_group;/* wavefronts that share those envs (1, 2, 4, 6 or 8)    */
-    int32_t rows_per_flush;          /* observation rows of an env staged before a flush      */
+    int32_t rows_per_flush;          /* rows a wavefront stages before they are stored: of the
+                                        env group, or of each env with the units in registers */
     int32_t dynamic_lds_bytes;
     /* the machine the launch shapes are tuned for: compare with the device's own properties */
     int32_t assumed_compute_units;            /* 256                                         */

@@ -51,8 +51,9 @@ struct KArgs {
                                    //     for the zone part of the rows
     int       script_offset;       // scripted units deciding in the observe stage: their LDS, floats
     int       groups_per_xcd;      // ceil(num_groups / 8)
-    int       twin;                // 2 or 4: that many wavefronts of a workgroup share the tiles of
-                                   //    its env group; the first of them steps the envs
+    int       twin;                // 2, 3, 4 or 8: a workgroup has that many times the wavefronts that hold
+                                   //    an env's units (one, or two from 65 units on); those step the
+                                   //    envs, all of them make tiles
     int       obs_chunks;          // workgroups that share the tiles of one env group (>= 1)
     int       tiles_per_chunk;     // tiles per such workgroup
     int       packed;              // 1: rows with the units in registers (tabx_observe_packed.h)
@@ -65,15 +66,16 @@ struct KArgs {
     PolicyArgs pa;
 };
 
-// Per-wavefront time stamps of an instrumented build (-DTABX_TRACE; compiled out of the product):
-// slot 0 kernel entry, 6 before the step stage, 1 after it (or after the hand-over), 2 / 3 / 4
-// observer loop start / first rows stored / loop end, 5 kernel end, 7 hardware ids.
+// Per-wavefront time stamps of an instrumented build (-DTABX_TRACE; compiled out of the product), eight
+// per wavefront, for up to eight wavefronts per workgroup: slot 0 kernel entry, 6 before the step stage,
+// 1 after it, 2 / 4 start and end of the rows, 5 kernel end, 7 hardware ids (3 is free).
 #ifdef TABX_TRACE
+constexpr int kTraceWaves = 8;
 __device__ unsigned long long g_trace[1 << 21];
 #define TABX_STAMP(slot)                                                                          \
     do {                                                                                          \
         if ((threadIdx.x & 63) == 0)                                                              \
-            g_trace[(((size_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 8 + (slot)) & ((1 << 21) - 1)] = \
+            g_trace[(((size_t)blockIdx.x * kTraceWaves + (threadIdx.x >> 6)) * 8 + (slot)) & ((1 << 21) - 1)] = \
                 wall_clock64();                                                                   \
     } while (0)
 #else
@@ -316,8 +318,9 @@ __device__ __forceinline__ LateArgs late_args()
     return (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
-// x / n for the small values that occur inside a workgroup (x < 1024, n <= 64: exact, since
-// x * (magic * n - 65536) < 1024 * 64), magic = ceil(65536 / n) from the host.
+// x / n for the small values that occur inside a workgroup, magic = ceil(65536 / n) from the host: exact
+// as long as x * (magic * n - 65536) < 65536, so for every x < 1024 with n <= 64, and for the zone chunks
+// of a group, x < 64 * 24 with n <= 24.
 __device__ __forceinline__ int quotient(int x, unsigned magic)
 {
     return (int)(__umul24((unsigned)x, magic) >> 16);

@@ -64,7 +64,7 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
         unsigned hw = 0, xcc = 0;
         asm volatile("s_getreg_b32 %0, hwreg(HW_REG_HW_ID)" : "=s"(hw));
         asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-        g_trace[(((size_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 8 + 7) & ((1 << 21) - 1)] =
+        g_trace[(((size_t)blockIdx.x * kTraceWaves + (threadIdx.x >> 6)) * 8 + 7) & ((1 << 21) - 1)] =
             ((unsigned long long)xcc << 32) | hw;
     }
 #endif
@@ -540,8 +540,10 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         a.copy_passes = (R * G * cpr + 63) / 64;
         // under one residency round (eight single-wavefront workgroups per CU)
         const bool small_batch = a.num_groups <= 8 * kComputeUnits;
-        // eight or more flushes of two rows and a short step stage (10v10 x 16384: 120 us with one
-        // wavefront per group, 101.5 with two; 5v5 x 65536 84 and 82; with body collisions 63.5 and 64)
+        // eight or more flushes of two rows (10v10 x 16384: 120 us with one wavefront per group, 101.5 with
+        // two; 5v5 x 65536 84 and 82); with body collisions the step stage is longer, and the two are level
+        // or either ahead (one / two: 10v10 x 8192 62.3 / 62.4, 9v9 x 15000 with ellipses 81 / 89, without
+        // 71 / 68, 12v12 x 10000 85 / 81, 16v16 x 4400 with ellipses 83 / 77)
         const bool long_chain = N >= 16 && !(p->collision_alpha > 0.0f);
         // a batch of at most three env groups per CU is one chain from the first load to the last store
         const bool tiny_batch = a.num_groups <= 3 * kComputeUnits && N > 4;

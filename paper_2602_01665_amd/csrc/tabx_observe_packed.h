@@ -187,6 +187,7 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
     // of an env group are spread over several short-lived workgroups
     const int i_begin = P.chunk * a.obs_per_chunk;
     const int i_end = (i_begin + a.obs_per_chunk < N) ? i_begin + a.obs_per_chunk : N;
+    TABX_STAMP(2);
     for (int i0 = i_begin; i0 < i_end; i0 += R) {
         v4 *const area = stage + (WAVES == 1 ? 0 : (i0 & 1) * row_chunks);
         for (int rr = 0; rr < R; ++rr) {
@@ -340,6 +341,7 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
 
+    TABX_STAMP(4);
     if (want_vis && WAVES == 1) {
         uint64_t *const vis_mask = late_args()->vis_mask;
         if (has && P.u >= i_begin && P.u < i_end) {

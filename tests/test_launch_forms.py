@@ -78,6 +78,25 @@ def test_every_form_has_a_gpu_test():
         assert {(2 * t > 64, _waves(2 * t, z, E, call)) for t, z, E, _ in rows.DECIDING} >= want
 
 
+def test_divisions_by_multiplication_are_exact():
+    """What a workgroup divides (by units per env, zone chunks, rows per pass, chunks of a row's tail), for
+    every shape and the largest dividend each occurs with."""
+    def exact(n, largest):
+        magic = (65536 + n - 1) // n
+        return all((x * magic) >> 16 == x // n for x in range(largest + 1))
+
+    for N in range(1, 65):
+        G = 64 // N
+        assert exact(N, 63)
+        for Z in range(17):
+            D, ZC = 16 * N + 6 * Z, (6 * Z + 3) // 4
+            S = max(1, min(G, 1280 // D))
+            assert exact(S, 63)
+            assert exact(4 + ZC, max(63, 2 * S * (4 + ZC) - 1))
+            if ZC:
+                assert exact(ZC, G * ZC - 1)
+
+
 @pytest.mark.parametrize("call", ["observe", "step_observe", "scripted_step_observe", "policy_step_observe"])
 def test_every_shape_fits_a_workgroup(call):
     """Dynamic LDS plus the most a kernel has besides (12 KB) within what a workgroup may take."""
