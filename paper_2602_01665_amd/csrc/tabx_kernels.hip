@@ -552,9 +552,10 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         // than two groups per CU: 20.6 and 24.1)
         const bool lone_groups = a.num_groups <= kComputeUnits;
         if (mode == MODE_OBSERVE) {
-            // about four flushes of two rows per workgroup (10v10: 3 workgroups per group 94.7 us, 2 96.8,
-            // 4 99), at most two where each fetches elliptical zones
-            const int flushes = (N + 1) / 2;
+            // about four flushes per workgroup (10v10, two rows a flush: 3 workgroups per group 94.7 us, 2 96.8,
+            // 4 99; 19 units, one row a flush, x 850: 5 8.6 us, 3 10.1), at most two where each fetches
+            // elliptical zones
+            const int flushes = packs ? (N + R - 1) / R : (N + 1) / 2;
             int share = N < 4 ? 1 : (flushes + 3) / 4 + (flushes < 8 ? 1 : 0);
             if (share > 8) share = 8;
             if (share > 2 && p->zone_shapes == 1) share = 2;

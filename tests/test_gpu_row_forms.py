@@ -73,3 +73,24 @@ def test_contacts_near_the_reach(team, E, slop, dynamics):
         over.update(dynamics=1, move_gain=2.0, restitution=0.5)
     print(f"[gpu] contacts N={2 * team} slop={slop} {over}", flush=True)
     _rollout(w, E, 8, True, **over)
+
+
+@pytest.mark.parametrize("N,E", [(9, 40), (19, 100), (31, 70), (33, 30)])
+def test_separate_rows_of_odd_units(N, E):
+    """Stand-alone observe of odd numbers of units: one row a flush, more workgroups per env group."""
+    import torch
+    from oracle.ref import RefEnv
+    from paper_2602_01665_amd.binding import TabxEnv
+    from tests.parity import compare_outputs
+    w = I.Workload(f"odd_{N}", E, (N + 1) // 2, 40.0, 0, "none", 1.0, "iid", seed=50 + N)
+    sc = I.make_scenario(w, E)
+    sc = {k: (v if v is None or v.ndim != 2 else np.ascontiguousarray(v[:, :N])) for k, v in sc.items()}
+    p = I.make_params(w, E, num_units=N)
+    ref, gpu = RefEnv(p, sc), TabxEnv(p, sc)
+    ref.reset()
+    gpu.reset()
+    ref.observe()
+    gpu.observe()
+    torch.cuda.synchronize()
+    print(f"[gpu] observe N={N} E={E}", flush=True)
+    compare_outputs(gpu, ref, f"N={N} E={E}: ")

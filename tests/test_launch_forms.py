@@ -66,6 +66,12 @@ def test_rows_of_a_tile(N, E, rows_):
     assert _info(N, 0, E, "step_observe")["rows_per_flush"] == rows_
 
 
+@pytest.mark.parametrize("N,share", [(10, 3), (19, 5), (20, 3), (31, 8), (32, 4), (33, 7), (5, 3)])
+def test_workgroups_that_share_an_observe(N, share):
+    groups = -(-3000 // (64 // N))
+    assert _info(N, 0, 3000, "observe")["workgroups"] == share * 8 * -(-groups // 8)
+
+
 def test_every_form_has_a_gpu_test():
     """The shapes of the GPU tests of the rows between them select every number of wavefronts (a single one
     for a plain tick is in test_gpu_parity's own list)."""
