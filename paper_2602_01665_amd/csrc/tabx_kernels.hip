@@ -547,10 +547,10 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         const bool long_chain = N >= 16 && !(p->collision_alpha > 0.0f);
         // a batch of at most three env groups per CU is one chain from the first load to the last store
         const bool tiny_batch = a.num_groups <= 3 * kComputeUnits && N > 4;
-        // ... and one group per CU with many tiles (32v32 x 200: 24.4 us with four wavefronts, 18 with
-        // eight; scripted 42 and 20; 15v15 x 120 15.4 and 12.5, 12v12 x 500 13.4 and 11.4; 20v20 x 600, more
-        // than two groups per CU: 20.6 and 24.1)
-        const bool lone_groups = a.num_groups <= kComputeUnits;
+        // ... and one group per CU with many tiles, or two with a tile per row (32v32 x 200: 24.4 us with four
+        // wavefronts, 18 with eight; scripted 42 and 20; 15v15 x 120 15.4 and 12.5, 12v12 x 500 13.4 and 11.4;
+        // 22v22 x 300 20.5 and 17.0, x 512 20.8 and 20.0; three groups per CU: 20v20 x 600 20.6 and 24.1)
+        const bool lone_groups = a.num_groups <= kComputeUnits, few_groups = a.num_groups <= 2 * kComputeUnits;
         if (mode == MODE_OBSERVE) {
             // about four flushes per workgroup (10v10, two rows a flush: 3 workgroups per group 94.7 us, 2 96.8,
             // 4 99; 19 units, one row a flush, x 850: 5 8.6 us, 3 10.1), at most two where each fetches
@@ -565,8 +565,9 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         } else if (mode == MODE_STEP_OBSERVE) {
             a.twin = packs && !small_batch && !long_chain ? 0 : 2;
             // (16v16 x 6144: 90 us with two wavefronts, 88 with four; 5v5 x 4096 14 and 12.5)
-            if ((N >= 32 || tiny_batch) && p->zone_shapes == 0) a.twin = 4;
-            if (lone_groups && (N > 32 || (N > 20 && p->zone_shapes == 0))) a.twin = 8;
+            if ((N >= 32 || tiny_batch) && (N > 20 || p->zone_shapes == 0)) a.twin = 4;
+            if (lone_groups && N > 20 && p->zone_shapes == 0) a.twin = 8;
+            if (few_groups && N > 32) a.twin = 8;
         } else if (rows) {
             // scripted: 10v10 x 16384 139 us with one wavefront per group, 121 with two; the policy as a
             // scan stage keeps them all waiting, so it has one unless the rows ask for tiles
@@ -579,9 +580,14 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
             2 * S * a.obs_dim <= 2 * kTileFloats)
             K = 2;
         // Likewise where four wavefronts have six or more tiles each and there are at most two groups per CU
-        // (20v20 x 400 18.8 -> 17.4 us, 15v15 x 800 17.1 -> 16.7; with fewer tiles, or three groups, one pass
-        // per tile is better: 10v10 x 1200 14.9 and 15.4, 12v12 x 1400 16.9 and 17.4).
-        if (mode == MODE_STEP_OBSERVE && a.twin == 4 && a.num_groups <= 2 * kComputeUnits && a.tiles >= 6 * a.twin)
+        // (15v15 x 800 17.1 -> 16.7 us, 12v12 with zones 15.8 -> 14.7; with fewer tiles, or three groups, one
+        // pass per tile is better: 10v10 x 1200 14.9 and 15.4, 12v12 x 1400 16.9 and 17.4).
+        if (mode == MODE_STEP_OBSERVE && a.twin == 4 && few_groups && a.tiles >= 6 * a.twin) K = 2;
+        // And with elliptical zones, whose lookups leave the other wavefronts waiting: where two share in
+        // up to four groups per CU (12v12 x 500 23.0 -> 20.8 us, 4v4 x 2000 14.3 -> 13.5; beyond, x 12000 20
+        // and 26), and where four do (30v30 x 1500 98 -> 84).
+        if (mode == MODE_STEP_OBSERVE && (a.twin == 2 || a.twin == 4) && p->zone_shapes == 1 && a.tiles >= 2 * a.twin &&
+            (N > 20 || a.num_groups <= 4 * kComputeUnits))
             K = 2;
     } else if (rows) {
         const int row_chunks = ((a.obs_dim + 3) / 4 + 3) & ~3, half = ((cpr >> 1) + 3) & ~3;

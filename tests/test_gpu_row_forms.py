@@ -75,6 +75,19 @@ def test_contacts_near_the_reach(team, E, slop, dynamics):
     _rollout(w, E, 8, True, **over)
 
 
+@pytest.mark.parametrize("team,zones,E,over", [
+    (4, 4, 50, {}), (10, 8, 40, {}), (12, 8, 41, dict(collision_alpha=0.8)), (21, 5, 270, {}), (30, 4, 300, {}),
+    (30, 4, 9, dict(num_levels=5, level_seed=3)), (16, 6, 3300, {}),
+])
+def test_rows_with_elliptical_zones(team, zones, E, over):
+    """Zones that the step looks up before the rows: two or four wavefronts per group, two passes per tile."""
+    w = I.Workload(f"ellipses_{2 * team}u", E, team, 40.0, 0, "ellipses", 1.0, "iid", max_zones=zones, steps=9,
+                   seed=300 + team)
+    sc = I.make_scenario(w, over.get("num_levels", E))
+    print(f"[gpu] ellipses N={2 * team} Z={zones} E={E} {over}", flush=True)
+    _rollout(w, E, 5, True, scenario=sc, max_steps=3, **over)
+
+
 @pytest.mark.parametrize("N,E", [(9, 40), (19, 100), (31, 70), (33, 30)])
 def test_separate_rows_of_odd_units(N, E):
     """Stand-alone observe of odd numbers of units: one row a flush, more workgroups per env group."""

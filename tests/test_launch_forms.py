@@ -36,7 +36,7 @@ def test_envs_of_two_wavefronts(N, Z, E, observe, tick, scripted, policy):
 
 # the same of envs of at most 64 units
 ONE = [
-    (64, 0, 200, 1, 8, 8, 1), (32, 1, 3, 2, 8, 4, 2), (33, 0, 200, 1, 8, 8, 1), (33, 0, 300, 1, 4, 4, 1), (22, 0, 500, 1, 8, 4, 1), (20, 0, 500, 1, 4, 4, 1),
+    (64, 0, 200, 1, 8, 8, 1), (32, 1, 3, 2, 8, 4, 2), (33, 0, 200, 1, 8, 8, 1), (33, 0, 300, 1, 8, 4, 1), (33, 0, 513, 1, 4, 4, 1), (22, 0, 500, 1, 8, 4, 1), (20, 0, 500, 1, 4, 4, 1),
     (20, 8, 700, 1, 4, 4, 1), (20, 8, 16384, 1, 2, 2, 1), (10, 0, 65536, 1, 1, 2, 1),
     (16, 3, 9, 2, 4, 4, 2), (20, 7, 200, 2, 4, 4, 2), (2, 16, 8200, 2, 2, 2, 2),
 ]
@@ -60,10 +60,17 @@ def test_envs_of_a_wavefront(N, Z, E, envs):
         assert info["workgroups"] * envs >= E
 
 
-@pytest.mark.parametrize("N,E,rows_", [(40, 400, 2), (40, 600, 1), (24, 800, 4), (24, 1400, 2), (24, 500, 2),
+@pytest.mark.parametrize("N,E,rows_", [(40, 400, 1), (40, 600, 1), (24, 800, 4), (24, 1400, 2), (24, 500, 2),
                                        (20, 1200, 3), (20, 16384, 6)])
 def test_rows_of_a_tile(N, E, rows_):
     assert _info(N, 0, E, "step_observe")["rows_per_flush"] == rows_
+
+
+@pytest.mark.parametrize("N,Z,E,waves,rows_", [(20, 8, 700, 2, 6), (20, 8, 4000, 2, 3), (24, 8, 500, 4, 4), (32, 8, 6000, 4, 4),
+                                               (43, 5, 100, 8, 1), (8, 4, 2000, 2, 16)])
+def test_elliptical_zones(N, Z, E, waves, rows_):
+    info = _info(N, Z, E, "step_observe", zone_shapes=1)
+    assert (info["wavefronts_per_env_group"], info["rows_per_flush"]) == (waves, rows_), info
 
 
 @pytest.mark.parametrize("N,share", [(10, 3), (19, 5), (20, 3), (31, 8), (32, 4), (33, 7), (5, 3)])
