@@ -375,11 +375,16 @@ __device__ __forceinline__ int third(int x) { return mul24(x, 171) >> 9; }
 // Chunk zc of env slot g, whose zones are row `row` of the descriptors.  Its four floats and the types of
 // the two slots they can belong to are fetched together: asking for the floats of active slots only is a
 // second round trip, which a small batch waits for (step of 30v33 x 252, four ellipses: 9.9 -> 9.1 us).
+// LATE: the arguments are read where they are needed.  The kernels of two wavefronts per env have no scalar
+// registers left for them (they would reserve scratch memory); in the others it costs (5v5 x 4096 11.3 ->
+// 12.1 us).
+template <bool LATE>
 __device__ __forceinline__ void put_zone_chunk(const KArgs &a, const ZoneLds &Z, int g, int zc, int row)
 {
-    const LateArgs late = late_args();       // (needed here only: not held in scalar registers)
-    const int zlen = 6 * late->p.max_zones;
-    const float *d = late->sc.zone_desc + (size_t)row * zlen;
+    const LateArgs late = late_args();
+    const int zlen = 6 * (LATE ? late->p.max_zones : a.p.max_zones);
+    const int ZC = LATE ? late->zone_chunks : a.zone_chunks;
+    const float *d = (LATE ? late->sc.zone_desc : a.sc.zone_desc) + (size_t)row * zlen;
     const int first_slot = 3 * (third(4 * zc) & ~1);         // first float of the slot of float 4 zc
     const int last_slot = first_slot + (4 * zc + 3 >= first_slot + 6 ? 6 : 0);
     const float kind[2] = {d[first_slot], d[last_slot < zlen ? last_slot : 0]};
@@ -396,20 +401,20 @@ __device__ __forceinline__ void put_zone_chunk(const KArgs &a, const ZoneLds &Z,
         v[k] = active ? v[k] : 0.0f;
         if (active && (comp == 1 || comp == 2)) rel = -1;
     }
-    Z.val[g * late->zone_chunks + zc] = make_float4(v[0], v[1], v[2], v[3]);
-    Z.rel[g * late->zone_chunks + zc] = rel;
+    Z.val[g * ZC + zc] = make_float4(v[0], v[1], v[2], v[3]);
+    Z.rel[g * ZC + zc] = rel;
 }
 
 // All zone chunks of the workgroup's envs, by the LANES lanes that call it (`l`: index among them).
-template <int LANES>
+template <int LANES, bool LATE>
 __device__ __forceinline__ void put_zones(const KArgs &a, const ZoneLds &Z, int grp, int l)
 {
     const LateArgs late = late_args();
     const int envs_here = envs_of_group(a, grp);
-    const int ZC = late->zone_chunks;
+    const int ZC = LATE ? late->zone_chunks : a.zone_chunks;
     for (int q = l; q < envs_here * ZC; q += LANES) {
-        const int g = quotient(q, late->magic_zc);
-        put_zone_chunk(a, Z, g, q - g * ZC, row_of(a, grp * a.envs_per_block + g));
+        const int g = quotient(q, LATE ? late->magic_zc : a.magic_zc);
+        put_zone_chunk<LATE>(a, Z, g, q - g * ZC, row_of(a, grp * a.envs_per_block + g));
     }
 }
 

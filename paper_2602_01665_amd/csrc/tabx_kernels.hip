@@ -79,7 +79,7 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
     // before the rows orders the two) or may move an env to another level, whose zones they then write
     const bool zones_elsewhere = TWIN && !DO_POLICY && a.p.num_levels == 0 && a.p.zone_shapes == 0;
     if (DO_OBS && TWIN && wave == WAVES && zones_elsewhere) {
-        put_zones<64>(a, Z, P.grp, (int)(threadIdx.x & 63));
+        put_zones<64, WAVES == 2>(a, Z, P.grp, (int)(threadIdx.x & 63));
         lds_barrier<1>();
         if (P.chunk == 0) global_state_zones<64>(a, Z, P.grp, (int)(threadIdx.x & 63));
     }
@@ -109,7 +109,7 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
         ZoneRegs Zr = {};
         if (PACKED) Zr = load_zone_regs(a, P);
         if (a.zones_in_lds && !zones_elsewhere) {
-            put_zones<64 * WAVES>(a, Z, P.grp, P.l);
+            put_zones<64 * WAVES, WAVES == 2>(a, Z, P.grp, P.l);
             group_barrier<WAVES>(sh);
         }
         fold_bytes(U);
@@ -620,11 +620,13 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         // it needs no more rounds over the machine than the one that lets the CU hold eight envs, which
         // leaves some SIMDs with four wavefronts and some with two.  (33v33, three / four: x 1200 91 / 86
         // us, x 1500 93 / 98, x 2048 162 / 127, x 2500 176 / 189, x 3000 185 / 202, x 4000 258 / 240.)
-        // It also has the code for rows that end on half a chunk, which costs the other 2 us.
-        // The same of the tick with the policy as a scan stage (x 1500 8 % between the two); the scripted tick's
+        // It also takes the rows that end on half a chunk: their code would cost the other kernel 2 us.  The
+        // tick with the policy as a scan stage likewise (x 1500 8 % between the two); the scripted tick's
         // kernel never has room for four.
         if (mode != MODE_SCRIPTED_STEP_OBSERVE && !a.twin) {
-            const size_t lds = (mode == MODE_POLICY_STEP_OBSERVE ? sizeof(Shared<2, false, true>) : sizeof(Shared<2, false, false>)) + 16 * (size_t)(row_chunks + half + 64 * a.copy_passes);
+            const size_t fixed = mode == MODE_POLICY_STEP_OBSERVE ? sizeof(Shared<2, false, true>)
+                                                                  : sizeof(Shared<2, false, false>);
+            const size_t lds = fixed + 16 * (size_t)(row_chunks + half + 64 * a.copy_passes);
             const int held = kLdsPerCuBytes / (int)lds_granules(lds);
             const auto rounds = [&](int envs) {
                 const int at_once = (envs < held ? envs : held) * kComputeUnits;

@@ -434,11 +434,13 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
             }
             if (a.zones_in_lds) {
                 // (level_rows holds an entry for every env of the group, and only for those)
-                const int ZC = late->zone_chunks, chunks = envs_of_group(a, P.grp) * ZC;
+                constexpr bool LATE = WAVES == 2;
+                const int ZC = LATE ? late->zone_chunks : a.zone_chunks;
+                const int chunks = envs_of_group(a, P.grp) * ZC;
                 for (int q = P.l; q < chunks; q += 64 * WAVES) {
-                    const int g = quotient(q, late->magic_zc);
+                    const int g = quotient(q, LATE ? late->magic_zc : a.magic_zc);
                     const int moved = sh.level_rows[g];
-                    if (moved >= 0) put_zone_chunk(a, Z, g, q - g * ZC, moved);
+                    if (moved >= 0) put_zone_chunk<LATE>(a, Z, g, q - g * ZC, moved);
                 }
                 group_barrier<WAVES>(sh);
             }
