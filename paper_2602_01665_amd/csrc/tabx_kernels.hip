@@ -583,6 +583,9 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         // (15v15 x 800 17.1 -> 16.7 us, 12v12 with zones 15.8 -> 14.7; with fewer tiles, or three groups, one
         // pass per tile is better: 10v10 x 1200 14.9 and 15.4, 12v12 x 1400 16.9 and 17.4).
         if (mode == MODE_STEP_OBSERVE && a.twin == 4 && few_groups && a.tiles >= 6 * a.twin) K = 2;
+        // ... and where they have eight or more each beyond five groups per CU, short of a full machine (32v32
+        // with zones x 1536 98 -> 92 us, 24v24 61.5 -> 57.4; x 1200 without zones 68.6 and 70.7).
+        if (mode == MODE_STEP_OBSERVE && a.twin == 4 && a.num_groups > 5 * kComputeUnits && a.tiles >= 8 * a.twin) K = 2;
         // And with elliptical zones, whose lookups leave the other wavefronts waiting: where two share in
         // up to four groups per CU (12v12 x 500 23.0 -> 20.8 us, 4v4 x 2000 14.3 -> 13.5; beyond, x 12000 20
         // and 26), and where four do (30v30 x 1500 98 -> 84).

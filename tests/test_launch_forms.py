@@ -61,7 +61,7 @@ def test_envs_of_a_wavefront(N, Z, E, envs):
 
 
 @pytest.mark.parametrize("N,E,rows_", [(40, 400, 1), (40, 600, 1), (24, 800, 4), (24, 1400, 2), (24, 500, 2),
-                                       (20, 1200, 3), (20, 16384, 6)])
+                                       (20, 1200, 3), (20, 16384, 6), (64, 1536, 2), (64, 1280, 1)])
 def test_rows_of_a_tile(N, E, rows_):
     assert _info(N, 0, E, "step_observe")["rows_per_flush"] == rows_
 
