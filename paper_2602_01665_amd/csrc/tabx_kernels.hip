@@ -162,13 +162,18 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
             const int end = first + a.tiles_per_chunk < a.tiles ? first + a.tiles_per_chunk : a.tiles;
             // Each wavefront writes one contiguous run of the group's tiles.  Taken in turn, tile by tile,
             // batches whose rows are a power of two bytes long lost a tenth of the store rate (16v16 without
-            // zones x 12000 155 us in turn, 137 like this; 32v32 x 6000 319 and 295; others are level).
+            // zones x 12000 155 us in turn, 137 like this; 32v32 x 6000 319 and 295).
+            // Odd numbers of units up to 20 go in turn: runs cost 9v8 with zones (x 4000 29.1 us in turn, 30.0 in
+            // runs; x 5003 32.7 and 34.4; x 20000 94.6 and 96.6); 5, 7, 13 and 21 units are level, and wider
+            // odd rows are better in runs (30v29 x 5000 232 us in turn, 229 in runs).
+            const bool in_turn = WAVES == 1 && (a.p.num_units & 1) && a.p.num_units < 21;
             const int share = (end - first + WAVES * TWIN - 1) / (WAVES * TWIN);
-            const int begin = first + wave * share, stop = begin + share < end ? begin + share : end;
+            const int begin = first + (in_turn ? wave : wave * share), step = in_turn ? WAVES * TWIN : 1;
+            const int stop = !in_turn && begin + share < end ? begin + share : end;
             if (a.zone_chunks == 0)
-                write_rows<WAVES, SCRIPT, true>(a, sh.rec, Z, stg, P.grp, begin, stop, script);
+                write_rows<WAVES, SCRIPT, true>(a, sh.rec, Z, stg, P.grp, begin, step, stop, script);
             else
-                write_rows<WAVES, SCRIPT, false>(a, sh.rec, Z, stg, P.grp, begin, stop, script);
+                write_rows<WAVES, SCRIPT, false>(a, sh.rec, Z, stg, P.grp, begin, step, stop, script);
         }
         TABX_STAMP(4);
         if (SCRIPT) {

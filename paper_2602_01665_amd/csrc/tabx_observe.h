@@ -126,7 +126,8 @@ __device__ __forceinline__ void global_state_zones(const KArgs &a, const ZoneLds
 // inverse, and staged_chunk(c + 32 k) = staged_chunk(c) + 32 k.
 __device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); }
 
-// Writes the rows of the tiles tile ... tile_end - 1 of env group `grp` (wavefront-uniform values).  `stg` is the calling wavefront's staging area.
+// Writes the rows of the tiles tile, tile + tile_step, ... < tile_end of env group `grp`
+// (wavefront-uniform values).  `stg` is the calling wavefront's staging area.
 //
 // A tile is the business of one wavefront.  WAVES == 1: the records of the next pass are fetched
 // before the tile goes out, so that their latency passes behind the stores.
@@ -142,7 +143,7 @@ __device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); 
 template <int WAVES, bool SCRIPT, bool FOLD>
 __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WAVES> &rec,
                                            const ZoneLds &Z, float *stg, int grp, int tile,
-                                           int tile_end, ScriptLds<WAVES> *script)
+                                           int tile_step, int tile_end, ScriptLds<WAVES> *script)
 {
     typedef float v4 __attribute__((ext_vector_type(4)));
     typedef float v2 __attribute__((ext_vector_type(2)));
@@ -233,7 +234,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         fetch(tile * T, 0, rows_of(tile));
     }
 
-    for (; tile < tile_end && tile * T < rows; ++tile) {
+    for (; tile < tile_end && tile * T < rows; tile += tile_step) {
         const int f0 = tile * T;                 // the tile's first row within the group
         const int rows_here = rows_of(tile);
         // where the tile starts relative to a 16-byte boundary (rows of 2 mod 4 floats)
@@ -345,7 +346,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         if (HALVES == 2) u = lane;
         copy_tail(f0, rows_here, pad, buf);
         {
-            const int next = tile + 1;
+            const int next = tile + tile_step;
             if (next < tile_end && next * T < rows) fetch(next * T, 0, rows_of(next));
         }
         lds_barrier<1>();
