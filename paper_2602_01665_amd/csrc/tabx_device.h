@@ -15,6 +15,7 @@ namespace tabx {
 
 constexpr int kTileFloats = 1280;  // a tile of rows is about 4 KB, at least one row
 constexpr int kMaxPasses = 10;     // most store passes of one flush of the packed form
+constexpr int kMaxHalfPasses = 5;  // ... of half a row of two wavefronts: 268 chunks at most
 constexpr int kPassBatch = 5;      // ... fetched from LDS together
 
 struct PolicyArgs {
@@ -62,8 +63,21 @@ struct KArgs {
     int       rows_per_flush;      // ... R: consecutive rows of an env staged before they are stored
     int       obs_per_chunk;       // ... observers per workgroup that shares an env group
     float     inv_cell;            // 1 / cell_size, used only when that is exact (power of two)
-    int       cell_pow2;
+    uint32_t  cells;               // FAST_CELL: cells of one row's grid
+    uint32_t  flags;               // Flag bits
     PolicyArgs pa;
+};
+
+// What a launch has to do besides the plain tick, one bit each.
+enum Flag : uint32_t {
+    DYNAMIC = 1,                   // persistent velocities
+    COLLIDE = 2,                   // body collisions
+    ELLIPSES = 4,                  // elliptical zones
+    CONE_BOUND = 8, HIT_ALL = 16,  // the two other readings of the hurtbox
+    KILLS = 32, RETURNS = 64,      // running episode metrics
+    LEVELS = 128,                  // level bank
+    FAST_CELL = 256,               // a cell grid; cell size a power of two, offsets by 24-bit products
+    EARLY_CELL = 512,              // a cell grid, and nothing but its own motion decides where a unit is
 };
 
 // Per-wavefront time stamps of an instrumented build (-DTABX_TRACE; compiled out of the product), eight
@@ -149,15 +163,16 @@ struct Unit {
 };
 
 // Where a lane sits: env slot g of the workgroup, unit u of that env, `base` =
-// workgroup lane of the env's unit 0, e = env index, k = e * N + u.
+// workgroup lane of the env's unit 0, e = env index, k = e * N + u.  A lane without a unit of its own
+// (`has` is false) stands at the group's first unit, so that every lane may load.
 struct Place {
     int grp;           // which run of G envs this workgroup owns
     int chunk;         // which share of the rows of these envs it writes (stand-alone observe)
     int l, g, u, base, e;
     bool has;
-    size_t k;
+    uint32_t k;        // (at most 2^30 units)
     int row;           // row of the scenario arrays that configures env e (its level, or e itself)
-    size_t ks;         // row * N + u
+    uint32_t ks;       // row * N + u
 };
 
 // What the observe stage needs of every unit, left in LDS by the wavefront that holds it.
@@ -258,6 +273,88 @@ __device__ __forceinline__ void group_barrier(Sh &sh)
     }
 }
 
+// The launch arguments where the kernel-argument segment holds them.  The kernels have more
+// argument words than scalar registers; fields that are needed once, late or rarely (episode
+// metrics, level bank, masks written at the end) are read through this pointer at the point of
+// use instead of sitting in registers, or spilled, from the first instruction on.
+typedef const __attribute__((address_space(4))) KArgs *LateArgs;
+__device__ __forceinline__ LateArgs late_args()
+{
+    return (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+// The launch arguments, fetched anew for the stage that follows.  A wavefront has too few scalar registers
+// for what all stages need between them, and what the compiler fetches once at the top it spills.
+__device__ __forceinline__ const KArgs &again()
+{
+    LateArgs p = late_args();
+    asm volatile("" : "+s"(p));
+    return *(const KArgs *)p;
+}
+
+// Brings all lines of the launch arguments into the scalar cache at once.  The stages read them where they need
+// them, and a lone wavefront would wait for each line in turn.
+__device__ __forceinline__ void warm_args()
+{
+    typedef const __attribute__((address_space(4))) uint32_t *Words;
+    const Words w = (Words)late_args();
+    uint32_t any = 0;
+#pragma unroll
+    for (int line = 0; line < (int)(sizeof(KArgs) / 64); ++line) any |= w[16 * line];
+    asm volatile("" ::"s"(any));
+}
+
+// Element k of a per-unit array (at most 2^30 elements: its byte offset fits 32 bits, so the
+// access is "uniform base + 32-bit lane offset" and needs no 64-bit address arithmetic per lane).
+template <class T>
+__device__ __forceinline__ T &at32(T *base, uint32_t k)
+{
+    char *const bytes = reinterpret_cast<char *>(const_cast<std::remove_const_t<T> *>(base));
+    return *reinterpret_cast<T *>(bytes + (uint32_t)(k * (uint32_t)sizeof(T)));
+}
+
+// The same index, made anew where it is used.  (An index that reaches the accesses from another basic block
+// is widened there, and each access then adds 64-bit addresses lane by lane.)
+__device__ __forceinline__ uint32_t here(uint32_t k)
+{
+    asm volatile("" : "+v"(k));
+    return k;
+}
+
+// Whether the launch has any of the bits.  (Tested where it is asked: kept from one place to the next, every
+// answer takes two scalar registers, of which there are too few.)
+__device__ __forceinline__ bool flagged(const KArgs &a, uint32_t bits)
+{
+    uint32_t f = a.flags;
+    asm volatile("" : "+s"(f));
+    return (f & bits) != 0;
+}
+
+// The zone code stored in the cell under a position (0 without a cell grid).
+__device__ __forceinline__ int grid_cell(const KArgs &a, int row, float x, float y)
+{
+    if (flagged(a, FAST_CELL)) {
+        // dividing by a power of two and multiplying by its reciprocal round identically
+        int cx = (int)(x * a.inv_cell), cy = (int)(y * a.inv_cell);
+        cx = cx > a.p.grid_w - 1 ? a.p.grid_w - 1 : cx;
+        cy = cy > a.p.grid_h - 1 ? a.p.grid_h - 1 : cy;
+        cx = cx < 0 ? 0 : cx;
+        cy = cy < 0 ? 0 : cy;
+        return (int)at32(a.sc.terrain, __umul24((uint32_t)row, a.cells) +
+                                           __umul24((uint32_t)cy, (uint32_t)a.p.grid_w) + (uint32_t)cx);
+    }
+    const LateArgs late = late_args();
+    const int8_t *const terrain = late->sc.terrain;
+    if (terrain == nullptr) return 0;
+    const int w = late->p.grid_w, h = late->p.grid_h;
+    int cx = (int)(x / late->p.cell_size), cy = (int)(y / late->p.cell_size);
+    cx = cx > w - 1 ? w - 1 : cx;
+    cy = cy > h - 1 ? h - 1 : cy;
+    cx = cx < 0 ? 0 : cx;
+    cy = cy < 0 ? 0 : cy;
+    return (int)terrain[((size_t)row * h + cy) * w + cx];
+}
+
 // Zone code under a position: low two bits = zone type, upper bits = zone identity; 0 = open.
 // Cell-grid zones: the code stored in the cell.  Elliptical zones (App. A "Zones"): the last
 // listed active zone whose ellipse holds the point, tested without division as
@@ -267,7 +364,7 @@ __device__ __forceinline__ void group_barrier(Sh &sh)
 __device__ __forceinline__ int zone_at(const KArgs &a, const float *zd, int row, float x, float y,
                                        float &own_effect)
 {
-    if (a.p.zone_shapes == 1) {
+    if (flagged(a, ELLIPSES)) {
         int code = 0;
         // four slots per round, their descriptors fetched together (a slot beyond the last one
         // re-reads the last and is masked out), so that the fetch latency is paid once per round
@@ -290,32 +387,13 @@ __device__ __forceinline__ int zone_at(const KArgs &a, const float *zd, int row,
         }
         return code;
     }
-    if (a.sc.terrain == nullptr) return 0;
-    // dividing by a power of two and multiplying by its reciprocal round identically
-    int cx = a.cell_pow2 ? (int)(x * a.inv_cell) : (int)(x / a.p.cell_size);
-    int cy = a.cell_pow2 ? (int)(y * a.inv_cell) : (int)(y / a.p.cell_size);
-    cx = cx > a.p.grid_w - 1 ? a.p.grid_w - 1 : cx;
-    cy = cy > a.p.grid_h - 1 ? a.p.grid_h - 1 : cy;
-    cx = cx < 0 ? 0 : cx;
-    cy = cy < 0 ? 0 : cy;
-    return (int)a.sc.terrain[((size_t)row * a.p.grid_h + cy) * a.p.grid_w + cx];
+    return grid_cell(a, row, x, y);
 }
-
 // Effect magnitude that applies in the zone just found: its own (elliptical zones) or the
 // global parameter (cell grid).
 __device__ __forceinline__ float zone_magnitude(const KArgs &a, float own_effect, float global_value)
 {
-    return a.p.zone_shapes == 1 ? own_effect : global_value;
-}
-
-// The launch arguments where the kernel-argument segment holds them.  The kernels have more
-// argument words than scalar registers; fields that are needed once, late or rarely (episode
-// metrics, level bank, masks written at the end) are read through this pointer at the point of
-// use instead of sitting in registers, or spilled, from the first instruction on.
-typedef const __attribute__((address_space(4))) KArgs *LateArgs;
-__device__ __forceinline__ LateArgs late_args()
-{
-    return (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    return flagged(a, ELLIPSES) ? +own_effect : +global_value;
 }
 
 // x / n for the small values that occur inside a workgroup, magic = ceil(65536 / n) from the host: exact
@@ -329,14 +407,8 @@ __device__ __forceinline__ int quotient(int x, unsigned magic)
 // Product of small non-negative values: one full-rate instruction.
 __device__ __forceinline__ int mul24(int x, int y) { return (int)__umul24((unsigned)x, (unsigned)y); }
 
-// Element k of a per-unit array (at most 2^30 elements: its byte offset fits 32 bits, so the
-// access is "uniform base + 32-bit lane offset" and needs no 64-bit address arithmetic per lane).
-template <class T>
-__device__ __forceinline__ const T &at32(const T *base, size_t k)
-{
-    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) +
-                                        (uint32_t)(k * sizeof(T)));
-}
+// The lanes of the wavefront for which `v` holds.
+__device__ __forceinline__ uint64_t lanes_where(bool v) { return __builtin_amdgcn_ballot_w64(v); }
 
 // Row of the scenario arrays that configures env `env`.
 __device__ __forceinline__ int row_of(const KArgs &a, int env)
@@ -418,69 +490,95 @@ __device__ __forceinline__ void put_zones(const KArgs &a, const ZoneLds &Z, int 
     }
 }
 
-__device__ __forceinline__ void load_spec(const KArgs &a, size_t k, Unit &U)
+__device__ __forceinline__ void load_spec(const KArgs &a, uint32_t k, Unit &U)
 {
+    U.enabled = at32(a.sc.enabled, k);
+    U.team = at32(a.sc.team, k);
     U.hmax = at32(a.sc.hmax, k);
     U.radius = at32(a.sc.radius, k);
-    U.mass = at32(a.sc.mass, k);
     U.speed = at32(a.sc.speed, k);
     U.dmg = at32(a.sc.dmg, k);
     U.range = at32(a.sc.range, k);
     U.cooldown = at32(a.sc.cooldown, k);
-    U.sight_angle = at32(a.sc.sight_angle, k);
     U.cos_half = at32(a.sc.sight_cos_half, k);
-    U.sight_range = at32(a.sc.sight_range, k);
     U.hurt_hw = at32(a.sc.hurt_halfwidth, k);
-    U.team = at32(a.sc.team, k);
-    U.enabled = at32(a.sc.enabled, k);
+    U.mass = at32(a.sc.mass, k);
+    U.sight_angle = at32(a.sc.sight_angle, k);
+    U.sight_range = at32(a.sc.sight_range, k);
 }
 
-__device__ __forceinline__ void load_state(const KArgs &a, size_t k, Unit &U)
+// The unit's state and specification; first what decides where the unit is after its move.  STEP_ONLY: no
+// rows follow, which alone need the mass (but for body collisions), the cone (but where it bounds the hurtbox)
+// and the sight; load_more has the exceptions.
+template <bool STEP_ONLY>
+__device__ __forceinline__ void load_unit(const KArgs &a, uint32_t k, uint32_t ks, Unit &U)
 {
+    U.alive = at32(a.st.alive, k);
+    U.enabled = at32(a.sc.enabled, ks);
     U.x = at32(a.st.x, k);
     U.y = at32(a.st.y, k);
     U.vx = at32(a.st.vx, k);
     U.vy = at32(a.st.vy, k);
-    U.theta = at32(a.st.theta, k);
-    U.hp = at32(a.st.hp, k);
-    U.cd = at32(a.st.cd, k);
-    U.reveal = at32(a.st.reveal, k);
+    __builtin_amdgcn_sched_barrier(0x78f);     // (no load crosses)
     U.cur_speed = at32(a.st.cur_speed, k);
-    U.alive = at32(a.st.alive, k);
+    U.theta = at32(a.st.theta, k);
+    U.cd = at32(a.st.cd, k);
+    U.hp = at32(a.st.hp, k);
+    U.reveal = at32(a.st.reveal, k);
+    U.team = at32(a.sc.team, ks);
+    U.hmax = at32(a.sc.hmax, ks);
+    U.dmg = at32(a.sc.dmg, ks);
+    U.range = at32(a.sc.range, ks);
+    U.hurt_hw = at32(a.sc.hurt_halfwidth, ks);
+    U.radius = at32(a.sc.radius, ks);
+    U.cooldown = at32(a.sc.cooldown, ks);
+    U.speed = at32(a.sc.speed, ks);
+    if (!STEP_ONLY) {
+        U.mass = at32(a.sc.mass, ks);
+        U.cos_half = at32(a.sc.sight_cos_half, ks);
+        U.sight_angle = at32(a.sc.sight_angle, ks);
+        U.sight_range = at32(a.sc.sight_range, ks);
+    }
+}
+
+__device__ __forceinline__ void load_more(const KArgs &a, uint32_t ks, Unit &U)
+{
+    if (flagged(a, COLLIDE)) U.mass = at32(late_args()->sc.mass, here(ks));
+    if (flagged(a, CONE_BOUND)) U.cos_half = at32(late_args()->sc.sight_cos_half, here(ks));
 }
 
 // The bytes as 0 or 1: any non-zero one means the adversaries, or alive.  Apart from the loads, since
 // folding a byte waits for it: what is asked for after that is a round trip later.  (The empty
 // instruction keeps the compiler from moving the folding, and with it the wait, up to the loads.)
-__device__ __forceinline__ void fold_bytes(Unit &U)
+__device__ __forceinline__ void fold_byte(int &byte)
 {
-    asm volatile("" : "+v"(U.team), "+v"(U.alive));
-    U.team = (U.team + 255) >> 8;
-    U.alive = (U.alive + 255) >> 8;
+    asm volatile("" : "+v"(byte));
+    byte = (byte + 255) >> 8;
 }
 
-__device__ __forceinline__ void store_state(const KArgs &a, size_t k, const Unit &U)
+__device__ __forceinline__ void store_state(const KArgs &a, uint32_t k, const Unit &U)
 {
-    a.st.x[k] = U.x;
-    a.st.y[k] = U.y;
-    a.st.vx[k] = U.vx;
-    a.st.vy[k] = U.vy;
-    a.st.theta[k] = U.theta;
-    a.st.hp[k] = U.hp;
-    a.st.cd[k] = U.cd;
-    a.st.reveal[k] = U.reveal;
-    a.st.cur_speed[k] = U.cur_speed;
-    a.st.alive[k] = (uint8_t)U.alive;
+    k = here(k);
+    at32(a.st.x, k) = U.x;
+    at32(a.st.y, k) = U.y;
+    at32(a.st.vx, k) = U.vx;
+    at32(a.st.vy, k) = U.vy;
+    at32(a.st.theta, k) = U.theta;
+    at32(a.st.hp, k) = U.hp;
+    at32(a.st.cd, k) = U.cd;
+    at32(a.st.reveal, k) = U.reveal;
+    at32(a.st.cur_speed, k) = U.cur_speed;
+    at32(a.st.alive, k) = (uint8_t)U.alive;
 }
 
 // Episode start for one unit: spawn pose, full health, timers cleared.  Returns
 // the terrain cell code under the spawn point.
-__device__ __forceinline__ int spawn_unit(const KArgs &a, const float *zd, int row, size_t ks,
+__device__ __forceinline__ int spawn_unit(const KArgs &a, const float *zd, int row, uint32_t ks,
                                           Unit &U, float &zeff)
 {
-    U.x = a.sc.init_x[ks];
-    U.y = a.sc.init_y[ks];
-    U.theta = a.sc.init_theta[ks];
+    U.x = at32(a.sc.init_x, ks);
+    U.y = at32(a.sc.init_y, ks);
+    U.theta = at32(a.sc.init_theta, ks);
     U.vx = 0.0f;
     U.vy = 0.0f;
     U.hp = U.enabled ? U.hmax : 0.0f;
@@ -493,58 +591,62 @@ __device__ __forceinline__ int spawn_unit(const KArgs &a, const float *zd, int r
     return code;
 }
 
-template <int WAVES>
+// SHARED_GROUPS: several workgroups may share the rows of an env group (stand-alone observe).
+template <int WAVES, bool SHARED_GROUPS = false>
 __device__ __forceinline__ Place locate(const KArgs &a)
 {
     Place P;
     const int N = a.p.num_units;
     P.l = (int)threadIdx.x;           // (only the wavefronts that step or publish hold units)
-    if (WAVES == 1) {
-        P.g = P.l / N;
-        P.u = P.l - P.g * N;
-    } else {
-        P.g = 0;
-        P.u = P.l;
-    }
     // Workgroups are dealt to the 8 XCDs round robin; give each XCD one contiguous eighth of
     // the env range, so that neighbouring env groups, which share the cache lines at the ends
     // of their SoA segments, meet in the same L2.
     const int slot = (int)(blockIdx.x >> 3);
-    const int in_xcd = a.obs_chunks > 1 ? slot / a.obs_chunks : slot;
-    P.chunk = slot - in_xcd * a.obs_chunks;
+    const int in_xcd = SHARED_GROUPS && a.obs_chunks > 1 ? slot / a.obs_chunks : slot;
+    P.chunk = SHARED_GROUPS ? slot - in_xcd * a.obs_chunks : 0;
     P.grp = in_xcd < a.groups_per_xcd ? (int)(blockIdx.x & 7) * a.groups_per_xcd + in_xcd : a.num_groups;
+    P.has = P.l < envs_of_group(a, P.grp) * N;
+    const int lane = P.has ? P.l : 0;
+    P.g = WAVES == 1 ? quotient(lane, a.magic_n) : 0;
+    P.base = WAVES == 1 ? mul24(P.g, N) : 0;
+    P.u = lane - P.base;
     P.e = P.grp * a.envs_per_block + P.g;
-    P.has = P.grp < a.num_groups && P.g < a.envs_per_block && P.u < N && P.e < a.p.num_envs;
-    P.base = P.has ? P.l - P.u : 0;
-    P.k = (size_t)P.e * N + P.u;
+    P.k = (uint32_t)(P.grp * a.envs_per_block) * (uint32_t)N + (uint32_t)lane;
     P.row = P.e;
-    if (a.p.num_levels > 0) {      // folded into the bank whatever the array holds
-        const int lv = P.has ? a.st.level[P.e] : 0;
+    P.ks = P.k;
+    if (a.p.num_levels > 0 && P.grp < a.num_groups) {      // folded into the bank whatever the array holds
+        const int lv = at32(a.st.level, (uint32_t)P.e);
         P.row = lv < 0 ? 0 : (lv >= a.p.num_levels ? a.p.num_levels - 1 : lv);
+        P.ks = (uint32_t)P.row * (uint32_t)N + (uint32_t)P.u;
     }
-    P.ks = (size_t)P.row * N + P.u;
     return P;
 }
 
-// How many lanes of the caller's env satisfy each of four predicates.
-template <int WAVES, class Sh>
+// The lanes of the caller's env (envs of one wavefront).
+__device__ __forceinline__ uint64_t lanes_of_env(const Place &P, int N)
+{
+    return (N >= 64 ? ~0ull : ((1ull << N) - 1ull)) << P.base;
+}
+
+// How many lanes of the caller's env satisfy each of K predicates.
+template <int WAVES, int K, class Sh>
 __device__ __forceinline__ void env_counts(Sh &sh, const Place &P, int N,
-                                           const bool (&pred)[4], int (&cnt)[4])
+                                           const bool (&pred)[K], int (&cnt)[K])
 {
     if (WAVES == 1) {
-        const uint64_t range = (N >= 64 ? ~0ull : ((1ull << N) - 1ull)) << P.base;
+        const uint64_t range = lanes_of_env(P, N);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cnt[q] = __popcll(__ballot(pred[q]) & range);
+        for (int q = 0; q < K; ++q) cnt[q] = __popcll(lanes_where(pred[q]) & range);
     } else {
         const int wv = P.l >> 6;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint64_t b = __ballot(pred[q]);
+        for (int q = 0; q < K; ++q) {
+            const uint64_t b = lanes_where(pred[q]);
             if ((P.l & 63) == 0) sh.ballots[wv][q] = b;
         }
         group_barrier<WAVES>(sh);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < K; ++q) {
             cnt[q] = 0;
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) cnt[q] += __popcll(sh.ballots[w][q]);
@@ -555,19 +657,41 @@ __device__ __forceinline__ void env_counts(Sh &sh, const Place &P, int N,
 
 // Mean health ratio of both teams over their enabled units (the bracketed means of
 // Eq. 1): the terms published in sh.share are added in ascending unit index; a term
-// of +0.0f (unit of the other team, or disabled) leaves a finite sum unchanged.
+// of +0.0f (unit of the other team, or disabled) leaves a finite sum unchanged.  Eight terms are
+// fetched together, also the last few (what lies behind the env's terms is fetched with them and not
+// added): one by one, each is a trip to LDS that a small batch waits for.
 template <class Sh>
 __device__ __forceinline__ void team_means(const Sh &sh, const Place &P, int N,
                                            int c0, int c1, float &m0, float &m1)
 {
+    static_assert(sizeof(sh.st.aim0) >= sizeof(sh.st.share) + 8 * sizeof(float2), "terms behind the last");
     float s0 = 0.0f, s1 = 0.0f;
-    for (int jj = 0; jj < N; ++jj) {
-        const float2 q = sh.st.share[P.base + jj];
-        s0 = s0 + q.x;
-        s1 = s1 + q.y;
+    const float2 *term = sh.st.share + P.base;
+    int left = N;
+    for (; left >= 8; left -= 8, term += 8) {
+        float2 q[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) q[k] = term[k];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            s0 = s0 + q[k].x;
+            s1 = s1 + q[k].y;
+        }
     }
-    m0 = c0 > 0 ? s0 / (float)c0 : 0.0f;
-    m1 = c1 > 0 ? s1 / (float)c1 : 0.0f;
+    if (left > 0) {
+        float2 q[7];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) q[k] = term[k];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+            if (k >= left) break;
+            s0 = s0 + q[k].x;
+            s1 = s1 + q[k].y;
+        }
+    }
+    const float r0 = s0 / (float)(c0 > 0 ? c0 : 1), r1 = s1 / (float)(c1 > 0 ? c1 : 1);
+    m0 = c0 > 0 ? r0 : 0.0f;
+    m1 = c1 > 0 ? r1 : 0.0f;
 }
 
 // Squared gap between attacker i's forward rectangle [0, L] x [-hw, hw] and the

@@ -43,7 +43,7 @@ namespace tabx {
 template <int WAVES, bool DO_POLICY, bool DO_STEP, bool DO_OBS, bool SCRIPT = false,
           int TWIN = 0, bool EVEN = false>
 __global__ __launch_bounds__(64 * WAVES * (TWIN ? TWIN : 1))
-__attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(const KArgs a)
+__attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(const KArgs args)
 {
     // without further wavefronts to share the rows with, the units stay in registers
     constexpr bool PACKED = DO_OBS && TWIN == 0;
@@ -68,10 +68,18 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
             ((unsigned long long)xcc << 32) | hw;
     }
 #endif
-    Place P = locate<WAVES>(a);
+    const KArgs &a = args;
+    // (The register that is named here keeps a SIMD at three of these wavefronts, or four: more of them stream
+    // slower.  One wavefront, three and four per SIMD: 5v5 x 65536 83.4 and 84.6 us; two, four and five: 64v64 x
+    // 4000 776 and 809; EVEN: see plan_shape.)
+    if constexpr (PACKED && (EVEN || (WAVES == 1 && DO_STEP))) asm volatile("" ::: "v135");
+    else if constexpr (PACKED && WAVES == 2) asm volatile("" ::: "v103");
+    warm_args();
+    Place P = locate<WAVES, DO_OBS && !DO_STEP>(a);
+    if (P.grp >= a.num_groups) return;           // (the grid is rounded up to the eight XCDs)
     const ZoneLds Z = zone_lds(a, dyn);
     ScriptLds<WAVES> *script = reinterpret_cast<ScriptLds<WAVES> *>(dyn + a.script_offset);
-    const float *zd = reinterpret_cast<const float *>(Z.val + (P.has ? P.g : 0) * a.zone_chunks);
+    const float *zd = reinterpret_cast<const float *>(Z.val + P.g * a.zone_chunks);
     Carry C = {1.0f, 0.0f, 0.0f, 0, false, 0, 0, 0.0f, 0.0f};
     float speed = 0.0f;
     // a wavefront that waits for the step fetches the zones meanwhile, unless the wavefronts that step
@@ -84,20 +92,20 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
         if (P.chunk == 0) global_state_zones<64>(a, Z, P.grp, (int)(threadIdx.x & 63));
     }
     if (lead) {
+        const KArgs &a = again();
         Unit U = {};
-        int code_u = 0;
+        int code_u = 0;                              // the zone code under the unit
+        StepIn in = {0, -1, 0.0f, 0, 0.0f, 0.0f, 0.0f};
+        load_unit<!DO_OBS && !DO_POLICY>(a, P.k, P.ks, U);
         PolicyIn pin = {};
-        if (P.has) {
-            load_spec(a, P.ks, U);
-            load_state(a, P.k, U);
-            if (DO_POLICY) load_policy(a, P, pin);
-        }
-        StepIn in = {};
-        if (DO_STEP) in = load_step(a, P);
+        if (DO_POLICY) load_policy(a, P, pin);
+        if (DO_STEP) load_step(a, P, in);
+        if (DO_STEP && !DO_OBS) load_more(a, P.ks, U);
+        if (DO_STEP) load_more_step(a, P, in);
         // scripted units: the action decided on at the end of the previous call and the memory, asked for
         // with the state (whether the unit is the policy's to move or not: one round trip for all)
         int told = 0, waiting = 0;
-        if (SCRIPT && P.has) {
+        if (SCRIPT) {
             const LateArgs late = late_args();
             const uint8_t *const controlled = late->pa.controlled;
             told = controlled ? at32(controlled, P.k) : 1;
@@ -106,42 +114,56 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
             C.mem_x = at32(late->pa.mem.mem_x, P.k);
             C.mem_y = at32(late->pa.mem.mem_y, P.k);
         }
+        // (a lane without a unit of its own has loaded the group's first one)
+        fold_byte(U.alive);
+        U.alive = P.has ? U.alive : 0;
+        U.enabled = P.has ? U.enabled : 0;
+        // the unit's move and the grid cell under it, which is asked for while the rest is on its way
+        float zeff = 0.0f;
+        int code = 0;
+        bool oob = false;
+        if (DO_STEP && !DO_POLICY) oob = move_unit(a, U, in);
+        if (!flagged(a, ELLIPSES) && (!DO_STEP || DO_POLICY || flagged(a, EARLY_CELL))) code = grid_cell(a, P.row, U.x, U.y);
         ZoneRegs Zr = {};
         if (PACKED) Zr = load_zone_regs(a, P);
         if (a.zones_in_lds && !zones_elsewhere) {
             put_zones<64 * WAVES, WAVES == 2>(a, Z, P.grp, P.l);
             group_barrier<WAVES>(sh);
         }
-        fold_bytes(U);
-        float zeff_unused = 0.0f;
+        if ((!DO_STEP || DO_POLICY) && flagged(a, ELLIPSES)) code = zone_at(a, zd, P.row, U.x, U.y, zeff);
+        fold_byte(U.team);
         int forced = -1;
         if (SCRIPT && told && U.enabled && U.alive) {
             forced = waiting;
-            late_args()->pa.actions_out[P.k] = (uint8_t)forced;
+            at32(late_args()->pa.actions_out, here(P.k)) = (uint8_t)forced;
         }
         if constexpr (DO_POLICY) {
-            float cu = 1.0f, su = 0.0f;
-            if (P.has) {
-                code_u = zone_at(a, zd, P.row, U.x, U.y, zeff_unused);
-                heading_sincos(U.theta, su, cu);
-            }
-            forced = policy_env<WAVES>(a, sh, P, U, pin, code_u, cu, su, zd);
+            float cu, su;
+            heading_sincos(U.theta, su, cu);
+            forced = policy_env<WAVES>(a, sh, P, U, pin, code, cu, su, zd);
         }
         TABX_STAMP(6);
         if (DO_STEP) {
-            const bool restarted = step_env<WAVES>(a, sh, Z, zd, P, U, code_u, C, in, forced);
+            const KArgs &a = again();
+            const int stood = DO_POLICY ? code : 0;
+            if (DO_POLICY) oob = move_unit(a, U, in);
+            if (flagged(a, COLLIDE)) collide_env<WAVES>(a, sh, P, U);
+            if (DO_POLICY || !flagged(a, EARLY_CELL)) code = zone_at(a, zd, P.row, U.x, U.y, zeff);
+            code_u = U.enabled ? code : stood;
+            const bool restarted = step_env<WAVES>(a, sh, Z, zd, P, U, code_u, zeff, oob, C, in, forced);
             if (PACKED && a.p.num_levels > 0 && restarted) {
                 // zone slots of the envs that changed level
                 const int row = Zr.lane ? sh.level_rows[Zr.zg] : -1;
                 if (row >= 0) Zr = load_zone_regs(a, P, row);
             }
-        } else if (DO_OBS && P.has) {
-            code_u = zone_at(a, zd, P.row, U.x, U.y, zeff_unused);
+        } else if (DO_OBS) {
+            code_u = code;
             heading_sincos(U.theta, C.su, C.cu);
             C.ratio = U.hp / U.hmax;       // (disabled units: masked in the rows)
         }
         TABX_STAMP(1);
         if constexpr (PACKED) {
+            const KArgs &a = again();
             observe_packed<WAVES, SCRIPT, SCRIPT || DO_POLICY, EVEN>(a, sh, dyn, P, U, code_u, C, Zr, told, script, zd);
         } else if constexpr (DO_OBS) {
             group_barrier<WAVES>(sh);          // the step stage is done with the LDS union
@@ -157,7 +179,8 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
         lds_barrier<2>();                  // the whole workgroup
         TABX_STAMP(2);
         float *stg = dyn + wave * a.stage_floats;
-        if (P.grp < a.num_groups) {
+        {
+            const KArgs &a = again();
             const int first = P.chunk * a.tiles_per_chunk;
             const int end = first + a.tiles_per_chunk < a.tiles ? first + a.tiles_per_chunk : a.tiles;
             // Each wavefront writes one contiguous run of the group's tiles.  Taken in turn, tile by tile,
@@ -190,20 +213,21 @@ __global__ __launch_bounds__(64 * WAVES) void tabx_reset_kernel(const KArgs a)
 {
     __shared__ Shared<WAVES, false, false> sh;
     Place P = locate<WAVES>(a);
+    if (P.grp >= a.num_groups) return;
     const int N = a.p.num_units;
     const bool go = P.has && !(a.env_mask && a.env_mask[P.e] == 0);
     if (a.p.num_levels > 0) {
         const int row = advance_level<WAVES>(a, sh, P, go);
         if (row >= 0) {
             P.row = row;
-            P.ks = (size_t)row * N + P.u;
+            P.ks = (uint32_t)row * (uint32_t)N + (uint32_t)P.u;
         }
     }
     Unit U = {};
     float ratio = 0.0f;
     if (go) {
         load_spec(a, P.ks, U);
-        fold_bytes(U);
+        fold_byte(U.team);
         float zeff = 0.0f;
         spawn_unit(a, a.sc.zone_desc + (size_t)P.row * 6 * a.p.max_zones, P.row, P.ks, U, zeff);
         ratio = U.enabled ? U.hp / U.hmax : 0.0f;
@@ -216,8 +240,8 @@ __global__ __launch_bounds__(64 * WAVES) void tabx_reset_kernel(const KArgs a)
     const bool en = go && U.enabled;
     sh.st.share[P.l] = make_float2((en && U.team == 0) ? ratio : 0.0f,
                                    (en && U.team != 0) ? ratio : 0.0f);
-    const bool pred[4] = {en && U.team == 0, en && U.team != 0, false, false};
-    int cnt[4];
+    const bool pred[2] = {en && U.team == 0, en && U.team != 0};
+    int cnt[2];
     env_counts<WAVES>(sh, P, N, pred, cnt);
     lds_barrier<WAVES>();
     float m0, m1;
@@ -244,9 +268,10 @@ __global__ __launch_bounds__(256) void tabx_global_state_kernel(const KArgs a, f
         const int u = (int)(tid - (size_t)e * N);
         const int row = row_of(a, e);
         Unit U = {};
-        load_spec(a, (size_t)row * N + u, U);
-        load_state(a, tid, U);
-        fold_bytes(U);
+        const uint32_t k = (uint32_t)tid, ks = (uint32_t)row * (uint32_t)N + (uint32_t)u;
+        load_unit<false>(a, k, ks, U);
+        fold_byte(U.team);
+        fold_byte(U.alive);
         float4 q[4];
         if (U.enabled) {
             float zeff = 0.0f;
@@ -365,6 +390,30 @@ static int check_state(const TabxParams *p, const TabxState *s)
     for (const void *q : m4)
         if (q && !aligned(q, 4)) return TABX_ERR_ALIGN;
     return TABX_OK;
+}
+
+// Whether v is a power of two whose reciprocal (`inv`) is exact.
+static bool power_of_two(float v, float *inv)
+{
+    int ex = 0;
+    *inv = 1.0f / v;
+    return frexpf(v, &ex) == 0.5f && ex > -100 && ex < 100;
+}
+
+// What the launch has to do besides the plain tick, and how it finds a unit's cell.
+static void set_flags(const TabxParams *p, const TabxState *st, KArgs &a)
+{
+    const uint64_t rows = p->num_levels > 0 ? p->num_levels : p->num_envs;
+    const uint64_t cells = (uint64_t)p->grid_w * (uint64_t)p->grid_h;
+    a.cells = (uint32_t)cells;
+    a.flags = (p->dynamics == 1 ? DYNAMIC : 0) | (p->collision_alpha > 0.0f ? COLLIDE : 0) |
+              (p->zone_shapes == 1 ? ELLIPSES : 0) | (p->hurtbox_cone ? CONE_BOUND : 0) |
+              (p->hit_all ? HIT_ALL : 0) | (st->kill_run ? KILLS : 0) | (st->ret_run ? RETURNS : 0) |
+              (p->num_levels > 0 ? LEVELS : 0) |
+              (cells > 0 && !(p->collision_alpha > 0.0f) ? EARLY_CELL : 0);
+    if (cells > 0 && power_of_two(p->cell_size, &a.inv_cell) && rows < (1u << 24) && cells < (1u << 24) &&
+        rows * cells <= 1ull << 32)
+        a.flags |= FAST_CELL;
 }
 
 // A wavefront's staging area for `floats` floats: whole store passes (64 lanes of 16 bytes).
@@ -513,12 +562,6 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     a.tiles = (G * N + S - 1) / S;
     a.num_groups = (p->num_envs + G - 1) / G;
     a.groups_per_xcd = (a.num_groups + 7) / 8;
-    {
-        int ex = 0;
-        const float mant = frexpf(p->cell_size, &ex);
-        a.cell_pow2 = (mant == 0.5f && ex > -100 && ex < 100) ? 1 : 0;
-        a.inv_cell = 1.0f / p->cell_size;
-    }
     // Long-lived wavefronts make a long tail at the end of the launch, and a wavefront's chain of
     // rows is the latency floor of a small batch, so the rows of an env group are split:
     //  - a stand-alone observe uses several workgroups per group (each loads the group's units and
@@ -698,6 +741,7 @@ static int run(Mode mode, const TabxParams *p, const TabxScenario *sc, const Tab
     a.vis_mask = vis_mask;
     a.action_mask = action_mask;
     a.obs_dim = 16 * p->num_units + 6 * p->max_zones;
+    set_flags(p, st, a);
     a.pa = {};
     if (deciding) {
         a.pa.pol = *policy;
@@ -784,12 +828,7 @@ int tabx_global_state(const TabxParams *p, const TabxScenario *sc, const TabxSta
     a.p = *p;
     a.sc = *sc;
     a.st = *st;
-    {
-        int ex = 0;
-        const float mant = frexpf(p->cell_size, &ex);
-        a.cell_pow2 = (mant == 0.5f && ex > -100 && ex < 100) ? 1 : 0;
-        a.inv_cell = 1.0f / p->cell_size;
-    }
+    tabx::set_flags(p, st, a);
     const size_t units = (size_t)p->num_envs * p->num_units;
     const size_t zones = (size_t)p->num_envs * 6 * p->max_zones;
     const size_t threads = units > zones ? units : zones;

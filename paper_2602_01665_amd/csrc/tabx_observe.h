@@ -151,7 +151,10 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     const int N = a.p.num_units;
     const int D = a.obs_dim;
     const int T = a.rows_per_tile, S = a.rows_per_pass;
-    const int ZC = a.zone_chunks;
+    const int ZC = a.zone_chunks, zlen = 6 * a.p.max_zones;
+    const unsigned magic_n = a.magic_n, magic_tc = a.magic_tc;
+    const int passes_per_tile = a.passes_per_tile;
+    float *const obs = a.obs;
     const int lane = (int)(threadIdx.x & 63);
     constexpr int HALVES = WAVES;
     const int rows = envs_of_group(a, grp) * N;
@@ -160,14 +163,14 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     const bool whole = (D & 3) == 0;             // rows are whole 16-byte chunks
     const bool grouped = (D & 15) == 0;          // ... and whole 64-byte groups
     // the lane's place in a pass: row slot s, unit u
-    const int s = WAVES == 1 ? quotient(lane, a.magic_n) : 0;
+    const int s = WAVES == 1 ? quotient(lane, magic_n) : 0;
     int u = WAVES == 1 ? lane - s * N : lane;
     const bool holds = s < S && (HALVES == 2 || u < N);
     // the rest of a row, copied chunk by chunk: the own block (four chunks) and the zone slots; without
     // zone slots the observer's own lane puts its block where the others put theirs, which saves the
     // extra trip through LDS
     const int TC = FOLD ? 0 : 4 + ZC;
-    const int ts0 = WAVES == 1 ? quotient(lane, a.magic_tc) : 0;
+    const int ts0 = WAVES == 1 ? quotient(lane, magic_tc) : 0;
     int vis_lo = 0, vis_hi = 0;
     uint64_t passes_done = 0;
     const int lane_chunk = whole ? staged_chunk(lane) : lane;
@@ -180,7 +183,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     float orange = 0.0f, ohw = 0.0f;
     auto fetch = [&](int f0, int r0, int rows_here) {
         f = f0 + (r0 + s < rows_here ? r0 + s : 0);
-        gN = WAVES == 1 ? mul24(quotient(f, a.magic_n), N) : 0;
+        gN = WAVES == 1 ? mul24(quotient(f, magic_n), N) : 0;
         i = f - gN;
         opos = *reinterpret_cast<const v2 *>(&rec.own[0][f].z);
         V = rec.view[f];
@@ -198,12 +201,12 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     // the copied part of the rows of a tile, into its staging area
     auto copy_tail = [&](int f0, int rows_here, int pad, float *buf) {
                 for (int q = lane, ts = ts0; q < rows_here * TC;
-                     q += 64, ts = WAVES == 1 ? quotient(q, a.magic_tc) : 0) {
+                     q += 64, ts = WAVES == 1 ? quotient(q, magic_tc) : 0) {
                     const int c = q - mul24(ts, TC);
                     const int tf = f0 + ts;
                     const int zc = c - 4;
                     const bool zone = zc >= 0;
-                    const int zi = WAVES == 1 ? mul24(quotient(tf, a.magic_n), ZC) + zc : zc;
+                    const int zi = WAVES == 1 ? mul24(quotient(tf, magic_n), ZC) + zc : zc;
                     const float4 v = zone ? Z.val[zi] : rec.own[0][c * (64 * WAVES) + tf];
                     const int rel = zone ? Z.rel[zi] : 0;
                     const v2 pos = *reinterpret_cast<const v2 *>(&rec.own[0][tf].z);
@@ -224,7 +227,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
                         // (a row ends on half a chunk: its second half belongs to the next row)
                         v2 *d = reinterpret_cast<v2 *>(buf + at);
                         d[0] = v2{to[0], to[1]};
-                        if (!zone || 4 * zc + 2 < 6 * a.p.max_zones) d[1] = v2{to[2], to[3]};
+                        if (!zone || 4 * zc + 2 < zlen) d[1] = v2{to[2], to[3]};
                     }
                 }
     };
@@ -241,7 +244,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         const int pad = pad_of(tile);
         float *const buf = stg;
         v4 *const vstage = reinterpret_cast<v4 *>(buf);
-        int pass = tile * a.passes_per_tile;
+        int pass = tile * passes_per_tile;
         for (int r0 = 0; r0 < rows_here; r0 += S, ++pass) {
 #pragma unroll 1
         for (int h = 0; h < HALVES; ++h) {
@@ -352,7 +355,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         lds_barrier<1>();
 
         // stream the finished rows: LDS chunk -> one 16-byte store, 1 KB per instruction
-        float *const out = a.obs + (row0 + f0) * D - pad;            // 16-byte aligned
+        float *const out = obs + (row0 + f0) * D - pad;            // 16-byte aligned
         const int floats = pad + rows_here * D;
         const int chunks = floats >> 2;          // (whole chunks, the first one perhaps half ours)
         const int first = pad >> 1;   // 0, or 1: chunk 0 starts in the previous row

@@ -74,7 +74,6 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
     const int zlen = 6 * a.p.max_zones;
     const bool has = P.has;
     const bool want_vis = late_args()->vis_mask != nullptr;
-    const bool want_gs = late_args()->st.global_state != nullptr;
     const int envs_here = envs_of_group(a, P.grp);
     const int lane = P.l & 63;
     const int wv = P.l >> 6;
@@ -116,16 +115,40 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
     const float own_alive = alive ? 1.0f : 0.0f;
     const float own_zone = (float)(code_u & 3);
     const float own_team = (float)U.team;
+    float *const global_state = late_args()->st.global_state;
+    if (global_state && P.chunk == 0) {
+        // the own block with its absolute position is the unit's block of the global state, the zone slots
+        // with absolute centres are its tail
+        if (has) {
+            f4u *gs = reinterpret_cast<f4u *>(global_state + (size_t)P.e * D + 16 * P.u);
+            auto masked = [own_mask](float v) { return __int_as_float(__float_as_int(v) & own_mask); };
+            gs[0] = f4u{masked(U.hp), masked(ratio), masked(U.x), masked(U.y)};
+            gs[1] = f4u{masked(U.theta), masked(U.range), masked(U.dmg), masked(U.cd)};
+            gs[2] = f4u{masked(cd_ratio), masked(U.radius), masked(U.mass), masked(U.sight_angle)};
+            gs[3] = f4u{masked(own_alive), masked(U.cur_speed), masked(own_zone), masked(own_team)};
+        }
+        if (Zr.lane) {
+            float *gz = global_state + (size_t)(P.grp * G + Zr.zg) * D + 16 * N + 4 * Zr.zc;
+            if (!HALF_CHUNK || zlen - 4 * Zr.zc >= 4) {
+                *reinterpret_cast<f4u *>(gz) = f4u{Zr.val[0], Zr.val[1], Zr.val[2], Zr.val[3]};
+            } else {
+                gz[0] = Zr.val[0];
+                gz[1] = Zr.val[1];
+            }
+        }
+    }
 
     const int zg = Zr.zg, zc = Zr.zc;
     const int zone_seer0 = WAVES == 1 ? zg * N : 0;        // lane of observer 0 of the zone lane's env
     const bool cone_free = a.p.hurtbox_cone == 0;          // the hurtbox is the plain rectangle
-    const int R = a.rows_per_flush;
+    const int R = WAVES == 2 ? 1 : a.rows_per_flush;
+    int copy_passes = a.copy_passes;
     const int zone_dst0 = (WAVES == 1 ? zg * R * D : 0) + 16 * N + 4 * zc;
 
     // ---- store passes: chunk t = 64 p + l of the staged rows -> (env slot, chunk in its R rows)
-    unsigned dst_off[kMaxPasses];
-    bool valid[kMaxPasses];
+    constexpr int PASSES = WAVES == 2 ? kMaxHalfPasses : kMaxPasses;
+    unsigned dst_off[PASSES];
+    bool valid[PASSES];
     // (WAVES == 2: each wavefront streams one contiguous half of the row, both whole 64-byte groups)
     const int half_row = ((CPR >> 1) + 3) & ~3;
     const int row_chunks = ((HALF_CHUNK ? (D + 3) >> 2 : CPR) + 3) & ~3;   // pitch of the two alternating row areas
@@ -136,7 +159,7 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
         int phys = first_chunk;
         int q = staged_chunk(first_chunk);
 #pragma unroll
-        for (int p = 0; p < kMaxPasses; ++p) {
+        for (int p = 0; p < PASSES; ++p) {
             valid[p] = phys < end && q < CPR && envs_here > 0;
             dst_off[p] = (unsigned)(4 * q);
             q += 64;
@@ -151,7 +174,7 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
             tg += 1;
         }
 #pragma unroll
-        for (int p = 0; p < kMaxPasses; ++p) {
+        for (int p = 0; p < PASSES; ++p) {
             // (a pass beyond copy_passes holds only chunks of env slots >= G >= envs_here)
             valid[p] = tg < envs_here;
             dst_off[p] = (unsigned)(tg * N * D + 4 * q);
@@ -188,14 +211,18 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
     const int i_begin = P.chunk * a.obs_per_chunk;
     const int i_end = (i_begin + a.obs_per_chunk < N) ? i_begin + a.obs_per_chunk : N;
     TABX_STAMP(2);
+    float4 A = sh.ob.pose[0], B = sh.ob.reach[0];        // the observer
+    int fi = sh.ob.seer[0];
     for (int i0 = i_begin; i0 < i_end; i0 += R) {
         v4 *const area = stage + (WAVES == 1 ? 0 : (i0 & 1) * row_chunks);
         for (int rr = 0; rr < R; ++rr) {
             const int i = i0 + rr;
             const int oi = P.base + i;
-            const float4 A = sh.ob.pose[oi];
-            const float4 B = sh.ob.reach[oi];
-            const int fi = sh.ob.seer[oi];
+            if (WAVES == 1) {
+                A = sh.ob.pose[oi];
+                B = sh.ob.reach[oi];
+                fi = sh.ob.seer[oi];
+            }
             const int buf = rr * D;
             // offset of this unit from the observer; `dot` is its component along the heading
             const float dx = U.x - A.x;
@@ -257,14 +284,6 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
                                masked(self ? U.cur_speed : (same_team ? 1.0f : 0.0f)),
                                masked(self ? own_zone : (hit ? 1.0f : 0.0f)),
                                masked(self ? own_team : U.cur_speed)};
-                if (self && want_gs) {
-                    // the own block with its absolute position is the unit's block of the global state
-                    f4u *gs = reinterpret_cast<f4u *>(late_args()->st.global_state + (size_t)P.e * D + 16 * P.u);
-                    gs[0] = w0;
-                    gs[1] = w1;
-                    gs[2] = w2;
-                    gs[3] = w3;
-                }
                 const int cb = (buf + blk_row0 + 16 * blk) >> 2;       // first 16-byte chunk of the block
                 if (blocks_aligned) {
                     // (cb is a multiple of 4: the block's chunks are permuted among themselves)
@@ -282,8 +301,8 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
                 }
             }
             if (Zr.lane) {
-                const float4 O = sh.ob.pose[zone_seer0 + i];
-                const int en = (sh.ob.seer[zone_seer0 + i] & 8) ? -1 : 0;
+                const float4 O = WAVES == 2 ? A : sh.ob.pose[zone_seer0 + i];
+                const int en = ((WAVES == 2 ? fi : sh.ob.seer[zone_seer0 + i]) & 8) ? -1 : 0;
                 const int xb = __float_as_int(O.x), yb = __float_as_int(O.y);
                 float zo[4];
 #pragma unroll
@@ -292,17 +311,14 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
                     zo[k] = __int_as_float(__float_as_int(Zr.val[k] - shift) & en);
                 }
                 area[staged_chunk((buf + zone_dst0) >> 2)] = v4{zo[0], zo[1], zo[2], zo[3]};
-                if (want_gs && i == 0) {
-                    // ... and the zone slots with absolute centres are its tail
-                    float *gz = late_args()->st.global_state + (size_t)(P.grp * G + zg) * D + 16 * N + 4 * zc;
-                    if (!HALF_CHUNK || zlen - 4 * zc >= 4) {
-                        *reinterpret_cast<f4u *>(gz) = f4u{Zr.val[0], Zr.val[1], Zr.val[2], Zr.val[3]};
-                    } else {
-                        gz[0] = Zr.val[0];
-                        gz[1] = Zr.val[1];
-                    }
-                }
             }
+        }
+        if (WAVES == 2) {
+            // the next observer, on its way while the row goes out
+            const int next = i0 + 1 < N ? i0 + 1 : i0;
+            A = sh.ob.pose[next];
+            B = sh.ob.reach[next];
+            fi = sh.ob.seer[next];
         }
         lds_barrier<WAVES>();
 
@@ -311,17 +327,19 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
         // the lane reads physical chunk first_chunk + 64 p in pass p: whole runs, in lane order; all
         // passes are fetched from LDS first, then the stores are issued
         const v4 *src = area + first_chunk;
-        v4 v[kMaxPasses];
+        // (counted anew: as ten answers kept from row to row they take twenty scalar registers)
+        asm volatile("" : "+s"(copy_passes));
+        v4 v[PASSES];
 #pragma unroll
-        for (int p = 0; p < kMaxPasses; ++p)
-            if (p < a.copy_passes) v[p] = src[p * 64];
+        for (int p = 0; p < PASSES; ++p)
+            if (p < copy_passes) v[p] = src[p * 64];
 #pragma unroll
-        for (int p = 0; p < kMaxPasses; ++p) {
+        for (int p = 0; p < PASSES; ++p) {
             int store = valid[p] ? 1 : 0;
             // (made opaque, the masks stay in vector registers and the stores of a row are tested one by
             // one: 33v33 x 1500 98 -> 93 us; with fewer envs per CU it costs, x 1000 77 -> 83)
             if (EVEN) asm volatile("" : "+v"(store));
-            if (p < a.copy_passes && store) {
+            if (p < copy_passes && store) {
                 // (single-wavefront rows go out non-temporal: they are never read back by the kernel, and
                 // the hint measurably raises the store rate there; it lowers it for 8 KB rows)
                 f4u o = v[p];

@@ -48,78 +48,60 @@ struct StepIn {
 
 // Issued with the state at the top of the kernel: whatever the wavefront waits for first (zones on
 // their way to LDS, a policy's memory), these are not a second round trip after it.
-__device__ __forceinline__ StepIn load_step(const KArgs &a, const Place &P)
+__device__ __forceinline__ void load_step(const KArgs &a, const Place &P, StepIn &in)
 {
-    StepIn in = {0, -1, 0.0f, 0, 0.0f, 0.0f, 0.0f};
-    const LateArgs late = late_args();
-    int8_t *const kill_run = late->st.kill_run;
-    float *const ret_run = late->st.ret_run;
-    const bool dynamic = late->p.dynamics == 1;
-    if (P.has) {
-        in.act = at32(a.actions, P.k);
-        in.t = at32(a.st.t, (size_t)P.e);
-        in.phi_prev = at32(a.st.phi_prev, (size_t)P.e);
-        if (kill_run) in.kills_run = at32(kill_run, (size_t)P.e);
-        if (ret_run) in.ret_run = at32(ret_run, (size_t)P.e);
-        if (dynamic) {
-            in.acx = at32(late->st.ax, P.k);
-            in.acy = at32(late->st.ay, P.k);
-        }
-    }
-    return in;
+    const uint32_t e = (uint32_t)P.e;
+    in.act = at32(a.actions, P.k);
+    in.t = at32(a.st.t, e);
+    in.phi_prev = at32(a.st.phi_prev, e);
 }
 
-// `forced` >= 0 replaces the unit's entry of the action array (the policy stage chose it).
-// `Z`: the zone descriptors of the group's envs in LDS, rewritten for envs that change level; `zd`
-// those of the lane's env.  Returns whether any env of the workgroup restarted.
-template <int WAVES, class Sh>
-__device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
-                                         const ZoneLds &Z, const float *zd,
-                                         Place &P, Unit &U, int &code_u, Carry &C,
-                                         const StepIn &in, int forced)
+// ... where the launch asks for them.
+__device__ __forceinline__ void load_more_step(const KArgs &a, const Place &P, StepIn &in)
 {
-    float zeff = 0.0f;             // effect magnitude of the zone under the unit (elliptical zones)
-    const int N = a.p.num_units;
-    const float dt = a.p.dt;
-    const bool has = P.has;
-    const int alive0 = has ? U.alive : 0;
-    const int act = forced >= 0 ? forced : in.act;
-    const int t_new = in.t + 1;
-    const float phi_prev = in.phi_prev;
-    const LateArgs late = late_args();
-    const bool want_kills = late->st.kill_run != nullptr;
-    const int kills_run = in.kills_run;
-    const float ret_run = in.ret_run;
-    float bdmg = 0.0f;
-    const bool dynamic = late->p.dynamics == 1;
-    float acx = in.acx, acy = in.acy;
-
-    // stage 1: cooldown / reveal timers, explicit Euler move, arena penalty + clip
-    if (has && U.enabled) {
-        float v = U.cd - dt;
-        U.cd = v > 0.0f ? v : 0.0f;
-        v = U.reveal - dt;
-        U.reveal = v > 0.0f ? v : 0.0f;
-        if (alive0) {
-            if (dynamic) {             // the velocity from the acceleration first, then the position
-                U.vx = U.vx + acx * dt;
-                U.vy = U.vy + acy * dt;
-            }
-            const float nx = U.x + U.vx * dt;
-            const float ny = U.y + U.vy * dt;
-            const bool oob = (nx < 0.0f) || (nx > a.p.map_w) || (ny < 0.0f) || (ny > a.p.map_h);
-            if (oob) bdmg = (a.p.boundary_frac * U.hmax) * dt;
-            U.x = clamp_between(nx, 0.0f, a.p.map_w);
-            U.y = clamp_between(ny, 0.0f, a.p.map_h);
+    if (flagged(a, DYNAMIC | KILLS | RETURNS)) {
+        const LateArgs late = late_args();
+        const uint32_t e = here((uint32_t)P.e), k = here(P.k);
+        if (flagged(a, DYNAMIC)) {
+            in.acx = at32(late->st.ax, k);
+            in.acy = at32(late->st.ay, k);
         }
+        if (flagged(a, KILLS)) in.kills_run = at32(late->st.kill_run, e);
+        if (flagged(a, RETURNS)) in.ret_run = at32(late->st.ret_run, e);
     }
+}
 
-    // stage 1b: overlapping bodies are pushed apart.  Every unit sums, over its partners in
-    // ascending index, the share of each overlap it has to give way for; all pairs are taken
-    // on the positions after the kinematic update; then the unit is clipped again.
-    if (a.p.collision_alpha > 0.0f) {
+// Stage 1: explicit Euler move, arena penalty + clip.  Returns whether the move took the unit out of the
+// arena.  (Of the unit's loads it needs the first six only.)
+__device__ __forceinline__ bool move_unit(const KArgs &a, Unit &U, const StepIn &in)
+{
+    const float dt = a.p.dt;
+    const bool moves = U.enabled && U.alive;
+    if (flagged(a, DYNAMIC)) {         // the velocity from the acceleration first, then the position
+        U.vx = moves ? U.vx + in.acx * dt : U.vx;
+        U.vy = moves ? U.vy + in.acy * dt : U.vy;
+    }
+    const float nx = U.x + U.vx * dt;
+    const float ny = U.y + U.vy * dt;
+    const bool oob = (nx < 0.0f) | (nx > a.p.map_w) | (ny < 0.0f) | (ny > a.p.map_h);
+    U.x = moves ? clamp_between(nx, 0.0f, a.p.map_w) : U.x;
+    U.y = moves ? clamp_between(ny, 0.0f, a.p.map_h) : U.y;
+    return moves & oob;
+}
+
+// Stage 1b: overlapping bodies are pushed apart.  Every unit sums, over its partners in
+// ascending index, the share of each overlap it has to give way for; all pairs are taken
+// on the positions after the kinematic update; then the unit is clipped again.
+template <int WAVES, class Sh>
+__device__ __forceinline__ void collide_env(const KArgs &a, Sh &sh, const Place &P, Unit &U)
+{
+    const int N = a.p.num_units;
+    const LateArgs late = late_args();
+    const bool dynamic = late->p.dynamics == 1;
+    const bool on = U.enabled != 0;
+    {
         // partner record: x, y, radius, mass (negative mass: not a body)
-        sh.st.pj[P.l] = make_float4(U.x, U.y, U.radius, (has && U.enabled) ? U.mass : -1.0f);
+        sh.st.pj[P.l] = make_float4(U.x, U.y, U.radius, on ? U.mass : -1.0f);
         // (with persistent velocities the partners' velocities travel in the next array, which
         // the combat stage rewrites only after the barrier that ends this stage)
         if (dynamic) sh.st.aim1[P.l] = make_float4(U.vx, U.vy, 0.0f, 0.0f);
@@ -158,7 +140,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
             close[w] = ((uint64_t)half[1] << 32) | half[0];
             // (not with itself, and only bodies)
             if (P.u >= 64 * w && P.u < 64 * w + 64) close[w] &= ~(1ull << (P.u & 63));
-            if (!has || !U.enabled) close[w] = 0ull;
+            if (!on) close[w] = 0ull;
         }
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) {
@@ -199,20 +181,42 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
                 ay = ay - (ce * ny);
             }
         }
-        if (has && U.enabled) {
-            U.x = clamp_between(U.x + ax, 0.0f, a.p.map_w);
-            U.y = clamp_between(U.y + ay, 0.0f, a.p.map_h);
-            if (dynamic) {
-                U.vx = U.vx + dvx;
-                U.vy = U.vy + dvy;
-            }
+        U.x = on ? clamp_between(U.x + ax, 0.0f, a.p.map_w) : U.x;
+        U.y = on ? clamp_between(U.y + ay, 0.0f, a.p.map_h) : U.y;
+        if (dynamic) {
+            U.vx = on ? U.vx + dvx : U.vx;
+            U.vy = on ? U.vy + dvy : U.vy;
         }
         group_barrier<WAVES>(sh);          // the partner records are rewritten for the combat stage
     }
+}
 
-    // the position is final for this tick: fetch the terrain cell under it now, the zone
-    // effects of stage 3 use it after the combat exchange
-    if (has && U.enabled) code_u = zone_at(a, zd, P.row, U.x, U.y, zeff);
+// The rest of the tick, from the actions on.
+// `forced` >= 0 replaces the unit's entry of the action array (the policy stage chose it).
+// `Z`: the zone descriptors of the group's envs in LDS, rewritten for envs that change level; `zd`
+// those of the lane's env; `oob`: the move took the unit out of the arena; `code_u`, `zeff`: the zone under it
+// and, for elliptical ones, its effect magnitude.  Returns whether any env of the workgroup restarted.
+//
+// A small batch is one chain of instructions, a lone wavefront issues one in about four cycles, and on a full
+// machine the wavefronts of a SIMD issue this stage in turn: so it is selects instead of branches, and what a
+// striker needs is looked up by its rank.
+template <int WAVES, class Sh>
+__device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
+                                         const ZoneLds &Z, const float *zd,
+                                         Place &P, Unit &U, int &code_u, float &zeff, bool oob,
+                                         Carry &C, const StepIn &in, int forced)
+{
+    const int N = a.p.num_units;
+    const float dt = a.p.dt;
+    const bool has = P.has;
+    const int alive0 = U.alive;
+    const bool on = U.enabled != 0;
+    const int act = alive0 ? (forced >= 0 ? forced : in.act) : TABX_ACT_NOOP;
+    const int t_new = in.t + 1;
+    const float phi_prev = in.phi_prev;
+    const LateArgs late = late_args();
+    float acx = 0.0f, acy = 0.0f;
+
     // The action array is the one input that is new in every tick, so its lines come from HBM,
     // where a read queues behind the observation stores for microseconds once those are
     // flowing, and every wavefront's step stage waits for its action bytes.  The first
@@ -221,80 +225,78 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
     // generations find them in the cache.  Measured with a fresh action batch per tick:
     // c3 108.6 -> 102.5 us, c4 95.4 -> 89.7 us (101 / 88 us with actions that are cached anyway).
     {
-        const size_t span = (size_t)a.groups_per_xcd * a.envs_per_block * N;   // units per XCD
-        const size_t first = (size_t)(blockIdx.x & 7) * span;
-        const size_t off = ((size_t)(blockIdx.x >> 3) * 64 + (size_t)(threadIdx.x & 63)) * 128;
-        if (off < span && first + off < (size_t)a.p.num_envs * N) C.warm = at32(a.actions, first + off);
+        const uint32_t span = (uint32_t)(a.groups_per_xcd * a.envs_per_block) * (uint32_t)N;   // units per XCD
+        if ((blockIdx.x >> 3) <= span / 8192u) {
+            const uint32_t off = ((blockIdx.x >> 3) * 64u + (threadIdx.x & 63u)) * 128u;
+            const uint64_t at = (uint64_t)(blockIdx.x & 7u) * span + off;
+            if (off < span && at < (uint32_t)a.p.num_envs * (uint32_t)N) C.warm = at32(a.actions, (uint32_t)at);
+        }
+    }
+
+    // stage 1, the timers
+    {
+        const float c = U.cd - dt, r = U.reveal - dt;
+        U.cd = on ? (c > 0.0f ? c : 0.0f) : U.cd;
+        U.reveal = on ? (r > 0.0f ? r : 0.0f) : U.reveal;
     }
 
     // stage 2a: movement sets next tick's velocity, rotation turns the heading now
-    float cu = 1.0f, su = 0.0f;
-    if (has) {
+    float cu, su;
+    {
         // the velocity the unit wants: its current speed along a move action, else none
-        float wx = 0.0f, wy = 0.0f;
-        if (alive0) {
-            const float sp = U.cur_speed;
-            if (act == TABX_ACT_MOVE_XP) wx = sp;
-            else if (act == TABX_ACT_MOVE_YP) wy = sp;
-            else if (act == TABX_ACT_MOVE_XM) wx = -sp;
-            else if (act == TABX_ACT_MOVE_YM) wy = -sp;
-        }
-        if (dynamic) {
+        const float sp = U.cur_speed;
+        const float wx = act == TABX_ACT_MOVE_XP ? sp : (act == TABX_ACT_MOVE_XM ? -sp : 0.0f);
+        const float wy = act == TABX_ACT_MOVE_YP ? sp : (act == TABX_ACT_MOVE_YM ? -sp : 0.0f);
+        if (flagged(a, DYNAMIC)) {
             // the acceleration for the next tick's physics stage; what is not alive holds neither
             acx = alive0 ? (wx - U.vx) * late->p.move_gain : 0.0f;
             acy = alive0 ? (wy - U.vy) * late->p.move_gain : 0.0f;
-            U.vx = alive0 ? U.vx : 0.0f;
-            U.vy = alive0 ? U.vy : 0.0f;
+            if (!alive0) U.vx = U.vy = 0.0f;
         } else {
             U.vx = wx;
             U.vy = wy;
         }
-        if (alive0) {
-            if (act == TABX_ACT_ROT_LEFT) {
-                float th = U.theta + (a.p.turn_rate * dt);
-                if (th >= kTwoPi) th = th - kTwoPi;
-                U.theta = th;
-            } else if (act == TABX_ACT_ROT_RIGHT) {
-                float th = U.theta - (a.p.turn_rate * dt);
-                if (th < 0.0f) th = th + kTwoPi;
-                U.theta = th;
-            }
-        }
+        float left = U.theta + (a.p.turn_rate * dt);
+        if (left >= kTwoPi) left = left - kTwoPi;
+        float right = U.theta - (a.p.turn_rate * dt);
+        if (right < 0.0f) right = right + kTwoPi;
+        if (act == TABX_ACT_ROT_LEFT) U.theta = left;
+        if (act == TABX_ACT_ROT_RIGHT) U.theta = right;
         heading_sincos(U.theta, su, cu);
     }
     // stage 2b: combat, seen from the victims.  Few units strike in a tick (the cooldowns see to
     // that), so instead of every unit scanning its env for targets, every unit tests itself
-    // against the strikers of its env only.  A striker publishes its pose and hurtbox; each unit
+    // against the strikers of its env only.  The n-th striker of an env (of those a wavefront holds) publishes
+    // its pose and hurtbox in the n-th place of the env; each unit
     // in that hurtbox (body circle against the forward rectangle, role filter, optionally the
     // sight cone's angle) bids for "closest" with an LDS atomic minimum over the 64-bit key
     // (squared distance bits, unit index): the smallest key is the closest valid body, the
     // lowest index among equally distant ones.
-    const bool cone_bound = a.p.hurtbox_cone != 0;
-    const bool hit_all = a.p.hit_all != 0;
-    const bool eligible = has && alive0 && act == TABX_ACT_ATTACK && U.cd <= 0.0f;
-    if (eligible) U.cd = U.cooldown;
+    const bool eligible = act == TABX_ACT_ATTACK && U.cd <= 0.0f;
+    int my_rank = -1;              // the unit's place if it strikes
+    int strikers[WAVES];           // how many the env has, per wavefront that holds its units
     {
-        const int want = (U.dmg < 0.0f) ? U.team : 1 - U.team;   // healers reach allies only
-        // the attack range is never negative: its sign bit carries the team the strike is for
-        const float range_want = __int_as_float(__float_as_int(U.range) | (want << 31));
-        sh.st.aim0[P.l] = make_float4(U.x, U.y, cu, su);
-        sh.st.aim1[P.l] = make_float4(range_want, U.hurt_hw, U.dmg, U.cos_half);
-        sh.st.best[P.l] = ~0ull;
-    }
-    // the strikers of this lane's env, as bit masks over its unit indices
-    uint64_t strikers[WAVES];
-    {
-        const uint64_t b = __ballot(eligible);
-        if (WAVES == 1) {
-            strikers[0] = (b >> P.base) & (N >= 64 ? ~0ull : ((1ull << N) - 1ull));
-        } else if ((P.l & 63) == 0) {
-            sh.ballots[P.l >> 6][0] = b;
+        const uint64_t b = lanes_where(eligible);
+        const uint64_t mine = WAVES == 1 ? b & lanes_of_env(P, N) : b;
+        const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)mine, 0u));
+        strikers[0] = __popcll(mine);
+        if (WAVES == 2 && (P.l & 63) == 0) sh.ballots[P.l >> 6][0] = b;
+        if (eligible) {
+            U.cd = U.cooldown;
+            my_rank = (WAVES == 1 ? P.base : P.l & 64) + rank;
+            const int want = (U.dmg < 0.0f) ? U.team : 1 - U.team;   // healers reach allies only
+            // the attack range is never negative: its sign bit carries the team the strike is for
+            const float range_want = __int_as_float(__float_as_int(U.range) | (want << 31));
+            sh.st.aim0[my_rank] = make_float4(U.x, U.y, cu, su);
+            sh.st.aim1[my_rank] = make_float4(range_want, U.hurt_hw, U.dmg, U.cos_half);
+            sh.st.best[my_rank] = ~0ull;
         }
     }
     group_barrier<WAVES>(sh);
     if (WAVES == 2) {
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) strikers[w] = sh.ballots[w][0];
+        for (int w = 0; w < WAVES; ++w) strikers[w] = __popcll(sh.ballots[w][0]);
     }
 
     float acc = 0.0f;              // what lands on this unit, strikers in ascending index
@@ -303,12 +305,10 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
         const float r2 = U.radius * U.radius;
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) {
-            uint64_t m = strikers[w];
-            while (m != 0ull) {
-                const int s_u = 64 * w + __builtin_ctzll(m);
-                m &= m - 1ull;
-                const float4 A0 = sh.st.aim0[P.base + s_u];
-                const float4 A1 = sh.st.aim1[P.base + s_u];
+            const int first = WAVES == 1 ? P.base : 64 * w;
+            for (int n = 0; lanes_where(n < strikers[w]) != 0ull; ++n) {
+                const float4 A0 = sh.st.aim0[first + n];
+                const float4 A1 = sh.st.aim1[first + n];
                 const int rb = __float_as_int(A1.x);
                 const float range = __int_as_float(rb & 0x7fffffff);
                 const int want = (rb >> 31) & 1;
@@ -317,16 +317,16 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
                 float along;
                 const float g2 = hurtbox_gap2(dx, dy, A0.z, A0.w, range, A1.y, -A1.y, along);
                 const float d2 = (dx * dx) + (dy * dy);
-                bool ok = alive0 && (U.team == want) && (s_u != P.u) && (g2 <= r2);
-                if (cone_bound) ok = ok && ((d2 == 0.0f) || (along >= A1.w * __builtin_sqrtf(d2)));
+                bool ok = alive0 && n < strikers[w] && U.team == want && first + n != my_rank && g2 <= r2;
+                if (flagged(a, CONE_BOUND)) ok = ok && ((d2 == 0.0f) || (along >= A1.w * __builtin_sqrtf(d2)));
                 if (ok) {
                     const unsigned long long key =
                         ((unsigned long long)(unsigned)__float_as_int(d2) << 32) | (unsigned)P.u;
-                    atomicMin(&sh.st.best[P.base + s_u], key);
-                    if (hit_all) {             // a strike lands on everybody in the hurtbox
-                        acc = acc + A1.z;
-                        struck = struck || (A1.z > 0.0f);
-                    }
+                    atomicMin(&sh.st.best[first + n], key);
+                }
+                if (flagged(a, HIT_ALL)) {                 // a strike lands on everybody in the hurtbox
+                    acc = ok ? acc + A1.z : acc;
+                    struck = struck || (ok && A1.z > 0.0f);
                 }
             }
         }
@@ -335,59 +335,52 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
 
     // stage 2c: a strike has landed if anybody bid; unless everybody in the hurtbox is struck,
     // the victims now look up which striker designated them
-    const bool landed = eligible && sh.st.best[P.l] != ~0ull;
-    if (!hit_all) {
+    bool landed = false;
+    if (eligible) landed = sh.st.best[my_rank] != ~0ull;
+    if (!flagged(a, HIT_ALL)) {
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) {
-            uint64_t m = strikers[w];
-            while (m != 0ull) {
-                const int s_u = 64 * w + __builtin_ctzll(m);
-                m &= m - 1ull;
-                const bool mine = (unsigned)sh.st.best[P.base + s_u] == (unsigned)P.u;
-                const float d = sh.st.aim1[P.base + s_u].z;
+            const int first = WAVES == 1 ? P.base : 64 * w;
+            for (int n = 0; lanes_where(n < strikers[w]) != 0ull; ++n) {
+                const bool mine = n < strikers[w] && (unsigned)sh.st.best[first + n] == (unsigned)P.u;
+                const float d = sh.st.aim1[first + n].z;
                 acc = acc + (mine ? d : 0.0f);
                 struck = struck || (mine && d > 0.0f);
             }
         }
     }
     struck = struck || (landed && U.dmg > 0.0f);
-    if (has && alive0) {
+    {
         // subtract once, together with the arena penalty; clamp
+        const float bdmg = oob ? (a.p.boundary_frac * U.hmax) * dt : 0.0f;
         const float h = (U.hp - acc) - bdmg;
-        U.hp = clamp_between(h, 0.0f, U.hmax);
-        if (struck) U.reveal = a.p.reveal_time;
+        U.hp = alive0 ? clamp_between(h, 0.0f, U.hmax) : U.hp;
+        if (alive0 && struck) U.reveal = a.p.reveal_time;
     }
     // (the ratio terms written next share LDS with the strikers' poses, which nobody reads any
     // more: the bids above were the last use, and a barrier has passed since)
 
     // stage 3: zone effects at the new position, alive flag
-    float ratio = 0.0f;
-    if (has) {
-        if (U.enabled) {
-            const int zone = code_u & 3;
-            if (alive0 && zone == TABX_ZONE_LAVA) {
-                const float h = U.hp - (zone_magnitude(a, zeff, a.p.lava_dps) * dt);
-                U.hp = h > 0.0f ? h : 0.0f;
-            }
-            U.cur_speed = zone == TABX_ZONE_SWAMP
-                              ? U.speed * zone_magnitude(a, zeff, a.p.swamp_mult) : U.speed;
-            U.alive = U.hp > 0.0f ? 1 : 0;
-            ratio = U.hp / U.hmax;
-        } else {
-            U.alive = 0;
-        }
+    float ratio;
+    {
+        const int zone = code_u & 3;
+        const float h = U.hp - (zone_magnitude(a, zeff, a.p.lava_dps) * dt);
+        U.hp = on && alive0 && zone == TABX_ZONE_LAVA ? (h > 0.0f ? h : 0.0f) : U.hp;
+        const float slowed = U.speed * zone_magnitude(a, zeff, a.p.swamp_mult);
+        if (on) U.cur_speed = zone == TABX_ZONE_SWAMP ? +slowed : +U.speed;
+        U.alive = on && U.hp > 0.0f ? 1 : 0;
+        ratio = U.hp / U.hmax;
+        ratio = on ? ratio : 0.0f;
     }
-    const bool en = has && U.enabled;
-    sh.st.share[P.l] = make_float2((en && U.team == 0) ? ratio : 0.0f,
-                                (en && U.team != 0) ? ratio : 0.0f);
-    const bool pred[4] = {en && U.team == 0, en && U.team != 0,
-                          has && U.alive && U.team == 0, has && U.alive && U.team != 0};
+    const bool first_team = on && U.team == 0, second_team = on && U.team != 0;
+    sh.st.share[P.l] = make_float2(first_team ? ratio : 0.0f, second_team ? ratio : 0.0f);
+    const bool pred[4] = {first_team, second_team, U.alive && U.team == 0, U.alive && U.team != 0};
     int cnt[4];
     env_counts<WAVES>(sh, P, N, pred, cnt);
     // episode metrics need the alive counts at entry as well (first loss of a unit)
-    int before[4] = {0, 0, 0, 0};
-    if (want_kills) {
-        const bool pred0[4] = {alive0 && U.team == 0, alive0 && U.team != 0, false, false};
+    int before[2] = {0, 0};
+    if (flagged(a, KILLS)) {
+        const bool pred0[2] = {alive0 && U.team == 0, alive0 && U.team != 0};
         env_counts<WAVES>(sh, P, N, pred0, before);
     }
     group_barrier<WAVES>(sh);
@@ -397,40 +390,37 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
     team_means(sh, P, N, cnt[0], cnt[1], m0, m1);
     const float phi = m0 - m1;
     const float dense = phi - phi_prev;
-    float r0 = dense, r1 = -dense;
     const bool done = has && (cnt[2] == 0 || cnt[3] == 0 || t_new >= a.p.max_steps);
     // does any env of this workgroup restart?  (one env per workgroup when WAVES == 2:
     // the flag is already uniform there, up to the idle lanes)
     bool any_done;
     if (WAVES == 1) {
-        any_done = __ballot(done) != 0ull;
+        any_done = lanes_where(done) != 0ull;
     } else {
-        const uint64_t b = __ballot(done);
+        const uint64_t b = lanes_where(done);
         if ((P.l & 63) == 0) sh.ballots[P.l >> 6][0] = b;
         group_barrier<WAVES>(sh);
         any_done = (sh.ballots[0][0] | sh.ballots[WAVES - 1][0]) != 0ull;
     }
-    if (done) {
-        const bool ally_win = m0 > m1;
-        r0 = r0 + (ally_win ? 1.0f : -1.0f);
-        r1 = r1 + (ally_win ? -1.0f : 1.0f);
-    }
-    if (has) a.rewards[P.k] = U.enabled ? (U.team ? r1 : r0) : 0.0f;
+    const float bonus = m0 > m1 ? 1.0f : -1.0f;
+    const float r0 = done ? dense + bonus : +dense;
+    const float r1 = done ? -dense - bonus : -dense;
+    if (has) at32(a.rewards, here(P.k)) = on ? (U.team ? +r1 : +r0) : 0.0f;
 
     // auto-reset of finished envs; the potential of the fresh state seeds phi_prev
     float phi_next = phi;
     group_barrier<WAVES>(sh);          // everyone has read the ratio terms of the finished tick
     if (any_done) {
-        bool en_next = en;
-        if (a.p.num_levels > 0) {
+        bool on_next = on;
+        if (flagged(a, LEVELS)) {
             // the finished envs move to their queued level: new specifications, new zones
             const int row = advance_level<WAVES>(a, sh, P, done);
             if (row >= 0) {
                 P.row = row;
-                P.ks = (size_t)row * N + P.u;
+                P.ks = (uint32_t)row * (uint32_t)N + (uint32_t)P.u;
                 load_spec(a, P.ks, U);
-                fold_bytes(U);
-                en_next = U.enabled != 0;
+                fold_byte(U.team);
+                on_next = U.enabled != 0;
             }
             if (a.zones_in_lds) {
                 // (level_rows holds an entry for every env of the group, and only for those)
@@ -448,7 +438,7 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
         if (done) {
             // a new episode remembers nothing
             uint8_t *const mem_valid = late->pa.mem.mem_valid;
-            if (mem_valid) mem_valid[P.k] = 0;
+            if (mem_valid) at32(mem_valid, P.k) = 0;
             code_u = spawn_unit(a, zd, P.row, P.ks, U, zeff);
             acx = 0.0f;
             acy = 0.0f;
@@ -456,49 +446,53 @@ __device__ __forceinline__ bool step_env(const KArgs &a, Sh &sh,
             heading_sincos(U.theta, su, cu);
         }
         int c0 = cnt[0], c1 = cnt[1];
-        if (a.p.num_levels > 0) {
+        if (flagged(a, LEVELS)) {
             // teams and placeholders may differ in the new level
-            const bool pred1[4] = {en_next && U.team == 0, en_next && U.team != 0, false, false};
-            int fresh[4];
+            const bool pred1[2] = {on_next && U.team == 0, on_next && U.team != 0};
+            int fresh[2];
             env_counts<WAVES>(sh, P, N, pred1, fresh);
             c0 = fresh[0];
             c1 = fresh[1];
         }
-        sh.st.share[P.l] = make_float2((en_next && U.team == 0) ? ratio : 0.0f,
-                                    (en_next && U.team != 0) ? ratio : 0.0f);
+        sh.st.share[P.l] = make_float2((on_next && U.team == 0) ? ratio : 0.0f,
+                                    (on_next && U.team != 0) ? ratio : 0.0f);
         group_barrier<WAVES>(sh);
         float f0, f1;
         team_means(sh, P, N, c0, c1, f0, f1);
         if (done) phi_next = f0 - f1;
     }
     if (has && P.u == 0) {
-        a.st.t[P.e] = done ? 0 : t_new;
-        a.st.phi_prev[P.e] = phi_next;
-        a.dones[P.e] = done ? 1 : 0;
+        const uint32_t e = here((uint32_t)P.e);
+        at32(a.st.t, e) = done ? 0 : t_new;
+        at32(a.st.phi_prev, e) = phi_next;
+        at32(a.dones, e) = done ? 1 : 0;
         // episode metrics: first loss of a unit, running allied return, summary at the end
         int kills = 0;
-        if (want_kills) {
-            kills = kills_run;
+        if (flagged(a, KILLS)) {
+            kills = in.kills_run;
             if (kills == 0) kills = (cnt[3] < before[1] ? 1 : 0) | (cnt[2] < before[0] ? 2 : 0);
-            late->st.kill_run[P.e] = (int8_t)(done ? 0 : kills);
+            at32(late->st.kill_run, e) = (int8_t)(done ? 0 : kills);
         }
         float ret = 0.0f;
-        if (late->st.ret_run) {
-            ret = ret_run + r0;
-            late->st.ret_run[P.e] = done ? 0.0f : ret;
+        if (flagged(a, RETURNS)) {
+            ret = in.ret_run + r0;
+            at32(late->st.ret_run, e) = done ? 0.0f : +ret;
         }
         if (done) {
             if (late->st.ep_count) late->st.ep_count[P.e] += 1;
             if (late->st.ep_len) late->st.ep_len[P.e] = t_new;
             if (late->st.ep_return && late->st.ret_run) late->st.ep_return[P.e] = ret;
             if (late->st.ep_win) late->st.ep_win[P.e] = (m0 > m1) ? 1 : 0;
-            if (late->st.ep_first_kill && want_kills) late->st.ep_first_kill[P.e] = (int8_t)kills;
+            if (late->st.ep_first_kill && late->st.kill_run) late->st.ep_first_kill[P.e] = (int8_t)kills;
         }
     }
-    if (has) store_state(a, P.k, U);
-    if (dynamic && has) {
-        late->st.ax[P.k] = acx;
-        late->st.ay[P.k] = acy;
+    if (has) {
+        store_state(a, P.k, U);
+        if (flagged(a, DYNAMIC)) {
+            const uint32_t k = here(P.k);
+            at32(late->st.ax, k) = acx;
+            at32(late->st.ay, k) = acy;
+        }
     }
     C.cu = cu;
     C.su = su;
