@@ -62,6 +62,8 @@ struct KArgs {
     int       copy_passes;         // ... store passes of one flush, <= kMaxPasses
     int       rows_per_flush;      // ... R: consecutive rows of an env staged before they are stored
     int       obs_per_chunk;       // ... observers per workgroup that shares an env group
+    unsigned  pace;                // least time from one flush of a wavefront to the next, in 1/16 of a tick of the
+                                   //     constant clock (10 ns); 0: none
     float     inv_cell;            // 1 / cell_size, used only when that is exact (power of two)
     uint32_t  cells;               // FAST_CELL: cells of one row's grid
     uint32_t  flags;               // Flag bits
@@ -79,6 +81,39 @@ enum Flag : uint32_t {
     FAST_CELL = 256,               // a cell grid; cell size a power of two, offsets by 24-bit products
     EARLY_CELL = 512,              // a cell grid, and nothing but its own motion decides where a unit is
 };
+
+// A paced wavefront (see plan_pace, tabx_kernels.hip): the low word of the constant clock (10 ns) when it starts,
+// and the wait until `due` ticks after that; nothing where `pace` / `due` is 0.  One block of scalar
+// instructions each: as a loop of the compiler's, the branches cost launches without a pace up to 5 %.
+__device__ __forceinline__ unsigned pace_start(unsigned pace)
+{
+    unsigned now;
+    asm volatile("s_mov_b32 %0, 0\n\t"
+                 "s_cmp_eq_u32 %1, 0\n\t"
+                 "s_cbranch_scc1 .Lstarted%=\n\t"
+                 "s_memrealtime vcc\n\t"
+                 "s_waitcnt lgkmcnt(0)\n\t"
+                 "s_mov_b32 %0, vcc_lo\n"
+                 ".Lstarted%=:"
+                 : "=&s"(now) : "s"(__builtin_amdgcn_readfirstlane((int)pace)) : "vcc", "scc");
+    return now;
+}
+
+__device__ __forceinline__ void pace_wait(unsigned since, unsigned due)
+{
+    asm volatile("s_cmp_eq_u32 %1, 0\n\t"
+                 "s_cbranch_scc1 .Lheld%=\n"
+                 ".Lhold%=:\n\t"
+                 "s_memrealtime vcc\n\t"
+                 "s_waitcnt lgkmcnt(0)\n\t"
+                 "s_sub_u32 vcc_lo, vcc_lo, %0\n\t"
+                 "s_cmp_ge_u32 vcc_lo, %1\n\t"
+                 "s_cbranch_scc1 .Lheld%=\n\t"
+                 "s_sleep 1\n\t"
+                 "s_branch .Lhold%=\n"
+                 ".Lheld%=:"
+                 : : "s"(__builtin_amdgcn_readfirstlane((int)since)), "s"(__builtin_amdgcn_readfirstlane((int)due)) : "vcc", "scc");
+}
 
 // Per-wavefront time stamps of an instrumented build (-DTABX_TRACE; compiled out of the product), eight
 // per wavefront, for up to eight wavefronts per workgroup: slot 0 kernel entry, 6 before the step stage,

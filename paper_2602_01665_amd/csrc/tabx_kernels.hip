@@ -459,6 +459,60 @@ static size_t plan_lds(Mode mode, KArgs &a, int waves)
     return floats * sizeof(float);
 }
 
+// How many wavefronts of the rows' kernels a SIMD holds (by their vector registers).
+static int wavefronts_per_simd(Mode mode, const KArgs &a, int waves)
+{
+    if (a.packed) return waves == 1 || a.even ? 3 : 4;
+    return mode == MODE_SCRIPTED_STEP_OBSERVE && waves == 1 ? 4 : 5;
+}
+
+// Holds the wavefronts of a launch to the pace at which HBM takes all their rows together (a.pace).
+// Where all workgroups are resident from the start and live as long as the launch, some of them write faster
+// than others: the even XCDs get more of HBM than the odd ones while both ask for all they can, and so do
+// wavefronts that share their SIMD with fewer others.  The launch then ends with the slow ones alone, which
+// cannot use what has become free (64v64 x 1024: workgroups of even XCDs end at 158 ... 173 us, of odd ones at
+// 184 ... 203).  A flush that is not due yet waits, and what it would have taken goes to those behind.
+// Measured, without / with: 64v64 x 1024 209 / 199 us, x 1300 278 / 250, 40v40 x 1500 136 / 124, 64v64 x 400
+// 100 / 89, 10v10 x 8192 with collisions and ellipses 62.5 / 58, 10v10 x 4000 with zones 35.2 / 30.0, 32v32 x 700
+// 44.1 / 36.5.  With several generations, workgroups of all ages side by side even each other out, and a pace
+// only costs (10v10 x 16384 102 / 108 ... 124 us).
+static void plan_pace(Mode mode, KArgs &a, int waves, size_t lds)
+{
+    a.pace = 0;
+    const bool rows = mode == MODE_OBSERVE || mode == MODE_STEP_OBSERVE ||
+                      mode == MODE_POLICY_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE;
+    if (!rows || a.obs_chunks > 1) return;
+    // Few rows: such a launch is mostly its start (5v5 x 6000, 38 MB: 13.4 us, 14.0 paced; x 8000 17.8 and 17.1).
+    const double bytes = 4.0 * a.obs_dim * a.p.num_units * a.p.num_envs;
+    if (bytes < 50e6) return;
+    const int w = waves * (a.twin ? a.twin : 1);
+    const bool policy = mode == MODE_POLICY_STEP_OBSERVE;
+    const size_t fixed = !a.packed    ? (waves == 1 ? sizeof(Shared<1, true, true>) : sizeof(Shared<2, true, true, true>))
+                         : waves == 1 ? (policy ? sizeof(Shared<1, false, true>) : sizeof(Shared<1, false, false>))
+                                      : (policy ? sizeof(Shared<2, false, true>) : sizeof(Shared<2, false, false>));
+    const int by_simd = 4 * wavefronts_per_simd(mode, a, waves) / w, by_lds = kLdsPerCuBytes / (int)lds_granules(fixed + lds);
+    if (a.num_groups > kComputeUnits * (by_simd < by_lds ? by_simd : by_lds)) return;
+    // Few flushes per wavefront: no time to fall behind in (tiles, 4v4 x 14000, four each: 18.4 us, 19.0 paced; units
+    // in registers, 5v5 x 16384, five each: 30.7 and 30.6 ... 33).
+    const int flushes = a.packed ? (a.p.num_units + a.rows_per_flush - 1) / a.rows_per_flush : (a.tiles + w - 1) / w;
+    if (flushes < (a.packed ? 8 : 5)) return;
+    // The rate, in TB/s of rows, at which a launch is shortest; up to 4 % to either side cost little, 10 % too slow
+    // costs that much and 10 % too fast leaves little of the gain.  Tiles: 6.0 (64v64 x 400, 27v28 x 1200); rows of
+    // whole 128-byte lines that the last-level cache takes all of 7.0 (6.5 ... 7.8: 32v32 x 700, 8v8 x 5000, 16v16 x
+    // 1300); rows that leave lines partly written, beyond that cache, 5.6 (32v32 with 8 zones x 1000); rows that end
+    // on half a chunk 5.2 (12v12 with 3 zones x 3000).  Units in registers: 5.85, rows of whole lines of two
+    // wavefronts 6.1.
+    const bool lines = a.obs_dim % 32 == 0, cached = bytes <= (double)kLastLevelCacheBytes;
+    double rate = lines ? (cached ? 7.0 : 6.0) : (cached ? 6.0 : 5.6);
+    if (a.obs_dim % 4 != 0) rate = 5.2;
+    if (a.packed) rate = waves == 2 && lines ? 6.1 : 5.85;
+    const double ticks = bytes / (rate * 1e12) * 100e6 / flushes;
+    // Two wavefronts with the units in registers take 0.9 us per row by themselves, and looking at the clock
+    // costs them 2 % (64v64 x 600 135.5 us and 138; x 700 145 and 140).
+    if (a.packed && waves == 2 && ticks < 90.0) return;
+    a.pace = (unsigned)(16.0 * ticks);
+}
+
 // Enqueues one kernel and returns the status of THIS launch (the runtime's sticky "last error"
 // is neither read nor cleared: an error the caller's own earlier work left pending stays theirs).
 template <class Kernel, class Arg0>
@@ -475,6 +529,7 @@ static hipError_t launch_mode(Mode mode, KArgs a, hipStream_t stream)
     const dim3 grid((unsigned)(8 * a.groups_per_xcd * a.obs_chunks));
     const dim3 block(64 * WAVES * (a.twin ? a.twin : 1));
     const size_t lds = plan_lds(mode, a, WAVES);
+    plan_pace(mode, a, WAVES, lds);
     switch (mode) {
     case MODE_RESET:
         return enqueue(tabx_reset_kernel<WAVES>, grid, block, lds, stream, a);

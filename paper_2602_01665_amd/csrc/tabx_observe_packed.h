@@ -211,6 +211,9 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
     const int i_begin = P.chunk * a.obs_per_chunk;
     const int i_end = (i_begin + a.obs_per_chunk < N) ? i_begin + a.obs_per_chunk : N;
     TABX_STAMP(2);
+    const unsigned pace = a.pace;
+    const unsigned first_row = pace_start(pace);
+    unsigned due = 0;
     float4 A = sh.ob.pose[0], B = sh.ob.reach[0];        // the observer
     int fi = sh.ob.seer[0];
     for (int i0 = i_begin; i0 < i_end; i0 += R) {
@@ -357,6 +360,8 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
         // lets its row stores land before it goes on.  Without this the XCDs drain at different
         // rates and the launch lasts as long as the slowest (64v64 x 1024: 217 us against 208).
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // ... and goes no faster than HBM takes all workgroups' rows together (plan_pace, tabx_kernels.hip)
+        pace_wait(first_row, (due += pace) >> 4);
     }
 
     TABX_STAMP(4);
