@@ -230,9 +230,8 @@ struct Scan {
     float4 pose[L];               // x, y, cos(theta), sin(theta)
     float4 body[L];               // radius, max health, health, -
     int    seer[L];               // alive | team<<1 | concealable<<2 | bush key<<8
-    float4 reach[L];              // attack range, hurtbox half-width, sight range^2, cos(cone / 2)
-    int    role[L];               // team | heals<<1 | assassin<<2 | bush key<<8
-    int    who[L];                // the n-th deciding unit: lane | lane of its env's unit 0 <<8 | unit<<16
+    float2 bound[L];              // beyond these squared distances, and behind this cone, nobody is seen (policy_env)
+    int    who[L];                // the n-th deciding unit: its lane
 };
 
 struct NoRecords {};

@@ -151,6 +151,29 @@ __device__ __forceinline__ void load_policy(const KArgs &a, const Place &P, Poli
     in.my = at32(a.pa.mem.mem_y, P.k);
 }
 
+// Marks the partners first ... first + count - 1 (at most 32) of an env, records from `base` on, that the unit
+// at (x, y), heading (cu, su), may see: bit b for partner first + b.  A mark costs eleven instructions, a root
+// and two products less than the test itself, and few partners are in sight (64 x 64 arena, one in fifteen).
+// `bound` is taken wide enough (see policy_env) that a pair left out fails the test.
+template <class Sh>
+__device__ __forceinline__ uint32_t mark_near(const Sh &sh, int base, int first, int count, float x, float y,
+                                              float cu, float su, float2 bound)
+{
+    const float4 *pose = sh.po.pose + base + first;
+    uint32_t bits = 0;
+#pragma unroll 4
+    for (int b = 0; b < count; ++b) {
+        const float dx = pose[b].x - x;
+        const float dy = pose[b].y - y;
+        const float d2 = __builtin_fmaf(dy, dy, dx * dx);
+        const float dot = __builtin_fmaf(dy, su, dx * cu);
+        const bool far = d2 > bound.x;
+        const bool behind = dot * __builtin_fabsf(dot) < __builtin_fmaf(bound.y, d2, -1e-30f);
+        bits = bits + bits + ((far | behind) ? 0u : 1u);
+    }
+    return count > 0 ? __builtin_bitreverse32(bits) >> (32 - count) : 0u;
+}
+
 // Decides for the lane's unit from the state in U (heading cosine / sine cu, su, zone code
 // code_u under it); returns the action, or -1 if the unit is not the policy's to move.  Writes
 // the action and the remembered target position.  All lanes of the workgroup call it.
@@ -165,118 +188,120 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P
     const bool concealable = in_bush && !(U.reveal > 0.0f);
     sh.po.pose[P.l] = make_float4(U.x, U.y, cu, su);
     sh.po.body[P.l] = make_float4(U.radius, U.hmax, U.hp, 0.0f);
-    sh.po.seer[P.l] = (P.has ? U.alive : 0) | (U.team << 1) | (concealable ? 4 : 0) | (my_key << 8);
+    sh.po.seer[P.l] = U.alive | (U.team << 1) | (concealable ? 4 : 0) | (my_key << 8);
     const bool decide = U.enabled && U.alive && in.told;
+    // What mark_near compares with.  A pair is seen if d2 <= sight^2 and dot >= c sqrt(d2), each product and sum
+    // rounded.  Marks round otherwise, by a few 2^-24 of sqrt(d2) in dot and of d2; c less 2^-18 leaves eight times
+    // that, and with z |z| growing in z the root needs no taking: dot |dot| >= c' |c'| d2.  What underflows is
+    // below 1e-30, and comparisons that meet a NaN mark.
+    const float cone = U.cos_half - 0x1p-18f;
+    const float sight2 = U.sight_range * U.sight_range;
+    const bool unit_heading = __builtin_fabsf(cu) + __builtin_fabsf(su) < 4.0f;      // (or theta is no heading)
+    const float2 bound = make_float2(__builtin_fmaf(sight2, 1.0f + 0x1p-20f, 1e-30f),
+                                     unit_heading ? cone * __builtin_fabsf(cone) : -__builtin_inff());
 
-    // Which lane scans for whom.  Usually half of the units decide (the adversaries), so as many lanes
-    // as there are to spare, `parts` in all, share the partners of each deciding unit, every one
-    // taking each parts-th of them (10v10 x 16384, adversaries: 25.4 -> 21 us, the scan being bound by
-    // VALU issue).  Merging a part (six shuffles) costs about two thirds of testing a partner, so parts^2
-    // stays within 2 N: two parts for 2v2, where eight took longer than no sharing.  Two wavefronts
-    // (N > 64): every lane scans for its own unit.
-    int parts = 1, part = 0, rank = 0;
-    int me = P.l, base = P.base, self = P.u;
-    float4 O = make_float4(U.x, U.y, cu, su);
-    float4 Q = make_float4(U.range, U.hurt_hw, U.sight_range * U.sight_range, U.cos_half);
-    int role = U.team | (U.dmg < 0.0f ? 2 : 0) | (U.speed >= a.pa.pol.assassin_speed ? 4 : 0) | (my_key << 8);
-    int count = 0;
+    // Which lane marks for whom.  Usually half of the units decide (the adversaries), so as many lanes
+    // as there are to spare, `parts` in all, share the partners of each deciding unit, a run of them each.  Two
+    // wavefronts (N > 64): every lane marks for its own unit.  (Heuristic call, adversaries, testing every pair and
+    // marking first: 10v10 x 16384 18.4 and 14.9 us, 32v32 x 1536 15.9 and 9.7, 64v64 x 1024 42.7 and 17.2.)
+    int parts = 1, rank = 0;
     if (WAVES == 1) {
-        const uint64_t deciding = __ballot(decide);
-        count = __popcll(deciding);
+        const uint64_t deciding = lanes_where(decide);
+        const int count = __popcll(deciding);
         rank = __popcll(deciding & ((1ull << P.l) - 1ull));
         if (count > 0) {
-            parts = 64 / count < 8 ? 64 / count : 8;
+            // 64 / count, eight at most
+            parts = 1 + (count <= 32) + (count <= 21) + (count <= 16) + (count <= 12) + (count <= 10) + (count <= 9) +
+                    (count <= 8);
             while (parts * parts > 2 * N) --parts;
         }
         if (parts > 1) {
-            sh.po.reach[P.l] = Q;
-            sh.po.role[P.l] = role;
-            if (decide) sh.po.who[rank] = P.l | (P.base << 8) | (P.u << 16);
+            sh.po.bound[P.l] = bound;
+            if (decide) sh.po.who[rank] = P.l | (P.base << 8);
         }
+    }
+    // the living units of the lane's env but the lane's own
+    uint64_t others[WAVES];
+    {
+        const uint64_t b = lanes_where(U.alive);
+        if (WAVES == 1) others[0] = (b >> P.base) & (N >= 64 ? ~0ull : (1ull << N) - 1ull);
+        else if ((P.l & 63) == 0) sh.ballots[P.l >> 6][0] = b;
     }
     group_barrier<WAVES>(sh);
-    if (WAVES == 1 && parts > 1) {
-        const int mine = quotient(P.l, (65536u + parts - 1) / parts);
-        part = P.l - mul24(mine, parts);
-        if (mine < count) {
-            const int w = sh.po.who[mine];
-            me = w & 0xff;
-            base = (w >> 8) & 0xff;
-            self = w >> 16;
-        }
-        O = sh.po.pose[me];
-        Q = sh.po.reach[me];
-        role = sh.po.role[me];
+    if (WAVES == 2) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) others[w] = sh.ballots[w][0];
     }
-    const int team = role & 1;
-    const bool healer = (role & 2) != 0;
-    const bool assassin = (role & 4) != 0;
+    uint64_t near[WAVES];
+    if (WAVES == 1 && parts > 1) {
+        // (quotients of integers below 128 by one of at most eight: half a step keeps them off the borders)
+        const float per = __builtin_amdgcn_rcpf((float)parts);
+        const int span = (int)(((float)(N + parts) - 0.5f) * per);                 // N / parts, rounded up: at most 32
+        const int mine = (int)(((float)P.l + 0.5f) * per), part = P.l - mul24(mine, parts);
+        const int w = sh.po.who[mine < 64 ? mine : 0];
+        const int me = w & 63, base = (w >> 8) & 63;               // (lanes to spare: whatever stands there)
+        const float4 O = sh.po.pose[me];
+        const int first = mul24(part, span), left = N - first;
+        const uint32_t bits = mark_near(sh, base, first, left < span ? left : span, O.x, O.y, O.z, O.w, sh.po.bound[me]);
+        near[0] = 0ull;
+        for (int p = 0; p < parts; ++p)
+            near[0] |= (uint64_t)(uint32_t)__shfl((int)bits, mul24(rank, parts) + p) << mul24(p, span);
+    } else {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            uint32_t half[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int first = 64 * w + 32 * h, left = N - first;
+                half[h] = mark_near(sh, P.base, first, left < 32 ? left : 32, U.x, U.y, cu, su, bound);
+            }
+            near[w] = ((uint64_t)half[1] << 32) | half[0];
+        }
+    }
 
-    // One scan, no divergent branches: the target by role (Healer: injured allies first, then
-    // nearest; Assassin: lowest maximum health, then nearest; others: nearest enemy; the lower index
-    // on ties), the nearest visible enemy, and whether anything worth a strike is in the hurtbox.
-    int tgt = -1, near = -1;
+    // The target by role (Healer: injured allies first, then nearest; Assassin: lowest maximum health, then
+    // nearest; others: nearest enemy; the lower index on ties), the nearest visible enemy, and whether anything
+    // worth a strike is in the hurtbox: the marked units in ascending index.
+    const bool healer = U.dmg < 0.0f;
+    const bool assassin = U.speed >= a.pa.pol.assassin_speed;
+    int tgt = -1, nearest = -1;
     bool can_hit = false, tgt_in_box = false;
     float tgt_d2 = 0.0f, tgt_key = 0.0f, near_d2 = 0.0f;
-    for (int j = part; j < N; j += parts) {
-        const int fj = sh.po.seer[base + j];
-        const float4 A = sh.po.pose[base + j];
-        const float4 B = sh.po.body[base + j];
-        const float dx = A.x - O.x;
-        const float dy = A.y - O.y;
-        float dot;
-        const float g2 = hurtbox_gap2(dx, dy, O.z, O.w, Q.x, Q.y, -Q.y, dot);
-        const float d2 = (dx * dx) + (dy * dy);
-        const bool in_range = d2 <= Q.z;
-        const bool in_cone = (d2 == 0.0f) || (dot >= Q.w * __builtin_sqrtf(d2));
-        const bool same_team = ((fj >> 1) & 1) == team;
-        const bool same_bush = (fj >> 8) == (role >> 8);
-        const bool concealed = (fj & 4) && !same_team && !same_bush;
-        const bool seen = (j != self) && (fj & 1) && in_range && in_cone && !concealed;
-        // (a seen unit is inside the cone, so a cone-bounded hurtbox needs no further test)
-        const bool attackable = seen && (healer == same_team) && (g2 <= B.x * B.x);
-        const bool injured = B.z < B.y;
-        can_hit = can_hit || (attackable && (!healer || injured));
-        const bool nearer = seen && !same_team && (near < 0 || d2 < near_d2);
-        near = nearer ? j : near;
-        near_d2 = nearer ? d2 : near_d2;
-        const bool candidate = seen && (healer == same_team);
-        const float key = healer ? (injured ? 0.0f : 1.0f) : (assassin ? B.y : 0.0f);
-        const bool better = candidate && (tgt < 0 || key < tgt_key || (key == tgt_key && d2 < tgt_d2));
-        tgt = better ? j : tgt;
-        tgt_d2 = better ? d2 : tgt_d2;
-        tgt_key = better ? key : tgt_key;
-        tgt_in_box = better ? attackable : tgt_in_box;
-    }
-    if (WAVES == 1 && parts > 1) {
-        // the parts of a unit sit in consecutive lanes: the first one merges the others' winners (the
-        // order of the scan: key, distance, index), then the unit's own lane fetches the result
-        const int tgt_p = tgt, near_p = near, flags_p = (can_hit ? 1 : 0) | (tgt_in_box ? 2 : 0);
-        const float tgt_d2_p = tgt_d2, tgt_key_p = tgt_key, near_d2_p = near_d2;
-        for (int p = 1; p < parts; ++p) {
-            const int from = P.l + p;
-            const int t = __shfl(tgt_p, from), n = __shfl(near_p, from), f = __shfl(flags_p, from);
-            const float td = __shfl(tgt_d2_p, from), tk = __shfl(tgt_key_p, from);
-            const float nd = __shfl(near_d2_p, from);
-            const bool better = t >= 0 && (tgt < 0 || tk < tgt_key ||
-                                           (tk == tgt_key && (td < tgt_d2 || (td == tgt_d2 && t < tgt))));
-            tgt = better ? t : tgt;
-            tgt_d2 = better ? td : tgt_d2;
-            tgt_key = better ? tk : tgt_key;
-            tgt_in_box = better ? (f & 2) != 0 : tgt_in_box;
-            const bool nearer = n >= 0 && (near < 0 || nd < near_d2 || (nd == near_d2 && n < near));
-            near = nearer ? n : near;
-            near_d2 = nearer ? nd : near_d2;
-            can_hit = can_hit || (f & 1) != 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        uint64_t m = decide ? near[w] & others[w] : 0ull;
+        if (P.u >= 64 * w && P.u < 64 * w + 64) m &= ~(1ull << (P.u & 63));
+        while (m != 0ull) {
+            const int j = 64 * w + __builtin_ctzll(m);
+            m &= m - 1ull;
+            const int fj = sh.po.seer[P.base + j];
+            const float4 A = sh.po.pose[P.base + j];
+            const float4 B = sh.po.body[P.base + j];
+            const float dx = A.x - U.x;
+            const float dy = A.y - U.y;
+            float dot;
+            const float g2 = hurtbox_gap2(dx, dy, cu, su, U.range, U.hurt_hw, -U.hurt_hw, dot);
+            const float d2 = (dx * dx) + (dy * dy);
+            const bool in_cone = (d2 == 0.0f) | (dot >= U.cos_half * __builtin_sqrtf(d2));
+            const bool same_team = ((fj >> 1) & 1) == U.team;
+            const bool same_bush = (fj >> 8) == my_key;
+            const bool concealed = (fj & 4) && !same_team && !same_bush;
+            const bool seen = (d2 <= sight2) & in_cone & !concealed;
+            // (a seen unit is inside the cone, so a cone-bounded hurtbox needs no further test)
+            const bool candidate = seen & (healer == same_team);
+            const bool attackable = candidate & (g2 <= B.x * B.x);
+            const bool injured = B.z < B.y;
+            can_hit = can_hit | (attackable & (!healer | injured));
+            const bool nearer = seen & !same_team & ((nearest < 0) | (d2 < near_d2));
+            nearest = nearer ? j : nearest;
+            near_d2 = nearer ? d2 : near_d2;
+            const float key = healer ? (injured ? 0.0f : 1.0f) : (assassin ? +B.y : 0.0f);
+            const bool better = candidate & ((tgt < 0) | (key < tgt_key) | ((key == tgt_key) & (d2 < tgt_d2)));
+            tgt = better ? j : tgt;
+            tgt_d2 = better ? d2 : tgt_d2;
+            tgt_key = better ? key : tgt_key;
+            tgt_in_box = better ? attackable : tgt_in_box;
         }
-        const int at = mul24(rank, parts);
-        tgt = __shfl(tgt, at);
-        tgt_d2 = __shfl(tgt_d2, at);
-        near = __shfl(near, at);
-        near_d2 = __shfl(near_d2, at);
-        const int flags = __shfl((can_hit ? 1 : 0) | (tgt_in_box ? 2 : 0), at);
-        can_hit = (flags & 1) != 0;
-        tgt_in_box = (flags & 2) != 0;
     }
 
     int act = -1;
@@ -287,9 +312,9 @@ __device__ __forceinline__ int policy_env(const KArgs &a, Sh &sh, const Place &P
         S.tgt_in_box = tgt_in_box;
         S.T = sh.po.pose[P.base + (tgt >= 0 ? tgt : 0)];
         S.tr = sh.po.body[P.base + (tgt >= 0 ? tgt : 0)].x;
-        S.any_enemy = near >= 0;
+        S.any_enemy = nearest >= 0;
         S.near_d2 = near_d2;
-        const float4 E = sh.po.pose[P.base + (near >= 0 ? near : 0)];
+        const float4 E = sh.po.pose[P.base + (nearest >= 0 ? nearest : 0)];
         S.near_dx = E.x - U.x;
         S.near_dy = E.y - U.y;
         S.can_hit = can_hit;
