@@ -675,17 +675,30 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
             // scripted: 10v10 x 16384 139 us with one wavefront per group, 121 with two; the policy as a
             // scan stage keeps them all waiting, so it has one unless the rows ask for tiles
             a.twin = mode == MODE_POLICY_STEP_OBSERVE && packs ? 0 : 2;
-            if (mode == MODE_SCRIPTED_STEP_OBSERVE && tiny_batch) a.twin = lone_groups && N > 32 ? 8 : 4;
+            // ... and four from 32 units on where there is more than one generation: with four tiles' passes in
+            // flight 16v16 with zones x 6144 105.5 -> 96 us, 20v20 x 5000 113 -> 109.5, 24v24 with zones x 3000
+            // 137 -> 123, 32v32 x 3000 172 -> 160; a single generation is paced, and two are better there
+            // (16v16 x 4000 54 us and 58, 32v32 x 1536 82 and 88).
+            if (mode == MODE_SCRIPTED_STEP_OBSERVE && (tiny_batch || (N >= 32 && !small_batch)))
+                a.twin = lone_groups && N > 32 ? 8 : 4;
         }
         // On a full machine a plain tick stores two passes' rows at a time: 10v10 x 16384 107 -> 101.5 us,
-        // 16v16 x 6144 93.8 -> 88; with a generation or less, shorter chains count (9v8 x 5003 39 and 48).
-        if (mode == MODE_STEP_OBSERVE && a.twin && !small_batch && a.tiles >= 8 * a.twin &&
+        // 16v16 x 6144 93.8 -> 88; with a generation or less, shorter chains count (9v8 x 5003 39 and 48).  A
+        // scripted tick, whose passes also bid, only where four wavefronts share (10v10 x 16384 122 and 131).
+        const bool wide_scripted = mode == MODE_SCRIPTED_STEP_OBSERVE && a.twin == 4;
+        if ((mode == MODE_STEP_OBSERVE || wide_scripted) && a.twin && !small_batch && a.tiles >= 8 * a.twin &&
             2 * S * a.obs_dim <= 2 * kTileFloats)
             K = 2;
         // Likewise where four wavefronts have six or more tiles each and there are at most two groups per CU
         // (15v15 x 800 17.1 -> 16.7 us, 12v12 with zones 15.8 -> 14.7; with fewer tiles, or three groups, one
         // pass per tile is better: 10v10 x 1200 14.9 and 15.4, 12v12 x 1400 16.9 and 17.4).
         if (mode == MODE_STEP_OBSERVE && a.twin == 4 && few_groups && a.tiles >= 6 * a.twin) K = 2;
+        // A scripted tick likewise, if there are at most three groups per two CUs or the tiles stay under 6.4 KB
+        // (15v15 x 799 21.2 -> 19.3 us, 20v20 x 500 20.9 -> 18.9; 16v16 with 8 KB x 799 18.5 -> 17.8, x 997 19.0
+        // and 20.2; 32v32 x 400 29.1 -> 27.7, x 500 29.9 and 30.1).
+        if (wide_scripted && few_groups && a.tiles >= 6 * a.twin &&
+            (2 * a.num_groups <= 3 * kComputeUnits || 2 * S * a.obs_dim <= 1600))
+            K = 2;
         // ... and where they have eight or more each beyond five groups per CU, short of a full machine (32v32
         // with zones x 1536 98 -> 92 us, 24v24 61.5 -> 57.4; x 1200 without zones 68.6 and 70.7).
         if (mode == MODE_STEP_OBSERVE && a.twin == 4 && a.num_groups > 5 * kComputeUnits && a.tiles >= 8 * a.twin) K = 2;
