@@ -68,6 +68,7 @@ struct KArgs {
     uint32_t  cells;               // FAST_CELL: cells of one row's grid
     uint32_t  flags;               // Flag bits
     PolicyArgs pa;
+    float *global_stream;          // where the global state goes if it is streamed (st.global_state is null then)
 };
 
 // What a launch has to do besides the plain tick, one bit each.

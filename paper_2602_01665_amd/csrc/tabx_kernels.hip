@@ -181,6 +181,11 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
         float *stg = dyn + wave * a.stage_floats;
         {
             const KArgs &a = again();
+            if constexpr (WAVES == 1) {
+                float *const global_state = late_args()->global_stream;
+                if (global_state && P.chunk == 0)
+                    stream_global_state<64 * TWIN>(a, sh.rec, Z, global_state, P.grp, (int)threadIdx.x);
+            }
             const int first = P.chunk * a.tiles_per_chunk;
             const int end = first + a.tiles_per_chunk < a.tiles ? first + a.tiles_per_chunk : a.tiles;
             // Each wavefront writes one contiguous run of the group's tiles.  Taken in turn, tile by tile,
@@ -313,6 +318,7 @@ constexpr int kLdsPerCuBytes = 160 * 1024;          // a CU's LDS, shared by its
 constexpr int kLdsPerWorkgroupBytes = 64 * 1024;    // the most one workgroup may take
 constexpr int kWavefrontLanes = 64;
 constexpr size_t kLdsGranuleBytes = 1280;           // LDS is given out in these
+constexpr size_t kL2Bytes = (size_t)32 << 20;                // the L2s of all XCDs
 constexpr size_t kLastLevelCacheBytes = (size_t)256 << 20;   // the cache in front of HBM, all XCDs
 
 static size_t lds_granules(size_t bytes) { return (bytes + kLdsGranuleBytes - 1) / kLdsGranuleBytes * kLdsGranuleBytes; }
@@ -762,6 +768,19 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     return waves;
 }
 
+// Where the global state is streamed to, or null: the lanes that hold the units write their blocks then.  Those
+// stores stay in the L2s and are overwritten there by the next tick, which is the better way as long as they fit
+// beside the rows that pass through: at five eighths of the L2s the two meet (stored / streamed: 12v12 x 12000, 18 MB,
+// 96 / 99 us, 16v16 x 9000, 18 MB, 107.5 / 110, 10v10 with zones x 14000, 21 MB, 96.5 / 95, x 15000, 22 MB, 106 / 100,
+// x 16384 115 / 108.5, scripted 122 / 116.5, 16v16 x 12000, 25 MB, 153 / 145, 9v8 with zones x 18000, 23 MB,
+// 107 / 104.5).  Launches with the units in registers, and envs of two wavefronts, have no use for it (a row of theirs
+// is as long as the state of its env, and there are as many as units).
+static float *plan_global(const KArgs &a)
+{
+    const size_t bytes = sizeof(float) * (size_t)a.p.num_envs * a.obs_dim;
+    return !a.packed && bytes > kL2Bytes / 8 * 5 ? a.st.global_state : nullptr;
+}
+
 static int run(Mode mode, const TabxParams *p, const TabxScenario *sc, const TabxState *st,
                const uint8_t *actions, const uint8_t *env_mask, float *rewards,
                uint8_t *dones, float *obs, uint64_t *vis_mask, uint8_t *action_mask,
@@ -821,6 +840,8 @@ static int run(Mode mode, const TabxParams *p, const TabxScenario *sc, const Tab
 
     hipStream_t s = (hipStream_t)stream;
     const int waves = plan_shape(mode, p, a);
+    a.global_stream = observing && waves == 1 ? plan_global(a) : nullptr;
+    if (a.global_stream) a.st.global_state = nullptr;
     const hipError_t err = waves == 1 ? launch_mode<1>(mode, a, s) : launch_mode<2>(mode, a, s);
     return err == hipSuccess ? TABX_OK : TABX_ERR_LAUNCH;
 }

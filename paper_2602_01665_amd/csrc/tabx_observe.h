@@ -112,6 +112,36 @@ __device__ __forceinline__ void global_state_zones(const KArgs &a, const ZoneLds
     }
 }
 
+// The global state of the workgroup's envs, from the records: every unit's own block, whose position is absolute,
+// then the zone slots with absolute centres, past the caches (see plan_global).  An env's part is one run of HBM, a
+// lane per 16-byte chunk, by LANES lanes (`l`: index among them): what goes past the caches has to be whole lines
+// (from the lanes that hold the units, 64 bytes apart, 10v10 x 16384 116 -> 126 us).
+template <int LANES>
+__device__ __forceinline__ void stream_global_state(const KArgs &a, const Records<64> &rec, const ZoneLds &Z,
+                                                    float *out, int grp, int l)
+{
+    const int N = a.p.num_units, D = a.obs_dim, ZC = a.zone_chunks, zlen = 6 * a.p.max_zones;
+    const int chunks = 4 * N + ZC, all = envs_of_group(a, grp) * chunks;
+    // (quotients below 64 of dividends below 2048: half a step keeps them off the borders)
+    const float per = __builtin_amdgcn_rcpf((float)chunks);
+    out += (size_t)grp * a.envs_per_block * D;
+    for (int q = l; q < all; q += LANES) {
+        const int g = (int)(((float)q + 0.5f) * per);
+        const int c = q - mul24(g, chunks), zc = c - 4 * N;
+        const int unit = mul24(g, N) + (zc < 0 ? c >> 2 : 0);
+        const float4 v = zc < 0 ? rec.own[0][64 * (c & 3) + unit] : Z.val[mul24(g, ZC) + zc];
+        const bool on = zc >= 0 || (__float_as_int(rec.mark[unit].y) & 8);
+        const f4u w = {on ? v.x : 0.0f, on ? v.y : 0.0f, on ? v.z : 0.0f, on ? v.w : 0.0f};
+        float *const d = out + (mul24(g, D) + 4 * c);
+        if (zc < 0 || zlen - 4 * zc >= 4) {
+            __builtin_nontemporal_store(w, reinterpret_cast<f4u *>(d));
+        } else {                                   // (zlen is even: half a chunk)
+            d[0] = w.x;
+            d[1] = w.y;
+        }
+    }
+}
+
 // Where 16-byte chunk c of a staged tile lives in LDS: the four chunks of every aligned 64-byte
 // group are permuted by the group's index (XOR with bits 3..4 of c).  Measured on gfx950
 // (SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE of one-pattern kernels): a 16-byte write of 64 lanes
