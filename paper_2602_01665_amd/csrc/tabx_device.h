@@ -43,6 +43,8 @@ struct KArgs {
     int       rows_per_tile;       // T: consecutive rows a wavefront assembles and stores together
     int       tiles;               // tiles of a full env group: ceil(G * N / T)
     int       passes_per_tile;     // T / S
+    uint32_t  line;                // a tile's image starts where its first row does in memory, modulo line + 1 floats
+    int       lines;               // enum Lines
     int       stage_floats;        // a wavefront's staging area in dynamic LDS (they come first)
     int       zone_chunks;         // ZC: 16-byte chunks of the zone part of a row
     unsigned  magic_n, magic_zc, magic_s, magic_tc;   // x / N, / ZC, / S, / (4 + ZC) as multiplications (see quotient)
@@ -70,6 +72,11 @@ struct KArgs {
     PolicyArgs pa;
     float *global_stream;          // where the global state goes if it is streamed (st.global_state is null then)
 };
+
+// How the tiles of a group lie in the 128-byte lines of the rows: each starts on one; neighbours share one, which each
+// writes its part of; a wavefront hands a shared one on to its next tile.
+template <int V> struct Constant { static constexpr int value = V; };
+enum Lines : int { LINES_OWN, LINES_SHARED, LINES_CARRIED };
 
 // What a launch has to do besides the plain tick, one bit each.
 enum Flag : uint32_t {

@@ -194,14 +194,20 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
             // Odd numbers of units up to 20 go in turn: runs cost 9v8 with zones (x 4000 29.1 us in turn, 30.0 in
             // runs; x 5003 32.7 and 34.4; x 20000 94.6 and 96.6); 5, 7, 13 and 21 units are level, and wider
             // odd rows are better in runs (30v29 x 5000 232 us in turn, 229 in runs).
-            const bool in_turn = WAVES == 1 && (a.p.num_units & 1) && a.p.num_units < 21;
+            const bool in_turn = WAVES == 1 && DO_STEP && (a.p.num_units & 1) && a.p.num_units < 21;
             const int share = (end - first + WAVES * TWIN - 1) / (WAVES * TWIN);
             const int begin = first + (in_turn ? wave : wave * share), step = in_turn ? WAVES * TWIN : 1;
             const int stop = !in_turn && begin + share < end ? begin + share : end;
-            if (a.zone_chunks == 0)
-                write_rows<WAVES, SCRIPT, true>(a, sh.rec, Z, stg, P.grp, begin, step, stop, script);
-            else
-                write_rows<WAVES, SCRIPT, false>(a, sh.rec, Z, stg, P.grp, begin, step, stop, script);
+            const auto rows = [&](auto fold, auto lines) {
+                write_rows<WAVES, SCRIPT, fold.value, lines.value>(a, sh.rec, Z, stg, P.grp, begin, step, stop, script);
+            };
+            const auto rows_by_lines = [&](auto fold) {
+                if (a.lines == LINES_OWN) rows(fold, Constant<LINES_OWN>{});
+                else if (a.lines == LINES_SHARED) rows(fold, Constant<LINES_SHARED>{});
+                else rows(fold, Constant<LINES_CARRIED>{});
+            };
+            if (a.zone_chunks == 0) rows_by_lines(Constant<1>{});
+            else rows_by_lines(Constant<0>{});
         }
         TABX_STAMP(4);
         if (SCRIPT) {
@@ -425,9 +431,11 @@ static void set_flags(const TabxParams *p, const TabxState *st, KArgs &a)
 // A wavefront's staging area for `floats` floats: whole store passes (64 lanes of 16 bytes).
 static size_t whole_passes(size_t floats) { return (floats + 255) / 256 * 256; }
 
-// The staging area of a tile of `rows` rows of `dim` floats; rows of 2 mod 4 floats may start in the middle
-// of a chunk.
-static size_t tile_floats(int rows, int dim) { return whole_passes((size_t)rows * dim + (dim % 4 ? 2 : 0)); }
+// The staging area of a tile of `rows` rows of `dim` floats, which starts anywhere within `line` + 1 floats.
+static size_t tile_floats(int rows, int dim, int line)
+{
+    return whole_passes((size_t)rows * dim + (dim % 32 ? line - 1 : 0));
+}
 
 // The zone descriptors of a workgroup's envs: 16-byte chunks with a mask each.
 static size_t zone_floats(const KArgs &a) { return ((size_t)a.envs_per_block * a.zone_chunks * 5 + 3) / 4 * 4; }
@@ -447,7 +455,7 @@ static size_t plan_lds(Mode mode, KArgs &a, int waves)
         } else {
             // one staging area per wavefront
             a.stage_floats = (int)(a.packed ? whole_passes((size_t)a.envs_per_block * a.rows_per_flush * a.obs_dim)
-                                            : tile_floats(a.rows_per_tile, a.obs_dim));
+                                            : tile_floats(a.rows_per_tile, a.obs_dim, a.line));
             floats = (size_t)a.stage_floats * waves * (a.twin ? a.twin : 1);
         }
     }
@@ -469,7 +477,7 @@ static size_t plan_lds(Mode mode, KArgs &a, int waves)
 static int wavefronts_per_simd(Mode mode, const KArgs &a, int waves)
 {
     if (a.packed) return waves == 1 || a.even ? 3 : 4;
-    return mode == MODE_SCRIPTED_STEP_OBSERVE && waves == 1 ? 4 : 5;
+    return mode == MODE_SCRIPTED_STEP_OBSERVE ? 4 : 5;
 }
 
 // Holds the wavefronts of a launch to the pace at which HBM takes all their rows together (a.pace).
@@ -506,11 +514,13 @@ static void plan_pace(Mode mode, KArgs &a, int waves, size_t lds)
     // costs that much and 10 % too fast leaves little of the gain.  Tiles: 6.0 (64v64 x 400, 27v28 x 1200); rows of
     // whole 128-byte lines that the last-level cache takes all of 7.0 (6.5 ... 7.8: 32v32 x 700, 8v8 x 5000, 16v16 x
     // 1300); rows that leave lines partly written, beyond that cache, 5.6 (32v32 with 8 zones x 1000); rows that end
-    // on half a chunk 5.2 (12v12 with 3 zones x 3000).  Units in registers: 5.85, rows of whole lines of two
+    // on half a chunk 6.5 where shared lines are handed on (24v24 with 5 zones x 1200 50.9 at 5.2, 48.0 at 6.5, 32v32
+    // with 3 x 1000 65.5 and 60.4), else 5.2 (10v10 with 3 x 4000 32.4, 36.8 at 5.6).  Units in registers: 5.85, rows of whole lines of two
     // wavefronts 6.1.
     const bool lines = a.obs_dim % 32 == 0, cached = bytes <= (double)kLastLevelCacheBytes;
     double rate = lines ? (cached ? 7.0 : 6.0) : (cached ? 6.0 : 5.6);
-    if (a.obs_dim % 4 != 0) rate = 5.2;
+    const bool handed_on = a.lines == LINES_CARRIED && !((a.p.num_units & 1) && a.p.num_units < 21);   // (not in turn)
+    if (a.obs_dim % 4 != 0) rate = handed_on ? 6.5 : 5.2;
     if (a.packed) rate = waves == 2 && lines ? 6.1 : 5.85;
     const double ticks = bytes / (rate * 1e12) * 100e6 / flushes;
     // Two wavefronts with the units in registers take 0.9 us per row by themselves, and looking at the clock
@@ -688,6 +698,12 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
             if (mode == MODE_SCRIPTED_STEP_OBSERVE && (tiny_batch || (N >= 32 && !small_batch)))
                 a.twin = lone_groups && N > 32 ? 8 : 4;
         }
+        // Tiles that share lines (see write_rows) are longer chains, and up to four groups per CU two wavefronts
+        // each are too few to hide them (two / four: 11v12 with 7 zones x 2000 27.9 / 23.5 us, 15v16 with 7 x 1800
+        // 38 / 34.5, scripted 28v28 with 2 x 800 56 / 40.5, 24v24 with 4 x 1000 49 / 37.5).
+        if (a.twin == 2 && (mode == MODE_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE) && N > 20 &&
+            a.num_groups <= 4 * kComputeUnits && a.obs_dim % 32 != 0 && p->zone_shapes == 0)
+            a.twin = 4;
         // On a full machine a plain tick stores two passes' rows at a time: 10v10 x 16384 107 -> 101.5 us,
         // 16v16 x 6144 93.8 -> 88; with a generation or less, shorter chains count (9v8 x 5003 39 and 48).  A
         // scripted tick, whose passes also bid, only where four wavefronts share (10v10 x 16384 122 and 131).
@@ -719,7 +735,7 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         a.copy_passes = ((half > row_chunks - half ? half : row_chunks - half) + 63) / 64;
         // What a workgroup with `w` wavefronts that make tiles takes of a CU's LDS.
         const auto tile_lds = [&](int w) {
-            return sizeof(Shared<2, true, true, true>) + sizeof(float) * (w * tile_floats(1, a.obs_dim) + zone_floats(a)) +
+            return sizeof(Shared<2, true, true, true>) + sizeof(float) * (w * tile_floats(1, a.obs_dim, 3) + zone_floats(a)) +
                    (mode == MODE_SCRIPTED_STEP_OBSERVE ? sizeof(ScriptLds<2>) : 0);
         };
         const int E = p->num_envs;
@@ -765,6 +781,21 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     a.rows_per_tile = K * S;
     a.tiles = (G * N + a.rows_per_tile - 1) / a.rows_per_tile;
     a.tiles_per_chunk = (a.tiles + a.obs_chunks - 1) / a.obs_chunks;
+    // A tile's image starts where the tile does within a line, unless that takes one more store instruction (and
+    // its share of the LDS) while the last-level cache takes all rows (7 units with 5 zones, 9 rows of 568 bytes, x
+    // 20000, observed: 22.5 us, 24.3 with the sixth; beyond, 10v10 with 3 zones x 16384 115 without, 103 with;
+    // rows of envs of two wavefronts fill their areas, which are planned for already).
+    const double bytes = 4.0 * a.obs_dim * N * p->num_envs;
+    const size_t tile = (size_t)a.rows_per_tile * a.obs_dim;
+    a.line = whole_passes(tile + 30) == whole_passes(tile + 2) ||
+                     (waves == 1 && bytes > (double)kLastLevelCacheBytes) ? 31 : 3;
+    // Shared lines are handed on from where the launch is mostly rows (see plan_pace), and beyond that cache from
+    // four tiles per wavefront on (5v5 with 3 zones x 65536, observed, two or three: 129 us, 134 handed on; 8v7 with
+    // one x 20000, four: 67 and 62.5).
+    const int per_wavefront = a.twin ? a.tiles_per_chunk / (waves * a.twin) : 0;
+    if (a.obs_dim % 4 == 0 && tile % 32 == 0 && G * N * a.obs_dim % 32 == 0) a.lines = LINES_OWN;
+    else if (a.line == 31 && bytes > 50e6 && (per_wavefront >= 4 || bytes <= (double)kLastLevelCacheBytes)) a.lines = LINES_CARRIED;
+    else a.lines = LINES_SHARED;
     return waves;
 }
 

@@ -163,6 +163,14 @@ __device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); 
 // before the tile goes out, so that their latency passes behind the stores.
 // WAVES == 2 (one env, a tile is one row): the wavefront goes over the units in two halves.
 // FOLD: there are no zone slots.
+// LINES (KArgs::lines): how the tiles lie in the 128-byte lines of the rows.  A line that is written in two parts,
+// by two store instructions or for two tiles, HBM takes twice.  So a tile's image starts at the place within a line
+// at which the tile does in memory, every store instruction then writes whole lines, and the line that two tiles of a
+// wavefront share goes out with the second one.  With tiles that start on a chunk / on a line / and that hand the
+// shared line on: 32v32 with 3 zones x 2000 135 / 123 / 115 us, 20v20 with one x 3000 85 / 80 / 74, 15v15 with 5 x
+// 8000 133 / 124 / 113, 27v28 with 4 x 1200 67.5 / 66 / 53, scripted 10v10 with 5 x 16384 123 / 116.5 / 110.  The
+// forms are code of their own: what the third one does costs small launches 2 to 4 % (10v11 with one zone x 64 11.4
+// and 11.8 us), and the second one's 1 % where no tile needs it (10v10 with 8 x 16384).
 //
 // SCRIPT: the units the heuristic policy moves decide their next action from the very pair
 // tests the observation rows are made of (App. A "Role-Appropriate Heuristic Policy Mechanism":
@@ -170,7 +178,7 @@ __device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); 
 // with LDS atomic minima for "its target" (key: the role's order, then distance, then index,
 // with "in its hurtbox" riding in the lowest bit) and for "its nearest enemy"; afterwards the
 // deciding units read their winners (decide_units).
-template <int WAVES, bool SCRIPT, bool FOLD>
+template <int WAVES, bool SCRIPT, bool FOLD, int LINES>
 __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WAVES> &rec,
                                            const ZoneLds &Z, float *stg, int grp, int tile,
                                            int tile_step, int tile_end, ScriptLds<WAVES> *script)
@@ -190,7 +198,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     const int rows = envs_of_group(a, grp) * N;
     const size_t row0 = (size_t)grp * a.envs_per_block * N;       // the group's first row
     uint64_t *const vis_mask = late_args()->vis_mask;
-    const bool whole = (D & 3) == 0;             // rows are whole 16-byte chunks
+    const bool whole = LINES == LINES_OWN || (D & 3) == 0;             // rows are whole 16-byte chunks
     const bool grouped = (D & 15) == 0;          // ... and whole 64-byte groups
     // the lane's place in a pass: row slot s, unit u
     const int s = WAVES == 1 ? quotient(lane, magic_n) : 0;
@@ -262,7 +270,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
                 }
     };
     auto rows_of = [&](int t) { const int left = rows - t * T; return left < T ? left : T; };
-    auto pad_of = [&](int t) { return whole ? 0 : 2 * (int)((row0 + t * T) & 1); };
+    auto pad_of = [&](int t) { return LINES == LINES_OWN ? 0 : (int)(((uint32_t)row0 + (uint32_t)(t * T)) * (uint32_t)D & a.line); };
     if (tile < tile_end && tile * T < rows) {
         fetch(tile * T, 0, rows_of(tile));
     }
@@ -270,10 +278,11 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
     const unsigned pace = a.pace;
     const unsigned first_row = pace_start(pace);
     unsigned due = 0;
+    bool carried = false;                        // the head of the tile's first line is there already
     for (; tile < tile_end && tile * T < rows; tile += tile_step) {
         const int f0 = tile * T;                 // the tile's first row within the group
         const int rows_here = rows_of(tile);
-        // where the tile starts relative to a 16-byte boundary (rows of 2 mod 4 floats)
+        // where the tile starts within a 128-byte line (or a 16-byte chunk: KArgs::line)
         const int pad = pad_of(tile);
         float *const buf = stg;
         v4 *const vstage = reinterpret_cast<v4 *>(buf);
@@ -388,10 +397,12 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         lds_barrier<1>();
 
         // stream the finished rows: LDS chunk -> one 16-byte store, 1 KB per instruction
-        float *const out = obs + (row0 + f0) * D - pad;            // 16-byte aligned
+        float *const out = obs + (row0 + f0) * D - pad;
         const int floats = pad + rows_here * D;
-        const int chunks = floats >> 2;          // (whole chunks, the first one perhaps half ours)
-        const int first = pad >> 1;   // 0, or 1: chunk 0 starts in the previous row
+        // LINES_CARRIED: a line that two tiles share goes out with the second one, if both are this wavefront's.
+        const bool carry = LINES == LINES_CARRIED && tile_step == 1 && tile + 1 < tile_end && (tile + 1) * T < rows && floats >= 32;
+        const int chunks = carry ? (floats & ~31) >> 2 : floats >> 2;
+        const int first = carried ? 0 : (pad + 3) >> 2;        // the first chunk that is the tile's alone
         const float4 *src = reinterpret_cast<const float4 *>(buf) + lane;
         char *dst = reinterpret_cast<char *>(out);
         for (int left = chunks, skip = first; left > 0; left -= 64 * kPassBatch, skip = 0) {
@@ -417,13 +428,22 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         }
         if (!whole) {
             // the half chunks at the two ends: lane 0 the first, lane 1 the last
-            const bool head = lane == 0 && pad != 0, tail = lane == 1 && (floats & 2) != 0;
+            const bool head = lane == 0 && (pad & 2) && !carried, tail = lane == 1 && (floats & 2) != 0 && !carry;
             if (head || tail) {
-                const int at = head ? 2 : floats - 2;
+                const int at = head ? pad : floats - 2;
                 *reinterpret_cast<v2 *>(out + at) = *reinterpret_cast<const v2 *>(buf + at);
             }
         }
         lds_barrier<1>();
+        carried = carry;
+        if (carry) {
+            const int rest = floats & 31, from = (floats - rest) >> 2;      // (the shared line, its first chunk)
+            if (whole) {
+                if (4 * lane < rest) vstage[staged_chunk(lane)] = vstage[staged_chunk(from + lane)];
+            } else if (2 * lane < rest) {
+                reinterpret_cast<v2 *>(buf)[lane] = reinterpret_cast<const v2 *>(buf)[2 * from + lane];
+            }
+        }
         // (8 KB rows: the wavefront lets its row land before it goes on, which keeps the XCDs together,
         // as in tabx_observe_packed.h: 64v64 x 512 125 us without, 117 with)
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
