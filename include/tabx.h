@@ -361,6 +361,17 @@ typedef struct TabxLaunchInfo {
 } TabxLaunchInfo;
 int tabx_launch_info(const TabxParams *params, int call, TabxLaunchInfo *info);
 
+/* Host-only, like tabx_launch_info: which form of the row writers a call with observations takes
+ * (`obs` on a 128-byte line, global_state given).  Results never depend on it. */
+typedef struct TabxRowForm {
+    int32_t lines;                   /* tiles of rows and 128-byte lines: 0 each tile starts on one,
+                                        1 neighbours share one, 2 a wavefront hands a shared one on
+                                        to its next tile; -1: no tiles (units in registers, no rows) */
+    int32_t pace;                    /* least time from one flush to the next, in 1/16 of 10 ns; 0: none */
+    int32_t streams_global_state;    /* 1: the global state goes past the caches                   */
+} TabxRowForm;
+int tabx_row_form(const TabxParams *params, int call, TabxRowForm *form);
+
 const char *tabx_strerror(int code);
 
 #ifdef __cplusplus

@@ -26,7 +26,7 @@ STATE_FLOAT = ("x", "y", "vx", "vy", "theta", "hp", "cd", "reveal", "cur_speed")
 EXPORTS = ("tabx_obs_dim", "tabx_num_actions", "tabx_reset", "tabx_step", "tabx_observe",
            "tabx_step_observe", "tabx_global_state", "tabx_heuristic_actions",
            "tabx_policy_step_observe", "tabx_scripted_step_observe", "tabx_part", "tabx_launch_info",
-           "tabx_strerror")
+           "tabx_row_form", "tabx_strerror")
 
 _I8 = C.POINTER(C.c_int8)
 _I32 = C.POINTER(C.c_int32)
@@ -157,6 +157,17 @@ def tabx_launch_info(params: TabxParams, call: str) -> dict:
     info = TabxLaunchInfo()
     _check(_lib.tabx_launch_info(C.byref(params), CALLS[call], C.byref(info)), "tabx_launch_info")
     return {n: getattr(info, n) for n, _ in TabxLaunchInfo._fields_}
+
+
+class TabxRowForm(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("lines", "pace", "streams_global_state")]
+
+
+def tabx_row_form(params: TabxParams, call: str) -> dict:
+    """Which form of the row writers the call takes (host only, nothing is enqueued)."""
+    form = TabxRowForm()
+    _check(_lib.tabx_row_form(C.byref(params), CALLS[call], C.byref(form)), "tabx_row_form")
+    return {n: getattr(form, n) for n, _ in TabxRowForm._fields_}
 
 
 def tabx_num_actions() -> int:

@@ -332,6 +332,13 @@ static size_t lds_granules(size_t bytes) { return (bytes + kLdsGranuleBytes - 1)
 enum Mode { MODE_RESET, MODE_STEP, MODE_OBSERVE, MODE_STEP_OBSERVE, MODE_POLICY,
             MODE_POLICY_STEP_OBSERVE, MODE_SCRIPTED_STEP_OBSERVE };
 
+// The calls that write observation rows.
+static bool has_rows(Mode mode)
+{
+    return mode == MODE_OBSERVE || mode == MODE_STEP_OBSERVE || mode == MODE_POLICY_STEP_OBSERVE ||
+           mode == MODE_SCRIPTED_STEP_OBSERVE;
+}
+
 static bool aligned(const void *p, size_t n) { return ((uintptr_t)p % n) == 0; }
 
 static int check_params(const TabxParams *p)
@@ -443,8 +450,7 @@ static size_t zone_floats(const KArgs &a) { return ((size_t)a.envs_per_block * a
 // Dynamic LDS of a launch and where its parts lie (fills the offsets in `a`).
 static size_t plan_lds(Mode mode, KArgs &a, int waves)
 {
-    const bool observing = mode == MODE_OBSERVE || mode == MODE_STEP_OBSERVE ||
-                           mode == MODE_POLICY_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE;
+    const bool observing = has_rows(mode);
     if (mode == MODE_RESET) return 0;
     size_t floats = 0;
     if (observing) {
@@ -493,9 +499,7 @@ static int wavefronts_per_simd(Mode mode, const KArgs &a, int waves)
 static void plan_pace(Mode mode, KArgs &a, int waves, size_t lds)
 {
     a.pace = 0;
-    const bool rows = mode == MODE_OBSERVE || mode == MODE_STEP_OBSERVE ||
-                      mode == MODE_POLICY_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE;
-    if (!rows || a.obs_chunks > 1) return;
+    if (!has_rows(mode) || a.obs_chunks > 1) return;
     // Few rows: such a launch is mostly its start (5v5 x 6000, 38 MB: 13.4 us, 14.0 paced; x 8000 17.8 and 17.1).
     const double bytes = 4.0 * a.obs_dim * a.p.num_units * a.p.num_envs;
     if (bytes < 50e6) return;
@@ -652,8 +656,7 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     const int R = waves == 1 && N % 2 == 0 && 2 * G * cpr <= 64 * kMaxPasses ? 2 : 1;
     const bool packs = waves == 2 || (a.obs_dim % 4 == 0 && G * a.zone_chunks <= 64 &&
                                       R * G * cpr <= 64 * kMaxPasses);
-    const bool rows = mode == MODE_OBSERVE || mode == MODE_STEP_OBSERVE ||
-                      mode == MODE_POLICY_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE;
+    const bool rows = has_rows(mode);
     a.rows_per_flush = R;
     if (waves == 1) {
         a.copy_passes = (R * G * cpr + 63) / 64;
@@ -812,6 +815,24 @@ static float *plan_global(const KArgs &a)
     return !a.packed && bytes > kL2Bytes / 8 * 5 ? a.st.global_state : nullptr;
 }
 
+// The plan of an entry point's call (enum TabxCall), for the queries that enqueue nothing.
+static int plan_call(const TabxParams *p, int call, const void *out, KArgs &a, Mode &mode, int &waves, size_t &lds)
+{
+    const int rc = check_params(p);
+    if (rc) return rc;
+    if (!out) return TABX_ERR_NULL;
+    if (call < TABX_CALL_RESET || call > TABX_CALL_SCRIPTED_STEP_OBSERVE) return TABX_ERR_SHAPE;
+    static const Mode modes[] = {MODE_RESET, MODE_STEP, MODE_OBSERVE, MODE_STEP_OBSERVE, MODE_POLICY,
+                                 MODE_POLICY_STEP_OBSERVE, MODE_SCRIPTED_STEP_OBSERVE};
+    mode = modes[call];
+    a.p = *p;
+    a.obs_dim = 16 * p->num_units + 6 * p->max_zones;
+    waves = plan_shape(mode, p, a);
+    lds = plan_lds(mode, a, waves);
+    plan_pace(mode, a, waves, lds);
+    return TABX_OK;
+}
+
 static int run(Mode mode, const TabxParams *p, const TabxScenario *sc, const TabxState *st,
                const uint8_t *actions, const uint8_t *env_mask, float *rewards,
                uint8_t *dones, float *obs, uint64_t *vis_mask, uint8_t *action_mask,
@@ -828,8 +849,7 @@ static int run(Mode mode, const TabxParams *p, const TabxScenario *sc, const Tab
                           mode == MODE_SCRIPTED_STEP_OBSERVE;
     const bool stepping = mode == MODE_STEP || mode == MODE_STEP_OBSERVE ||
                           mode == MODE_POLICY_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE;
-    const bool observing = mode == MODE_OBSERVE || mode == MODE_STEP_OBSERVE ||
-                           mode == MODE_POLICY_STEP_OBSERVE || mode == MODE_SCRIPTED_STEP_OBSERVE;
+    const bool observing = has_rows(mode);
     if (deciding) {
         if (!policy || !memory || !actions_out) return TABX_ERR_NULL;
         if (!memory->mem_x || !memory->mem_y || !memory->mem_valid) return TABX_ERR_NULL;
@@ -1041,18 +1061,12 @@ int tabx_part(const TabxParams *p, const TabxScenario *sc, const TabxState *st, 
 int tabx_launch_info(const TabxParams *p, int call, TabxLaunchInfo *info)
 {
     using namespace tabx;
-    const int rc = check_params(p);
-    if (rc) return rc;
-    if (!info) return TABX_ERR_NULL;
-    if (call < TABX_CALL_RESET || call > TABX_CALL_SCRIPTED_STEP_OBSERVE) return TABX_ERR_SHAPE;
-    static const Mode modes[] = {MODE_RESET, MODE_STEP, MODE_OBSERVE, MODE_STEP_OBSERVE, MODE_POLICY,
-                                 MODE_POLICY_STEP_OBSERVE, MODE_SCRIPTED_STEP_OBSERVE};
-    const Mode mode = modes[call];
     KArgs a = {};
-    a.p = *p;
-    a.obs_dim = 16 * p->num_units + 6 * p->max_zones;
-    const int waves = plan_shape(mode, p, a);
-    const size_t lds = plan_lds(mode, a, waves);
+    Mode mode;
+    int waves;
+    size_t lds;
+    const int rc = plan_call(p, call, info, a, mode, waves, lds);
+    if (rc) return rc;
     info->workgroups = 8 * a.groups_per_xcd * a.obs_chunks;
     info->threads_per_workgroup = 64 * waves * (a.twin ? a.twin : 1);
     info->envs_per_workgroup = a.envs_per_block;
@@ -1063,6 +1077,23 @@ int tabx_launch_info(const TabxParams *p, int call, TabxLaunchInfo *info)
     info->assumed_lds_per_cu_bytes = kLdsPerCuBytes;
     info->assumed_lds_per_workgroup_bytes = kLdsPerWorkgroupBytes;
     info->assumed_wavefront_lanes = kWavefrontLanes;
+    return TABX_OK;
+}
+
+int tabx_row_form(const TabxParams *p, int call, TabxRowForm *form)
+{
+    using namespace tabx;
+    KArgs a = {};
+    Mode mode;
+    int waves;
+    size_t lds;
+    const int rc = plan_call(p, call, form, a, mode, waves, lds);
+    if (rc) return rc;
+    float any;
+    a.st.global_state = &any;
+    form->lines = has_rows(mode) && !a.packed ? a.lines : -1;
+    form->pace = (int32_t)a.pace;
+    form->streams_global_state = has_rows(mode) && waves == 1 && plan_global(a) != nullptr;
     return TABX_OK;
 }
 

@@ -9,9 +9,12 @@ from tests.test_gpu_row_forms import _scene
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("team,zones,E,fused,levels", [
+STREAMED = [
     (10, 8, 14300, True, 0), (16, 3, 9901, True, 0), (1, 5, 84701, True, 0), (1, 5, 84701, False, 0),
-    (12, 0, 13700, True, 0), (10, 8, 14300, True, 61), (20, 1, 8200, True, 7)])
+    (12, 0, 13700, True, 0), (10, 8, 14300, True, 61), (20, 1, 8200, True, 7)]
+
+
+@pytest.mark.parametrize("team,zones,E,fused,levels", STREAMED)
 def test_streamed_global_state(team, zones, E, fused, levels):
     rows = levels or E
     w, sc = _scene(team, zones, rows)

@@ -24,6 +24,7 @@ HELD = [
     (_kernel(2, 0, 1, 1, 0, 0), 4), (_kernel(2, 0, 0, 0, 0, 1), 3), (_kernel(2, 0, 1, 0, 0, 1), 3),
     (_kernel(2, 1, 1, 0, 0, 1), 3), (_kernel(2, 0, 1, 0, 2, 0), 5), (_kernel(2, 0, 1, 0, 3, 0), 5),
     (_kernel(2, 1, 1, 0, 2, 0), 5), (_kernel(2, 0, 1, 1, 2, 0), 4), (_kernel(2, 0, 1, 1, 3, 0), 4),
+    (_kernel(2, 0, 0, 0, 2, 0), 5), (_kernel(2, 0, 0, 0, 3, 0), 5),
 ]
 
 
@@ -52,8 +53,11 @@ def test_paced_rows(team, zones, E, over):
     _rollout(w, E, 2, True, scenario=sc, max_steps=5, **over)
 
 
+SCRIPTED = [(10, 8, 4000), (40, 0, 1200)]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("team,zones,E", [(10, 8, 4000), (40, 0, 1200)])
+@pytest.mark.parametrize("team,zones,E", SCRIPTED)
 def test_paced_rows_with_deciding_units(team, zones, E):
     w, sc = _scene(team, zones, E)
     print(f"[gpu] paced scripted N={2 * team} Z={zones} E={E}", flush=True)

@@ -1,0 +1,70 @@
+"""Which form of the row writers the GPU tests of these forms select (host only): a moved threshold must not leave
+a form without its test."""
+import ctypes as C
+
+import pytest
+
+from paper_2602_01665_amd import binding as B
+from paper_2602_01665_amd import inputs as I
+from tests import test_gpu_global_stream as stream
+from tests import test_gpu_shared_lines as shared
+from tests import test_pace as pace
+
+NONE, OWN, SHARED, CARRIED = -1, 0, 1, 2        # TabxRowForm.lines
+
+
+def _form(N, Z, E, call="step_observe", **over):
+    return B.tabx_row_form(B.make_params(I.custom_params(N, 40.0, 0, Z, num_envs=E, **over)), call)
+
+
+def test_errors_and_calls_without_rows():
+    form = B.TabxRowForm()
+    p = B.make_params(I.custom_params(20, 40.0, 0, 8, num_envs=4000))
+    assert B._lib.tabx_row_form(C.byref(p), 7, C.byref(form)) == -2
+    assert B._lib.tabx_row_form(C.byref(p), 3, None) == -1
+    assert B._lib.tabx_row_form(None, 3, C.byref(form)) == -1
+    for call in ("reset", "step", "heuristic_actions"):
+        assert B.tabx_row_form(p, call) == dict(lines=NONE, pace=0, streams_global_state=0), call
+
+
+SHARED_ONLY = {(20, 3, 1901), (60, 9, 401), (10, 1, 17003), (4, 7, 56001)}
+IN_REGISTERS = {(72, 2, 700)}
+
+
+def test_ticks_with_shared_lines():
+    for team, Z, E in shared.BIG:
+        key = (2 * team, Z, E)
+        want = SHARED if key in SHARED_ONLY else NONE if key in IN_REGISTERS else CARRIED
+        assert _form(*key)["lines"] == want, key
+
+
+def test_other_calls_with_shared_lines():
+    assert [_form(2 * t, Z, E, "observe")["lines"] for t, Z, E in shared.OBSERVED] == \
+        [CARRIED, SHARED, CARRIED, CARRIED, CARRIED]
+    assert {_form(2 * t, Z, E, "scripted_step_observe")["lines"] for t, Z, E in shared.SCRIPTED} == {CARRIED}
+    assert [_form(N, Z, E)["lines"] for N, Z, E in shared.ODD] == \
+        [CARRIED, CARRIED, CARRIED, CARRIED, CARRIED, CARRIED, SHARED, SHARED]
+
+
+def test_paced_launches():
+    for team, Z, E, over in pace.PACED:
+        assert _form(2 * team, Z, E, **over)["pace"] > 0, (team, Z, E)
+    for team, Z, E in pace.SCRIPTED:
+        assert _form(2 * team, Z, E, "scripted_step_observe")["pace"] > 0, (team, Z, E)
+
+
+@pytest.mark.parametrize("N,Z,E,paced", [
+    (20, 8, 1698, False), (20, 8, 1699, True), (64, 0, 190, False), (64, 0, 191, True),      # 50 MB of rows
+    (20, 8, 6144, True), (20, 8, 6145, False), (64, 0, 1280, True), (64, 0, 1281, False),    # one generation
+    (32, 0, 1024, False), (32, 0, 1025, True),                   # flushes per wavefront
+    (128, 0, 670, False), (128, 0, 671, True)])                  # two wavefronts, units in registers
+def test_edges_of_the_pace(N, Z, E, paced):
+    assert (_form(N, Z, E)["pace"] > 0) == paced
+
+
+def test_streamed_global_states():
+    for team, Z, E, fused, levels in stream.STREAMED:
+        over = dict(num_levels=levels) if levels else {}
+        call = "step_observe" if fused else "observe"
+        assert _form(2 * team, Z, E, call, **over)["streams_global_state"] == 1, (team, Z, E)
+    assert _form(20, 8, 14000)["streams_global_state"] == 0
