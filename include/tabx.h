@@ -367,7 +367,8 @@ typedef struct TabxRowForm {
     int32_t lines;                   /* tiles of rows and 128-byte lines: 0 each tile starts on one,
                                         1 neighbours share one, 2 a wavefront hands a shared one on
                                         to its next tile; -1: no tiles (units in registers, no rows) */
-    int32_t pace;                    /* least time from one flush to the next, in 1/16 of 10 ns; 0: none */
+    int32_t pace;                    /* a wavefront's flush n begins no sooner than n times this after its
+                                        first, in 1/16 of 10 ns; 0: at will */
     int32_t streams_global_state;    /* 1: the global state goes past the caches                   */
 } TabxRowForm;
 int tabx_row_form(const TabxParams *params, int call, TabxRowForm *form);

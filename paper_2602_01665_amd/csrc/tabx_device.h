@@ -64,8 +64,8 @@ struct KArgs {
     int       copy_passes;         // ... store passes of one flush, <= kMaxPasses
     int       rows_per_flush;      // ... R: consecutive rows of an env staged before they are stored
     int       obs_per_chunk;       // ... observers per workgroup that shares an env group
-    unsigned  pace;                // least time from one flush of a wavefront to the next, in 1/16 of a tick of the
-                                   //     constant clock (10 ns); 0: none
+    unsigned  pace;                // a wavefront begins its flush n (from 0) no sooner than n times this after its
+                                   //     first, in 1/16 of a tick of the constant clock (10 ns); 0: at will
     float     inv_cell;            // 1 / cell_size, used only when that is exact (power of two)
     uint32_t  cells;               // FAST_CELL: cells of one row's grid
     uint32_t  flags;               // Flag bits
@@ -90,8 +90,8 @@ enum Flag : uint32_t {
     EARLY_CELL = 512,              // a cell grid, and nothing but its own motion decides where a unit is
 };
 
-// A paced wavefront (see plan_pace, tabx_kernels.hip): the low word of the constant clock (10 ns) when it starts,
-// and the wait until `due` ticks after that; nothing where `pace` / `due` is 0.  One block of scalar
+// A paced wavefront (see plan_pace, tabx_kernels.hip): the low word of the constant clock (10 ns) when it starts
+// its rows, and the wait until `due` ticks after that; nothing where `pace` / `due` is 0.  One block of scalar
 // instructions each: as a loop of the compiler's, the branches cost launches without a pace up to 5 %.
 __device__ __forceinline__ unsigned pace_start(unsigned pace)
 {

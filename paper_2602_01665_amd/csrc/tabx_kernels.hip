@@ -492,9 +492,10 @@ static int wavefronts_per_simd(Mode mode, const KArgs &a, int waves)
 // wavefronts that share their SIMD with fewer others.  The launch then ends with the slow ones alone, which
 // cannot use what has become free (64v64 x 1024: workgroups of even XCDs end at 158 ... 173 us, of odd ones at
 // 184 ... 203).  A flush that is not due yet waits, and what it would have taken goes to those behind.
-// Measured, without / with: 64v64 x 1024 209 / 199 us, x 1300 278 / 250, 40v40 x 1500 136 / 124, 64v64 x 400
-// 100 / 89, 10v10 x 8192 with collisions and ellipses 62.5 / 58, 10v10 x 4000 with zones 35.2 / 30.0, 32v32 x 700
-// 44.1 / 36.5.  With several generations, workgroups of all ages side by side even each other out, and a pace
+// Measured, without / with: 64v64 x 1024 211.5 / 198.5 us, x 1300 278 / 247.5, 40v40 x 1500 135 / 122, 64v64 x 400
+// 100 / 89, 10v10 x 8192 with collisions and ellipses 60.5 / 54.5, 10v10 x 4000 with zones 35 / 28.5, 32v32 x 700
+// 44 / 36.5.  (The wait is between flushes only: with one after the last as well the masks, the decisions of
+// scripted units and the workgroup's end came later, 57, 29.2 and 37.4 in the last three.)  With several generations, workgroups of all ages side by side even each other out, and a pace
 // only costs (10v10 x 16384 102 / 108 ... 124 us).
 static void plan_pace(Mode mode, KArgs &a, int waves, size_t lds)
 {

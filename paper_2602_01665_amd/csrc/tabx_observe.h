@@ -447,8 +447,9 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         // (8 KB rows: the wavefront lets its row land before it goes on, which keeps the XCDs together,
         // as in tabx_observe_packed.h: 64v64 x 512 125 us without, 117 with)
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        // (a launch that is one generation of workgroups: see plan_pace, tabx_kernels.hip)
-        pace_wait(first_row, (due += pace) >> 4);
+        // (a launch that is one generation of workgroups: see plan_pace, tabx_kernels.hip; what follows the last
+        // tile waits for nothing)
+        if (tile + tile_step < tile_end && (tile + tile_step) * T < rows) pace_wait(first_row, (due += pace) >> 4);
     }
     if (WAVES == 1 && vis_mask) {
         // lane l writes row l of the group, if it was this wavefront's: row l % S of pass l / S

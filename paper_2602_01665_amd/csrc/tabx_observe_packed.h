@@ -361,7 +361,7 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
         // rates and the launch lasts as long as the slowest (64v64 x 1024: 217 us against 208).
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         // ... and goes no faster than HBM takes all workgroups' rows together (plan_pace, tabx_kernels.hip)
-        pace_wait(first_row, (due += pace) >> 4);
+        if (i0 + R < i_end) pace_wait(first_row, (due += pace) >> 4);
     }
 
     TABX_STAMP(4);
