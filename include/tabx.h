@@ -137,6 +137,12 @@ typedef struct TabxParams {
     int32_t  dynamics;
     float    move_gain;           /* per time unit; move_gain * dt in (0, 1] is sensible       */
     float    restitution;         /* coefficient of restitution e, normally in [0, 1]          */
+    /* 0 (default): the launch has the machine to itself.  Non-zero: other work runs beside it, such
+     * as another part of the batch or a learner's kernels on a second stream.  A launch whose
+     * workgroups are all resident from the start spreads its stores over the time HBM takes for all
+     * of them; workgroups that had to wait for a place would be spread over that time again.
+     * Results never depend on it.  tabx_part sets it for a part of a batch. */
+    int32_t  shared_machine;
 } TabxParams;
 
 /* The scenario: unit specifications and zones (the unit and zone axes of the
@@ -323,8 +329,8 @@ int tabx_scripted_step_observe(const TabxParams *params, const TabxScenario *sce
 
 /* Host-only helper for processing a batch in parts (see TabxParams.env_id_offset): fills
  * part_params / part_scenario / part_state with the structs of the envs [first_env,
- * first_env + count) of the given batch: num_envs = count, env_id_offset advanced, every
- * per-unit pointer advanced by first_env * N elements, every per-env pointer by first_env,
+ * first_env + count) of the given batch: num_envs = count, env_id_offset advanced,
+ * shared_machine set unless it is the whole batch, every per-unit pointer advanced by first_env * N elements, every per-env pointer by first_env,
  * terrain and zone_desc by first_env rows (scenario arrays are left alone when they are a bank
  * of levels); NULL pointers stay NULL.  The caller advances the other arrays the same way:
  * actions, rewards, action_mask, controlled and the policy memory by first_env * N, dones by

@@ -48,7 +48,8 @@ class TabxParams(C.Structure):
                [("zone_shapes", C.c_int32), ("num_levels", C.c_int32), ("level_seed", C.c_uint32),
                 ("hurtbox_cone", C.c_int32), ("hit_all", C.c_int32),
                 ("env_id_offset", C.c_int32), ("dynamics", C.c_int32),
-                ("move_gain", C.c_float), ("restitution", C.c_float)]
+                ("move_gain", C.c_float), ("restitution", C.c_float),
+                ("shared_machine", C.c_int32)]
 
 
 class TabxScenario(C.Structure):
@@ -336,6 +337,7 @@ class TabxEnv:
                        env_id_offset=self.p.get("env_id_offset", 0) + start)
             v.params, v.scenario, v.state = tabx_part(self.params, self.scenario, self.state,
                                                       start, count)
+            v.p["shared_machine"] = v.params.shared_machine
             names = list(SCENARIO_FLOAT) + ["team", "enabled"]
             v.sc = {n: (self.sc[n] if L > 0 else unit(self.sc[n])) for n in names}
             v.sc["terrain"] = self.sc["terrain"] if L > 0 else env(self.sc["terrain"])

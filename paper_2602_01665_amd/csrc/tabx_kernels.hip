@@ -501,6 +501,12 @@ static void plan_pace(Mode mode, KArgs &a, int waves, size_t lds)
 {
     a.pace = 0;
     if (!has_rows(mode) || a.obs_chunks > 1) return;
+    // Beside other work (unpaced / paced): a workgroup that had to wait for its place cannot see that it is late and
+    // would take all of the launch's time once more (10v10 with collisions and ellipses, 2 x 8192 on two streams
+    // 91 / 95.5 us, x 8192 beside a product of 2048 x 2048 matrices 74 / 88; scripted 10v10 with zones 2 x 4000
+    // 43.6 / 46).  Envs of two wavefronts take about that time per row by themselves and keep the gain (64v64 2 x
+    // 512 233 / 222, x 1024 beside the product 218 / 208).
+    if (a.p.shared_machine && waves == 1) return;
     // Few rows: such a launch is mostly its start (5v5 x 6000, 38 MB: 13.4 us, 14.0 paced; x 8000 17.8 and 17.1).
     const double bytes = 4.0 * a.obs_dim * a.p.num_units * a.p.num_envs;
     if (bytes < 50e6) return;
@@ -1021,6 +1027,7 @@ int tabx_part(const TabxParams *p, const TabxScenario *sc, const TabxState *st, 
     *pp = *p;
     pp->num_envs = count;
     pp->env_id_offset = p->env_id_offset + first_env;
+    if (count < p->num_envs) pp->shared_machine = 1;
     *psc = *sc;
     if (p->num_levels == 0) {          // one scenario row per env: the part starts at its own
         const float **f[] = {&psc->init_x, &psc->init_y, &psc->init_theta, &psc->hmax, &psc->radius,

@@ -27,7 +27,8 @@ def build() -> str:
 
 
 def is_stale() -> bool:
-    return (not os.path.exists(BINARY)) or os.path.getmtime(BINARY) < os.path.getmtime(SOURCE)
+    sources = (SOURCE, os.path.join(_ROOT, "include", "tabx.h"))
+    return (not os.path.exists(BINARY)) or os.path.getmtime(BINARY) < max(map(os.path.getmtime, sources))
 
 
 if __name__ == "__main__":

@@ -25,6 +25,7 @@ def _same(a, b, what):
     ("c3_16384env_10v10", 50, 3, 4),          # ragged parts, level bank, scripted adversaries
     ("c3e_16384env_10v10_ellipses", 37, 2, 0),
     ("c2_4096env_5v5", 4096, 2, 0),           # parts larger than one residency round
+    ("c3_16384env_10v10", 8000, 2, 0),        # parts that would be paced if each were alone
     ("c5_1024env_64v64", 6, 2, 3),
 ])
 def test_parts_equal_the_whole_batch(name, E, k, levels):

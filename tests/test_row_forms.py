@@ -68,3 +68,17 @@ def test_streamed_global_states():
         call = "step_observe" if fused else "observe"
         assert _form(2 * team, Z, E, call, **over)["streams_global_state"] == 1, (team, Z, E)
     assert _form(20, 8, 14000)["streams_global_state"] == 0
+
+
+def test_a_part_of_a_batch_is_not_held_to_a_pace():
+    """Its launch shares the machine with the other parts': a workgroup of it may start late."""
+    for team, Z, E, over in pace.PACED:
+        p = B.make_params(I.custom_params(2 * team, 40.0, 0, Z, num_envs=2 * E, **over))
+        for first, count, part in ((0, E, True), (E, E, True), (0, 2 * E, False)):
+            mine = B.tabx_part(p, B.TabxScenario(), B.TabxState(), first, count)[0]
+            assert mine.shared_machine == int(part)
+            held = B.tabx_row_form(mine, "step_observe")["pace"] > 0
+            if part:
+                assert held == (2 * team > 64), (team, Z, E)
+    p.shared_machine = 1                        # (a part of a part, and a caller's own setting)
+    assert B.tabx_part(p, B.TabxScenario(), B.TabxState(), 0, p.num_envs)[0].shared_machine == 1
