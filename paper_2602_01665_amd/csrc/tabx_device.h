@@ -45,6 +45,7 @@ struct KArgs {
     int       passes_per_tile;     // T / S
     uint32_t  line;                // a tile's image starts where its first row does in memory, modulo line + 1 floats
     int       lines;               // enum Lines
+    int       in_turn;             // the tiles are dealt to the wavefronts one by one, not in runs
     int       stage_floats;        // a wavefront's staging area in dynamic LDS (they come first)
     int       zone_chunks;         // ZC: 16-byte chunks of the zone part of a row
     unsigned  magic_n, magic_zc, magic_s, magic_tc;   // x / N, / ZC, / S, / (4 + ZC) as multiplications (see quotient)

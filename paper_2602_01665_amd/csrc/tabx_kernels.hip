@@ -188,13 +188,8 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
             }
             const int first = P.chunk * a.tiles_per_chunk;
             const int end = first + a.tiles_per_chunk < a.tiles ? first + a.tiles_per_chunk : a.tiles;
-            // Each wavefront writes one contiguous run of the group's tiles.  Taken in turn, tile by tile,
-            // batches whose rows are a power of two bytes long lost a tenth of the store rate (16v16 without
-            // zones x 12000 155 us in turn, 137 like this; 32v32 x 6000 319 and 295).
-            // Odd numbers of units up to 20 go in turn: runs cost 9v8 with zones (x 4000 29.1 us in turn, 30.0 in
-            // runs; x 5003 32.7 and 34.4; x 20000 94.6 and 96.6); 5, 7, 13 and 21 units are level, and wider
-            // odd rows are better in runs (30v29 x 5000 232 us in turn, 229 in runs).
-            const bool in_turn = WAVES == 1 && DO_STEP && (a.p.num_units & 1) && a.p.num_units < 21;
+            // (see plan_shape)
+            const bool in_turn = WAVES == 1 && DO_STEP && a.in_turn;
             const int share = (end - first + WAVES * TWIN - 1) / (WAVES * TWIN);
             const int begin = first + (in_turn ? wave : wave * share), step = in_turn ? WAVES * TWIN : 1;
             const int stop = !in_turn && begin + share < end ? begin + share : end;
@@ -530,8 +525,7 @@ static void plan_pace(Mode mode, KArgs &a, int waves, size_t lds)
     // wavefronts 6.1.
     const bool lines = a.obs_dim % 32 == 0, cached = bytes <= (double)kLastLevelCacheBytes;
     double rate = lines ? (cached ? 7.0 : 6.0) : (cached ? 6.0 : 5.6);
-    const bool handed_on = a.lines == LINES_CARRIED && !((a.p.num_units & 1) && a.p.num_units < 21);   // (not in turn)
-    if (a.obs_dim % 4 != 0) rate = handed_on ? 6.5 : 5.2;
+    if (a.obs_dim % 4 != 0) rate = a.lines == LINES_CARRIED ? 6.5 : 5.2;
     if (a.packed) rate = waves == 2 && lines ? 6.1 : 5.85;
     const double ticks = bytes / (rate * 1e12) * 100e6 / flushes;
     // Two wavefronts with the units in registers take 0.9 us per row by themselves, and looking at the clock
@@ -799,12 +793,22 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     const size_t tile = (size_t)a.rows_per_tile * a.obs_dim;
     a.line = whole_passes(tile + 30) == whole_passes(tile + 2) ||
                      (waves == 1 && bytes > (double)kLastLevelCacheBytes) ? 31 : 3;
-    // Shared lines are handed on from where the launch is mostly rows (see plan_pace), and beyond that cache from
-    // four tiles per wavefront on (5v5 with 3 zones x 65536, observed, two or three: 129 us, 134 handed on; 8v7 with
-    // one x 20000, four: 67 and 62.5).
+    // Each wavefront writes one contiguous run of the group's tiles.  Taken in turn, tile by tile,
+    // batches whose rows are a power of two bytes long lost a tenth of the store rate (16v16 without
+    // zones x 12000 155 us in turn, 137 like this; 32v32 x 6000 319 and 295).
+    // Ticks of odd numbers of units up to 20 go in turn: runs cost 9v8 with zones (x 4000 29.1 us in turn, 30.0 in
+    // runs; x 5003 32.7 and 34.4; x 20000 94.6 and 96.6; all with tiles that share lines and hand none on); 5, 7, 13
+    // and 21 units are level, and wider odd rows are better in runs (30v29 x 5000 232 us in turn, 229 in runs).
+    a.in_turn = rows && waves == 1 && a.twin && mode != MODE_OBSERVE && (N & 1) && N < 21;
+    // Shared lines are handed on where a wavefront has neighbouring tiles, from where the launch is mostly rows (see
+    // plan_pace), and beyond that cache from four tiles per wavefront on (5v5 with 3 zones x 65536, observed, two or
+    // three: 129 us, 134 handed on; 8v7 with one x 20000, four: 67 and 62.5).  Where none can be, the code that hands
+    // them on costs 1 % (9v8 with 7 ellipses x 5003 34.0 us, 33.5 without;
+    // scripted 8v7 with 5 x 10000 52.2 and 51.6).
     const int per_wavefront = a.twin ? a.tiles_per_chunk / (waves * a.twin) : 0;
+    const bool neighbours = !a.in_turn && a.tiles_per_chunk > waves * a.twin;
     if (a.obs_dim % 4 == 0 && tile % 32 == 0 && G * N * a.obs_dim % 32 == 0) a.lines = LINES_OWN;
-    else if (a.line == 31 && bytes > 50e6 && (per_wavefront >= 4 || bytes <= (double)kLastLevelCacheBytes)) a.lines = LINES_CARRIED;
+    else if (neighbours && a.line == 31 && bytes > 50e6 && (per_wavefront >= 4 || bytes <= (double)kLastLevelCacheBytes)) a.lines = LINES_CARRIED;
     else a.lines = LINES_SHARED;
     return waves;
 }

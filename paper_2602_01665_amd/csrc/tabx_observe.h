@@ -399,8 +399,9 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         // stream the finished rows: LDS chunk -> one 16-byte store, 1 KB per instruction
         float *const out = obs + (row0 + f0) * D - pad;
         const int floats = pad + rows_here * D;
-        // LINES_CARRIED: a line that two tiles share goes out with the second one, if both are this wavefront's.
-        const bool carry = LINES == LINES_CARRIED && tile_step == 1 && tile + 1 < tile_end && (tile + 1) * T < rows && floats >= 32;
+        // LINES_CARRIED: a line that two tiles share goes out with the second one, if both are this wavefront's
+        // (whose tiles are neighbours: plan_shape).
+        const bool carry = LINES == LINES_CARRIED && tile + 1 < tile_end && (tile + 1) * T < rows && floats >= 32;
         const int chunks = carry ? (floats & ~31) >> 2 : floats >> 2;
         const int first = carried ? 0 : (pad + 3) >> 2;        // the first chunk that is the tile's alone
         const float4 *src = reinterpret_cast<const float4 *>(buf) + lane;

@@ -27,7 +27,7 @@ def test_errors_and_calls_without_rows():
         assert B.tabx_row_form(p, call) == dict(lines=NONE, pace=0, streams_global_state=0), call
 
 
-SHARED_ONLY = {(20, 3, 1901), (60, 9, 401), (10, 1, 17003), (4, 7, 56001)}
+SHARED_ONLY = {(20, 3, 1901), (60, 9, 401), (10, 1, 17003), (4, 7, 56001), (2, 1, 300007)}
 IN_REGISTERS = {(72, 2, 700)}
 
 
@@ -43,7 +43,28 @@ def test_other_calls_with_shared_lines():
         [CARRIED, SHARED, CARRIED, CARRIED, CARRIED]
     assert {_form(2 * t, Z, E, "scripted_step_observe")["lines"] for t, Z, E in shared.SCRIPTED} == {CARRIED}
     assert [_form(N, Z, E)["lines"] for N, Z, E in shared.ODD] == \
-        [CARRIED, CARRIED, CARRIED, CARRIED, CARRIED, CARRIED, SHARED, SHARED]
+        [SHARED, SHARED, CARRIED, CARRIED, CARRIED, SHARED, SHARED, SHARED]
+
+
+@pytest.mark.parametrize("call", ["step_observe", "scripted_step_observe", "policy_step_observe", "observe"])
+def test_lines_are_handed_on_only_between_tiles_of_one_wavefront(call):
+    """Ticks of odd numbers of units up to 20 deal their tiles in turn, and a wavefront with one tile has nobody to
+    hand a line on to."""
+    handed_on = 0
+    for N in range(1, 65):
+        for Z in (0, 1, 3, 7, 8):
+            for E in (2001, 5003, 12001, 60001, 300007):
+                if 4 * N * (16 * N + 6 * Z) * E > 4e9:
+                    continue
+                info = B.tabx_launch_info(B.make_params(I.custom_params(N, 40.0, 0, Z, num_envs=E)), call)
+                if _form(N, Z, E, call)["lines"] != CARRIED:
+                    continue
+                handed_on += 1
+                assert call == "observe" or N % 2 == 0 or N > 20, (N, Z, E)
+                share = info["workgroups"] // (8 * -(-E // (8 * info["envs_per_workgroup"])))   # per env group
+                tiles = -(-info["envs_per_workgroup"] * N // info["rows_per_flush"])
+                assert -(-tiles // share) > info["wavefronts_per_env_group"], (N, Z, E, info)
+    assert handed_on > 50
 
 
 def test_paced_launches():
