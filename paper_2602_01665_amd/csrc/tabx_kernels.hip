@@ -512,6 +512,10 @@ static void plan_pace(Mode mode, KArgs &a, int waves, size_t lds)
                                       : (policy ? sizeof(Shared<2, false, true>) : sizeof(Shared<2, false, false>));
     const int by_simd = 4 * wavefronts_per_simd(mode, a, waves) / w, by_lds = kLdsPerCuBytes / (int)lds_granules(fixed + lds);
     if (a.num_groups > kComputeUnits * (by_simd < by_lds ? by_simd : by_lds)) return;
+    // Tiles of envs of two wavefronts that share lines go out at 3.9 to 4.4 TB/s at most, and looking at the clock
+    // costs them 1 % (33v33 with 7 zones x 1000 77.8 us, 78.8 paced, 64v64 with 3 x 400 120.0 and 121.1); rows of
+    // whole chunks whose lines are handed on reach the pace (64v64 with 2 x 400 96.5, 92.6 paced).
+    if (waves == 2 && !a.packed && (a.lines == LINES_SHARED || a.obs_dim % 4 != 0)) return;
     // Few flushes per wavefront: no time to fall behind in (tiles, 4v4 x 14000, four each: 18.4 us, 19.0 paced; units
     // in registers, 5v5 x 16384, five each: 30.7 and 30.6 ... 33).
     const int flushes = a.packed ? (a.p.num_units + a.rows_per_flush - 1) / a.rows_per_flush : (a.tiles + w - 1) / w;
@@ -807,8 +811,14 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     // scripted 8v7 with 5 x 10000 52.2 and 51.6).
     const int per_wavefront = a.twin ? a.tiles_per_chunk / (waves * a.twin) : 0;
     const bool neighbours = !a.in_turn && a.tiles_per_chunk > waves * a.twin;
+    // Envs of two wavefronts wait for their chain of rows until HBM takes no more, and the moves of a handed-on line
+    // are part of it: rows of whole chunks, which gain less than those that end within one, hand on beyond five
+    // quarters of the cache (shared / handed on and paced: 50v50 with 2 zones x 300 57.5 / 60.3 us, x 400, 258 MB,
+    // 66.9 / 69.9, x 512, 330 MB, 75.8 / 75.0, 64v64 with 2 x 256 78.4 / 80.2, x 400, 422 MB, 101 / 92.6; half a
+    // chunk at the end: 40v40 with one x 300, 123 MB, 60.2 / 58.1, 50v50 with 3 x 700 114 / 110).
+    const bool worth = bytes > (waves == 2 && a.obs_dim % 4 == 0 ? 1.25 * (double)kLastLevelCacheBytes : 50e6);
     if (a.obs_dim % 4 == 0 && tile % 32 == 0 && G * N * a.obs_dim % 32 == 0) a.lines = LINES_OWN;
-    else if (neighbours && a.line == 31 && bytes > 50e6 && (per_wavefront >= 4 || bytes <= (double)kLastLevelCacheBytes)) a.lines = LINES_CARRIED;
+    else if (neighbours && a.line == 31 && worth && (per_wavefront >= 4 || bytes <= (double)kLastLevelCacheBytes)) a.lines = LINES_CARRIED;
     else a.lines = LINES_SHARED;
     return waves;
 }

@@ -39,7 +39,7 @@ def test_wavefronts_a_simd_holds(kernels):  # noqa: F811
 PACED = [
     # team size, zone slots, envs, overrides
     (10, 8, 4000, {}), (12, 3, 3000, {}), (16, 0, 1300, {}), (32, 0, 500, {}),   # tiles: two, four, eight wavefronts
-    (40, 0, 400, {}), (33, 7, 1000, {}),                                         # ... of envs of two
+    (40, 0, 400, {}), (33, 7, 1000, {}), (64, 2, 400, {}),                       # ... of envs of two
     (40, 0, 1200, {}), (33, 7, 1400, {}),                                        # two wavefronts, units in registers
     (10, 8, 8192, dict(collision_alpha=0.8)),                                    # one
 ]
