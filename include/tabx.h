@@ -375,6 +375,7 @@ typedef struct TabxRowForm {
                                         to its next tile; -1: no tiles (units in registers, no rows) */
     int32_t pace;                    /* a wavefront's flush n begins no sooner than n times this after its
                                         first, in 1/16 of 10 ns; 0: at will */
+    int32_t wavefronts_per_simd;     /* how many the kernel's vector registers let a SIMD hold; -1: no rows */
     int32_t streams_global_state;    /* 1: the global state goes past the caches                   */
 } TabxRowForm;
 int tabx_row_form(const TabxParams *params, int call, TabxRowForm *form);

@@ -161,7 +161,7 @@ def tabx_launch_info(params: TabxParams, call: str) -> dict:
 
 
 class TabxRowForm(C.Structure):
-    _fields_ = [(n, C.c_int32) for n in ("lines", "pace", "streams_global_state")]
+    _fields_ = [(n, C.c_int32) for n in ("lines", "pace", "wavefronts_per_simd", "streams_global_state")]
 
 
 def tabx_row_form(params: TabxParams, call: str) -> dict:

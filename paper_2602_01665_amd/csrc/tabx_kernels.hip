@@ -603,6 +603,8 @@ static hipError_t launch_mode(Mode mode, KArgs a, hipStream_t stream)
             return enqueue(tabx_tick_kernel<2, false, true, true, true, 3>, grid, block, lds, stream, a);
         if (a.twin)
             return enqueue(tabx_tick_kernel<2, false, true, true, true, 2>, grid, block, lds, stream, a);
+        if (a.even)
+            return enqueue(tabx_tick_kernel<2, false, true, true, true, 0, true>, grid, block, lds, stream, a);
         return enqueue(tabx_tick_kernel<2, false, true, true, true>, grid, block, lds, stream, a);
     }
     return hipErrorInvalidValue;
@@ -770,18 +772,21 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
         // leaves some SIMDs with four wavefronts and some with two.  (33v33, three / four: x 1200 91 / 86
         // us, x 1500 93 / 98, x 2048 162 / 127, x 2500 176 / 189, x 3000 185 / 202, x 4000 258 / 240.)
         // It also takes the rows that end on half a chunk: their code would cost the other kernel 2 us.  The
-        // tick with the policy as a scan stage likewise (x 1500 8 % between the two); the scripted tick's
-        // kernel never has room for four.
-        if (mode != MODE_SCRIPTED_STEP_OBSERVE && !a.twin) {
+        // tick with the policy as a scan stage likewise (x 1500 8 % between the two), and the scripted tick, both
+        // of whose kernels have that code (three / four: x 1300 94.8 / 101.7 us, x 1500 97.2 / 105.0, x 2048
+        // 170 / 121, x 3000 199.5 / 209, x 4000 271 / 253, with 7 zones x 1500 103.5 / 111, 40v40 x 1800 218 / 153).
+        if (!a.twin) {
             const size_t fixed = mode == MODE_POLICY_STEP_OBSERVE ? sizeof(Shared<2, false, true>)
                                                                   : sizeof(Shared<2, false, false>);
-            const size_t lds = fixed + 16 * (size_t)(row_chunks + half + 64 * a.copy_passes);
+            const bool scripted = mode == MODE_SCRIPTED_STEP_OBSERVE;
+            const size_t lds = fixed + 16 * (size_t)(row_chunks + half + 64 * a.copy_passes) +
+                               (scripted ? sizeof(ScriptLds<2>) : 0);
             const int held = kLdsPerCuBytes / (int)lds_granules(lds);
             const auto rounds = [&](int envs) {
                 const int at_once = (envs < held ? envs : held) * kComputeUnits;
                 return (E + at_once - 1) / at_once;
             };
-            a.even = a.obs_dim % 4 != 0 || (E > 5 * kComputeUnits && rounds(6) == rounds(8));
+            a.even = (!scripted && a.obs_dim % 4 != 0) || (E > 5 * kComputeUnits && rounds(6) == rounds(8));
         }
     }
     a.packed = rows && a.twin == 0;
@@ -1115,6 +1120,7 @@ int tabx_row_form(const TabxParams *p, int call, TabxRowForm *form)
     a.st.global_state = &any;
     form->lines = has_rows(mode) && !a.packed ? a.lines : -1;
     form->pace = (int32_t)a.pace;
+    form->wavefronts_per_simd = has_rows(mode) ? wavefronts_per_simd(mode, a, waves) : -1;
     form->streams_global_state = has_rows(mode) && waves == 1 && plan_global(a) != nullptr;
     return TABX_OK;
 }

@@ -47,7 +47,8 @@ def test_rows(team, zones, E, ticks, fused):
 
 
 DECIDING = [(8, 3, 9, 8), (25, 0, 7, 6), (10, 8, 50, 6), (31, 5, 300, 3), (10, 8, 2100, 3), (33, 0, 520, 3), (33, 3, 520, 3), (50, 4, 5, 6), (64, 16, 3, 6),
-            (33, 3, 1030, 2), (33, 0, 1290, 2), (64, 0, 20, 4), (10, 8, 2400, 2)]
+            (33, 3, 1030, 2), (33, 0, 1290, 2), (64, 0, 20, 4), (10, 8, 2400, 2),
+            (33, 7, 1290, 2), (40, 1, 1540, 2)]
 
 
 @pytest.mark.parametrize("form", ["scripted", "scan"])

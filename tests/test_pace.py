@@ -24,7 +24,7 @@ HELD = [
     (_kernel(2, 0, 1, 1, 0, 0), 4), (_kernel(2, 0, 0, 0, 0, 1), 3), (_kernel(2, 0, 1, 0, 0, 1), 3),
     (_kernel(2, 1, 1, 0, 0, 1), 3), (_kernel(2, 0, 1, 0, 2, 0), 5), (_kernel(2, 0, 1, 0, 3, 0), 5),
     (_kernel(2, 1, 1, 0, 2, 0), 5), (_kernel(2, 0, 1, 1, 2, 0), 4), (_kernel(2, 0, 1, 1, 3, 0), 4),
-    (_kernel(2, 0, 0, 0, 2, 0), 5), (_kernel(2, 0, 0, 0, 3, 0), 5),
+    (_kernel(2, 0, 0, 0, 2, 0), 5), (_kernel(2, 0, 0, 0, 3, 0), 5), (_kernel(2, 0, 1, 1, 0, 1), 3),
 ]
 
 

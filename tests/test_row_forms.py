@@ -24,7 +24,7 @@ def test_errors_and_calls_without_rows():
     assert B._lib.tabx_row_form(C.byref(p), 3, None) == -1
     assert B._lib.tabx_row_form(None, 3, C.byref(form)) == -1
     for call in ("reset", "step", "heuristic_actions"):
-        assert B.tabx_row_form(p, call) == dict(lines=NONE, pace=0, streams_global_state=0), call
+        assert B.tabx_row_form(p, call) == dict(lines=NONE, pace=0, wavefronts_per_simd=-1, streams_global_state=0), call
 
 
 SHARED_ONLY = {(20, 3, 1901), (60, 9, 401), (10, 1, 17003), (4, 7, 56001), (2, 1, 300007)}
@@ -90,6 +90,21 @@ def test_edges_of_the_pace(N, Z, E, paced):
 def test_tiles_of_two_wavefronts(N, Z, E, lines, paced):
     form = _form(N, Z, E)
     assert (form["lines"], form["pace"] > 0) == (lines, paced), form
+
+
+@pytest.mark.parametrize("N,Z,E,held", [
+    (66, 0, 1280, 4), (66, 0, 1281, 3), (66, 0, 1536, 3), (66, 0, 1537, 4), (66, 0, 2048, 4), (66, 0, 2049, 3),
+    (66, 0, 3072, 3), (66, 0, 3073, 4), (128, 0, 1024, 4), (100, 0, 1500, 3)])
+def test_units_in_registers_three_or_four_wavefronts_per_simd(N, Z, E, held):
+    for call in ("step_observe", "scripted_step_observe", "policy_step_observe"):
+        assert _form(N, Z, E, call)["wavefronts_per_simd"] == held, call
+
+
+def test_units_in_registers_half_a_chunk():
+    """Only the plain launches need the kernel with three for such rows."""
+    for E, scripted in ((1025, 4), (1281, 3), (2048, 4)):
+        forms = [_form(66, 7, E, c)["wavefronts_per_simd"] for c in ("step_observe", "observe", "scripted_step_observe")]
+        assert forms == [3, 3, scripted], E
 
 
 def test_streamed_global_states():
