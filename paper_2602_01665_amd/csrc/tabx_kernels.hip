@@ -481,6 +481,30 @@ static int wavefronts_per_simd(Mode mode, const KArgs &a, int waves)
     return mode == MODE_SCRIPTED_STEP_OBSERVE ? 4 : 5;
 }
 
+// Whether all workgroups of a launch with rows are resident from its start.
+static bool one_generation(Mode mode, const KArgs &a, int waves, size_t lds)
+{
+    const int w = waves * (a.twin ? a.twin : 1);
+    const bool policy = mode == MODE_POLICY_STEP_OBSERVE;
+    const size_t fixed = !a.packed    ? (waves == 1 ? sizeof(Shared<1, true, true>) : sizeof(Shared<2, true, true, true>))
+                         : waves == 1 ? (policy ? sizeof(Shared<1, false, true>) : sizeof(Shared<1, false, false>))
+                                      : (policy ? sizeof(Shared<2, false, true>) : sizeof(Shared<2, false, false>));
+    const int by_simd = 4 * wavefronts_per_simd(mode, a, waves) / w, by_lds = kLdsPerCuBytes / (int)lds_granules(fixed + lds);
+    return a.num_groups <= kComputeUnits * (by_simd < by_lds ? by_simd : by_lds);
+}
+
+// Flushes of a wavefront, and how long HBM takes, at 6 TB/s, for one of each wavefront of the launch.
+static int flushes_per_wavefront(const KArgs &a, int waves)
+{
+    const int w = waves * (a.twin ? a.twin : 1);
+    return a.packed ? (a.p.num_units + a.rows_per_flush - 1) / a.rows_per_flush : (a.tiles + w - 1) / w;
+}
+
+static double hbm_us_per_flush(const KArgs &a, int waves)
+{
+    return 4.0 * a.obs_dim * a.p.num_units * a.p.num_envs / 6e6 / flushes_per_wavefront(a, waves);
+}
+
 // Holds the wavefronts of a launch to the pace at which HBM takes all their rows together (a.pace).
 // Where all workgroups are resident from the start and live as long as the launch, some of them write faster
 // than others: the even XCDs get more of HBM than the odd ones while both ask for all they can, and so do
@@ -505,21 +529,19 @@ static void plan_pace(Mode mode, KArgs &a, int waves, size_t lds)
     // Few rows: such a launch is mostly its start (5v5 x 6000, 38 MB: 13.4 us, 14.0 paced; x 8000 17.8 and 17.1).
     const double bytes = 4.0 * a.obs_dim * a.p.num_units * a.p.num_envs;
     if (bytes < 50e6) return;
-    const int w = waves * (a.twin ? a.twin : 1);
-    const bool policy = mode == MODE_POLICY_STEP_OBSERVE;
-    const size_t fixed = !a.packed    ? (waves == 1 ? sizeof(Shared<1, true, true>) : sizeof(Shared<2, true, true, true>))
-                         : waves == 1 ? (policy ? sizeof(Shared<1, false, true>) : sizeof(Shared<1, false, false>))
-                                      : (policy ? sizeof(Shared<2, false, true>) : sizeof(Shared<2, false, false>));
-    const int by_simd = 4 * wavefronts_per_simd(mode, a, waves) / w, by_lds = kLdsPerCuBytes / (int)lds_granules(fixed + lds);
-    if (a.num_groups > kComputeUnits * (by_simd < by_lds ? by_simd : by_lds)) return;
+    if (!one_generation(mode, a, waves, lds)) return;
     // Tiles of envs of two wavefronts that share lines go out at 3.9 to 4.4 TB/s at most, and looking at the clock
     // costs them 1 % (33v33 with 7 zones x 1000 77.8 us, 78.8 paced, 64v64 with 3 x 400 120.0 and 121.1); rows of
     // whole chunks whose lines are handed on reach the pace (64v64 with 2 x 400 96.5, 92.6 paced).
     if (waves == 2 && !a.packed && (a.lines == LINES_SHARED || a.obs_dim % 4 != 0)) return;
     // Few flushes per wavefront: no time to fall behind in (tiles, 4v4 x 14000, four each: 18.4 us, 19.0 paced; units
     // in registers, 5v5 x 16384, five each: 30.7 and 30.6 ... 33).
-    const int flushes = a.packed ? (a.p.num_units + a.rows_per_flush - 1) / a.rows_per_flush : (a.tiles + w - 1) / w;
+    const int flushes = flushes_per_wavefront(a, waves);
     if (flushes < (a.packed ? 8 : 5)) return;
+    // ... nor where a wavefront needs longer for a tile than HBM for one of each (by the microseconds that is, unpaced
+    // and paced: tiles that start on lines, 0.67 ... 1.0 level to 2 % slower, 1.0 ... 1.3 2 % faster, then 7; others
+    // 0.9 ... 1.2 1 % slower, 1.2 ... 1.3 level, then 1 to 7 % faster).
+    if (waves == 1 && !a.packed && hbm_us_per_flush(a, waves) < (a.lines == LINES_OWN ? 1.0 : 1.2)) return;
     // The rate, in TB/s of rows, at which a launch is shortest; up to 4 % to either side cost little, 10 % too slow
     // costs that much and 10 % too fast leaves little of the gain.  Tiles: 6.0 (64v64 x 400, 27v28 x 1200); rows of
     // whole 128-byte lines that the last-level cache takes all of 7.0 (6.5 ... 7.8: 32v32 x 700, 8v8 x 5000, 16v16 x
@@ -821,9 +843,20 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     // quarters of the cache (shared / handed on and paced: 50v50 with 2 zones x 300 57.5 / 60.3 us, x 400, 258 MB,
     // 66.9 / 69.9, x 512, 330 MB, 75.8 / 75.0, 64v64 with 2 x 256 78.4 / 80.2, x 400, 422 MB, 101 / 92.6; half a
     // chunk at the end: 40v40 with one x 300, 123 MB, 60.2 / 58.1, 50v50 with 3 x 700 114 / 110).
-    const bool worth = bytes > (waves == 2 && a.obs_dim % 4 == 0 ? 1.25 * (double)kLastLevelCacheBytes : 50e6);
+    const double worth = waves == 2 && a.obs_dim % 4 == 0 ? 1.25 * (double)kLastLevelCacheBytes : 50e6;
+    // Likewise a tick of one generation in which HBM has taken a tile of every wavefront before the next ones are made;
+    // rows of whole chunks gain more, the more so the more lines a wavefront hands on (shared / handed on, in order of
+    // the microseconds that is per tile; whole chunks, up to eight tiles: 13v13 with 4 zones x 1267, 1.38, 18.6 / 19.5,
+    // scripted 63 units x 314, 1.66, 4 % slower, 59 or 60 with 4 x 465, 2.29, 13 % faster; more: scripted 35 x 1275,
+    // 0.93, 32.6 / 35.3, 20v20 with 4 x 583, 1.03, 23.2 / 24.9, 10v10 with 4 x 2906, 1.33, 24.9 / 23.0, 15v15 with 2 x
+    // 2710, 1.78, 49.7 / 37.8; half a chunk at the end: 13v13 with 7 x 1070, 1.21, 20.4 / 21.8, scripted 18v18 with
+    // 7 x 1573, 1.30, 48.3 / 50.1, 53 with 7 x 741, 1.66, 41.2 / 39.4).
+    const bool chain_bound = waves == 1 && a.twin && a.obs_chunks == 1 &&
+                             hbm_us_per_flush(a, waves) < (a.obs_dim % 4 == 0 && flushes_per_wavefront(a, waves) > 8 ? 1.25 : 1.6) &&
+                             one_generation(mode, a, waves, plan_lds(mode, a, waves));
     if (a.obs_dim % 4 == 0 && tile % 32 == 0 && G * N * a.obs_dim % 32 == 0) a.lines = LINES_OWN;
-    else if (neighbours && a.line == 31 && worth && (per_wavefront >= 4 || bytes <= (double)kLastLevelCacheBytes)) a.lines = LINES_CARRIED;
+    else if (neighbours && a.line == 31 && bytes > worth && !chain_bound &&
+             (per_wavefront >= 4 || bytes <= (double)kLastLevelCacheBytes)) a.lines = LINES_CARRIED;
     else a.lines = LINES_SHARED;
     return waves;
 }

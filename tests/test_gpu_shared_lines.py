@@ -13,9 +13,9 @@ BIG = [
     # team size, zone slots, envs (50 MB of rows and more)
     (10, 3, 1901), (10, 4, 2003), (10, 3, 10001), (10, 5, 2500), (16, 5, 1000), (16, 1, 1801), (15, 5, 4801), (12, 2, 2503),
     (11, 7, 2001), (32, 3, 390), (24, 4, 803), (30, 9, 401), (5, 3, 8003), (5, 1, 17003), (2, 7, 56001), (1, 1, 300007),
-    (33, 7, 601), (50, 3, 520), (36, 2, 700)]
+    (33, 7, 601), (50, 3, 520), (36, 2, 700), (10, 5, 4001)]
 OBSERVED = [(5, 3, 8003), (5, 3, 40001), (8, 1, 6001), (11, 7, 2001), (33, 7, 601)]
-SCRIPTED = [(10, 5, 2500), (16, 5, 4100), (24, 4, 803), (33, 3, 700), (28, 2, 801)]
+SCRIPTED = [(10, 5, 2500), (16, 5, 4100), (24, 4, 803), (33, 3, 700), (28, 2, 801), (10, 5, 4001)]
 # units, zone slots, envs
 ODD = [(9, 7, 12001), (17, 7, 3001), (21, 3, 2501), (23, 7, 2001), (31, 1, 1001), (17, 0, 9001), (3, 9, 40001), (1, 3, 400009)]
 

@@ -27,7 +27,7 @@ def test_errors_and_calls_without_rows():
         assert B.tabx_row_form(p, call) == dict(lines=NONE, pace=0, wavefronts_per_simd=-1, streams_global_state=0), call
 
 
-SHARED_ONLY = {(20, 3, 1901), (60, 9, 401), (10, 1, 17003), (4, 7, 56001), (2, 1, 300007)}
+SHARED_ONLY = {(20, 3, 1901), (20, 5, 2500), (60, 9, 401), (10, 1, 17003), (4, 7, 56001), (2, 1, 300007)}
 IN_REGISTERS = {(72, 2, 700)}
 
 
@@ -41,7 +41,8 @@ def test_ticks_with_shared_lines():
 def test_other_calls_with_shared_lines():
     assert [_form(2 * t, Z, E, "observe")["lines"] for t, Z, E in shared.OBSERVED] == \
         [CARRIED, SHARED, CARRIED, CARRIED, CARRIED]
-    assert {_form(2 * t, Z, E, "scripted_step_observe")["lines"] for t, Z, E in shared.SCRIPTED} == {CARRIED}
+    assert [_form(2 * t, Z, E, "scripted_step_observe")["lines"] for t, Z, E in shared.SCRIPTED] == \
+        [SHARED, CARRIED, CARRIED, CARRIED, CARRIED, CARRIED]
     assert [_form(N, Z, E)["lines"] for N, Z, E in shared.ODD] == \
         [SHARED, SHARED, CARRIED, CARRIED, CARRIED, SHARED, SHARED, SHARED]
 
@@ -105,6 +106,20 @@ def test_units_in_registers_half_a_chunk():
     for E, scripted in ((1025, 4), (1281, 3), (2048, 4)):
         forms = [_form(66, 7, E, c)["wavefronts_per_simd"] for c in ("step_observe", "observe", "scripted_step_observe")]
         assert forms == [3, 3, scripted], E
+
+
+@pytest.mark.parametrize("N,Z,E,lines,paced", [
+    # 1.6 us of HBM per tile of each wavefront, whole chunks and more than eight tiles 1.25; one generation
+    (20, 4, 2725, SHARED, True), (20, 4, 2726, CARRIED, True), (30, 2, 1300, SHARED, True), (30, 2, 1301, CARRIED, True),
+    (20, 5, 3428, SHARED, True), (20, 5, 3429, CARRIED, True), (60, 4, 325, SHARED, True), (60, 4, 326, CARRIED, True),
+    (53, 7, 712, SHARED, True), (53, 7, 713, CARRIED, True),
+    # several generations
+    (22, 2, 7000, CARRIED, False),
+    # the pace: 1.2 us, tiles that start on lines 1.0
+    (20, 4, 2616, SHARED, False), (20, 4, 2617, SHARED, True), (26, 0, 1802, OWN, False), (26, 0, 1803, OWN, True)])
+def test_wavefronts_that_hbm_waits_for(N, Z, E, lines, paced):
+    form = _form(N, Z, E)
+    assert (form["lines"], form["pace"] > 0) == (lines, paced), form
 
 
 def test_streamed_global_states():
