@@ -28,9 +28,9 @@ def _check_memory(gpu, ref, E, N, where):
         assert np.array_equal(g[valid == 1], ref.mem[k][valid == 1]), where + k
 
 
-def _policy_rollout(w, E, steps, tier, who, scenario=None, seed=5, fused=False, **override):
+def _policy_rollout(w, E, steps, tier, who, scenario=None, seed=5, fused=False, global_state=False, **override):
     """who: "adversaries" (allies act at random), "both", or "allies".  fused: the policy runs
-    inside the tick launch (tabx_policy_step_observe)."""
+    inside the tick launch (tabx_policy_step_observe).  global_state: the tick leaves it as well."""
     import torch
     from oracle.ref import RefEnv
     from paper_2602_01665_amd.binding import TabxEnv
@@ -38,7 +38,7 @@ def _policy_rollout(w, E, steps, tier, who, scenario=None, seed=5, fused=False, 
     sc = I.make_scenario(w, E) if scenario is None else scenario
     N = p["num_units"]
     ref = RefEnv(p, sc)
-    gpu = TabxEnv(p, sc, want_metrics=True)
+    gpu = TabxEnv(p, sc, want_metrics=True, want_global_state=global_state)
     ref.reset()
     gpu.reset()
     team = np.asarray(sc["team"]).reshape(E, N)
@@ -63,6 +63,8 @@ def _policy_rollout(w, E, steps, tier, who, scenario=None, seed=5, fused=False, 
             _check_memory(gpu, ref, E, N, where)
             compare_state(gpu.state_numpy(), ref.st, where)
             compare_outputs(gpu, ref, where, check_obs=True)
+            if global_state:
+                assert np.array_equal(gpu.gs_live.cpu().numpy(), ref.global_state()), where + "global state"
             hist += np.bincount(a[ctl == 1], minlength=8)
             dones += int(ref.dones.sum())
             continue
@@ -313,7 +315,7 @@ def test_full_size_scripted_tick_every_env():
     assert dones >= E
 
 
-def _scripted_rollout(w, E, steps, tier, who, scenario=None, seed=5, **override):
+def _scripted_rollout(w, E, steps, tier, who, scenario=None, seed=5, global_state=False, **override):
     """tabx_scripted_step_observe (decisions taken inside the observe stage, applied by the next
     call) against the checker's decide-then-step sequence: actions, states, observations,
     memories and the waiting decisions must all agree, tick by tick."""
@@ -325,7 +327,7 @@ def _scripted_rollout(w, E, steps, tier, who, scenario=None, seed=5, **override)
     sc = I.make_scenario(w, L if L else E) if scenario is None else scenario
     N = p["num_units"]
     ref = RefEnv(p, sc)
-    gpu = TabxEnv(p, sc, want_metrics=True)
+    gpu = TabxEnv(p, sc, want_metrics=True, want_global_state=global_state)
     ref.reset()
     gpu.reset()
     team = np.asarray(sc["team"]).reshape(-1, N)
@@ -355,6 +357,8 @@ def _scripted_rollout(w, E, steps, tier, who, scenario=None, seed=5, **override)
         assert np.array_equal(got, a), where + f"actions differ at {np.argwhere(got != a)[:4].tolist()}"
         compare_state(gpu.state_numpy(), ref.st, where)
         compare_outputs(gpu, ref, where, check_obs=True)
+        if global_state:
+            assert np.array_equal(gpu.gs_live.cpu().numpy(), ref.global_state()), where + "global state"
         hist += np.bincount(a[ctl == 1], minlength=8)
         dones += int(ref.dones.sum())
     return hist, dones

@@ -5,7 +5,7 @@ import pytest
 
 from paper_2602_01665_amd import inputs as I
 from tests.test_gpu_parity import _rollout
-from tests.test_gpu_policy import _scripted_rollout
+from tests.test_gpu_policy import _policy_rollout, _scripted_rollout
 from tests.test_gpu_row_forms import _scene
 from tests.test_launch_forms import _waves
 
@@ -74,6 +74,56 @@ def test_odd_numbers_of_units(N, Z, E):
         torch.cuda.synchronize()
         assert torch.equal(env.obs[first:first + few], one.obs), first
         assert torch.equal(env.vis[first:first + few], one.vis), first
+
+
+# the policy as a scan stage
+POLICY = [(10, 3, 3501), (15, 5, 4801), (11, 7, 2001), (32, 3, 1001), (33, 3, 700), (8, 7, 6007), (17, 1, 9001)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("team,zones,E", POLICY)
+def test_policy(team, zones, E):
+    w, sc = _scene(team, zones, E)
+    print(f"[gpu] shared lines, policy N={2 * team} Z={zones} E={E}", flush=True)
+    _policy_rollout(w, E, 2, "medium", "adversaries", scenario=sc, fused=True, max_steps=4)
+
+
+# tiles that start on lines, share them, hand them on; units in registers; of envs of one and of two wavefronts
+OFF_LINES = [(20, 8, 2501), (20, 7, 4001), (20, 3, 1901), (24, 4, 803), (10, 0, 9001), (66, 7, 601), (128, 0, 40),
+             (66, 0, 700), (17, 7, 3001)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", ["step_observe", "scripted_step_observe"])
+@pytest.mark.parametrize("off", [4, 8, 20, 28])
+@pytest.mark.parametrize("N,Z,E", OFF_LINES)
+def test_rows_that_start_off_a_line(N, Z, E, off, call):
+    """`obs` needs 16 bytes: the same rows 16 ... 112 bytes off a 128-byte line, and nothing written beside them.
+    (Parts of a batch start there: 17 units with 7 slots, a part of a multiple of four envs.)"""
+    import torch
+    from paper_2602_01665_amd.binding import TabxEnv
+    print(f"[gpu] obs {4 * off} bytes off a line, {call} N={N} Z={Z} E={E}", flush=True)
+    _, sc = _scene((N + 1) // 2, Z, E)
+    sc = {k: (v[:, :N].copy() if getattr(v, "ndim", 0) == 2 else v) for k, v in sc.items()}
+    p = I.custom_params(N, 40.0, 20, Z, num_envs=E)
+    on, beside = TabxEnv(p, sc), TabxEnv(p, sc)
+    assert on.obs.data_ptr() % 128 == 0
+    pad = torch.full((on.obs.numel() + 64,), 7.5, device=on.device)
+    assert pad.data_ptr() % 128 == 0
+    beside.obs = pad[32 + off:32 + off + on.obs.numel()].view_as(on.obs)
+    acts = torch.randint(0, 8, (E, N), dtype=torch.uint8, device=on.device, generator=torch.Generator(on.device).manual_seed(2))
+    pol = I.policy("medium", 3)
+    for env in (on, beside):
+        env.reset()
+        env.prime_scripted(pol, None)
+        for _ in range(2):
+            if call == "step_observe":
+                env.step_observe(acts)
+            else:
+                env.scripted_step_observe(pol, None, acts.clone())
+    torch.cuda.synchronize()
+    assert torch.equal(on.obs, beside.obs) and torch.equal(on.vis, beside.vis)
+    assert bool((pad[:32 + off] == 7.5).all()) and bool((pad[32 + off + on.obs.numel():] == 7.5).all())
 
 
 @pytest.mark.parametrize("N,Z,E,tick,scripted", [(56, 2, 800, 4, 4), (24, 4, 2048, 4, 4), (24, 4, 2049, 2, 2), (23, 7, 2000, 4, 4),

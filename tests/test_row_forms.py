@@ -47,6 +47,14 @@ def test_other_calls_with_shared_lines():
         [SHARED, SHARED, CARRIED, CARRIED, CARRIED, SHARED, SHARED, SHARED]
 
 
+def test_policy_ticks_and_rows_off_a_line():
+    assert [_form(2 * t, Z, E, "policy_step_observe")["lines"] for t, Z, E in shared.POLICY] == \
+        [SHARED, CARRIED, SHARED, SHARED, CARRIED, CARRIED, CARRIED]
+    for call, fourth in (("step_observe", OWN), ("scripted_step_observe", SHARED)):
+        assert [_form(N, Z, E, call)["lines"] for N, Z, E in shared.OFF_LINES] == \
+            [SHARED, CARRIED, SHARED, fourth, OWN, CARRIED, OWN, NONE, SHARED]
+
+
 @pytest.mark.parametrize("call", ["step_observe", "scripted_step_observe", "policy_step_observe", "observe"])
 def test_lines_are_handed_on_only_between_tiles_of_one_wavefront(call):
     """Ticks of odd numbers of units up to 20 deal their tiles in turn, and a wavefront with one tile has nobody to
@@ -128,6 +136,9 @@ def test_streamed_global_states():
         call = "step_observe" if fused else "observe"
         assert _form(2 * team, Z, E, call, **over)["streams_global_state"] == 1, (team, Z, E)
     assert _form(20, 8, 14000)["streams_global_state"] == 0
+    for call, cases in (("scripted_step_observe", stream.SCRIPTED), ("policy_step_observe", stream.POLICY)):
+        for team, Z, E in cases:
+            assert _form(2 * team, Z, E, call)["streams_global_state"] == int((team, Z, E) not in stream.STORED), (call, team, Z, E)
 
 
 def test_a_part_of_a_batch_is_not_held_to_a_pace():
