@@ -44,6 +44,7 @@ struct KArgs {
     int       tiles;               // tiles of a full env group: ceil(G * N / T)
     int       passes_per_tile;     // T / S
     uint32_t  line;                // a tile's image starts where its first row does in memory, modulo line + 1 floats
+                                   //     (of an `obs` on a 128-byte line: elsewhere more lines are shared)
     int       lines;               // enum Lines
     int       in_turn;             // the tiles are dealt to the wavefronts one by one, not in runs
     int       stage_floats;        // a wavefront's staging area in dynamic LDS (they come first)

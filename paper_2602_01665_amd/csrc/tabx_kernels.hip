@@ -474,7 +474,9 @@ static size_t plan_lds(Mode mode, KArgs &a, int waves)
     return floats * sizeof(float);
 }
 
-// How many wavefronts of the rows' kernels a SIMD holds (by their vector registers).
+// How many wavefronts of the rows' kernels a SIMD holds (by their vector registers).  (Of the scripted tiles of envs of
+// two wavefronts there are never more than the four per SIMD that 98 registers leave: four workgroups of four in a CU's
+// LDS, or six wavefronts in batches of two envs per CU.)
 static int wavefronts_per_simd(Mode mode, const KArgs &a, int waves)
 {
     if (a.packed) return waves == 1 || a.even ? 3 : 4;

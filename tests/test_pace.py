@@ -4,6 +4,8 @@ import re
 
 import pytest
 
+from paper_2602_01665_amd import inputs as I
+from paper_2602_01665_amd.binding import make_params, tabx_launch_info
 from tests.test_gpu_parity import _rollout
 from tests.test_gpu_policy import _scripted_rollout
 from tests.test_gpu_row_forms import _scene
@@ -34,6 +36,27 @@ def test_wavefronts_a_simd_holds(kernels):  # noqa: F811
     for part, held in HELD:
         (count,) = [v for k, v in registers.items() if part in k]
         assert 512 // (-(-count // 8) * 8) == held, (part, count)
+
+
+def test_scripted_tiles_of_two_wavefronts_need_no_fifth(kernels):  # noqa: F811
+    """Four per SIMD are all that the CUs' LDS or the batch ask for: a fifth, which fewer than 97 registers would
+    allow, is never there."""
+    text = kernels[1]
+    seen = 0
+    for N in range(65, 129):
+        for Z in (0, 1, 2, 3, 7, 16):
+            for E in (64, 300, 512, 513, 900):
+                info = tabx_launch_info(make_params(I.custom_params(N, 40.0, 0, Z, num_envs=E)), "scripted_step_observe")
+                w = info["wavefronts_per_env_group"]
+                if w == 2:
+                    continue
+                name = _kernel(2, 0, 1, 1, w // 2, 0)
+                static = int(re.search(r"\.amdhsa_kernel \w*" + name + r"\w*\n\s+\.amdhsa_group_segment_fixed_size (\d+)",
+                                       text).group(1))
+                block = -(-(static + info["dynamic_lds_bytes"]) // 1280) * 1280
+                assert min(160 * 1024 // block, -(-E // 256)) * w <= 16, (N, Z, E, w, block)
+                seen += 1
+    assert seen > 500
 
 
 PACED = [
