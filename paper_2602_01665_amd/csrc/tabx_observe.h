@@ -276,8 +276,11 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         fetch(tile * T, 0, rows_of(tile));
     }
 
+    // (tiles of two wavefronts that share lines are never paced, and the test for it cost them 2 to 3 %: 50v50 with 2
+    // zones x 400 67.6 us, 65.9 without)
+    constexpr bool PACED = WAVES == 1 || LINES != LINES_SHARED;
     const unsigned pace = a.pace;
-    const unsigned first_row = pace_start(pace);
+    const unsigned first_row = PACED ? pace_start(pace) : 0u;
     unsigned due = 0;
     bool carried = false;                        // the head of the tile's first line is there already
     for (; tile < tile_end && tile * T < rows; tile += tile_step) {
@@ -451,7 +454,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         // (a launch that is one generation of workgroups: see plan_pace, tabx_kernels.hip; what follows the last
         // tile waits for nothing)
-        if (tile + tile_step < tile_end && (tile + tile_step) * T < rows) pace_wait(first_row, (due += pace) >> 4);
+        if (PACED && tile + tile_step < tile_end && (tile + tile_step) * T < rows) pace_wait(first_row, (due += pace) >> 4);
     }
     if (WAVES == 1 && vis_mask) {
         // lane l writes row l of the group, if it was this wavefront's: row l % S of pass l / S

@@ -130,6 +130,20 @@ def test_wavefronts_that_hbm_waits_for(N, Z, E, lines, paced):
     assert (form["lines"], form["pace"] > 0) == (lines, paced), form
 
 
+def test_shared_lines_of_two_wavefronts_are_never_paced():
+    """Their kernels leave the pace out."""
+    shared_lines = 0
+    for N in range(65, 129):
+        for Z in (0, 1, 2, 3, 7, 16):
+            for E in (200, 300, 400, 512, 513, 700, 1000):
+                for call in ("step_observe", "scripted_step_observe", "policy_step_observe", "observe"):
+                    form = _form(N, Z, E, call)
+                    if form["lines"] == SHARED:
+                        shared_lines += 1
+                        assert form["pace"] == 0, (N, Z, E, call)
+    assert shared_lines > 500
+
+
 def test_streamed_global_states():
     for team, Z, E, fused, levels in stream.STREAMED:
         over = dict(num_levels=levels) if levels else {}
