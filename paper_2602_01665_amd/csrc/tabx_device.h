@@ -3,6 +3,7 @@
 // agree on, zone lookup, state load / store and the lane-to-unit mapping.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -26,8 +27,24 @@ struct PolicyArgs {
     uint8_t         *next_action;  // scripted tick: decided at the end of one call, applied by the next
 };
 
+// What the kernels read of TabxParams: all of it but the planner's last field, with which every pointer behind would
+// lie eight bytes further in its cache line (stand-alone observe 13v13 x 68 8.28 us, then 8.49; step x 263 5.70, 5.83).
+struct KParams {
+    int32_t  num_envs, num_units, grid_w, grid_h, max_zones, max_steps;
+    float    map_w, map_h, cell_size, dt, turn_rate, lava_dps, swamp_mult, reveal_time, boundary_frac;
+    float    collision_alpha, collision_slop;
+    int32_t  zone_shapes, num_levels;
+    uint32_t level_seed;
+    int32_t  hurtbox_cone, hit_all, env_id_offset, dynamics;
+    float    move_gain, restitution;
+};
+static_assert(sizeof(KParams) == offsetof(TabxParams, shared_machine) && sizeof(TabxParams) == sizeof(KParams) + 4 &&
+              offsetof(KParams, zone_shapes) == offsetof(TabxParams, zone_shapes) &&
+              offsetof(KParams, level_seed) == offsetof(TabxParams, level_seed) &&
+              offsetof(KParams, move_gain) == offsetof(TabxParams, move_gain), "the same fields, but for the last");
+
 struct KArgs {
-    TabxParams   p;
+    KParams      p;
     TabxScenario sc;
     TabxState    st;
     const uint8_t *actions;
@@ -46,7 +63,6 @@ struct KArgs {
     uint32_t  line;                // a tile's image starts where its first row does in memory, modulo line + 1 floats
                                    //     (of an `obs` on a 128-byte line: elsewhere more lines are shared)
     int       lines;               // enum Lines
-    int       in_turn;             // the tiles are dealt to the wavefronts one by one, not in runs
     int       stage_floats;        // a wavefront's staging area in dynamic LDS (they come first)
     int       zone_chunks;         // ZC: 16-byte chunks of the zone part of a row
     unsigned  magic_n, magic_zc, magic_s, magic_tc;   // x / N, / ZC, / S, / (4 + ZC) as multiplications (see quotient)
@@ -71,6 +87,8 @@ struct KArgs {
     float     inv_cell;            // 1 / cell_size, used only when that is exact (power of two)
     uint32_t  cells;               // FAST_CELL: cells of one row's grid
     uint32_t  flags;               // Flag bits
+    int       in_turn;             // the tiles are dealt to the wavefronts one by one, not in runs
+    int       shared_machine;      // TabxParams.shared_machine (for plan_pace)
     PolicyArgs pa;
     float *global_stream;          // where the global state goes if it is streamed (st.global_state is null then)
 };

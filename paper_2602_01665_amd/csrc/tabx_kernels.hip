@@ -27,6 +27,7 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include <string.h>
 
 #include "tabx.h"
 
@@ -164,7 +165,7 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
         TABX_STAMP(1);
         if constexpr (PACKED) {
             const KArgs &a = again();
-            observe_packed<WAVES, SCRIPT, SCRIPT || DO_POLICY, EVEN>(a, sh, dyn, P, U, code_u, C, Zr, told, script, zd);
+            observe_packed<WAVES, SCRIPT, SCRIPT || DO_POLICY, EVEN, WAVES == 1 && !DO_STEP>(a, sh, dyn, P, U, code_u, C, Zr, told, script, zd);
         } else if constexpr (DO_OBS) {
             group_barrier<WAVES>(sh);          // the step stage is done with the LDS union
             publish_units<WAVES, SCRIPT>(a, sh, P, U, code_u, C.ratio, C.cu, C.su, told, script);
@@ -194,7 +195,7 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
             const int begin = first + (in_turn ? wave : wave * share), step = in_turn ? WAVES * TWIN : 1;
             const int stop = !in_turn && begin + share < end ? begin + share : end;
             const auto rows = [&](auto fold, auto lines) {
-                write_rows<WAVES, SCRIPT, fold.value, lines.value>(a, sh.rec, Z, stg, P.grp, begin, step, stop, script);
+                write_rows<WAVES, SCRIPT, fold.value, lines.value, WAVES == 1 && !DO_STEP>(a, sh.rec, Z, stg, P.grp, begin, step, stop, script);
             };
             const auto rows_by_lines = [&](auto fold) {
                 if (a.lines == LINES_OWN) rows(fold, Constant<LINES_OWN>{});
@@ -414,6 +415,12 @@ static bool power_of_two(float v, float *inv)
     return frexpf(v, &ex) == 0.5f && ex > -100 && ex < 100;
 }
 
+static void take_params(const TabxParams *p, KArgs &a)
+{
+    memcpy(&a.p, p, sizeof a.p);
+    a.shared_machine = p->shared_machine;
+}
+
 // What the launch has to do besides the plain tick, and how it finds a unit's cell.
 static void set_flags(const TabxParams *p, const TabxState *st, KArgs &a)
 {
@@ -521,13 +528,13 @@ static double hbm_us_per_flush(const KArgs &a, int waves)
 static void plan_pace(Mode mode, KArgs &a, int waves, size_t lds)
 {
     a.pace = 0;
-    if (!has_rows(mode) || a.obs_chunks > 1) return;
+    if (!has_rows(mode) || (mode == MODE_OBSERVE && waves == 1)) return;     // (several workgroups share a group there)
     // Beside other work (unpaced / paced): a workgroup that had to wait for its place cannot see that it is late and
     // would take all of the launch's time once more (10v10 with collisions and ellipses, 2 x 8192 on two streams
     // 91 / 95.5 us, x 8192 beside a product of 2048 x 2048 matrices 74 / 88; scripted 10v10 with zones 2 x 4000
     // 43.6 / 46).  Envs of two wavefronts take about that time per row by themselves and keep the gain (64v64 2 x
     // 512 233 / 222, x 1024 beside the product 218 / 208).
-    if (a.p.shared_machine && waves == 1) return;
+    if (a.shared_machine && waves == 1) return;
     // Few rows: such a launch is mostly its start (5v5 x 6000, 38 MB: 13.4 us, 14.0 paced; x 8000 17.8 and 17.1).
     const double bytes = 4.0 * a.obs_dim * a.p.num_units * a.p.num_envs;
     if (bytes < 50e6) return;
@@ -888,7 +895,7 @@ static int plan_call(const TabxParams *p, int call, const void *out, KArgs &a, M
     static const Mode modes[] = {MODE_RESET, MODE_STEP, MODE_OBSERVE, MODE_STEP_OBSERVE, MODE_POLICY,
                                  MODE_POLICY_STEP_OBSERVE, MODE_SCRIPTED_STEP_OBSERVE};
     mode = modes[call];
-    a.p = *p;
+    take_params(p, a);
     a.obs_dim = 16 * p->num_units + 6 * p->max_zones;
     waves = plan_shape(mode, p, a);
     lds = plan_lds(mode, a, waves);
@@ -931,7 +938,7 @@ static int run(Mode mode, const TabxParams *p, const TabxScenario *sc, const Tab
         if (!aligned(obs, 16) || (vis_mask && !aligned(vis_mask, 16))) return TABX_ERR_ALIGN;
     }
     KArgs a;
-    a.p = *p;
+    take_params(p, a);
     a.sc = *sc;
     a.st = *st;
     a.actions = actions;
@@ -1028,7 +1035,7 @@ int tabx_global_state(const TabxParams *p, const TabxScenario *sc, const TabxSta
     if (!out) return TABX_ERR_NULL;
     if (!tabx::aligned(out, 16)) return TABX_ERR_ALIGN;
     tabx::KArgs a = {};
-    a.p = *p;
+    tabx::take_params(p, a);
     a.sc = *sc;
     a.st = *st;
     tabx::set_flags(p, st, a);

@@ -173,13 +173,14 @@ __device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); 
 // forms are code of their own: what the third one does costs small launches 2 to 4 % (10v11 with one zone x 64 11.4
 // and 11.8 us), and the second one's 1 % where no tile needs it (10v10 with 8 x 16384).
 //
+// UNPACED: see tabx_observe_packed.h.
 // SCRIPT: the units the heuristic policy moves decide their next action from the very pair
 // tests the observation rows are made of (App. A "Role-Appropriate Heuristic Policy Mechanism":
 // a unit acts on what it sees and can reach).  Every unit that a deciding observer sees bids
 // with LDS atomic minima for "its target" (key: the role's order, then distance, then index,
 // with "in its hurtbox" riding in the lowest bit) and for "its nearest enemy"; afterwards the
 // deciding units read their winners (decide_units).
-template <int WAVES, bool SCRIPT, bool FOLD, int LINES>
+template <int WAVES, bool SCRIPT, bool FOLD, int LINES, bool UNPACED>
 __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WAVES> &rec,
                                            const ZoneLds &Z, float *stg, int grp, int tile,
                                            int tile_step, int tile_end, ScriptLds<WAVES> *script)
@@ -454,7 +455,7 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         // (a launch that is one generation of workgroups: see plan_pace, tabx_kernels.hip; what follows the last
         // tile waits for nothing)
-        if (PACED && tile + tile_step < tile_end && (tile + tile_step) * T < rows) pace_wait(first_row, (due += pace) >> 4);
+        if (PACED && (UNPACED || (tile + tile_step < tile_end && (tile + tile_step) * T < rows))) pace_wait(first_row, (due += pace) >> 4);
     }
     if (WAVES == 1 && vis_mask) {
         // lane l writes row l of the group, if it was this wavefront's: row l % S of pass l / S
