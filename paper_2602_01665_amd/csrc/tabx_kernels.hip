@@ -165,7 +165,7 @@ __attribute__((amdgpu_waves_per_eu(1, EVEN ? 3 : 8))) void tabx_tick_kernel(cons
         TABX_STAMP(1);
         if constexpr (PACKED) {
             const KArgs &a = again();
-            observe_packed<WAVES, SCRIPT, SCRIPT || DO_POLICY, EVEN, WAVES == 1 && !DO_STEP>(a, sh, dyn, P, U, code_u, C, Zr, told, script, zd);
+            observe_packed<WAVES, SCRIPT, SCRIPT || DO_POLICY, EVEN>(a, sh, dyn, P, U, code_u, C, Zr, told, script, zd);
         } else if constexpr (DO_OBS) {
             group_barrier<WAVES>(sh);          // the step stage is done with the LDS union
             publish_units<WAVES, SCRIPT>(a, sh, P, U, code_u, C.ratio, C.cu, C.su, told, script);

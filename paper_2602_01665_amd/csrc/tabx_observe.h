@@ -173,7 +173,8 @@ __device__ __forceinline__ int staged_chunk(int c) { return c ^ ((c >> 3) & 3); 
 // forms are code of their own: what the third one does costs small launches 2 to 4 % (10v11 with one zone x 64 11.4
 // and 11.8 us), and the second one's 1 % where no tile needs it (10v10 with 8 x 16384).
 //
-// UNPACED: see tabx_observe_packed.h.
+// UNPACED: a launch that is never paced (stand-alone observe of envs of one wavefront).
+//
 // SCRIPT: the units the heuristic policy moves decide their next action from the very pair
 // tests the observation rows are made of (App. A "Role-Appropriate Heuristic Policy Mechanism":
 // a unit acts on what it sees and can reach).  Every unit that a deciding observer sees bids
@@ -277,14 +278,20 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         fetch(tile * T, 0, rows_of(tile));
     }
 
-    // (tiles of two wavefronts that share lines are never paced, and the test for it cost them 2 to 3 %: 50v50 with 2
-    // zones x 400 67.6 us, 65.9 without)
-    constexpr bool PACED = WAVES == 1 || LINES != LINES_SHARED;
+    // (stand-alone observe of envs of one wavefront, and tiles of two that share lines, are never paced, and the test
+    // for it cost them 1 to 3 %: 15v15 with 5 zones x 8000, observed, 98.7 us, 95.4 without, 32v32 with 7 x 15 8.55 and
+    // 8.44, the tick of 50v50 with 2 x 400 67.6 and 65.9)
+    constexpr bool PACED = !UNPACED && (WAVES == 1 || LINES != LINES_SHARED);
     const unsigned pace = a.pace;
     const unsigned first_row = PACED ? pace_start(pace) : 0u;
     unsigned due = 0;
     bool carried = false;                        // the head of the tile's first line is there already
     for (; tile < tile_end && tile * T < rows; tile += tile_step) {
+        // (a launch that is one generation of workgroups: see plan_pace, tabx_kernels.hip.  Here, with nothing due
+        // before the first tile, and not behind a branch after all but the last: small batches 1 to 2 % shorter, 30v29
+        // with 12 zones x 79 19.6 us and 19.2)
+        if (PACED) pace_wait(first_row, due >> 4);
+        due += pace;
         const int f0 = tile * T;                 // the tile's first row within the group
         const int rows_here = rows_of(tile);
         // where the tile starts within a 128-byte line (or a 16-byte chunk: KArgs::line)
@@ -453,9 +460,6 @@ __device__ __forceinline__ void write_rows(const KArgs &a, const Records<64 * WA
         // (8 KB rows: the wavefront lets its row land before it goes on, which keeps the XCDs together,
         // as in tabx_observe_packed.h: 64v64 x 512 125 us without, 117 with)
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        // (a launch that is one generation of workgroups: see plan_pace, tabx_kernels.hip; what follows the last
-        // tile waits for nothing)
-        if (PACED && (UNPACED || (tile + tile_step < tile_end && (tile + tile_step) * T < rows))) pace_wait(first_row, (due += pace) >> 4);
     }
     if (WAVES == 1 && vis_mask) {
         // lane l writes row l of the group, if it was this wavefront's: row l % S of pass l / S

@@ -56,10 +56,9 @@ __device__ __forceinline__ ZoneRegs load_zone_regs(const KArgs &a, const Place &
 }
 
 // DECIDING: a launch with a policy.  EVEN: see plan_shape (tabx_kernels.hip), at most three wavefronts per SIMD.
-// UNPACED: a launch that is never paced (stand-alone observe of envs of one wavefront).
 // `stg`: the staging area, G * R rows (WAVES == 2: two alternating areas of one row); `C`: what the step
 // stage left (heading, health ratio); `told`: the policy moves the unit (SCRIPT, see tabx_observe.h).
-template <int WAVES, bool SCRIPT, bool DECIDING, bool EVEN, bool UNPACED, class Sh>
+template <int WAVES, bool SCRIPT, bool DECIDING, bool EVEN, class Sh>
 __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *stg, const Place &P,
                                                const Unit &U, int code_u, const Carry &C,
                                                const ZoneRegs &Zr, int told,
@@ -218,6 +217,9 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
     float4 A = sh.ob.pose[0], B = sh.ob.reach[0];        // the observer
     int fi = sh.ob.seer[0];
     for (int i0 = i_begin; i0 < i_end; i0 += R) {
+        // (no faster than HBM takes all workgroups' rows together: plan_pace, tabx_kernels.hip)
+        pace_wait(first_row, due >> 4);
+        due += pace;
         v4 *const area = stage + (WAVES == 1 ? 0 : (i0 & 1) * row_chunks);
         for (int rr = 0; rr < R; ++rr) {
             const int i = i0 + rr;
@@ -361,10 +363,6 @@ __device__ __forceinline__ void observe_packed(const KArgs &a, Sh &sh, float *st
         // lets its row stores land before it goes on.  Without this the XCDs drain at different
         // rates and the launch lasts as long as the slowest (64v64 x 1024: 217 us against 208).
         if (WAVES == 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        // ... and goes no faster than HBM takes all workgroups' rows together (plan_pace, tabx_kernels.hip)
-        // (unpaced it does nothing, but with the compiler's code around a branch, or without it, small batches take 1.5 %
-        // longer: 13v13 x 68, observed, 8.16 us and 8.30)
-        if (UNPACED || i0 + R < i_end) pace_wait(first_row, (due += pace) >> 4);
     }
 
     TABX_STAMP(4);
