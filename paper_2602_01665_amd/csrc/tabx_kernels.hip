@@ -859,10 +859,10 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     // scripted 63 units x 314, 1.66, 4 % slower, 59 or 60 with 4 x 465, 2.29, 13 % faster; more: scripted 35 x 1275,
     // 0.93, 32.6 / 35.3, 20v20 with 4 x 583, 1.03, 23.2 / 24.9, 10v10 with 4 x 2906, 1.33, 24.9 / 23.0, 15v15 with 2 x
     // 2710, 1.78, 49.7 / 37.8; half a chunk at the end: 13v13 with 7 x 1070, 1.21, 20.4 / 21.8, scripted 18v18 with
-    // 7 x 1573, 1.30, 48.3 / 50.1, 53 with 7 x 741, 1.66, 41.2 / 39.4).
+    // 7 x 1573, 1.30, 48.3 / 50.1, 15v14 with one x 2567, 1.56, 45.6 / 43.3, 53 with 7 x 741, 1.66, 41.2 / 39.4).
     const auto chain_bound = [&] {
         return waves == 1 && a.obs_chunks == 1 &&
-               hbm_us_per_flush(a, waves) < (a.obs_dim % 4 == 0 && flushes_per_wavefront(a, waves) > 8 ? 1.25 : 1.6) &&
+               hbm_us_per_flush(a, waves) < (a.obs_dim % 4 == 0 && flushes_per_wavefront(a, waves) > 8 ? 1.25 : 1.5) &&
                one_generation(mode, a, waves, plan_lds(mode, a, waves));
     };
     if (a.obs_dim % 4 == 0 && tile % 32 == 0 && G * N * a.obs_dim % 32 == 0) a.lines = LINES_OWN;

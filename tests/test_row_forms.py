@@ -117,10 +117,10 @@ def test_units_in_registers_half_a_chunk():
 
 
 @pytest.mark.parametrize("N,Z,E,lines,paced", [
-    # 1.6 us of HBM per tile of each wavefront, whole chunks and more than eight tiles 1.25; one generation
-    (20, 4, 2725, SHARED, True), (20, 4, 2726, CARRIED, True), (30, 2, 1300, SHARED, True), (30, 2, 1301, CARRIED, True),
-    (20, 5, 3428, SHARED, True), (20, 5, 3429, CARRIED, True), (60, 4, 325, SHARED, True), (60, 4, 326, CARRIED, True),
-    (53, 7, 712, SHARED, True), (53, 7, 713, CARRIED, True),
+    # 1.5 us of HBM per tile of each wavefront, whole chunks and more than eight tiles 1.25; one generation
+    (20, 4, 2725, SHARED, True), (20, 4, 2726, CARRIED, True), (30, 2, 1219, SHARED, True), (30, 2, 1220, CARRIED, True),
+    (20, 5, 3214, SHARED, True), (20, 5, 3215, CARRIED, True), (60, 4, 304, SHARED, True), (60, 4, 305, CARRIED, True),
+    (53, 7, 667, SHARED, True), (53, 7, 668, CARRIED, True),
     # several generations
     (22, 2, 7000, CARRIED, False),
     # the pace: 1.2 us, tiles that start on lines 1.0
