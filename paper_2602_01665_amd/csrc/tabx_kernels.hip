@@ -848,11 +848,14 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
     const int per_wavefront = a.twin ? a.tiles_per_chunk / (waves * a.twin) : 0;
     const bool neighbours = !a.in_turn && a.tiles_per_chunk > waves * a.twin;
     // Envs of two wavefronts wait for their chain of rows until HBM takes no more, and the moves of a handed-on line
-    // are part of it: rows of whole chunks, which gain less than those that end within one, hand on beyond five
-    // quarters of the cache (shared / handed on and paced: 50v50 with 2 zones x 300 57.5 / 60.3 us, x 400, 258 MB,
-    // 66.9 / 69.9, x 512, 330 MB, 75.8 / 75.0, 64v64 with 2 x 256 78.4 / 80.2, x 400, 422 MB, 101 / 92.6; half a
-    // chunk at the end: 40v40 with one x 300, 123 MB, 60.2 / 58.1, 50v50 with 3 x 700 114 / 110).
-    const double worth = waves == 2 && a.obs_dim % 4 == 0 ? 1.25 * (double)kLastLevelCacheBytes : 50e6;
+    // are part of it: rows of whole chunks, which gain less than those that end within one, hand on where four
+    // wavefronts write them and HBM takes 2.1 us for a row of each (shared / handed on and paced: 50v50 with 2 zones x
+    // 480, 2.06 us, 7 % slower, x 512, 2.2, 81.5 / 77.5; 64v64 with 2 x 330, 1.81, 83 / 86.5, x 400, 2.2, 101 / 93; 55v55
+    // with 6 x 440, 2.07, 8 % faster; with six wavefronts, 1.1 ... 2.5 us, 4 to 7 % slower in all of 53; half a chunk at
+    // the end: 40v40 with one x 300, 123 MB, 60.2 / 58.1, 50v50 with 3 x 700 114 / 110).
+    const auto chain_of_two = [&] {
+        return waves == 2 && a.obs_dim % 4 == 0 && !(a.twin == 2 && hbm_us_per_flush(a, waves) >= 2.1);
+    };
     // Likewise a tick of one generation in which HBM has taken a tile of every wavefront before the next ones are made;
     // rows of whole chunks gain more, the more so the more lines a wavefront hands on (shared / handed on, in order of
     // the microseconds that is per tile; whole chunks, up to eight tiles: 13v13 with 4 zones x 1267, 1.38, 18.6 / 19.5,
@@ -866,8 +869,8 @@ static int plan_shape(Mode mode, const TabxParams *p, KArgs &a)
                one_generation(mode, a, waves, plan_lds(mode, a, waves));
     };
     if (a.obs_dim % 4 == 0 && tile % 32 == 0 && G * N * a.obs_dim % 32 == 0) a.lines = LINES_OWN;
-    else if (neighbours && a.line == 31 && bytes > worth &&
-             (per_wavefront >= 4 || bytes <= (double)kLastLevelCacheBytes) && !chain_bound()) a.lines = LINES_CARRIED;
+    else if (neighbours && a.line == 31 && bytes > 50e6 &&
+             (per_wavefront >= 4 || bytes <= (double)kLastLevelCacheBytes) && !chain_of_two() && !chain_bound()) a.lines = LINES_CARRIED;
     else a.lines = LINES_SHARED;
     return waves;
 }

@@ -94,7 +94,8 @@ def test_edges_of_the_pace(N, Z, E, paced):
 
 
 @pytest.mark.parametrize("N,Z,E,lines,paced", [
-    (100, 2, 518, NONE, False), (100, 2, 512, SHARED, False), (128, 2, 318, SHARED, False), (128, 2, 319, CARRIED, True),
+    (100, 2, 518, NONE, False), (100, 2, 488, SHARED, False), (100, 2, 489, CARRIED, True), (100, 2, 300, SHARED, False),
+    (128, 2, 382, SHARED, False), (128, 2, 383, CARRIED, True),
     (128, 3, 319, CARRIED, False), (80, 1, 300, CARRIED, False), (128, 0, 319, OWN, True)])
 def test_tiles_of_two_wavefronts(N, Z, E, lines, paced):
     form = _form(N, Z, E)
